@@ -1,0 +1,216 @@
+// Choice of the tiled GEMM's tile and K split (gemm_tiled.hpp), its launcher, and the row kernel
+// that stands between two GEMMs: adds the K-split partials to the residual rows and normalises.
+#include "kernels.hpp"
+#include "device_util.hpp"
+
+namespace ls {
+
+bool launch_gemm_tiled_bf16(int epi, const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out,
+                            const RopeAppend& rope, hipStream_t st);
+bool launch_gemm_tiled_f32(int epi, const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out,
+                           const RopeAppend& rope, hipStream_t st);
+
+bool gemm_tiled_supported(uint32_t dt, int epi, int M, int N, int K) {
+  const size_t e = dt == F32 ? 4 : 2, wrows = (size_t)N * (epi == TILED_SWIGLU ? 2 : 1);
+  // half k-steps; whole 16-column fragments; 32-bit byte offsets into both operands
+  return M >= 1 && N >= 16 && N % 16 == 0 && K >= 64 && K % (int)(64 / e) == 0 && wrows * K * e < (1ull << 32) &&
+         (size_t)M * K * e < (1ull << 32);
+}
+
+// Time of a launch, in microseconds, from what the kernel's sweep over tiles showed (7B and 13B
+// layers, 1..2048 rows, cold weights): a k-step of a workgroup costs 0.05 us + 2.4 ns per tile
+// row it brings into LDS, whatever the arithmetic (64 x 64 0.41, 64 x 128 0.53, 128 x 128 0.67,
+// 160 x 128 0.76, 256 x 128 0.95 us measured), in fp32 at least what its matrix work takes at 0.55
+// of a TFLOP/s per CU; one workgroup fits a CU, so the launch takes as many rounds as its fullest XCD has
+// workgroups for its 32 CUs; every K split writes and reads an fp32 tile.
+TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool may_split, size_t scratch_bytes, float* us) {
+  TiledPlan best;
+  float best_us = 1e30f;
+  if (gemm_tiled_supported(dt, epi, M, N, K)) {
+    static const int tiles[][2] = {{32, 64}, {32, 128}, {64, 64}, {64, 128}, {96, 128}, {128, 64}, {128, 128}, {160, 128}, {256, 128}};
+    const int kb = dt == F32 ? 32 : 64, nk = (K + kb - 1) / kb;
+    for (const auto& t : tiles) {
+      const int bm = t[0], bn = t[1];
+      if (epi == TILED_SWIGLU && bn == 64) continue;
+      const int ncols = epi == TILED_SWIGLU ? bn / 2 : bn;
+      const int tiles_m = (M + bm - 1) / bm, panels = ((N + ncols - 1) / ncols + 7) / 8;
+      float step = 0.05f + 0.0024f * (float)(bm + bn);
+      if (dt == F32) {
+        const float mma = (float)bm * (float)bn * 64.f / 0.55e6f;
+        if (mma > step) step = mma;
+      }
+      for (int s = 1; s <= 8; ++s) {
+        if (s > 1 && (!may_split || (size_t)s * M * N * sizeof(float) > scratch_bytes || nk < 2 * s)) break;
+        const long per_xcd = (long)panels * tiles_m * s;
+        const float rounds = (float)((per_xcd + 31) / 32);
+        const float t_us = rounds * ((float)((nk + s - 1) / s) * step + 2.5f) + (float)s * (float)M * (float)N * 8.f / 4e6f;
+        if (t_us < best_us) {
+          best_us = t_us;
+          best.bm = bm; best.bn = bn; best.splits = s;
+        }
+      }
+    }
+  }
+  if (us) *us = best_us;
+  return best;
+}
+
+bool launch_gemm_tiled(uint32_t dt, int epi, const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out,
+                       const RopeAppend& rope, hipStream_t st) {
+  if (!p.splits) return false;
+  return dt == F32 ? launch_gemm_tiled_f32(epi, p, A, W, M, N, K, out, rope, st)
+                   : launch_gemm_tiled_bf16(epi, p, A, W, M, N, K, out, rope, st);
+}
+
+namespace {
+
+// One 256-thread workgroup per row; the row lives in registers (eight 16-byte pieces per thread, all
+// requested before the first use).  Bound by latency for few rows, by HBM for many: this one pass
+// stands for the separate load (or embedding gather), residual add, norm and store passes.
+template <class T, int SRC>
+__global__ void __launch_bounds__(256) k_rows(RowsArgs a) {
+  typedef T T4 __attribute__((ext_vector_type(4)));
+  __shared__ float wsum[4];
+  const int r = blockIdx.x, nv = a.d >> 2;
+  if constexpr (SRC != ROWS_RESID) {
+    if (threadIdx.x == 0) {
+      if (a.cu) {  // prompt pass: find b with cu[b] <= r < cu[b + 1]
+        int lo = 0, hi = a.batch;
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if (a.cu[mid] <= r) lo = mid; else hi = mid;
+        }
+        const int c0 = a.cu[lo], c1 = a.cu[lo + 1];
+        a.row_seq[r] = lo;
+        a.row_pos[r] = r - c0;
+        if (r == c1 - 1) {
+          a.last_rows[lo] = r;
+          a.seq_lens[lo] = c1 - c0;
+        }
+      } else {  // generation step: a sequence without room is left alone and marked -1
+        const int p = a.seq_lens[r];
+        const bool ok = p >= 0 && p < a.max_seq;
+        a.row_seq[r] = r;
+        a.row_pos[r] = ok ? p : -1;
+        a.last_rows[r] = r;
+        if (ok) a.seq_lens[r] = p + 1;
+      }
+    }
+  }
+  auto widen = [](const T* p, bool vec) {
+    f32x4 v;
+    if (vec) {
+      const T4 t = *reinterpret_cast<const T4*>(p);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = to_f(t[e]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = to_f(p[e]);
+    }
+    return v;
+  };
+  float* xr = a.x + (size_t)r * a.d;
+  f32x4 v[8];
+  if constexpr (SRC == ROWS_RESID) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int idx = threadIdx.x + 256 * i;
+      v[i] = idx < nv ? reinterpret_cast<const f32x4*>(xr)[idx] : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    for (int s = 0; s < a.splits; ++s) {
+      const f32x4* pr = reinterpret_cast<const f32x4*>(a.part + ((size_t)s * a.rows + r) * a.d);
+      f32x4 p[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int idx = threadIdx.x + 256 * i;
+        p[i] = idx < nv ? pr[idx] : f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] += p[i];
+    }
+  } else {
+    const T* src;
+    if constexpr (SRC == ROWS_EMBED) {
+      int id = ((const int32_t*)a.in)[r];
+      id = id < 0 ? 0 : (id >= a.vocab ? a.vocab - 1 : id);  // an id outside the table is clamped
+      src = (const T*)a.table + (size_t)id * a.d;
+    } else {
+      src = (const T*)a.in + (size_t)r * a.d;
+    }
+    const bool vec = (reinterpret_cast<uintptr_t>(src) & (sizeof(T4) - 1)) == 0;  // the caller's buffer may lie anywhere
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int idx = threadIdx.x + 256 * i;
+      v[i] = idx < nv ? widen(src + idx * 4, vec) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+  if (a.out) {  // the stage's output rows
+    T* o = (T*)a.out + (size_t)r * a.d;
+    const bool vec = (reinterpret_cast<uintptr_t>(o) & (sizeof(T4) - 1)) == 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int idx = threadIdx.x + 256 * i;
+      if (idx < nv) {
+        T4 t;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = from_f<T>(v[i][e]);
+        if (vec) *reinterpret_cast<T4*>(o + idx * 4) = t;
+        else
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[idx * 4 + e] = t[e];
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int idx = threadIdx.x + 256 * i;
+    if (idx < nv) reinterpret_cast<f32x4*>(xr)[idx] = v[i];
+  }
+  if (!a.gamma) return;
+  // RMSNorm, the sum of squares in the order of k_rmsnorm_vec: a norm folded into this pass and one
+  // made on its own give the same bits
+  f32x4 g[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int idx = threadIdx.x + 256 * i;
+    g[i] = idx < nv ? widen((const T*)a.gamma + idx * 4, true) : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) ss += v[i][0] * v[i][0] + v[i][1] * v[i][1] + v[i][2] * v[i][2] + v[i][3] * v[i][3];
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  const float inv = 1.0f / sqrtf(((wsum[0] + wsum[1]) + (wsum[2] + wsum[3])) / (float)a.d + a.eps);
+  T* yr = (T*)a.y + (size_t)r * a.d;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int idx = threadIdx.x + 256 * i;
+    if (idx < nv) {
+      T4 t;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[e] = from_f<T>(v[i][e] * inv * g[i][e]);
+      *reinterpret_cast<T4*>(yr + idx * 4) = t;
+    }
+  }
+}
+
+template <class T>
+void launch_rows_t(int src, const RowsArgs& a, hipStream_t st) {
+  if (src == ROWS_RESID) k_rows<T, ROWS_RESID><<<a.rows, 256, 0, st>>>(a);
+  else if (src == ROWS_HIDDEN) k_rows<T, ROWS_HIDDEN><<<a.rows, 256, 0, st>>>(a);
+  else k_rows<T, ROWS_EMBED><<<a.rows, 256, 0, st>>>(a);
+}
+
+}  // namespace
+
+bool rows_supported(int d) { return d % 4 == 0 && d <= 8192; }
+
+void launch_rows(uint32_t dt, int src, const RowsArgs& a, hipStream_t st) {
+  if (a.rows <= 0) return;
+  if (dt == F32) launch_rows_t<float>(src, a, st);
+  else launch_rows_t<bf16>(src, a, st);
+}
+
+}  // namespace ls

@@ -95,6 +95,45 @@ bool gemm_mfma_rope_supported(int M, int N, int K, int hq, int hkv, int hd);
 void launch_gemm_mfma_rope(const void* A, const void* W, int M, int N, int K, void* out, const RopeAppend& rope,
                            hipStream_t st);
 
+// GEMM in tiles of bm rows x bn weight rows, K cut `splits` ways (gemm_tiled.hpp): row counts between the
+// weight-streaming kernels and the 256 x 256 tiles in bf16, every fp32 GEMM whose K is a multiple of 16.
+// Output: TILED_PART fp32 partial tiles part[split][M][N] (one split: an fp32 matrix), TILED_STORE
+// the storage type, TILED_SWIGLU silu(gate) * up, TILED_ROPE as launch_gemm_mfma_rope.
+enum TiledEpi : int { TILED_PART = 0, TILED_STORE = 1, TILED_SWIGLU = 2, TILED_ROPE = 3 };
+struct TiledPlan {
+  int bm = 0, bn = 0, splits = 0;  // splits == 0: not supported
+};
+// The plan with the shortest estimated time, which `us` receives; partial tiles have to fit scratch_bytes.
+TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool may_split, size_t scratch_bytes, float* us);
+bool launch_gemm_tiled(uint32_t dt, int epi, const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out,
+                       const RopeAppend& rope, hipStream_t st);
+// Estimated time of launch_gemm_mfma (ncols: output columns of a tile, 256 or with SwiGLU 128).
+float gemm_mfma_us(int M, int N, int K, int ncols);
+
+// One pass over rows of width d (a multiple of 4, at most 8192).  Source: the residual rows plus `splits`
+// partial tiles, the call's hidden rows, or embedding rows; the latter two also write the call's
+// bookkeeping (row -> sequence and position, last rows, seq_lens).  Result: the stage's output rows
+// (out), or the residual rows x and, with a gain, their RMSNorm y.
+enum RowsSrc : int { ROWS_RESID = 0, ROWS_HIDDEN = 1, ROWS_EMBED = 2 };
+struct RowsArgs {
+  int rows = 0, d = 0;
+  float* x = nullptr;
+  const float* part = nullptr;
+  int splits = 0;
+  const void* in = nullptr;
+  const void* table = nullptr;
+  int vocab = 0;
+  const int32_t* cu = nullptr;  // prompt pass: sequence bounds; nullptr: generation step
+  int batch = 0, max_seq = 0;
+  int32_t *row_seq = nullptr, *row_pos = nullptr, *last_rows = nullptr, *seq_lens = nullptr;
+  void* out = nullptr;
+  const void* gamma = nullptr;
+  void* y = nullptr;
+  float eps = 0.f;
+};
+bool rows_supported(int d);
+void launch_rows(uint32_t dt, int src, const RowsArgs& a, hipStream_t st);
+
 // bf16 weight-streaming kernel for decode steps (M <= 64); needs N % 16 == 0, K % 128 == 0.
 // ks = wavefronts that split K inside a workgroup (4, 8, 16), 0 = chosen from the shape.
 // Optional RMSNorm fusion of the decode step (all pointers device memory).  The gain of a

@@ -136,6 +136,9 @@ struct Carve {
       attn_part, attn_part_bytes, total;
 };
 
+// more than 64 MiB of partial tiles are never wanted: a call that long fills the chip without splits
+constexpr size_t TILED_SCRATCH_MAX = 64u << 20;
+
 Carve carve(const ls_cfg* c, int lo, int hi) {
   Carve w{};
   const size_t e = isz(c), T = c->max_tokens, B = c->max_batch, d = c->hidden;
@@ -160,11 +163,15 @@ Carve carve(const ls_cfg* c, int lo, int hi) {
   w.ss_a = take(B * ((d + 15) / 16) * sizeof(float));
   w.ss_b = take(B * ((d + 15) / 16) * sizeof(float));
   {
-    // split-K scratch of the decode GEMMs for 17..64 rows (bf16 only)
+    // split-K scratch: the decode GEMMs for 17..64 rows (bf16 only)
     size_t cols = qkv_cols > 2 * (size_t)c->ffn ? qkv_cols : 2 * (size_t)c->ffn;
     if (d > cols) cols = d;
     if (last && c->vocab > cols) cols = c->vocab;
     w.splitk_bytes = (c->dtype == LS_DTYPE_BF16 && B > 16) ? ls::gemm_scratch_bytes((int)B, cols) : 0;
+    // partial tiles of the tiled GEMMs that write residual rows: at most eight splits of every row
+    size_t part = 8 * T * d * sizeof(float);
+    if (part > TILED_SCRATCH_MAX) part = TILED_SCRATCH_MAX;
+    if (part > w.splitk_bytes) w.splitk_bytes = part;
     w.splitk = take(w.splitk_bytes);
   }
   // partial results of the grouped-query decode attention for contexts split over workgroups
@@ -191,15 +198,19 @@ struct Block {
   bool landed;
 };
 
+// The host has seen the block's copy complete.
+inline bool landed(Block& b) {
+  if (!b.landed && b.state == ENQUEUED) {
+    if (hipEventQuery(b.loaded) == hipSuccess) b.landed = true;
+    else (void)hipGetLastError();  // hipErrorNotReady from the query is not an error
+  }
+  return b.landed;
+}
+
 // The gate: order stream `st` after the block's copy (nothing to enqueue once the copy is
 // known to have completed).
 inline hipError_t gate(Block& b, hipStream_t st) {
-  if (b.landed) return hipSuccess;
-  if (hipEventQuery(b.loaded) == hipSuccess) {
-    b.landed = true;
-    return hipSuccess;
-  }
-  (void)hipGetLastError();  // hipErrorNotReady from the query is not an error
+  if (landed(b)) return hipSuccess;
   return hipStreamWaitEvent(st, b.loaded, 0);
 }
 
@@ -616,48 +627,121 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     return LS_OK;
   }
 
+  // ---- prompt passes, and generation steps of fp32 or of more than 64 rows.  Rows of up to 8192
+  // columns (rows_one_pass) are loaded, added up and normalised by launch_rows, which takes the
+  // norm that follows along wherever its gain is already there.
   if (timed) LS_HIP(hipEventRecord(s->pass_start, st));
-  if (prefill) launch_row_index_prefill(cu_dev, batch, rows, row_seq, row_pos, last_rows, st);
-  else launch_row_index_decode(kv->seq_lens, batch, c.max_seq, row_seq, row_pos, last_rows, st);
+  const bool rows_one_pass = rows_supported(d);
+  const int n_layers = s->hi - s->lo;
+  auto tensor = [&](Block& b, int i) {
+    TensorSpan sp[6];
+    block_tensors(&c, b.layer, sp, nullptr);
+    return (const void*)(s->slab + b.off + sp[i].off);
+  };
+  // a norm that is timed on its own is launched on its own
+  auto norm_alone = [&](Block& b) { return probing && s->probe_op == LS_OP_NORM && s->probe_layer == b.layer; };
+  bool y_ready = false;  // y holds the normalised rows the next GEMM reads
 
+  const void* table = nullptr;
   if (s->first) {
     Block* eb = s->find(LS_BLOCK_EMBED);
     LS_HIP(gate(*eb, st));  // gate: embedding block has landed
-    launch_embed(dt, s->slab + eb->off, (const int32_t*)in, x, rows, d, c.vocab, st);
+    table = s->slab + eb->off;
+  }
+  if (rows_one_pass) {
+    RowsArgs ra;
+    ra.rows = rows; ra.d = d; ra.x = x; ra.in = in; ra.table = table; ra.vocab = c.vocab;
+    ra.cu = prefill ? cu_dev : nullptr; ra.batch = batch; ra.max_seq = c.max_seq;
+    ra.row_seq = row_seq; ra.row_pos = row_pos; ra.last_rows = last_rows; ra.seq_lens = kv->seq_lens;
+    Block& b0 = s->blocks[s->layer0];
+    if (landed(b0) && !norm_alone(b0)) {
+      ra.gamma = tensor(b0, 0); ra.y = y; ra.eps = c.rms_eps;
+      y_ready = true;
+    }
+    launch_rows(dt, s->first ? ROWS_EMBED : ROWS_HIDDEN, ra, st);
   } else {
-    launch_load_hidden(dt, in, x, (size_t)rows * d, st);
+    if (prefill) launch_row_index_prefill(cu_dev, batch, rows, row_seq, row_pos, last_rows, st);
+    else launch_row_index_decode(kv->seq_lens, batch, c.max_seq, row_seq, row_pos, last_rows, st);
+    if (s->first) launch_embed(dt, table, (const int32_t*)in, x, rows, d, c.vocab, st);
+    else launch_load_hidden(dt, in, x, (size_t)rows * d, st);
   }
 
-  for (int li = 0; li < s->hi - s->lo; ++li) {
+  // The tiled GEMM takes every fp32 projection it supports, and the bf16 ones of more than 16 rows in
+  // a prompt pass (64 in a generation step) where it is estimated faster than the 256 x 256 tiles.
+  // Partial tiles of a generation step fit the static scratch too, so that both entry points take
+  // the same plans.
+  const size_t part_bytes = prefill || gsc.bytes < LS_STATIC_SCRATCH_BYTES ? gsc.bytes : LS_STATIC_SCRATCH_BYTES;
+  auto plan = [&](int epi, int N, int K) {
+    if (dt == BF16 && rows <= (prefill ? 16 : 64)) return TiledPlan{};
+    float us = 0.f;
+    const TiledPlan p = gemm_tiled_plan(dt, epi, rows, N, K, epi == TILED_PART, part_bytes, &us);
+    if (dt == BF16 && rows > 64 && gemm_mfma_supported(rows, N, K) &&
+        gemm_mfma_us(rows, N, K, epi == TILED_SWIGLU ? 128 : 256) <= us)
+      return TiledPlan{};
+    return p;
+  };
+  // attention of fp32 and of shapes without a fused kernel wants rotated rows and a filled cache
+  const bool attn_rotates = !prefill && dt == BF16 && (attn_decode_supported(hq, hkv, hd) || attn_decode_gqa_supported(hq, hkv, hd));
+  const bool rope_tiles = !attn_rotates && hd % 16 == 0;  // a 16-column fragment inside one head
+  const TiledPlan p_qkv = attn_rotates ? plan(TILED_STORE, qkv_cols, d) : rope_tiles ? plan(TILED_ROPE, qkv_cols, d) : TiledPlan{};
+  const TiledPlan p_o = rows_one_pass && gsc.splitk ? plan(TILED_PART, d, hq * hd) : TiledPlan{};
+  const TiledPlan p_gu = plan(TILED_SWIGLU, F, d);
+  const TiledPlan p_dn = rows_one_pass && gsc.splitk ? plan(TILED_PART, d, F) : TiledPlan{};
+
+  // x += A W^T, then what follows a residual add: the rows' norm with `gamma` (y), the stage's
+  // output (to_out), or nothing
+  auto residual = [&](const TiledPlan& p, const void* A, const void* W, int K, const void* gamma, bool to_out) {
+    RowsArgs ra;
+    ra.rows = rows; ra.d = d; ra.x = x; ra.gamma = gamma; ra.y = y; ra.eps = c.rms_eps; ra.out = to_out ? out : nullptr;
+    if (p.splits) {
+      launch_gemm_tiled(dt, TILED_PART, p, A, W, rows, d, K, gsc.splitk, RopeAppend{}, st);
+      ra.part = gsc.splitk; ra.splits = p.splits;
+      launch_rows(dt, ROWS_RESID, ra, st);
+    } else {
+      launch_gemm(dt, EPI_RESID, A, W, rows, d, K, nullptr, x, st, &gsc);
+      if (to_out) launch_store_hidden(dt, x, out, (size_t)rows * d, st);
+      else if (gamma) launch_rmsnorm(dt, x, gamma, y, rows, d, c.rms_eps, nullptr, st);
+    }
+  };
+
+  for (int li = 0; li < n_layers; ++li) {
     Block& b = s->blocks[s->layer0 + li];
-    TensorSpan sp[6];
-    block_tensors(&c, b.layer, sp, nullptr);
-    const char* base = s->slab + b.off;
     // the gate: nothing of this layer may read its weights before its block has landed
     LS_HIP(gate(b, st));
     if (timed) LS_HIP(hipEventRecord(s->comp_start[li], st));
     char* kc = (char*)kv->k + li * kv_layer;
     char* vc = (char*)kv->v + li * kv_layer;
 
-    PROBE(LS_OP_NORM, launch_rmsnorm(dt, x, base + sp[0].off, y, rows, d, c.rms_eps, nullptr, st));
-    // many-row prompt passes: RoPE and the cache append ride in the QKV projection's epilogue
-    const bool rope_in_gemm = prefill && dt == BF16 && rows > 64 && attn_prefill_supported(hq, hkv, hd) &&
-                              gemm_mfma_rope_supported(rows, qkv_cols, d, hq, hkv, hd);
-    if (rope_in_gemm) {
-      RopeAppend ra;
-      ra.cs = cs; ra.row_seq = row_seq; ra.row_pos = row_pos;
-      ra.hq = hq; ra.hkv = hkv; ra.hd = hd; ra.max_seq = c.max_seq;
-      ra.kc = (__bf16*)kc; ra.vc = (__bf16*)vc;
-      PROBE(LS_OP_GEMM_QKV, launch_gemm_mfma_rope(y, base + sp[1].off, rows, qkv_cols, d, qkv, ra, st));
+    if (!y_ready) PROBE(LS_OP_NORM, launch_rmsnorm(dt, x, tensor(b, 0), y, rows, d, c.rms_eps, nullptr, st));
+    RopeAppend ra;
+    ra.cs = cs; ra.row_seq = row_seq; ra.row_pos = row_pos;
+    ra.hq = hq; ra.hkv = hkv; ra.hd = hd; ra.max_seq = c.max_seq;
+    ra.kc = (__bf16*)kc; ra.vc = (__bf16*)vc;
+    // RoPE and the cache append ride in the QKV projection's epilogue
+    bool roped = p_qkv.splits && !attn_rotates;
+    if (p_qkv.splits) {
+      PROBE(LS_OP_GEMM_QKV, launch_gemm_tiled(dt, roped ? TILED_ROPE : TILED_STORE, p_qkv, y, tensor(b, 1), rows, qkv_cols, d,
+                                              qkv, ra, st));
+    } else if (prefill && dt == BF16 && rows > 64 && attn_prefill_supported(hq, hkv, hd) &&
+               gemm_mfma_rope_supported(rows, qkv_cols, d, hq, hkv, hd)) {
+      roped = true;
+      PROBE(LS_OP_GEMM_QKV, launch_gemm_mfma_rope(y, tensor(b, 1), rows, qkv_cols, d, qkv, ra, st));
     } else {
-      PROBE(LS_OP_GEMM_QKV, launch_gemm(dt, EPI_STORE, y, base + sp[1].off, rows, qkv_cols, d, qkv, nullptr, st, &gsc));
+      PROBE(LS_OP_GEMM_QKV, launch_gemm(dt, EPI_STORE, y, tensor(b, 1), rows, qkv_cols, d, qkv, nullptr, st, &gsc));
     }
     PROBE(LS_OP_ATTENTION, launch_attention_block(dt, cu_dev, batch, max_len, qkv, cs, kc, vc, row_seq, row_pos, rows,
-                                                  hq, hkv, hd, c.max_seq, attn, st, nullptr, 0, rope_in_gemm));
-    PROBE(LS_OP_GEMM_O, launch_gemm(dt, EPI_RESID, attn, base + sp[2].off, rows, d, hq * hd, nullptr, x, st, &gsc));
-    launch_rmsnorm(dt, x, base + sp[3].off, y, rows, d, c.rms_eps, nullptr, st);
-    PROBE(LS_OP_GEMM_GATEUP, launch_gemm(dt, EPI_SWIGLU, y, base + sp[4].off, rows, F, d, hbuf, nullptr, st, &gsc));
-    PROBE(LS_OP_GEMM_DOWN, launch_gemm(dt, EPI_RESID, hbuf, base + sp[5].off, rows, d, F, nullptr, x, st, &gsc));
+                                                  hq, hkv, hd, c.max_seq, attn, st, nullptr, 0, roped));
+    PROBE(LS_OP_GEMM_O, residual(p_o, attn, tensor(b, 2), hq * hd, tensor(b, 3), false));
+    if (p_gu.splits)
+      PROBE(LS_OP_GEMM_GATEUP, launch_gemm_tiled(dt, TILED_SWIGLU, p_gu, y, tensor(b, 4), rows, F, d, hbuf, RopeAppend{}, st));
+    else
+      PROBE(LS_OP_GEMM_GATEUP, launch_gemm(dt, EPI_SWIGLU, y, tensor(b, 4), rows, F, d, hbuf, nullptr, st, &gsc));
+    // the next layer's norm goes along only if its block is known to be there: nothing of this
+    // layer waits for it
+    const bool more = li + 1 < n_layers;
+    Block* next = more ? &s->blocks[s->layer0 + li + 1] : nullptr;
+    y_ready = more && p_dn.splits && landed(*next) && !norm_alone(*next);
+    PROBE(LS_OP_GEMM_DOWN, residual(p_dn, hbuf, tensor(b, 5), F, y_ready ? tensor(*next, 0) : nullptr, !more && !s->last));
     if (timed) LS_HIP(hipEventRecord(s->comp_end[li], st));
   }
 #undef PROBE
@@ -671,14 +755,18 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     LS_HIP(gate(*hb, st));  // gate: head block has landed
     float* logits = logits_out ? logits_out : (float*)(ws + s->w.logits);
     launch_rmsnorm(dt, x, base + sp[0].off, y, batch, d, c.rms_eps, last_rows, st);
-    launch_gemm(dt, EPI_F32, y, base + sp[1].off, batch, c.vocab, d, logits, nullptr, st, &gsc);
+    const TiledPlan p_head = (dt == F32 || batch > 64) && ((uintptr_t)logits & 15) == 0
+                                 ? gemm_tiled_plan(dt, TILED_PART, batch, (int)c.vocab, d, false, 0, nullptr)
+                                 : TiledPlan{};
+    if (p_head.splits) launch_gemm_tiled(dt, TILED_PART, p_head, y, base + sp[1].off, batch, c.vocab, d, logits, RopeAppend{}, st);
+    else launch_gemm(dt, EPI_F32, y, base + sp[1].off, batch, c.vocab, d, logits, nullptr, st, &gsc);
     launch_argmax(logits, batch, c.vocab, (int32_t*)out, st);
-  } else {
-    launch_store_hidden(dt, x, out, (size_t)rows * d, st);
   }
 
-  if (prefill) launch_seq_lens_set(cu_dev, batch, kv->seq_lens, st);
-  else launch_seq_lens_inc(batch, c.max_seq, kv->seq_lens, st);
+  if (!rows_one_pass) {
+    if (prefill) launch_seq_lens_set(cu_dev, batch, kv->seq_lens, st);
+    else launch_seq_lens_inc(batch, c.max_seq, kv->seq_lens, st);
+  }
   if (timed) LS_HIP(hipEventRecord(s->pass_end, st));
   LS_HIP(hipGetLastError());
   return LS_OK;
