@@ -1,8 +1,8 @@
-// bf16 decode attention, fused with RoPE and the KV-cache append of the new row: one query
-// row per sequence against its KV cache (GQA aware).
+// Decode attention (bf16 and fp32), fused with RoPE and the KV-cache append of the new row: one
+// query row per sequence against its KV cache (GQA aware).
 //
 // The step's q, k, v are read un-rotated from the projection output.  q is rotated in
-// registers; the new key is rotated, rounded to bf16 and written to the cache row `pos`
+// registers; the new key is rotated, rounded to storage type and written to the cache row `pos`
 // together with the new value by wave 0, which also feeds them to its own softmax state
 // straight from registers -- no wavefront of this kernel reads cache row `pos`, so there is
 // no ordering problem between that store and the streaming loads.
@@ -16,8 +16,14 @@
 // completes the score, and every key slot runs its own online softmax (running max and sum)
 // so that no cross-slot traffic is needed inside the loop.  Slots are merged by shuffles,
 // wavefronts through LDS in wave order: the result does not depend on timing.
+//
+// One sequence of 3000 keys on 32 heads is 32 workgroups on 256 CUs; there contexts are also cut into
+// chunks that are workgroups of their own, merged in chunk order by a second kernel (see
+// chunks_for).
 #include "kernels.hpp"
 #include "device_util.hpp"
+
+#include <algorithm>
 
 namespace ls {
 
@@ -35,19 +41,28 @@ namespace {
 #ifndef LS_ATTN_U
 #define LS_ATTN_U 1
 #endif
-constexpr int waves_for(int g) { return g == 1 ? LS_ATTN_NW1 : LS_ATTN_NW; }
+// fp32 rows are twice as wide per lane: 8 wavefronts
+template <class T> constexpr int waves_for(int g) { return g == 1 && sizeof(T) == 2 ? LS_ATTN_NW1 : LS_ATTN_NW; }
 
-template <int HD, int G>
+constexpr int PART_HDR = 4;  // floats in front of a chunk's partial result: maximum, sum
+
+template <class T> struct Vec8;
+template <> struct Vec8<bf16> { typedef bf16x8 type; };
+template <> struct Vec8<float> { typedef float type __attribute__((ext_vector_type(8))); };
+
+template <class T, int HD, int G>
 // with one query head per kv head the kernel fits 64 registers: eight wavefronts per SIMD, two
 // 16-wavefront workgroups per CU
-__global__ void __launch_bounds__(waves_for(G) * 64, (G == 1 ? 8 : 1))
-k_attn_decode(const bf16* __restrict__ qkv, int qkv_stride, const float2* __restrict__ cs,
-              bf16* __restrict__ kc, bf16* __restrict__ vc, const int32_t* __restrict__ row_seq,
-              const int32_t* __restrict__ row_pos, int hq, int hkv, int max_seq, bf16* __restrict__ out) {
-  constexpr int NW = waves_for(G);
+__global__ void __launch_bounds__(waves_for<T>(G) * 64, (G == 1 && sizeof(T) == 2 ? 8 : 1))
+k_attn_decode(const T* __restrict__ qkv, int qkv_stride, const float2* __restrict__ cs,
+              T* __restrict__ kc, T* __restrict__ vc, const int32_t* __restrict__ row_seq,
+              const int32_t* __restrict__ row_pos, int hq, int hkv, int max_seq, T* __restrict__ out,
+              float* __restrict__ part, int nchunk, int chunk_keys) {
+  typedef typename Vec8<T>::type T8;
+  constexpr int NW = waves_for<T>(G);
   constexpr int LPK = HD / 8;     // lanes per key
   constexpr int KPI = 64 / LPK;   // keys per load instruction
-  constexpr int U = (G >= 4) ? 2 : LS_ATTN_U;  // load instructions in flight per operand
+  constexpr int U = (G >= 4 && sizeof(T) == 2) ? 2 : LS_ATTN_U;  // load instructions in flight per operand
   __shared__ float sm_m[NW][G], sm_l[NW][G];
   __shared__ float sm_acc[NW][G][HD];
   const int r = blockIdx.x, kh = blockIdx.y;
@@ -55,11 +70,14 @@ k_attn_decode(const bf16* __restrict__ qkv, int qkv_stride, const float2* __rest
   const int pos = row_pos[r];
   if (pos < 0) return;  // a sequence with no room left: whole workgroup leaves together
   const int seq = row_seq[r];
-  const int ctx = pos;  // keys 0..pos-1 come from the cache, key `pos` from this step's row
+  // keys 0..pos-1 come from the cache, key `pos` from this step's row; this workgroup's chunk of the
+  // former (the last chunk is open-ended), the latter goes with chunk 0
+  const int c0 = blockIdx.z * chunk_keys, ctx = (int)blockIdx.z == nchunk - 1 ? pos : min(c0 + chunk_keys, pos);
+  if (c0 >= pos && blockIdx.z) return;
   const int slot = lane / LPK, dl = lane % LPK;
-  bf16* kb = kc + ((size_t)seq * hkv + kh) * max_seq * HD;
-  bf16* vb = vc + ((size_t)seq * hkv + kh) * max_seq * HD;
-  const bf16* row = qkv + (size_t)r * qkv_stride;
+  T* kb = kc + ((size_t)seq * hkv + kh) * max_seq * HD;
+  T* vb = vc + ((size_t)seq * hkv + kh) * max_seq * HD;
+  const T* row = qkv + (size_t)r * qkv_stride;
 
   // cos/sin of this lane's four pairs (dims 8 dl + 2i, 8 dl + 2i + 1) at position pos
   float2 rot[4];
@@ -71,18 +89,18 @@ k_attn_decode(const bf16* __restrict__ qkv, int qkv_stride, const float2* __rest
   float q[G][8];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    const bf16x8 qv = *reinterpret_cast<const bf16x8*>(row + (size_t)(kh * G + g) * HD + dl * 8);
+    const T8 qv = *reinterpret_cast<const T8*>(row + (size_t)(kh * G + g) * HD + dl * 8);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float u0 = (float)qv[2 * i], u1 = (float)qv[2 * i + 1];
+      const float u0 = to_f(qv[2 * i]), u1 = to_f(qv[2 * i + 1]);
       q[g][2 * i] = (u0 * rot[i].x - u1 * rot[i].y) * scale;
       q[g][2 * i + 1] = (u0 * rot[i].y + u1 * rot[i].x) * scale;
     }
   }
 
   // contiguous key range of this wave, a multiple of KPI keys
-  const int chunk = ((ctx + NW * KPI - 1) / (NW * KPI)) * KPI;
-  const int k_begin = wave * chunk, k_end = min(k_begin + chunk, ctx);
+  const int chunk = ((ctx - c0 + NW * KPI - 1) / (NW * KPI)) * KPI;
+  const int k_begin = c0 + wave * chunk, k_end = min(k_begin + chunk, ctx);
 
   float m[G], l[G], acc[G][8];
 #pragma unroll
@@ -111,23 +129,23 @@ k_attn_decode(const bf16* __restrict__ qkv, int qkv_stride, const float2* __rest
 
   // the new row first (wave 0): rotate k, round both to bf16, append to the cache, attend to
   // it.  Done before the cache stream so that the rotation table is dead inside the loop.
-  if (wave == 0) {
-    const bf16x8 kn = *reinterpret_cast<const bf16x8*>(row + (size_t)(hq + kh) * HD + dl * 8);
-    const bf16x8 vn = *reinterpret_cast<const bf16x8*>(row + (size_t)(hq + hkv + kh) * HD + dl * 8);
-    bf16x8 kr;
+  if (wave == 0 && blockIdx.z == 0) {
+    const T8 kn = *reinterpret_cast<const T8*>(row + (size_t)(hq + kh) * HD + dl * 8);
+    const T8 vn = *reinterpret_cast<const T8*>(row + (size_t)(hq + hkv + kh) * HD + dl * 8);
+    T8 kr;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float u0 = (float)kn[2 * i], u1 = (float)kn[2 * i + 1];
-      kr[2 * i] = (bf16)(u0 * rot[i].x - u1 * rot[i].y);
-      kr[2 * i + 1] = (bf16)(u0 * rot[i].y + u1 * rot[i].x);
+      const float u0 = to_f(kn[2 * i]), u1 = to_f(kn[2 * i + 1]);
+      kr[2 * i] = from_f<T>(u0 * rot[i].x - u1 * rot[i].y);
+      kr[2 * i + 1] = from_f<T>(u0 * rot[i].y + u1 * rot[i].x);
     }
     if (slot == 0) {
-      *reinterpret_cast<bf16x8*>(kb + (size_t)pos * HD + dl * 8) = kr;
-      *reinterpret_cast<bf16x8*>(vb + (size_t)pos * HD + dl * 8) = vn;
+      *reinterpret_cast<T8*>(kb + (size_t)pos * HD + dl * 8) = kr;
+      *reinterpret_cast<T8*>(vb + (size_t)pos * HD + dl * 8) = vn;
     }
     float kx[8], vx[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) { kx[e] = (float)kr[e]; vx[e] = (float)vn[e]; }
+    for (int e = 0; e < 8; ++e) { kx[e] = to_f(kr[e]); vx[e] = to_f(vn[e]); }
     const bool valid = slot == 0;
     LS_KEY_UPDATE(kx, vx, valid)
   }
@@ -138,8 +156,8 @@ k_attn_decode(const bf16* __restrict__ qkv, int qkv_stride, const float2* __rest
   _Pragma("unroll") for (int u = 0; u < U; ++u) {                                             \
     if ((j0_) + u * KPI < k_end) {                                                            \
       const int key_ = min((j0_) + u * KPI + slot, ctx - 1); /* clamped: a valid cache row */ \
-      kf[buf][u] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(kb + (size_t)key_ * HD + dl * 8)); \
-      vf[buf][u] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(vb + (size_t)key_ * HD + dl * 8)); \
+      kf[buf][u] = __builtin_nontemporal_load(reinterpret_cast<const T8*>(kb + (size_t)key_ * HD + dl * 8)); \
+      vf[buf][u] = __builtin_nontemporal_load(reinterpret_cast<const T8*>(vb + (size_t)key_ * HD + dl * 8)); \
     }                                                                                         \
   }
 #define LS_FOLD_GROUP(buf, j0_)                                                               \
@@ -148,15 +166,15 @@ k_attn_decode(const bf16* __restrict__ qkv, int qkv_stride, const float2* __rest
       const bool valid = ((j0_) + u * KPI + slot) < k_end;                                    \
       float kx[8], vx[8];                                                                     \
       _Pragma("unroll") for (int e = 0; e < 8; ++e) {                                         \
-        kx[e] = (float)kf[buf][u][e];                                                         \
-        vx[e] = (float)vf[buf][u][e];                                                         \
+        kx[e] = to_f(kf[buf][u][e]);                                                        \
+        vx[e] = to_f(vf[buf][u][e]);                                                        \
       }                                                                                       \
       LS_KEY_UPDATE(kx, vx, valid)                                                            \
     }                                                                                         \
   }
   {
     constexpr int STEP = KPI * U;
-    bf16x8 kf[2][U], vf[2][U];
+    T8 kf[2][U], vf[2][U];
     LS_LOAD_GROUP(0, k_begin)
     for (int j0 = k_begin; j0 < k_end; j0 += 2 * STEP) {
       LS_LOAD_GROUP(1, j0 + STEP)
@@ -208,28 +226,81 @@ k_attn_decode(const bf16* __restrict__ qkv, int qkv_stride, const float2* __rest
       num += sm_acc[w][g][d] * wt;
       den += sm_l[w][g] * wt;
     }
-    out[(size_t)r * (hkv * G * HD) + (size_t)(kh * G + g) * HD + d] = (bf16)(num / den);
+    if (nchunk == 1 || pos <= chunk_keys) {  // the sequence is this one chunk
+      out[(size_t)r * (hkv * G * HD) + (size_t)(kh * G + g) * HD + d] = from_f<T>(num / den);
+    } else {
+      float* pp = part + ((((size_t)r * hkv + kh) * G + g) * nchunk + blockIdx.z) * (HD + PART_HDR);
+      pp[PART_HDR + d] = num;
+      if (d == 0) { pp[0] = mm; pp[1] = den; }
+    }
   }
 }
 
-template <int HD, int G>
-void launch_g(const void* qkv, int qkv_stride, const float* cs, void* kc, void* vc, const int32_t* row_seq,
-              const int32_t* row_pos, int rows, int hkv, int max_seq, void* out, hipStream_t st) {
-  dim3 grid(rows, hkv);
-  k_attn_decode<HD, G><<<grid, waves_for(G) * 64, 0, st>>>((const bf16*)qkv, qkv_stride, (const float2*)cs, (bf16*)kc, (bf16*)vc,
-                                                  row_seq, row_pos, hkv * G, hkv, max_seq, (bf16*)out);
+// Second pass for sequences longer than one chunk: the chunks' partial results in chunk order.
+template <class T, int HD>
+__global__ void __launch_bounds__(HD)
+k_attn_decode_merge(const float* __restrict__ part, const int32_t* __restrict__ row_pos, int hq, int nchunk, int chunk_keys,
+                    T* __restrict__ out) {
+  const int r = blockIdx.x, h = blockIdx.y, d = threadIdx.x;
+  const int pos = row_pos[r];
+  if (pos <= chunk_keys) return;  // no room left, or the first pass wrote this row
+  const int nch = min((pos + chunk_keys - 1) / chunk_keys, nchunk);
+  const float* p0 = part + ((size_t)r * hq + h) * nchunk * (HD + PART_HDR);
+  float mm = -INFINITY;
+#pragma unroll 8
+  for (int c = 0; c < nch; ++c) mm = fmaxf(mm, p0[c * (HD + PART_HDR)]);
+  float num = 0.f, den = 0.f;
+#pragma unroll 8
+  for (int c = 0; c < nch; ++c) {
+    const float* p = p0 + c * (HD + PART_HDR);
+    const float wt = __expf(p[0] - mm);  // every chunk holds a visible key: finite
+    num += p[PART_HDR + d] * wt;
+    den += p[1] * wt;
+  }
+  out[((size_t)r * hq + h) * HD + d] = from_f<T>(num / den);
 }
 
-template <int HD>
-bool launch_hd(int g, const void* qkv, int qkv_stride, const float* cs, void* kc, void* vc, const int32_t* row_seq,
-               const int32_t* row_pos, int rows, int hkv, int max_seq, void* out, hipStream_t st) {
+// Chunks per sequence.  One workgroup per (sequence, kv head) reads its cache at about 50 GB/s, 10 us
+// for 1000 keys of 128 bf16 dimensions, so 128 of them saturate HBM and contexts are cut only
+// below that, up to WG_TARGET workgroups in all.  The chunks' start and the merge kernel cost about
+// 5 us: below CHUNK_FROM keys nothing is gained (8 x 32 heads, 600 keys: two chunks 20 us, one 15.4;
+// 32 heads, 3000 keys: 35 us whole, 11 + 4.7 in 16 chunks; a target of 256 workgroups does the same).
+constexpr int WG_TARGET = 512, CHUNK_MIN = 128, CHUNK_FROM = 640;
+int chunks_for(int rows, int hkv, int max_keys) {
+  const int base = rows * hkv;
+  if (base >= 128 || max_keys < CHUNK_FROM) return 1;
+  return std::max(1, std::min((WG_TARGET + base - 1) / base, max_keys / CHUNK_MIN));
+}
+
+struct Args {
+  const void* qkv;
+  int qkv_stride;
+  const float* cs;
+  void *kc, *vc;
+  const int32_t *row_seq, *row_pos;
+  int rows, hkv, max_seq;
+  void* out;
+  float* part;
+  int nchunk, chunk_keys;
+};
+
+template <class T, int HD, int G>
+void launch_g(const Args& a, hipStream_t st) {
+  k_attn_decode<T, HD, G><<<dim3(a.rows, a.hkv, a.nchunk), waves_for<T>(G) * 64, 0, st>>>(
+      (const T*)a.qkv, a.qkv_stride, (const float2*)a.cs, (T*)a.kc, (T*)a.vc, a.row_seq, a.row_pos, a.hkv * G, a.hkv, a.max_seq,
+      (T*)a.out, a.part, a.nchunk, a.chunk_keys);
+  if (a.nchunk > 1)
+    k_attn_decode_merge<T, HD><<<dim3(a.rows, a.hkv * G), HD, 0, st>>>(a.part, a.row_pos, a.hkv * G, a.nchunk, a.chunk_keys, (T*)a.out);
+}
+
+template <class T, int HD>
+void launch_hd(int g, const Args& a, hipStream_t st) {
   switch (g) {
-    case 1: launch_g<HD, 1>(qkv, qkv_stride, cs, kc, vc, row_seq, row_pos, rows, hkv, max_seq, out, st); return true;
-    case 2: launch_g<HD, 2>(qkv, qkv_stride, cs, kc, vc, row_seq, row_pos, rows, hkv, max_seq, out, st); return true;
-    case 4: launch_g<HD, 4>(qkv, qkv_stride, cs, kc, vc, row_seq, row_pos, rows, hkv, max_seq, out, st); return true;
-    case 8: launch_g<HD, 8>(qkv, qkv_stride, cs, kc, vc, row_seq, row_pos, rows, hkv, max_seq, out, st); return true;
+    case 1: launch_g<T, HD, 1>(a, st); break;
+    case 2: launch_g<T, HD, 2>(a, st); break;
+    case 4: launch_g<T, HD, 4>(a, st); break;
+    case 8: launch_g<T, HD, 8>(a, st); break;
   }
-  return false;
 }
 
 }  // namespace
@@ -239,13 +310,29 @@ bool attn_decode_supported(int hq, int hkv, int hd) {
   return (hd == 128 || hd == 64) && (g == 1 || g == 2 || g == 4 || g == 8);
 }
 
-void launch_attn_decode(const void* qkv, int qkv_stride, const float* cs_table, void* kc, void* vc,
+// covers every launch of at most `rows` sequences: rows * hkv * chunks stays below WG_TARGET + 128
+size_t attn_decode_scratch_bytes(int hq, int hkv, int hd, int max_keys) {
+  if (!attn_decode_supported(hq, hkv, hd) || max_keys < CHUNK_FROM) return 0;
+  return (size_t)(WG_TARGET + 128) * (hq / hkv) * (hd + PART_HDR) * sizeof(float);
+}
+
+void launch_attn_decode(uint32_t dt, const void* qkv, int qkv_stride, const float* cs_table, void* kc, void* vc,
                         const int32_t* row_seq, const int32_t* row_pos, int rows, int hq, int hkv, int hd,
-                        int max_seq, void* out, hipStream_t st) {
+                        int max_seq, void* out, hipStream_t st, int max_keys, float* scratch, size_t scratch_bytes) {
   if (rows <= 0) return;
-  const int g = hq / hkv;
-  if (hd == 128) launch_hd<128>(g, qkv, qkv_stride, cs_table, kc, vc, row_seq, row_pos, rows, hkv, max_seq, out, st);
-  else launch_hd<64>(g, qkv, qkv_stride, cs_table, kc, vc, row_seq, row_pos, rows, hkv, max_seq, out, st);
+  const int g = hq / hkv, keys = std::min(std::max(max_keys, 1), max_seq);
+  int nchunk = chunks_for(rows, hkv, keys);
+  int chunk_keys = (keys + nchunk - 1) / nchunk;
+  if (nchunk > 1 && (!scratch || (size_t)rows * hq * nchunk * (hd + PART_HDR) * sizeof(float) > scratch_bytes)) nchunk = 1;
+  if (nchunk == 1) chunk_keys = max_seq;
+  const Args a = {qkv, qkv_stride, cs_table, kc, vc, row_seq, row_pos, rows, hkv, max_seq, out, scratch, nchunk, chunk_keys};
+  if (dt == F32) {
+    if (hd == 128) launch_hd<float, 128>(g, a, st);
+    else launch_hd<float, 64>(g, a, st);
+  } else {
+    if (hd == 128) launch_hd<bf16, 128>(g, a, st);
+    else launch_hd<bf16, 64>(g, a, st);
+  }
 }
 
 }  // namespace ls

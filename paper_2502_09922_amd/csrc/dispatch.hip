@@ -43,13 +43,18 @@ void launch_attention_block(uint32_t dt, const int32_t* cu_seqlens, int batch, i
                            max_len, attn_scratch, attn_scratch_bytes);
     return;
   }
-  if (dt == BF16 && decode && attn_decode_supported(hq, hkv, hd)) {
-    launch_attn_decode(qkv, qkv_stride, cs_table, kcache, vcache, row_seq, row_pos, rows, hq, hkv, hd, max_seq, out, st);
+  if (decode && attn_decode_supported(hq, hkv, hd)) {
+    launch_attn_decode(dt, qkv, qkv_stride, cs_table, kcache, vcache, row_seq, row_pos, rows, hq, hkv, hd, max_seq, out, st,
+                       max_len, attn_scratch, attn_scratch_bytes);
     return;
   }
   if (!rope_done) launch_rope_append(dt, qkv, cs_table, row_seq, row_pos, rows, hq, hkv, hd, max_seq, kcache, vcache, st);
   if (dt == BF16 && !decode && attn_prefill_supported(hq, hkv, hd)) {
     launch_attn_prefill(qkv, qkv_stride, kcache, vcache, cu_seqlens, batch, max_len, hq, hkv, hd, max_seq, out, st);
+    return;
+  }
+  if (dt == F32 && !decode && attn_prefill_f32_supported(hq, hkv, hd)) {
+    launch_attn_prefill_f32(qkv, qkv_stride, kcache, vcache, cu_seqlens, batch, max_len, hq, hkv, hd, max_seq, out, st);
     return;
   }
   launch_attention_generic(dt, qkv, qkv_stride, kcache, vcache, row_seq, row_pos, rows, hq, hkv, hd, max_seq, out, st);

@@ -184,12 +184,15 @@ void launch_attention_block(uint32_t dt, const int32_t* cu_seqlens, int batch, i
                             hipStream_t st, float* attn_scratch = nullptr, size_t attn_scratch_bytes = 0,
                             bool rope_done = false);
 
-// bf16 split-KV decode attention fused with RoPE and the cache append; head_dim 64 or 128,
-// Hq/Hkv in {1,2,4,8}.
+// Split-KV decode attention fused with RoPE and the cache append (bf16 and fp32); head_dim 64 or
+// 128, Hq/Hkv in {1,2,4,8}.  max_keys: an upper bound of the cached keys of any row.  Where
+// rows x kv heads are few, contexts are cut into chunks that run as workgroups of their own and leave
+// partial results in `scratch` (attn_decode_scratch_bytes; none: one workgroup each).
 bool attn_decode_supported(int hq, int hkv, int hd);
-void launch_attn_decode(const void* qkv, int qkv_stride, const float* cs_table, void* kc, void* vc,
+size_t attn_decode_scratch_bytes(int hq, int hkv, int hd, int max_keys);
+void launch_attn_decode(uint32_t dt, const void* qkv, int qkv_stride, const float* cs_table, void* kc, void* vc,
                         const int32_t* row_seq, const int32_t* row_pos, int rows, int hq, int hkv, int hd,
-                        int max_seq, void* out, hipStream_t st);
+                        int max_seq, void* out, hipStream_t st, int max_keys, float* scratch, size_t scratch_bytes);
 
 // bf16 decode attention on the matrix cores for grouped-query models (head_dim 128,
 // 2 <= Hq/Hkv <= 16), fused with RoPE and the cache append like launch_attn_decode.
@@ -208,11 +211,10 @@ bool attn_prefill_supported(int hq, int hkv, int hd);
 void launch_attn_prefill(const void* qkv, int qkv_stride, const void* kc, const void* vc, const int32_t* cu_seqlens,
                          int batch, int max_len, int hq, int hkv, int hd, int max_seq, void* out, hipStream_t st);
 
-// bf16 split-KV decode attention; head_dim 64 or 128, Hq/Hkv in {1,2,4,8}.
-bool attn_decode_supported(int hq, int hkv, int hd);
-void launch_attn_decode(const void* qkv, int qkv_stride, const void* kc, const void* vc, const int32_t* row_seq,
-                        const int32_t* row_pos, int rows, int hq, int hkv, int hd, int max_seq, void* out,
-                        hipStream_t st);
+// The same in fp32; head_dim 64 or 128.
+bool attn_prefill_f32_supported(int hq, int hkv, int hd);
+void launch_attn_prefill_f32(const void* qkv, int qkv_stride, const void* kc, const void* vc, const int32_t* cu_seqlens,
+                             int batch, int max_len, int hq, int hkv, int hd, int max_seq, void* out, hipStream_t st);
 
 void launch_attention_generic(uint32_t dt, const void* qkv, int qkv_stride, const void* kcache,
                               const void* vcache, const int32_t* row_seq, const int32_t* row_pos, int rows,

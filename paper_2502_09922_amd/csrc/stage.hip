@@ -174,10 +174,12 @@ Carve carve(const ls_cfg* c, int lo, int hi) {
     if (part > w.splitk_bytes) w.splitk_bytes = part;
     w.splitk = take(w.splitk_bytes);
   }
-  // partial results of the grouped-query decode attention for contexts split over workgroups
+  // partial results of the decode attention for contexts split over workgroups
   w.attn_part_bytes = c->dtype == LS_DTYPE_BF16
                           ? ls::attn_decode_gqa_scratch_bytes((int)B, (int)c->n_q_heads, (int)c->n_kv_heads, (int)c->max_seq)
                           : 0;
+  const size_t chunks = ls::attn_decode_scratch_bytes((int)c->n_q_heads, (int)c->n_kv_heads, (int)c->head_dim, (int)c->max_seq);
+  if (chunks > w.attn_part_bytes) w.attn_part_bytes = chunks;
   w.attn_part = take(w.attn_part_bytes);
   (void)lo;
   w.total = off;
@@ -680,8 +682,9 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
       return TiledPlan{};
     return p;
   };
-  // attention of fp32 and of shapes without a fused kernel wants rotated rows and a filled cache
-  const bool attn_rotates = !prefill && dt == BF16 && (attn_decode_supported(hq, hkv, hd) || attn_decode_gqa_supported(hq, hkv, hd));
+  // attention without a fused kernel, and that of a prompt pass, wants rotated rows and a filled cache
+  const bool attn_rotates =
+      !prefill && (attn_decode_supported(hq, hkv, hd) || (dt == BF16 && attn_decode_gqa_supported(hq, hkv, hd)));
   const bool rope_tiles = !attn_rotates && hd % 16 == 0;  // a 16-column fragment inside one head
   const TiledPlan p_qkv = attn_rotates ? plan(TILED_STORE, qkv_cols, d) : rope_tiles ? plan(TILED_ROPE, qkv_cols, d) : TiledPlan{};
   const TiledPlan p_o = rows_one_pass && gsc.splitk ? plan(TILED_PART, d, hq * hd) : TiledPlan{};
@@ -730,7 +733,9 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
       PROBE(LS_OP_GEMM_QKV, launch_gemm(dt, EPI_STORE, y, tensor(b, 1), rows, qkv_cols, d, qkv, nullptr, st, &gsc));
     }
     PROBE(LS_OP_ATTENTION, launch_attention_block(dt, cu_dev, batch, max_len, qkv, cs, kc, vc, row_seq, row_pos, rows,
-                                                  hq, hkv, hd, c.max_seq, attn, st, nullptr, 0, roped));
+                                                  hq, hkv, hd, c.max_seq, attn, st,
+                                                  s->w.attn_part_bytes ? (float*)(ws + s->w.attn_part) : nullptr,
+                                                  s->w.attn_part_bytes, roped));
     PROBE(LS_OP_GEMM_O, residual(p_o, attn, tensor(b, 2), hq * hd, tensor(b, 3), false));
     if (p_gu.splits)
       PROBE(LS_OP_GEMM_GATEUP, launch_gemm_tiled(dt, TILED_SWIGLU, p_gu, y, tensor(b, 4), rows, F, d, hbuf, RopeAppend{}, st));
