@@ -27,7 +27,7 @@ TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool may_sp
   TiledPlan best;
   float best_us = 1e30f;
   if (gemm_tiled_supported(dt, epi, M, N, K)) {
-    static const int tiles[][2] = {{32, 64}, {32, 128}, {64, 64}, {64, 128}, {96, 128}, {128, 64}, {128, 128}, {160, 128}, {256, 128}};
+    static const int tiles[][2] = {{32, 64}, {32, 128}, {64, 64}, {64, 128}, {96, 128}, {128, 64}, {128, 128}, {160, 128}, {160, 256}, {256, 128}};
     const int kb = dt == F32 ? 32 : 64, nk = (K + kb - 1) / kb;
     for (const auto& t : tiles) {
       const int bm = t[0], bn = t[1];
@@ -64,13 +64,15 @@ bool launch_gemm_tiled(uint32_t dt, int epi, const TiledPlan& p, const void* A, 
 
 namespace {
 
-// One 256-thread workgroup per row; the row lives in registers (eight 16-byte pieces per thread, all
-// requested before the first use).  Bound by latency for few rows, by HBM for many: this one pass
-// stands for the separate load (or embedding gather), residual add, norm and store passes.
-template <class T, int SRC>
-__global__ void __launch_bounds__(256) k_rows(RowsArgs a) {
+// One workgroup per row; the row lives in registers (P 16-byte pieces per thread, P * NT * 4 columns at
+// most).  This one pass stands for the separate load (or embedding gather), residual add, norm and
+// store passes.  Many rows are bound by HBM: 256 threads, eight workgroups per CU.  With few rows it is the
+// latency of a chain of loads: 1024 threads, and the partial tiles four at a time in flight
+// (45..311 rows of 4096 columns, 4 to 8 splits: 8.5 us with 256 threads and one split after the other).
+template <class T, int SRC, int NT, int P>
+__global__ void __launch_bounds__(NT) k_rows(RowsArgs a) {
   typedef T T4 __attribute__((ext_vector_type(4)));
-  __shared__ float wsum[4];
+  __shared__ float wsum[NT / 64];
   const int r = blockIdx.x, nv = a.d >> 2;
   if constexpr (SRC != ROWS_RESID) {
     if (threadIdx.x == 0) {
@@ -110,23 +112,31 @@ __global__ void __launch_bounds__(256) k_rows(RowsArgs a) {
     return v;
   };
   float* xr = a.x + (size_t)r * a.d;
-  f32x4 v[8];
+  f32x4 v[P];
   if constexpr (SRC == ROWS_RESID) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int idx = threadIdx.x + 256 * i;
+    for (int i = 0; i < P; ++i) {
+      const int idx = threadIdx.x + NT * i;
       v[i] = idx < nv ? reinterpret_cast<const f32x4*>(xr)[idx] : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    for (int s = 0; s < a.splits; ++s) {
-      const f32x4* pr = reinterpret_cast<const f32x4*>(a.part + ((size_t)s * a.rows + r) * a.d);
-      f32x4 p[8];
+    const size_t split = (size_t)a.rows * a.d;
+    constexpr int U = P <= 2 ? 4 : 1;  // splits in flight
+    for (int s = 0; s < a.splits; s += U) {
+      f32x4 p[U][P];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int idx = threadIdx.x + 256 * i;
-        p[i] = idx < nv ? pr[idx] : f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int u = 0; u < U; ++u) {
+        const f32x4* pr = reinterpret_cast<const f32x4*>(a.part + (size_t)min(s + u, a.splits - 1) * split + (size_t)r * a.d);
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+          const int idx = threadIdx.x + NT * i;
+          p[u][i] = idx < nv ? pr[idx] : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
       }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] += p[i];
+      for (int u = 0; u < U; ++u)  // in split order
+        if (s + u < a.splits)
+#pragma unroll
+          for (int i = 0; i < P; ++i) v[i] += p[u][i];
     }
   } else {
     const T* src;
@@ -139,8 +149,8 @@ __global__ void __launch_bounds__(256) k_rows(RowsArgs a) {
     }
     const bool vec = (reinterpret_cast<uintptr_t>(src) & (sizeof(T4) - 1)) == 0;  // the caller's buffer may lie anywhere
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int idx = threadIdx.x + 256 * i;
+    for (int i = 0; i < P; ++i) {
+      const int idx = threadIdx.x + NT * i;
       v[i] = idx < nv ? widen(src + idx * 4, vec) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
   }
@@ -148,8 +158,8 @@ __global__ void __launch_bounds__(256) k_rows(RowsArgs a) {
     T* o = (T*)a.out + (size_t)r * a.d;
     const bool vec = (reinterpret_cast<uintptr_t>(o) & (sizeof(T4) - 1)) == 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int idx = threadIdx.x + 256 * i;
+    for (int i = 0; i < P; ++i) {
+      const int idx = threadIdx.x + NT * i;
       if (idx < nv) {
         T4 t;
 #pragma unroll
@@ -162,31 +172,33 @@ __global__ void __launch_bounds__(256) k_rows(RowsArgs a) {
     }
     return;
   }
+  if (!a.norm_only)
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int idx = threadIdx.x + 256 * i;
-    if (idx < nv) reinterpret_cast<f32x4*>(xr)[idx] = v[i];
-  }
+    for (int i = 0; i < P; ++i) {
+      const int idx = threadIdx.x + NT * i;
+      if (idx < nv) reinterpret_cast<f32x4*>(xr)[idx] = v[i];
+    }
   if (!a.gamma) return;
-  // RMSNorm, the sum of squares in the order of k_rmsnorm_vec: a norm folded into this pass and one
-  // made on its own give the same bits
-  f32x4 g[8];
+  f32x4 g[P];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int idx = threadIdx.x + 256 * i;
+  for (int i = 0; i < P; ++i) {
+    const int idx = threadIdx.x + NT * i;
     g[i] = idx < nv ? widen((const T*)a.gamma + idx * 4, true) : f32x4{0.f, 0.f, 0.f, 0.f};
   }
   float ss = 0.f;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) ss += v[i][0] * v[i][0] + v[i][1] * v[i][1] + v[i][2] * v[i][2] + v[i][3] * v[i][3];
+  for (int i = 0; i < P; ++i) ss += v[i][0] * v[i][0] + v[i][1] * v[i][1] + v[i][2] * v[i][2] + v[i][3] * v[i][3];
   ss = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = ss;
   __syncthreads();
-  const float inv = 1.0f / sqrtf(((wsum[0] + wsum[1]) + (wsum[2] + wsum[3])) / (float)a.d + a.eps);
+  float tot = 0.f;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) tot += wsum[w];
+  const float inv = 1.0f / sqrtf(tot / (float)a.d + a.eps);
   T* yr = (T*)a.y + (size_t)r * a.d;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int idx = threadIdx.x + 256 * i;
+  for (int i = 0; i < P; ++i) {
+    const int idx = threadIdx.x + NT * i;
     if (idx < nv) {
       T4 t;
 #pragma unroll
@@ -196,11 +208,19 @@ __global__ void __launch_bounds__(256) k_rows(RowsArgs a) {
   }
 }
 
+template <class T, int NT, int P>
+void launch_rows_n(int src, const RowsArgs& a, hipStream_t st) {
+  if (src == ROWS_RESID) k_rows<T, ROWS_RESID, NT, P><<<a.rows, NT, 0, st>>>(a);
+  else if (src == ROWS_HIDDEN) k_rows<T, ROWS_HIDDEN, NT, P><<<a.rows, NT, 0, st>>>(a);
+  else k_rows<T, ROWS_EMBED, NT, P><<<a.rows, NT, 0, st>>>(a);
+}
+
+// up to 512 rows every one of them fits the chip at once with 1024 threads.  The choice depends on
+// the call's rows only: a norm folded into a residual add and one launched on its own give the same bits.
 template <class T>
 void launch_rows_t(int src, const RowsArgs& a, hipStream_t st) {
-  if (src == ROWS_RESID) k_rows<T, ROWS_RESID><<<a.rows, 256, 0, st>>>(a);
-  else if (src == ROWS_HIDDEN) k_rows<T, ROWS_HIDDEN><<<a.rows, 256, 0, st>>>(a);
-  else k_rows<T, ROWS_EMBED><<<a.rows, 256, 0, st>>>(a);
+  if (a.rows <= 512) launch_rows_n<T, 1024, 2>(src, a, st);
+  else launch_rows_n<T, 256, 8>(src, a, st);
 }
 
 }  // namespace

@@ -149,6 +149,16 @@ __device__ __forceinline__ void read_frags(unsigned xa0, unsigned wa0, unsigned 
         : LS_O(w0[0]), LS_O(w0[1]), LS_O(w0[2]), LS_O(w0[3]), LS_O(x0[0]), LS_O(x0[1]), LS_O(x0[2]), LS_O(x0[3]),
         LS_O(w1[0]), LS_O(w1[1]), LS_O(w1[2]), LS_O(w1[3]), LS_O(x1[0]), LS_O(x1[1]), LS_O(x1[2]), LS_O(x1[3])
         : "v"(xa0), "v"(wa0), "v"(xa1), "v"(wa1) : "memory");
+  else if constexpr (TM == 5 && TN == 4)
+    asm volatile(
+        LS_R(0, 19, 0) LS_R(1, 19, 2048) LS_R(2, 19, 4096) LS_R(3, 19, 6144) LS_R(4, 18, 0) LS_R(5, 18, 2048)
+        LS_R(6, 18, 4096) LS_R(7, 18, 6144) LS_R(8, 18, 8192) LS_R(9, 21, 0) LS_R(10, 21, 2048) LS_R(11, 21, 4096)
+        LS_R(12, 21, 6144) LS_R(13, 20, 0) LS_R(14, 20, 2048) LS_R(15, 20, 4096) LS_R(16, 20, 6144)
+        LS_R(17, 20, 8192) LS_W
+        : LS_O(w0[0]), LS_O(w0[1]), LS_O(w0[2]), LS_O(w0[3]), LS_O(x0[0]), LS_O(x0[1]), LS_O(x0[2]), LS_O(x0[3]),
+        LS_O(x0[4]), LS_O(w1[0]), LS_O(w1[1]), LS_O(w1[2]), LS_O(w1[3]), LS_O(x1[0]), LS_O(x1[1]), LS_O(x1[2]),
+        LS_O(x1[3]), LS_O(x1[4])
+        : "v"(xa0), "v"(wa0), "v"(xa1), "v"(wa1) : "memory");
 }
 #undef LS_R
 #undef LS_W
@@ -361,6 +371,7 @@ bool launch_epi(const TiledPlan& p, const void* A, const void* W, int M, int N, 
   LS_TILE(128, 128, 2, 4, 2)
   LS_TILE(160, 128, 2, 5, 2)
   LS_TILE(256, 128, 4, 4, 4)
+  if constexpr (sizeof(T) == 2) LS_TILE(160, 256, 2, 5, 4)
   if constexpr (EPI != TILED_SWIGLU) {  // (gate and up need two fragments of a wavefront)
     LS_TILE(32, 64, 2, 1, 1)
     LS_TILE(64, 64, 2, 2, 1)

@@ -113,7 +113,7 @@ float gemm_mfma_us(int M, int N, int K, int ncols);
 // One pass over rows of width d (a multiple of 4, at most 8192).  Source: the residual rows plus `splits`
 // partial tiles, the call's hidden rows, or embedding rows; the latter two also write the call's
 // bookkeeping (row -> sequence and position, last rows, seq_lens).  Result: the stage's output rows
-// (out), or the residual rows x and, with a gain, their RMSNorm y.
+// (out), or the residual rows x (not with norm_only) and, with a gain, their RMSNorm y.
 enum RowsSrc : int { ROWS_RESID = 0, ROWS_HIDDEN = 1, ROWS_EMBED = 2 };
 struct RowsArgs {
   int rows = 0, d = 0;
@@ -130,6 +130,7 @@ struct RowsArgs {
   const void* gamma = nullptr;
   void* y = nullptr;
   float eps = 0.f;
+  bool norm_only = false;
 };
 bool rows_supported(int d);
 void launch_rows(uint32_t dt, int src, const RowsArgs& a, hipStream_t st);

@@ -691,6 +691,15 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   const TiledPlan p_gu = plan(TILED_SWIGLU, F, d);
   const TiledPlan p_dn = rows_one_pass && gsc.splitk ? plan(TILED_PART, d, F) : TiledPlan{};
 
+  auto norm = [&](const void* gamma) {
+    if (rows_one_pass) {
+      RowsArgs ra;
+      ra.rows = rows; ra.d = d; ra.x = x; ra.gamma = gamma; ra.y = y; ra.eps = c.rms_eps; ra.norm_only = true;
+      launch_rows(dt, ROWS_RESID, ra, st);
+    } else {
+      launch_rmsnorm(dt, x, gamma, y, rows, d, c.rms_eps, nullptr, st);
+    }
+  };
   // x += A W^T, then what follows a residual add: the rows' norm with `gamma` (y), the stage's
   // output (to_out), or nothing
   auto residual = [&](const TiledPlan& p, const void* A, const void* W, int K, const void* gamma, bool to_out) {
@@ -703,7 +712,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     } else {
       launch_gemm(dt, EPI_RESID, A, W, rows, d, K, nullptr, x, st, &gsc);
       if (to_out) launch_store_hidden(dt, x, out, (size_t)rows * d, st);
-      else if (gamma) launch_rmsnorm(dt, x, gamma, y, rows, d, c.rms_eps, nullptr, st);
+      else if (gamma) norm(gamma);
     }
   };
 
@@ -715,7 +724,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     char* kc = (char*)kv->k + li * kv_layer;
     char* vc = (char*)kv->v + li * kv_layer;
 
-    if (!y_ready) PROBE(LS_OP_NORM, launch_rmsnorm(dt, x, tensor(b, 0), y, rows, d, c.rms_eps, nullptr, st));
+    if (!y_ready) PROBE(LS_OP_NORM, norm(tensor(b, 0)));
     RopeAppend ra;
     ra.cs = cs; ra.row_seq = row_seq; ra.row_pos = row_pos;
     ra.hq = hq; ra.hkv = hkv; ra.hd = hd; ra.max_seq = c.max_seq;
