@@ -20,23 +20,28 @@ bool gemm_tiled_supported(uint32_t dt, int epi, int M, int N, int K) {
 // Time of a launch, in microseconds, from what the kernel's sweep over tiles showed (7B and 13B
 // layers, 1..2048 rows, cold weights): a k-step of a workgroup costs 0.05 us + 2.4 ns per tile
 // row it brings into LDS, whatever the arithmetic (64 x 64 0.41, 64 x 128 0.53, 128 x 128 0.67,
-// 160 x 128 0.76, 256 x 128 0.95 us measured), in fp32 at least what its matrix work takes at 0.55
-// of a TFLOP/s per CU; one workgroup fits a CU, so the launch takes as many rounds as its fullest XCD has
+// 160 x 128 0.76, 256 x 128 0.95 us measured), in fp32 at least its matrix work (64 x 64 at 0.4,
+// 64 x 128 at 0.46, 96 x 128 at 0.58, 128 x 128 at 0.64, 256 x 128 at 0.8 TFLOP/s per CU); one
+// workgroup fits a CU, so the launch takes as many rounds as its fullest XCD has
 // workgroups for its 32 CUs; every K split writes and reads an fp32 tile.
 TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool may_split, size_t scratch_bytes, float* us) {
   TiledPlan best;
   float best_us = 1e30f;
   if (gemm_tiled_supported(dt, epi, M, N, K)) {
-    static const int tiles[][2] = {{32, 64}, {32, 128}, {64, 64}, {64, 128}, {96, 128}, {128, 64}, {128, 128}, {160, 128}, {160, 256}, {256, 128}};
+    struct Shape { int bm, bn; bool f32, glu; };
+#define LS_TILE(bm_, bn_, wm_, tm_, tn_, f32_, glu_) {bm_, bn_, f32_, glu_},
+    static const Shape tiles[] = {LS_TILED_TILES(LS_TILE)};
+#undef LS_TILE
     const int kb = dt == F32 ? 32 : 64, nk = (K + kb - 1) / kb;
     for (const auto& t : tiles) {
-      const int bm = t[0], bn = t[1];
-      if (epi == TILED_SWIGLU && bn == 64) continue;
+      const int bm = t.bm, bn = t.bn;
+      if ((dt == F32 && !t.f32) || (epi == TILED_SWIGLU && !t.glu)) continue;
       const int ncols = epi == TILED_SWIGLU ? bn / 2 : bn;
       const int tiles_m = (M + bm - 1) / bm, panels = ((N + ncols - 1) / ncols + 7) / 8;
       float step = 0.05f + 0.0024f * (float)(bm + bn);
       if (dt == F32) {
-        const float mma = (float)bm * (float)bn * 64.f / 0.55e6f;
+        const float area = (float)(bm * bn);
+        const float mma = 64.f * area / (bm * bn >= 96 * 128 ? 0.45e6f + 10.7f * area : 0.36e6f + 12.f * area) + 0.05f;
         if (mma > step) step = mma;
       }
       for (int s = 1; s <= 8; ++s) {

@@ -28,7 +28,7 @@
 // kernel takes 27 / 10 / 36 / 19.  fp32: 321 rows 0.08-0.11 PFLOP/s of the 0.154 a large matrix
 // product reaches (the 64 x 64 tile on vector FMAs that did this before: 0.024).
 //
-// fp32 uses v_mfma_f32_16x16x4_f32: a lane's 16-byte chunk holds four consecutive k, and element
+// fp32 uses v_mfma_f32_16x16x4_f32 (large tiles: mma_split): a lane's 16-byte chunk holds four consecutive k, and element
 // e of all four lane groups together is one instruction's k = 4: both operands agree on which k
 // a lane's element e is, and a sum does not care in what order k is visited.  So the fp32
 // fragments are read from LDS exactly like the bf16 ones, four instructions per fragment pair.
@@ -45,6 +45,10 @@ namespace tiled {
 
 constexpr int ROWB = 128;  // bytes of a row in one k-step
 constexpr int WAVES = 8;
+// fp32 tiles of this many elements or more are multiplied as bf16 parts (mma_split); in smaller ones the
+// splitting, which every wavefront repeats for its operands, costs more than it saves (64 x 64: 320 rows
+// of the 7B QKV 425 us in fp32, 516 split; 96 x 128 411 and 349, 256 x 128 495 and 337).
+constexpr int SPLIT_FROM = 96 * 128;
 
 // Tile of 16 WM TM rows x 16 WN TN columns, wavefronts WM x WN, ring as deep as LDS allows (at most
 // eight stages: no shape gained from more).
@@ -79,6 +83,65 @@ __device__ __forceinline__ void mma(f32x4 (&acc)[TM][TN], const u32x4 (&w)[TN], 
       for (int j = 0; j < TN; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f32x4, w[j])[e], __builtin_bit_cast(f32x4, x[i])[e],
                                                          acc[i][j], 0, 0, 0);
+}
+
+// A finite fp32 value is exactly the sum of three bf16 values: the upper 16 bits of it, of what they
+// leave, and of what those leave (8 significand bits each).  part[0..2][p]: the three parts of the
+// pieces a and b of a row, two values per register.
+__device__ __forceinline__ void split3(u32x4 a, u32x4 b, u32x4 (&part)[3]) {
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    unsigned u0 = p < 2 ? a[2 * p] : b[2 * p - 4], u1 = p < 2 ? a[2 * p + 1] : b[2 * p - 3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      part[s][p] = __builtin_amdgcn_perm(u1, u0, 0x07060302);  // the upper halves of both
+      if (s < 2) {
+        u0 = __float_as_uint(__uint_as_float(u0) - __uint_as_float(u0 & 0xFFFF0000u));
+        u1 = __float_as_uint(__uint_as_float(u1) - __uint_as_float(u1 & 0xFFFF0000u));
+      }
+    }
+  }
+}
+
+// acc[i][j] += w[j] x[i]^T over a whole fp32 k-step, as six bf16 products of the operands' parts: all but
+// mid * lo, lo * mid and lo * lo, which are below 2^-24 of a product.  Why: v_mfma_f32_16x16x4_f32
+// moves 4 k in 32 cycles, the six bf16 instructions 32 k in 96; the splitting costs 11 vector
+// instructions per pair of values, about as long again (placing them between the matrix instructions
+// of the row block before changed nothing).  Error against float64 at K = 11008: 1.5e-6, with fp32
+// instructions 1.9e-6: fewer additions.  An infinity has no parts (inf - inf): a k-step that holds
+// one is multiplied in fp32.
+template <int TM, int TN>
+__device__ __forceinline__ void mma_split(f32x4 (&acc)[TM][TN], const u32x4 (&w0)[TN], const u32x4 (&x0)[TM],
+                                          const u32x4 (&w1)[TN], const u32x4 (&x1)[TM]) {
+  float big = 0.f;
+  auto seen = [&](u32x4 v) {
+    const f32x4 f = __builtin_bit_cast(f32x4, v);
+    big = fmaxf(fmaxf(fabsf(f[0]), fabsf(f[1])), big);
+    big = fmaxf(fmaxf(fabsf(f[2]), fabsf(f[3])), big);
+  };
+#pragma unroll
+  for (int i = 0; i < TM; ++i) { seen(x0[i]); seen(x1[i]); }
+#pragma unroll
+  for (int j = 0; j < TN; ++j) { seen(w0[j]); seen(w1[j]); }
+  if (__builtin_amdgcn_ballot_w64(big == INFINITY) != 0) {
+    mma<TM, TN>(acc, w0, x0, float{});
+    mma<TM, TN>(acc, w1, x1, float{});
+    return;
+  }
+  u32x4 xs[TM][3], ws[TN][3];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) split3(x0[i], x1[i], xs[i]);
+#pragma unroll
+  for (int j = 0; j < TN; ++j) split3(w0[j], w1[j], ws[j]);
+  constexpr int PW[6] = {2, 0, 1, 1, 0, 0}, PX[6] = {0, 2, 1, 0, 1, 0};  // smallest products first
+#pragma unroll
+  for (int p = 0; p < 6; ++p)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ws[j][PW[p]]),
+                                                            __builtin_bit_cast(bf16x8, xs[i][PX[p]]), acc[i][j], 0, 0, 0);
 }
 
 // The operand fragments of a k-step: of each half, TM activation row blocks and TN weight row blocks, 16 rows
@@ -177,6 +240,7 @@ k_gemm_tiled(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int
              int tiles_n, RopeAppend rp) {
   constexpr int NS = TL::NS, F = TL::F, TM = TL::TM, TN = TL::TN, WN = TL::WN, BM = TL::BM, BN = TL::BN;
   constexpr bool GLU = EPI == TILED_SWIGLU;
+  constexpr bool SPLIT = sizeof(T) == 4 && TL::BM * TL::BN >= SPLIT_FROM;
   constexpr int NCOLS = GLU ? BN / 2 : BN;
   constexpr int KB = ROWB / (int)sizeof(T);  // elements of a row in one k-step
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -272,9 +336,20 @@ k_gemm_tiled(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int
     const unsigned so = slot * TL::STAGE;
     u32x4 x0[TM], w0[TN], x1[TM], w1[TN];
     read_frags<TM, TN>(xb + so + c0, wb + so + c0, xb + so + c1, wb + so + c1, x0, w0, x1, w1);
-    mma<TM, TN>(acc, w0, x0, T{});
-    if (t + NS - 1 < n) fill(fslot, next_k());  // issued while the matrix pipe works on the first half
-    if (!ragged || t0 + t != nk - 1) mma<TM, TN>(acc, w1, x1, T{});  // chunks 4..7 of a ragged last k-step hold nothing
+    if constexpr (SPLIT) {
+      if (t + NS - 1 < n) fill(fslot, next_k());
+      if (ragged && t0 + t == nk - 1) {  // chunks 4..7 of a ragged last k-step hold nothing
+#pragma unroll
+        for (int i = 0; i < TM; ++i) x1[i] = u32x4{0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < TN; ++j) w1[j] = u32x4{0, 0, 0, 0};
+      }
+      mma_split<TM, TN>(acc, w0, x0, w1, x1);
+    } else {
+      mma<TM, TN>(acc, w0, x0, T{});
+      if (t + NS - 1 < n) fill(fslot, next_k());  // issued while the matrix pipe works on the first half
+      if (!ragged || t0 + t != nk - 1) mma<TM, TN>(acc, w1, x1, T{});  // see above
+    }
     slot = slot + 1 == NS ? 0 : slot + 1;
     fslot = fslot + 1 == NS ? 0 : fslot + 1;
   }
@@ -363,20 +438,13 @@ void launch_tile(const TiledPlan& p, const void* A, const void* W, int M, int N,
 template <class T, int EPI>
 bool launch_epi(const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out, const RopeAppend& rp,
                 hipStream_t st) {
-#define LS_TILE(bm_, bn_, wm_, tm_, tn_) \
-  if (p.bm == bm_ && p.bn == bn_) { launch_tile<T, Tile<wm_, tm_, tn_>, EPI>(p, A, W, M, N, K, out, rp, st); return true; }
-  LS_TILE(32, 128, 2, 1, 2)
-  LS_TILE(64, 128, 2, 2, 2)
-  LS_TILE(96, 128, 2, 3, 2)
-  LS_TILE(128, 128, 2, 4, 2)
-  LS_TILE(160, 128, 2, 5, 2)
-  LS_TILE(256, 128, 4, 4, 4)
-  if constexpr (sizeof(T) == 2) LS_TILE(160, 256, 2, 5, 4)
-  if constexpr (EPI != TILED_SWIGLU) {  // (gate and up need two fragments of a wavefront)
-    LS_TILE(32, 64, 2, 1, 1)
-    LS_TILE(64, 64, 2, 2, 1)
-    LS_TILE(128, 64, 2, 4, 1)
-  }
+#define LS_TILE(bm_, bn_, wm_, tm_, tn_, f32_, glu_)                                     \
+  if constexpr ((sizeof(T) == 2 || f32_) && (EPI != TILED_SWIGLU || glu_))               \
+    if (p.bm == bm_ && p.bn == bn_) {                                                    \
+      launch_tile<T, Tile<wm_, tm_, tn_>, EPI>(p, A, W, M, N, K, out, rp, st);           \
+      return true;                                                                       \
+    }
+  LS_TILED_TILES(LS_TILE)
 #undef LS_TILE
   return false;
 }

@@ -100,6 +100,19 @@ void launch_gemm_mfma_rope(const void* A, const void* W, int M, int N, int K, vo
 // Output: TILED_PART fp32 partial tiles part[split][M][N] (one split: an fp32 matrix), TILED_STORE
 // the storage type, TILED_SWIGLU silu(gate) * up, TILED_ROPE as launch_gemm_mfma_rope.
 enum TiledEpi : int { TILED_PART = 0, TILED_STORE = 1, TILED_SWIGLU = 2, TILED_ROPE = 3 };
+// The tiles there are: rows, weight rows, wavefront rows, 16-row fragments and 16-weight-row fragments of a
+// wavefront, in fp32 too, with SwiGLU too (gate and up are two fragments of one wavefront).
+#define LS_TILED_TILES(X)         \
+  X(32, 64, 2, 1, 1, true, false)  \
+  X(32, 128, 2, 1, 2, true, true)  \
+  X(64, 64, 2, 2, 1, true, false)  \
+  X(64, 128, 2, 2, 2, true, true)  \
+  X(96, 128, 2, 3, 2, true, true)  \
+  X(128, 64, 2, 4, 1, true, false) \
+  X(128, 128, 2, 4, 2, true, true) \
+  X(160, 128, 2, 5, 2, true, true) \
+  X(160, 256, 2, 5, 4, false, true) \
+  X(256, 128, 4, 4, 4, true, true)
 struct TiledPlan {
   int bm = 0, bn = 0, splits = 0;  // splits == 0: not supported
 };

@@ -90,3 +90,30 @@ def test_input_and_output_buffers_at_odd_addresses(name, batch):
     got = both(odd(x), odd(torch.zeros_like(x[:batch])))
     assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
     gpu.close()
+
+
+def test_fp32_infinities_pass_through_the_split_products():
+    """Large fp32 tiles are multiplied as bf16 parts, which an infinity does not have: a k-step that holds one is
+    multiplied in fp32, and every other column of the row stays what it is."""
+    import torch
+
+    shape = S("f32", 1, 512, 4, 4, 64, 512, 0)
+    gpu = make_gpu(shape, 11, 0, 1, 1, 512, 500)
+    view = gpu.block_view(0)
+    from paper_2502_09922_amd import binding as b
+    import ctypes as C
+
+    off, nb = C.c_size_t(), C.c_size_t()
+    b.check(b.lib.ls_block_tensor(C.byref(gpu.cfg), 0, 5, C.byref(off), C.byref(nb)))  # w_down [hidden, ffn]
+    wd = view[off.value : off.value + nb.value].view(torch.float32).view(512, 512)
+    x = to_dev(shape, synth.hidden_states(shape, 12, 500))
+    clean = gpu.prefill(x, [500]).clone()
+    h = gpu.workspace_region(b.LS_WS_FFN, 500).clone()
+    wd[7, 100] = float("inf")
+    got = gpu.prefill(x, [500])
+    others = torch.arange(512, device="cuda") != 7
+    scale = clean.abs().max()
+    assert ((got - clean)[:, others].abs() <= 1e-5 * scale).all()
+    want = torch.where(h[:, 100] > 0, float("inf"), -float("inf"))
+    assert torch.equal(got[:, 7], want)
+    gpu.close()
