@@ -1,4 +1,6 @@
-// bf16 weight-streaming GEMM for decode batches of 17..64 rows: C[M,N] = X[M,K] W[N,K]^T.
+// bf16 weight-streaming GEMM for decode batches of 17..64 rows: C[M,N] = X[M,K] W[N,K]^T.  Used where the
+// tiled GEMM's row kernel does not reach (hidden sizes above 8192) and for the logits of 17..64 rows of a
+// caller whose buffer is not 16-byte aligned.
 //
 // Still bound by streaming W out of HBM once, but at 17..64 rows the activation operand
 // is no longer negligible: if every wavefront fetched its own X fragments (as the kernel

@@ -10,9 +10,10 @@
 // Data path: both operands are K-contiguous; a k-step is 128 bytes of every row (64 bf16 or 32
 // fp32).  Rows go from global memory straight into LDS (global_load_lds_dwordx4) into a ring of
 // NS stages, 16-byte chunks XOR-swizzled by (row/2)&7 as in k_gemm_mfma, so that the 16 rows a
-// quarter-wave reads fall into different banks.  One barrier per k-step: behind it the stage of
+// quarter-wave reads fall into different banks.  One barrier per stage (one or two
+// k-steps): behind it the stage of
 // this k-step has landed for every wavefront (each waited for its own fills, counted) and the stage of the
-// previous one has been read by all, so its slot takes the fills of k-step t + NS - 1.
+// previous one has been read by all, so its slot takes the fills NS - 1 stages ahead.
 //
 // What bounds it: the fills.  With the LDS reads and the MFMAs taken out the kernel takes as long
 // as with them (1024 rows x 22016 x 4096, tiles of 128 x 128: 235 of 237 us), with the fills
@@ -56,10 +57,14 @@ template <int WM_, int TM_, int TN_>
 struct Tile {
   static constexpr int WM = WM_, WN = WAVES / WM_, TM = TM_, TN = TN_;
   static constexpr int BM = 16 * WM * TM, BN = 16 * WN * TN;
-  static constexpr int STAGE = (BM + BN) * ROWB;
+  static constexpr int SUB = (BM + BN) * ROWB;  // one k-step
+  // k-steps per barrier: where a step is short the barrier and the LDS latency behind it are a good part of it
+  // (64 x 64: 28 -> 24 us for 45 rows of the 7B QKV); larger tiles want the ring's finer steps (96 x 128: +30 %)
+  static constexpr int KS = BM + BN <= 192 ? 2 : 1;
+  static constexpr int STAGE = KS * SUB;
   static constexpr int FIT = 160 * 1024 / STAGE, NS = FIT > 8 ? 8 : FIT;
   static constexpr int SMEM = NS * STAGE;
-  static constexpr int NFILL = (BM + BN) / 8;              // fill instructions of a stage, eight rows each
+  static constexpr int NFILL = (BM + BN) / 8;              // fill instructions of a k-step, eight rows each
   static constexpr int F = (NFILL + WAVES - 1) / WAVES;    // ... of a wavefront
 };
 
@@ -238,7 +243,7 @@ template <class T, class TL, int EPI, bool ONCE>
 __global__ void __launch_bounds__(WAVES * 64, 2)
 k_gemm_tiled(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int K, void* __restrict__ outv, int tiles_m,
              int tiles_n, RopeAppend rp) {
-  constexpr int NS = TL::NS, F = TL::F, TM = TL::TM, TN = TL::TN, WN = TL::WN, BM = TL::BM, BN = TL::BN;
+  constexpr int NS = TL::NS, F = TL::F, KS = TL::KS, TM = TL::TM, TN = TL::TN, WN = TL::WN, BM = TL::BM, BN = TL::BN;
   constexpr bool GLU = EPI == TILED_SWIGLU;
   constexpr bool SPLIT = sizeof(T) == 4 && TL::BM * TL::BN >= SPLIT_FROM;
   constexpr int NCOLS = GLU ? BN / 2 : BN;
@@ -256,7 +261,7 @@ k_gemm_tiled(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int
   const int nk = (K + KB - 1) / KB;
   const bool ragged = K % KB != 0;  // the last k-step is only half there (K is a multiple of KB / 2)
   const int t0 = (int)((long)blockIdx.y * nk / gridDim.y), t1 = (int)((long)(blockIdx.y + 1) * nk / gridDim.y);
-  const int n = t1 - t0;
+  const int n = t1 - t0, ng = (n + KS - 1) / KS;  // k-steps, and groups of KS of them
   // ONCE: no other workgroup reads these weights.  Their fills are non-temporal, and the k-steps
   // are visited in cyclic order from a start of the tile's own: with rows a power of two apart
   // (hidden sizes 4096, 8192) workgroups in lock step would all ask the same memory channels.
@@ -287,7 +292,7 @@ k_gemm_tiled(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int
     const int grow = in < BM / 8 ? min(m0 + row, M - 1) : weight_row(row - BM);
     off[i] = (unsigned)((size_t)grow * K * sizeof(T)) + c * 16;
   }
-  auto fill = [&](int slot, int kt) {
+  auto fill = [&](int sub, int kt) {
     const size_t kofs = (size_t)kt * ROWB;
     if (ragged && kt == nk - 1) {
       // the last fill of all; chunks 4..7 lie past the end of the row: the lanes that fill them
@@ -301,7 +306,7 @@ k_gemm_tiled(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int
 #pragma unroll
     for (int i = 0; i < F; ++i) {
       const int in = min(wave + WAVES * i, TL::NFILL - 1);
-      lds_void* to = (lds_void*)(smem + slot * TL::STAGE + in * 1024);
+      lds_void* to = (lds_void*)(smem + sub * TL::SUB + in * 1024);
       if ((i + 1) * WAVES <= BM / 8 || (i * WAVES < BM / 8 && in < BM / 8))
         __builtin_amdgcn_global_load_lds((const void*)((const char*)A + kofs + off[i]), to, 16, 0, 0);
       else
@@ -320,35 +325,46 @@ k_gemm_tiled(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int
   const unsigned c0 = (unsigned)((lq ^ ((l16 >> 1) & 7)) << 4), c1 = c0 ^ 64;
   const unsigned xb = lds0 + (wm * 16 * TM + l16) * ROWB, wb = lds0 + BM * ROWB + (wn * 16 * TN + l16) * ROWB;
 
+  // the fills of group g (of the last group only what there is: waits for it count nothing as young)
+  auto fill_group = [&](int slot, int g) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      if (KS == 1 || g * KS + s < n) fill(slot * KS + s, next_k());
+  };
 #pragma unroll
   for (int p = 0; p < NS - 1; ++p)
-    if (p < n) fill(p, next_k());
+    if (p < ng) fill_group(p, p);
   int slot = 0, fslot = NS - 1;
-  for (int t = 0; t < n; ++t) {
+  for (int g = 0; g < ng; ++g) {
     asm volatile("" ::: "memory");
-    // own fills of this k-step have landed: those of the NS - 2 k-steps after it may still be on their way
-    if (t + NS - 1 <= n) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NS - 2) * F));
+    // own fills of this group have landed: those of the NS - 2 groups after it may still be on their way
+    if (g + NS - 1 < ng || (KS == 1 && g + NS - 1 == ng)) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NS - 2) * KS * F));
     else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
-    const unsigned so = slot * TL::STAGE;
-    u32x4 x0[TM], w0[TN], x1[TM], w1[TN];
-    read_frags<TM, TN>(xb + so + c0, wb + so + c0, xb + so + c1, wb + so + c1, x0, w0, x1, w1);
-    if constexpr (SPLIT) {
-      if (t + NS - 1 < n) fill(fslot, next_k());
-      if (ragged && t0 + t == nk - 1) {  // chunks 4..7 of a ragged last k-step hold nothing
 #pragma unroll
-        for (int i = 0; i < TM; ++i) x1[i] = u32x4{0, 0, 0, 0};
+    for (int s = 0; s < KS; ++s) {
+      const int t = g * KS + s;
+      if (KS > 1 && t >= n) break;
+      const unsigned so = (slot * KS + s) * TL::SUB;
+      u32x4 x0[TM], w0[TN], x1[TM], w1[TN];
+      read_frags<TM, TN>(xb + so + c0, wb + so + c0, xb + so + c1, wb + so + c1, x0, w0, x1, w1);
+      if constexpr (SPLIT) {
+        if (s == 0 && g + NS - 1 < ng) fill_group(fslot, g + NS - 1);
+        if (ragged && t0 + t == nk - 1) {  // chunks 4..7 of a ragged last k-step hold nothing
 #pragma unroll
-        for (int j = 0; j < TN; ++j) w1[j] = u32x4{0, 0, 0, 0};
+          for (int i = 0; i < TM; ++i) x1[i] = u32x4{0, 0, 0, 0};
+#pragma unroll
+          for (int j = 0; j < TN; ++j) w1[j] = u32x4{0, 0, 0, 0};
+        }
+        mma_split<TM, TN>(acc, w0, x0, w1, x1);
+      } else {
+        mma<TM, TN>(acc, w0, x0, T{});
+        if (s == 0 && g + NS - 1 < ng) fill_group(fslot, g + NS - 1);  // issued while the matrix pipe works on the first half
+        if (!ragged || t0 + t != nk - 1) mma<TM, TN>(acc, w1, x1, T{});  // see above
       }
-      mma_split<TM, TN>(acc, w0, x0, w1, x1);
-    } else {
-      mma<TM, TN>(acc, w0, x0, T{});
-      if (t + NS - 1 < n) fill(fslot, next_k());  // issued while the matrix pipe works on the first half
-      if (!ragged || t0 + t != nk - 1) mma<TM, TN>(acc, w1, x1, T{});  // see above
     }
     slot = slot + 1 == NS ? 0 : slot + 1;
     fslot = fslot + 1 == NS ? 0 : fslot + 1;

@@ -558,8 +558,14 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   } while (0)
   const size_t kv_layer = (size_t)c.max_batch * hkv * c.max_seq * hd * e;
 
+  // bf16 calls of up to 16 rows (12 where layers are wide) take the weight-streaming GEMMs, larger ones the
+  // tiled GEMM.  Steps of two layers, streaming / tiled: 7B 8 rows 178 / 217 us, 16 rows 215 / 241,
+  // 24 rows 285 / 270, 64 rows 388 / 352; 13B 8 rows 292 / 300, 16 rows 357 / 325, 64 rows 500 / 461;
+  // 70B 8 rows 599 / 615, 16 rows 650 / 628, 64 rows 749 / 677.
+  const bool few_rows = dt == BF16 && rows <= (d > 4096 ? 12 : 16);
+
   // ---- decode step with the RMSNorms folded into the weight-streaming GEMMs
-  const bool fused = !prefill && dt == BF16 && d % 16 == 0 &&
+  const bool fused = !prefill && dt == BF16 && d % 16 == 0 && (few_rows || !rows_supported(d)) &&
                      (attn_decode_supported(hq, hkv, hd) || attn_decode_gqa_supported(hq, hkv, hd)) &&
                      gemm_decode_fusable(rows, qkv_cols, d) && gemm_decode_fusable(rows, d, hq * hd) &&
                      gemm_decode_fusable(rows, F, d) && gemm_decode_fusable(rows, d, F);
@@ -629,7 +635,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     return LS_OK;
   }
 
-  // ---- prompt passes, and generation steps of fp32 or of more than 64 rows.  Rows of up to 8192
+  // ---- prompt passes, and generation steps of fp32 or of more than few rows.  Rows of up to 8192
   // columns (rows_one_pass) are loaded, added up and normalised by launch_rows, which takes the
   // norm that follows along wherever its gain is already there.
   if (timed) LS_HIP(hipEventRecord(s->pass_start, st));
@@ -668,13 +674,13 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     else launch_load_hidden(dt, in, x, (size_t)rows * d, st);
   }
 
-  // The tiled GEMM takes every fp32 projection it supports, and the bf16 ones of more than 16 rows in
-  // a prompt pass (64 in a generation step) where it is estimated faster than the 256 x 256 tiles.
+  // The tiled GEMM takes every fp32 projection it supports, and the bf16 ones of all but few rows
+  // where it is estimated faster than the 256 x 256 tiles.
   // Partial tiles of a generation step fit the static scratch too, so that both entry points take
   // the same plans.
   const size_t part_bytes = prefill || gsc.bytes < LS_STATIC_SCRATCH_BYTES ? gsc.bytes : LS_STATIC_SCRATCH_BYTES;
   auto plan = [&](int epi, int N, int K) {
-    if (dt == BF16 && rows <= (prefill ? 16 : 64)) return TiledPlan{};
+    if (few_rows) return TiledPlan{};
     float us = 0.f;
     const TiledPlan p = gemm_tiled_plan(dt, epi, rows, N, K, epi == TILED_PART, part_bytes, &us);
     if (dt == BF16 && rows > 64 && gemm_mfma_supported(rows, N, K) &&
@@ -769,7 +775,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     LS_HIP(gate(*hb, st));  // gate: head block has landed
     float* logits = logits_out ? logits_out : (float*)(ws + s->w.logits);
     launch_rmsnorm(dt, x, base + sp[0].off, y, batch, d, c.rms_eps, last_rows, st);
-    const TiledPlan p_head = (dt == F32 || batch > 64) && ((uintptr_t)logits & 15) == 0
+    const TiledPlan p_head = (dt == F32 || batch > (d > 4096 ? 12 : 16)) && ((uintptr_t)logits & 15) == 0
                                  ? gemm_tiled_plan(dt, TILED_PART, batch, (int)c.vocab, d, false, 0, nullptr)
                                  : TiledPlan{};
     if (p_head.splits) launch_gemm_tiled(dt, TILED_PART, p_head, y, base + sp[1].off, batch, c.vocab, d, logits, RopeAppend{}, st);
