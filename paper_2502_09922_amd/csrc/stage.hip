@@ -189,12 +189,22 @@ Carve carve(const ls_cfg* c, int lo, int hi) {
 enum BlockState { NOT_LOADED = 0, ENQUEUED = 1 };
 constexpr int PROBE_CAP = 512;
 
+// A layer block is copied as four pieces in the order the layer reads them: attention norm and QKV weights, O weights
+// and FFN norm, gate-up weights, down weights.  The layer starts with the first piece's arrival, and
+// when the last block of a stage has landed only its down projection is left to do (7B layers, 8 x 512
+// tokens: 0.35 ms behind the copy instead of 1.4).
+constexpr int PIECES = 4;
+constexpr size_t PIECES_FROM = 8u << 20;  // smaller blocks go in one copy: a piece costs a few microseconds of its own
+
 struct Block {
   int layer;
   size_t off, bytes;
   int state;
   bool timed;  // copy_start / loaded bracket a copy made with profiling on
   hipEvent_t copy_start, loaded;
+  // A layer block copied in pieces (pieces_of): piece[g] is recorded behind piece g, `loaded` behind the last.
+  bool in_pieces;
+  hipEvent_t piece[PIECES - 1];
   // the host has seen `loaded` complete since the block was enqueued: the bytes are in HBM for
   // all work enqueued from now on, on any stream, and the gate needs no event wait any more
   bool landed;
@@ -209,11 +219,11 @@ inline bool landed(Block& b) {
   return b.landed;
 }
 
-// The gate: order stream `st` after the block's copy (nothing to enqueue once the copy is
-// known to have completed).
-inline hipError_t gate(Block& b, hipStream_t st) {
+// The gate: order stream `st` after the copy of the block's pieces up to `piece` (nothing to enqueue once
+// the whole copy is known to have completed).
+inline hipError_t gate(Block& b, hipStream_t st, int piece = PIECES - 1) {
   if (landed(b)) return hipSuccess;
-  return hipStreamWaitEvent(st, b.loaded, 0);
+  return hipStreamWaitEvent(st, b.in_pieces && piece < PIECES - 1 ? b.piece[piece] : b.loaded, 0);
 }
 
 }  // namespace
@@ -345,6 +355,8 @@ ls_status ls_stage_create(const ls_cfg* cfg, int lo, int hi, void* weight_slab, 
     for (auto& b : s->blocks) {
       if (b.copy_start) (void)hipEventDestroy(b.copy_start);
       if (b.loaded) (void)hipEventDestroy(b.loaded);
+      for (auto e : b.piece)
+        if (e) (void)hipEventDestroy(e);
     }
     for (auto e : s->comp_start) (void)hipEventDestroy(e);
     for (auto e : s->comp_end) (void)hipEventDestroy(e);
@@ -357,7 +369,10 @@ ls_status ls_stage_create(const ls_cfg* cfg, int lo, int hi, void* weight_slab, 
     delete s;
   };
   for (auto& b : s->blocks) {
-    if (hipEventCreate(&b.copy_start) != hipSuccess || hipEventCreate(&b.loaded) != hipSuccess) {
+    bool ok = hipEventCreate(&b.copy_start) == hipSuccess && hipEventCreate(&b.loaded) == hipSuccess;
+    if (b.layer >= lo && b.layer < hi)
+      for (auto& e : b.piece) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    if (!ok) {
       cleanup();
       return fail(LS_ERR_HIP, "ls_stage_create: hipEventCreate failed");
     }
@@ -401,6 +416,8 @@ void ls_stage_destroy(ls_stage* s) {
   for (auto& b : s->blocks) {
     (void)hipEventDestroy(b.copy_start);
     (void)hipEventDestroy(b.loaded);
+    for (auto e : b.piece)
+      if (e) (void)hipEventDestroy(e);
   }
   for (auto e : s->comp_start) (void)hipEventDestroy(e);
   for (auto e : s->comp_end) (void)hipEventDestroy(e);
@@ -444,8 +461,19 @@ ls_status ls_stage_load_block(ls_stage* s, const void* host_ptr, int layer, void
     LS_HIP(hipEventRecord(b->copy_start, st));
     if (s->origin_block < 0) s->origin_block = (int)(b - s->blocks.data());
   }
-  LS_HIP(hipMemcpyAsync(s->slab + b->off, host_ptr, b->bytes, hipMemcpyHostToDevice, st));
-  LS_HIP(hipEventRecord(b->loaded, st));
+  b->in_pieces = b->piece[0] && b->bytes >= PIECES_FROM;
+  if (b->in_pieces) {
+    TensorSpan sp[6];
+    block_tensors(&s->cfg, layer, sp, nullptr);
+    const size_t cut[PIECES + 1] = {0, sp[2].off, sp[4].off, sp[5].off, b->bytes};
+    for (int g = 0; g < PIECES; ++g) {
+      LS_HIP(hipMemcpyAsync(s->slab + b->off + cut[g], (const char*)host_ptr + cut[g], cut[g + 1] - cut[g], hipMemcpyHostToDevice, st));
+      LS_HIP(hipEventRecord(g + 1 < PIECES ? b->piece[g] : b->loaded, st));
+    }
+  } else {
+    LS_HIP(hipMemcpyAsync(s->slab + b->off, host_ptr, b->bytes, hipMemcpyHostToDevice, st));
+    LS_HIP(hipEventRecord(b->loaded, st));
+  }
   b->state = ENQUEUED;
   b->landed = false;
   return LS_OK;
@@ -471,6 +499,7 @@ ls_status ls_stage_load_layers(ls_stage* s, const void* host_ptr, int first, int
   for (int l = first; l <= last; ++l) {
     Block* b = s->find(l);
     b->timed = s->profiling;
+    b->in_pieces = false;
     LS_HIP(hipEventRecord(b->loaded, st));
     b->state = ENQUEUED;
     b->landed = false;
@@ -484,6 +513,7 @@ ls_status ls_stage_adopt_block(ls_stage* s, int layer, void* hip_stream) {
   if (!b) return fail(LS_ERR_BLOCK_RANGE, "ls_stage_adopt_block: block %d is not held by stage [%d,%d)", layer, s->lo, s->hi);
   if (b->state != NOT_LOADED) return fail(LS_ERR_ALREADY_LOADED, "ls_stage_adopt_block: block %d already enqueued", layer);
   b->timed = false;
+  b->in_pieces = false;
   LS_HIP(hipEventRecord(b->loaded, (hipStream_t)hip_stream));
   b->state = ENQUEUED;
   b->landed = false;
@@ -724,8 +754,9 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
 
   for (int li = 0; li < n_layers; ++li) {
     Block& b = s->blocks[s->layer0 + li];
-    // the gate: nothing of this layer may read its weights before its block has landed
-    LS_HIP(gate(b, st));
+    // the gates: nothing of this layer may read weights before their piece of the block has landed
+    // (a timed layer starts with its whole block, so that its time is that of its kernels)
+    LS_HIP(gate(b, st, timed ? PIECES - 1 : 0));
     if (timed) LS_HIP(hipEventRecord(s->comp_start[li], st));
     char* kc = (char*)kv->k + li * kv_layer;
     char* vc = (char*)kv->v + li * kv_layer;
@@ -751,7 +782,9 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
                                                   hq, hkv, hd, c.max_seq, attn, st,
                                                   s->w.attn_part_bytes ? (float*)(ws + s->w.attn_part) : nullptr,
                                                   s->w.attn_part_bytes, roped));
+    LS_HIP(gate(b, st, 1));
     PROBE(LS_OP_GEMM_O, residual(p_o, attn, tensor(b, 2), hq * hd, tensor(b, 3), false));
+    LS_HIP(gate(b, st, 2));
     if (p_gu.splits)
       PROBE(LS_OP_GEMM_GATEUP, launch_gemm_tiled(dt, TILED_SWIGLU, p_gu, y, tensor(b, 4), rows, F, d, hbuf, RopeAppend{}, st));
     else
@@ -761,6 +794,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     const bool more = li + 1 < n_layers;
     Block* next = more ? &s->blocks[s->layer0 + li + 1] : nullptr;
     y_ready = more && p_dn.splits && landed(*next) && !norm_alone(*next);
+    LS_HIP(gate(b, st, 3));
     PROBE(LS_OP_GEMM_DOWN, residual(p_dn, hbuf, tensor(b, 5), F, y_ready ? tensor(*next, 0) : nullptr, !more && !s->last));
     if (timed) LS_HIP(hipEventRecord(s->comp_end[li], st));
   }
