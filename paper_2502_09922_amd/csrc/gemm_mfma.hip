@@ -162,7 +162,8 @@ __device__ __forceinline__ bf16x4 to_bf16x4(f32x4 v) {
   return y;
 }
 
-constexpr int EPI_ROPE = 4;  // EPI_STORE with RoPE and the KV-cache append (QKV projection of a prompt pass)
+constexpr int EPI_RESID_OUT = 5;  // EPI_RESID whose sums are the stage's output
+constexpr int EPI_ROPE = 4;       // EPI_STORE with RoPE and the KV-cache append (QKV projection of a prompt pass)
 
 // Epilogue of one tile, for one 64-column slice of a wavefront's 128 x 128 results: the four
 // fragments accf[i][J0 .. J0 + 3], whose element r is
@@ -383,8 +384,13 @@ __device__ __forceinline__ void store_tile_f32(f32x4 (&acc)[8][8], int m0, int n
 // fp32 read-modify-write of the residual rows for a wavefront's whole 128 x 128 results, 16
 // bytes per lane: the old values of RB row blocks (8 RB loads of 16 bytes per lane) are
 // requested before the first sum is stored; the operand fragments' registers are free by then.
+// OUT: the sums are the stage's output rows, rounded to bf16 into `out`, and the residual rows stay as they
+// are: no store pass reads them again (13B shape, 32768 rows: that pass took 237 us, half of its bytes
+// were written by this epilogue).
+template <bool OUT>
 __device__ __forceinline__ void add_tile_to_residual(f32x4 (&acc)[8][8], int m0, int n0, int M, int N,
-                                                     float* __restrict__ resid, int wm, int wn, int l16, int lq) {
+                                                     float* __restrict__ resid, bf16* __restrict__ out, int wm, int wn,
+                                                     int l16, int lq) {
   constexpr int RB = 4;
   const bool vec = (N & 3) == 0;
   asm volatile("" : "+v"(l16), "+v"(lq));  // see store_tile
@@ -404,6 +410,20 @@ __device__ __forceinline__ void add_tile_to_residual(f32x4 (&acc)[8][8], int m0,
 #pragma unroll
           for (int r = 0; r < 4; ++r) old[ii][j][r] = (m < M && n + r < N) ? p[r] : 0.f;
       }
+    if constexpr (OUT) {
+      // two fragments side by side give eight consecutive columns per lane (N is a multiple of 32: both
+      // fragments are inside the matrix or outside)
+#pragma unroll
+      for (int ii = 0; ii < RB; ++ii)
+#pragma unroll
+        for (int jp = 0; jp < 4; ++jp) {
+          const int m = m0 + wm * 128 + (i2 + ii) * 16 + l16, n = n0 + wn * 128 + jp * 32;
+          const u32x4 o = side_by_side(to_bf16x4(old[ii][2 * jp] + acc[i2 + ii][2 * jp]),
+                                       to_bf16x4(old[ii][2 * jp + 1] + acc[i2 + ii][2 * jp + 1]));  // every lane takes part
+          if (m < M && n < N) *reinterpret_cast<u32x4*>(out + (size_t)m * N + n + 8 * lq) = o;
+        }
+      continue;
+    }
 #pragma unroll
     for (int ii = 0; ii < RB; ++ii)
 #pragma unroll
@@ -684,7 +704,9 @@ k_gemm_mfma(const bf16* __restrict__ A, const bf16* __restrict__ W, int M, int N
     LS_WAITL(0)
     LS_SB()
     if constexpr (EPI == EPI_RESID) {
-      add_tile_to_residual(acc, m0, n0, M, N, resid, wm, wn, l16, lq);
+      add_tile_to_residual<false>(acc, m0, n0, M, N, resid, nullptr, wm, wn, l16, lq);
+    } else if constexpr (EPI == EPI_RESID_OUT) {
+      add_tile_to_residual<true>(acc, m0, n0, M, N, resid, (bf16*)outv, wm, wn, l16, lq);
     } else if constexpr (EPI == EPI_F32) {
       store_tile_f32(acc, m0, n0, M, N, (float*)outv, wm, wn, l16, lq);
     } else {
@@ -762,6 +784,14 @@ bool gemm_mfma_rope_supported(int M, int N, int K, int hq, int hkv, int hd) {
 void launch_gemm_mfma_rope(const void* A, const void* W, int M, int N, int K, void* out, const RopeAppend& rope,
                            hipStream_t st) {
   launch_t<EPI_ROPE>(A, W, M, N, K, out, nullptr, st, rope);
+}
+
+bool gemm_mfma_resid_out_supported(int M, int N, int K, const void* out) {
+  return gemm_mfma_supported(M, N, K) && N % 32 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+}
+
+void launch_gemm_mfma_resid_out(const void* A, const void* W, int M, int N, int K, const float* resid, void* out, hipStream_t st) {
+  launch_t<EPI_RESID_OUT>(A, W, M, N, K, out, const_cast<float*>(resid), st);
 }
 
 void launch_gemm_mfma(Epilogue epi, const void* A, const void* W, int M, int N, int K, void* out, float* resid,

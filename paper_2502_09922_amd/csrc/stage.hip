@@ -745,6 +745,8 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
       launch_gemm_tiled(dt, TILED_PART, p, A, W, rows, d, K, gsc.splitk, RopeAppend{}, st);
       ra.part = gsc.splitk; ra.splits = p.splits;
       launch_rows(dt, ROWS_RESID, ra, st);
+    } else if (to_out && dt == BF16 && rows > 64 && gemm_mfma_resid_out_supported(rows, d, K, out)) {
+      launch_gemm_mfma_resid_out(A, W, rows, d, K, x, out, st);
     } else {
       launch_gemm(dt, EPI_RESID, A, W, rows, d, K, nullptr, x, st, &gsc);
       if (to_out) launch_store_hidden(dt, x, out, (size_t)rows * d, st);
