@@ -10,12 +10,19 @@ bool launch_gemm_tiled_bf16(int epi, const TiledPlan& p, const void* A, const vo
 bool launch_gemm_tiled_f32(int epi, const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out,
                            const RopeAppend& rope, hipStream_t st);
 
+int gemm_rows_f32_splits(int epi, int M, int N, int K, bool may_split, size_t scratch_bytes);
+bool launch_gemm_rows_f32(int epi, const void* A, const void* W, int M, int N, int K, int splits, void* out, hipStream_t st);
+
 bool gemm_tiled_supported(uint32_t dt, int epi, int M, int N, int K) {
   const size_t e = dt == F32 ? 4 : 2, wrows = (size_t)N * (epi == TILED_SWIGLU ? 2 : 1);
   // half k-steps; whole 16-column fragments; 32-bit byte offsets into both operands
   return M >= 1 && N >= 16 && N % 16 == 0 && K >= 64 && K % (int)(64 / e) == 0 && wrows * K * e < (1ull << 32) &&
          (size_t)M * K * e < (1ull << 32);
 }
+
+// One fp32 layer of the 7B shape on vector FMAs / through the tiles: 1 row 176 / 244 us, 4 rows and the LM head
+// 299 / 352, 8 rows 219 / 250; the FMAs of each further row cost 6 us, the tiles nothing up to 32.
+constexpr int ROWS_F32_MAX = 8;
 
 // Time of a launch, in microseconds, from what the kernel's sweep over tiles showed (7B and 13B
 // layers, 1..2048 rows, cold weights): a k-step of a workgroup costs 0.05 us + 2.4 ns per tile
@@ -27,6 +34,13 @@ bool gemm_tiled_supported(uint32_t dt, int epi, int M, int N, int K) {
 TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool may_split, size_t scratch_bytes, float* us) {
   TiledPlan best;
   float best_us = 1e30f;
+  if (dt == F32 && M <= ROWS_F32_MAX) {  // bm == 0: the kernel for few fp32 rows
+    best.splits = gemm_rows_f32_splits(epi, M, N, K, may_split, scratch_bytes);
+    if (best.splits) {
+      if (us) *us = 0.f;
+      return best;
+    }
+  }
   if (gemm_tiled_supported(dt, epi, M, N, K)) {
     struct Shape { int bm, bn; bool f32, glu; };
 #define LS_TILE(bm_, bn_, wm_, tm_, tn_, f32_, glu_) {bm_, bn_, f32_, glu_},
@@ -63,6 +77,7 @@ TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool may_sp
 bool launch_gemm_tiled(uint32_t dt, int epi, const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out,
                        const RopeAppend& rope, hipStream_t st) {
   if (!p.splits) return false;
+  if (!p.bm) return launch_gemm_rows_f32(epi, A, W, M, N, K, p.splits, out, st);
   return dt == F32 ? launch_gemm_tiled_f32(epi, p, A, W, M, N, K, out, rope, st)
                    : launch_gemm_tiled_bf16(epi, p, A, W, M, N, K, out, rope, st);
 }
