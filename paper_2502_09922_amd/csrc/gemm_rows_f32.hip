@@ -103,11 +103,12 @@ bool launch_e(const float* A, const float* W, int M, int N, int K, int splits, f
 }  // namespace
 
 // 0: not supported.  512 workgroups (two per CU) where K is long enough, at least two pieces of a row per part.
-int gemm_rows_f32_splits(int epi, int M, int N, int K, bool may_split, size_t scratch_bytes) {
+int gemm_rows_f32_splits(int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes) {
   if (M < 1 || M > 8 || epi == TILED_ROPE || K < 4 || K % 4) return 0;
+  if (to_scratch && (size_t)M * N * sizeof(float) > scratch_bytes) return 0;
   const int wgs = (N + 15) / 16, nb = (K / 4 + 63) / 64;
   int s = 1;
-  while (may_split && s < 8 && wgs * s < 512 && nb >= 4 * s && (size_t)(2 * s) * M * N * sizeof(float) <= scratch_bytes) s *= 2;
+  while (to_scratch && s < 8 && wgs * s < 512 && nb >= 4 * s && (size_t)(2 * s) * M * N * sizeof(float) <= scratch_bytes) s *= 2;
   return s;
 }
 

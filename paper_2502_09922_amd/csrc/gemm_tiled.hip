@@ -10,7 +10,7 @@ bool launch_gemm_tiled_bf16(int epi, const TiledPlan& p, const void* A, const vo
 bool launch_gemm_tiled_f32(int epi, const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out,
                            const RopeAppend& rope, hipStream_t st);
 
-int gemm_rows_f32_splits(int epi, int M, int N, int K, bool may_split, size_t scratch_bytes);
+int gemm_rows_f32_splits(int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes);
 bool launch_gemm_rows_f32(int epi, const void* A, const void* W, int M, int N, int K, int splits, void* out, hipStream_t st);
 
 bool gemm_tiled_supported(uint32_t dt, int epi, int M, int N, int K) {
@@ -31,11 +31,11 @@ constexpr int ROWS_F32_MAX = 8;
 // 64 x 128 at 0.46, 96 x 128 at 0.58, 128 x 128 at 0.64, 256 x 128 at 0.8 TFLOP/s per CU); one
 // workgroup fits a CU, so the launch takes as many rounds as its fullest XCD has
 // workgroups for its 32 CUs; every K split writes and reads an fp32 tile.
-TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool may_split, size_t scratch_bytes, float* us) {
+TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us) {
   TiledPlan best;
   float best_us = 1e30f;
   if (dt == F32 && M <= ROWS_F32_MAX) {  // bm == 0: the kernel for few fp32 rows
-    best.splits = gemm_rows_f32_splits(epi, M, N, K, may_split, scratch_bytes);
+    best.splits = gemm_rows_f32_splits(epi, M, N, K, to_scratch, scratch_bytes);
     if (best.splits) {
       if (us) *us = 0.f;
       return best;
@@ -59,7 +59,8 @@ TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool may_sp
         if (mma > step) step = mma;
       }
       for (int s = 1; s <= 8; ++s) {
-        if (s > 1 && (!may_split || (size_t)s * M * N * sizeof(float) > scratch_bytes || nk < 2 * s)) break;
+        // partial tiles, also those of a single split, have to fit the scratch
+        if ((to_scratch && (size_t)s * M * N * sizeof(float) > scratch_bytes) || (s > 1 && (!to_scratch || nk < 2 * s))) break;
         const long per_xcd = (long)panels * tiles_m * s;
         const float rounds = (float)((per_xcd + 31) / 32);
         const float t_us = rounds * ((float)((nk + s - 1) / s) * step + 2.5f) + (float)s * (float)M * (float)N * 8.f / 4e6f;

@@ -119,8 +119,9 @@ enum TiledEpi : int { TILED_PART = 0, TILED_STORE = 1, TILED_SWIGLU = 2, TILED_R
 struct TiledPlan {
   int bm = 0, bn = 0, splits = 0;  // splits == 0: not supported
 };
-// The plan with the shortest estimated time, which `us` receives; partial tiles have to fit scratch_bytes.
-TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool may_split, size_t scratch_bytes, float* us);
+// The plan with the shortest estimated time, which `us` receives.  to_scratch: the output is partial tiles,
+// splits * M * N floats, which have to fit scratch_bytes; otherwise it is the caller's matrix and K is not cut.
+TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us);
 bool launch_gemm_tiled(uint32_t dt, int epi, const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out,
                        const RopeAppend& rope, hipStream_t st);
 // Estimated time of launch_gemm_mfma (ncols: output columns of a tile, 256 or with SwiGLU 128).

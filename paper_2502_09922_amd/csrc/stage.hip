@@ -171,6 +171,8 @@ Carve carve(const ls_cfg* c, int lo, int hi) {
     // partial tiles of the tiled GEMMs that write residual rows: at most eight splits of every row
     size_t part = 8 * T * d * sizeof(float);
     if (part > TILED_SCRATCH_MAX) part = TILED_SCRATCH_MAX;
+    // fp32 has no other fast GEMM: one partial tile of every row always fits
+    if (c->dtype == LS_DTYPE_F32 && part < T * d * sizeof(float)) part = T * d * sizeof(float);
     if (part > w.splitk_bytes) w.splitk_bytes = part;
     w.splitk = take(w.splitk_bytes);
   }

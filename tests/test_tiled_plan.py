@@ -1,0 +1,55 @@
+"""The tiled GEMM's choice of tile and K split, on the CPU: partial tiles fit the scratch they are given whatever the
+shape (a single split's too), only tiles that exist for the type and epilogue are chosen, what is not
+partial tiles is not split, and shapes the kernel does not take get no plan."""
+import ctypes as C
+import random
+
+from paper_2502_09922_amd import binding
+
+F32, BF16 = 0, 1
+PART, STORE, SWIGLU, ROPE = range(4)
+
+
+class Plan(C.Structure):
+    _fields_ = [("bm", C.c_int), ("bn", C.c_int), ("splits", C.c_int)]
+
+
+def plan(dt, epi, m, n, k, to_scratch, scratch):
+    fn = binding.lib._ZN2ls15gemm_tiled_planEjiiiibmPf
+    fn.restype = Plan
+    fn.argtypes = [C.c_uint32, C.c_int, C.c_int, C.c_int, C.c_int, C.c_bool, C.c_size_t, C.POINTER(C.c_float)]
+    us = C.c_float()
+    return fn(dt, epi, m, n, k, to_scratch, scratch, C.byref(us))
+
+
+def test_plans_over_random_shapes():
+    rng = random.Random(7)
+    seen = set()
+    for _ in range(20000):
+        dt, epi = rng.choice([F32, BF16]), rng.choice([PART, STORE, SWIGLU, ROPE])
+        m = int(2 ** rng.uniform(0, 15))
+        n, k = 16 * rng.randint(1, 1800), rng.choice([16, 32, 128]) * rng.randint(1, 220)
+        scratch = rng.choice([0, 1 << 16, 16 << 20, 64 << 20])
+        p = plan(dt, epi, m, n, k, epi == PART, scratch)
+        if not p.splits:
+            continue
+        if epi == PART:
+            assert p.splits * m * n * 4 <= scratch, (dt, m, n, k, scratch, p.splits)
+        else:
+            assert p.splits == 1
+        if p.bm == 0:
+            assert dt == F32 and m <= 8 and epi != ROPE and k % 4 == 0
+            continue
+        assert k % (16 if dt == F32 else 32) == 0 and k >= 64
+        assert not (dt == F32 and p.bn == 256) and not (epi == SWIGLU and p.bn == 64)
+        assert p.splits == 1 or -(-k // (32 if dt == F32 else 64)) >= 2 * p.splits  # k-steps of a split
+        seen.add((dt, p.bm, p.bn))
+    assert len(seen) >= 14  # the rule spreads over the tiles there are
+
+
+def test_no_plan_for_what_the_kernel_does_not_take():
+    big = 64 << 20
+    for dt, m, n, k in ((BF16, 40, 100, 512), (BF16, 40, 512, 48), (F32, 40, 512, 72), (F32, 40, 8, 64), (BF16, 40, 1 << 20, 1 << 14)):
+        assert plan(dt, STORE, m, n, k, False, 0).splits == 0
+    assert plan(BF16, PART, 3000, 8192, 8192, True, big).splits == 0  # 98 MB of partial tiles
+    assert plan(BF16, PART, 2000, 8192, 8192, True, big).splits == 1
