@@ -23,10 +23,10 @@
 // prefetch of later lines (loads return in order, so the fills behind it wait for it: up to 1.6 x
 // slower for few rows); the two halves of a workgroup a phase apart, one reading LDS while the
 // other multiplies (no gain, 256-row tiles 8 % slower).
-// Measured with cold weights, 7B layer (QKV / O / gate-up / down): 100 rows 34 / 13 / 45 / 23 us,
-// 311 rows 49 / 20 / 91 / 40, 1024 rows 118 / 38 / 177 / 88 (0.9-1.05 PFLOP/s); k_gemm_mfma takes
+// Measured with cold weights, 7B layer (QKV / O / gate-up / down): 100 rows 33 / 13 / 45 / 22 us,
+// 311 rows 48 / 19 / 75 / 39, 1024 rows 118 / 37 / 177 / 86 (0.9-1.05 PFLOP/s); k_gemm_mfma takes
 // 104 / 106 / 102 / 242 for anything up to 256 rows and k_gemm_skinny 41 / 17 / 52 / 38 for 45, where this
-// kernel takes 27 / 10 / 36 / 19.  fp32: 321 rows 0.08-0.11 PFLOP/s of the 0.154 a large matrix
+// kernel takes 24 / 10 / 36 / 19.  fp32: 321 rows 0.08-0.11 PFLOP/s of the 0.154 a large matrix
 // product reaches (the 64 x 64 tile on vector FMAs that did this before: 0.024).
 //
 // fp32 uses v_mfma_f32_16x16x4_f32 (large tiles: mma_split): a lane's 16-byte chunk holds four consecutive k, and element
@@ -280,10 +280,11 @@ k_gemm_tiled(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int
       return min(n0 + r, N - 1);
     }
   };
-  // This wavefront's fills: instructions wave, wave + 8, ... of the stage's (activation rows first,
-  // eight rows each; where their number is no multiple of the wavefronts', some fill the last
-  // rows twice with the same bytes, so that every wavefront has as many to wait for).  Lane l
-  // supplies physical chunk l%8 of row l/8: byte offsets from the operand, both below 4 GB.
+  // This wavefront's fills: instructions wave, wave + 8, ... of a k-step's (activation rows first, eight
+  // rows each).  Lane l supplies physical chunk l%8 of row l/8: byte offsets from the operand, both
+  // below 4 GB.  Where their number is no multiple of the wavefronts', some have one less to wait
+  // for; letting them fill the last rows once more instead stalls the CU's cache on lines that are
+  // on their way already (32 x 64 tiles, 32 rows of the 13B QKV: 39 us against 32).
   unsigned off[F];
 #pragma unroll
   for (int i = 0; i < F; ++i) {
@@ -305,11 +306,11 @@ k_gemm_tiled(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int
     }
 #pragma unroll
     for (int i = 0; i < F; ++i) {
-      const int in = min(wave + WAVES * i, TL::NFILL - 1);
+      const int in = wave + WAVES * i;
       lds_void* to = (lds_void*)(smem + sub * TL::SUB + in * 1024);
       if ((i + 1) * WAVES <= BM / 8 || (i * WAVES < BM / 8 && in < BM / 8))
         __builtin_amdgcn_global_load_lds((const void*)((const char*)A + kofs + off[i]), to, 16, 0, 0);
-      else
+      else if ((i + 1) * WAVES <= TL::NFILL || in < TL::NFILL)
         __builtin_amdgcn_global_load_lds((const void*)((const char*)W + kofs + off[i]), to, 16, 0, ONCE ? 2 : 0);
     }
   };
@@ -338,8 +339,12 @@ k_gemm_tiled(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int
   for (int g = 0; g < ng; ++g) {
     asm volatile("" ::: "memory");
     // own fills of this group have landed: those of the NS - 2 groups after it may still be on their way
-    if (g + NS - 1 < ng || (KS == 1 && g + NS - 1 == ng)) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NS - 2) * KS * F));
-    else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    if (g + NS - 1 < ng || (KS == 1 && g + NS - 1 == ng)) {
+      if (TL::NFILL % WAVES == 0 || wave < TL::NFILL % WAVES) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NS - 2) * KS * F));
+      else __builtin_amdgcn_s_waitcnt(waitcnt_vm((NS - 2) * KS * (F - 1)));
+    } else {
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    }
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);

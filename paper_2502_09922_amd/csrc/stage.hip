@@ -590,11 +590,11 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   } while (0)
   const size_t kv_layer = (size_t)c.max_batch * hkv * c.max_seq * hd * e;
 
-  // bf16 calls of up to 16 rows (12 where layers are wide) take the weight-streaming GEMMs, larger ones the
-  // tiled GEMM.  Steps of two layers, streaming / tiled: 7B 8 rows 178 / 217 us, 16 rows 215 / 241,
-  // 24 rows 285 / 270, 64 rows 388 / 352; 13B 8 rows 292 / 300, 16 rows 357 / 325, 64 rows 500 / 461;
-  // 70B 8 rows 599 / 615, 16 rows 650 / 628, 64 rows 749 / 677.
-  const bool few_rows = dt == BF16 && rows <= (d > 4096 ? 12 : 16);
+  // bf16 calls of up to 16 rows (8 where layers are wide) take the weight-streaming GEMMs, larger ones the
+  // tiled GEMM.  Steps of two layers, streaming / tiled: 7B 8 rows 178 / 204 us, 16 rows 216 / 227,
+  // 24 rows 285 / 270, 64 rows 388 / 352; 13B 5 rows 265 / 263, 12 rows 317 / 284, 64 rows 500 / 461;
+  // 70B 8 rows 594 / 601, 12 rows 618 / 604, 64 rows 749 / 677.
+  const bool few_rows = dt == BF16 && rows <= (d > 4096 ? 8 : 16);
 
   // ---- decode step with the RMSNorms folded into the weight-streaming GEMMs
   const bool fused = !prefill && dt == BF16 && d % 16 == 0 && (few_rows || !rows_supported(d)) &&
@@ -813,7 +813,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     LS_HIP(gate(*hb, st));  // gate: head block has landed
     float* logits = logits_out ? logits_out : (float*)(ws + s->w.logits);
     launch_rmsnorm(dt, x, base + sp[0].off, y, batch, d, c.rms_eps, last_rows, st);
-    const TiledPlan p_head = (dt == F32 || batch > (d > 4096 ? 12 : 16)) && ((uintptr_t)logits & 15) == 0
+    const TiledPlan p_head = (dt == F32 || batch > (d > 4096 ? 8 : 16)) && ((uintptr_t)logits & 15) == 0
                                  ? gemm_tiled_plan(dt, TILED_PART, batch, (int)c.vocab, d, false, 0, nullptr)
                                  : TiledPlan{};
     if (p_head.splits) launch_gemm_tiled(dt, TILED_PART, p_head, y, base + sp[1].off, batch, c.vocab, d, logits, RopeAppend{}, st);
