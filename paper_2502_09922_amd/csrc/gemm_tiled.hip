@@ -255,3 +255,24 @@ void launch_rows(uint32_t dt, int src, const RowsArgs& a, hipStream_t st) {
 }
 
 }  // namespace ls
+
+// For the tests, which choose a tile themselves to reach its edges; not declared in ls_stage.h.  Both return 0
+// where there is no plan, or where the launch would not be one that the kernels take.
+extern "C" int ls_test_tiled_plan(uint32_t dt, int epi, int M, int N, int K, int to_scratch, size_t scratch_bytes, int* plan) {
+  const ls::TiledPlan p = ls::gemm_tiled_plan(dt, epi, M, N, K, to_scratch != 0, scratch_bytes, nullptr);
+  plan[0] = p.bm; plan[1] = p.bn; plan[2] = p.splits;
+  return p.splits != 0;
+}
+
+// A [M,K], W [N,K] (SwiGLU: [2N,K]), out [M,N] in the storage type, TILED_PART: fp32 [splits][M][N].
+extern "C" int ls_test_tiled_gemm(uint32_t dt, int epi, int bm, int bn, int splits, const void* A, const void* W, int M, int N,
+                                  int K, void* out, void* hip_stream) {
+  using namespace ls;
+  const int nk = dt == F32 ? (K + 31) / 32 : (K + 63) / 64;
+  if ((dt != F32 && dt != BF16) || epi < TILED_PART || epi > TILED_SWIGLU || !A || !W || !out) return 0;
+  if (!gemm_tiled_supported(dt, epi, M, N, K) || splits < 1 || splits > 8) return 0;
+  if (splits > 1 && (epi != TILED_PART || nk < 2 * splits)) return 0;
+  TiledPlan p;
+  p.bm = bm; p.bn = bn; p.splits = splits;
+  return bm > 0 && launch_gemm_tiled(dt, epi, p, A, W, M, N, K, out, RopeAppend{}, (hipStream_t)hip_stream);
+}

@@ -10,16 +10,17 @@ F32, BF16 = 0, 1
 PART, STORE, SWIGLU, ROPE = range(4)
 
 
-class Plan(C.Structure):
-    _fields_ = [("bm", C.c_int), ("bn", C.c_int), ("splits", C.c_int)]
+class Plan:
+    def __init__(self, bm, bn, splits):
+        self.bm, self.bn, self.splits = bm, bn, splits
 
 
 def plan(dt, epi, m, n, k, to_scratch, scratch):
-    fn = binding.lib._ZN2ls15gemm_tiled_planEjiiiibmPf
-    fn.restype = Plan
-    fn.argtypes = [C.c_uint32, C.c_int, C.c_int, C.c_int, C.c_int, C.c_bool, C.c_size_t, C.POINTER(C.c_float)]
-    us = C.c_float()
-    return fn(dt, epi, m, n, k, to_scratch, scratch, C.byref(us))
+    fn = binding.lib.ls_test_tiled_plan
+    fn.argtypes = [C.c_uint32, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_int * 3)]
+    out = (C.c_int * 3)()
+    fn(dt, epi, m, n, k, to_scratch, scratch, C.byref(out))
+    return Plan(*out)
 
 
 def test_plans_over_random_shapes():
