@@ -48,7 +48,7 @@ constexpr int ROWB = 128;  // bytes of a row in one k-step
 constexpr int WAVES = 8;
 // fp32 tiles of this many elements or more are multiplied as bf16 parts (mma_split); in smaller ones the
 // splitting, which every wavefront repeats for its operands, costs more than it saves (64 x 64: 320 rows
-// of the 7B QKV 425 us in fp32, 516 split; 96 x 128 411 and 349, 256 x 128 495 and 337).
+// of the 7B QKV 425 us in fp32, 516 split; 96 x 128 411 and 382, 256 x 128 495 and 370).
 constexpr int SPLIT_FROM = 96 * 128;
 
 // Tile of 16 WM TM rows x 16 WN TN columns, wavefronts WM x WN, ring as deep as LDS allows (at most
@@ -90,31 +90,45 @@ __device__ __forceinline__ void mma(f32x4 (&acc)[TM][TN], const u32x4 (&w)[TN], 
                                                          acc[i][j], 0, 0, 0);
 }
 
-// A finite fp32 value is exactly the sum of three bf16 values: the upper 16 bits of it, of what they
-// leave, and of what those leave (8 significand bits each).  part[0..2][p]: the three parts of the
-// pieces a and b of a row, two values per register.
+// An fp32 value as the sum of three bf16 values, each the rest rounded to the nearest: of a value in [1, 2) the
+// second is at most 2^-8, the third at most 2^-17 (a multiple of 2^-23), both of either sign.  (Henry, Tang,
+// Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations",
+// ARITH 2019.)  The sum is exact from 2^-102 on; of smaller values what lies below 2^-126 may be lost, as
+// bf16 parts end there.  part[0..2][p]: the three parts of the pieces a and b of a row, two values per register.
+// The rest is taken by v_dot2 (-1 * part + 0 * its neighbour + value, exact), one instruction where widening
+// and subtracting are two; seven instructions per pair of values.
 __device__ __forceinline__ void split3(u32x4 a, u32x4 b, u32x4 (&part)[3]) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  // (-1, 0) and (0, -1).  In registers: a constant in the instruction is not read as a pair of bf16 values.
+  unsigned take0 = 0x0000BF80u, take1 = 0xBF800000u;
+  asm("" : "+s"(take0), "+s"(take1));
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
-    unsigned u0 = p < 2 ? a[2 * p] : b[2 * p - 4], u1 = p < 2 ? a[2 * p + 1] : b[2 * p - 3];
+    float f0 = __uint_as_float(p < 2 ? a[2 * p] : b[2 * p - 4]), f1 = __uint_as_float(p < 2 ? a[2 * p + 1] : b[2 * p - 3]);
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
-      part[s][p] = __builtin_amdgcn_perm(u1, u0, 0x07060302);  // the upper halves of both
-      if (s < 2) {
-        u0 = __float_as_uint(__uint_as_float(u0) - __uint_as_float(u0 & 0xFFFF0000u));
-        u1 = __float_as_uint(__uint_as_float(u1) - __uint_as_float(u1 & 0xFFFF0000u));
-      }
+    for (int s = 0; s < 2; ++s) {
+      const bf16x2 h = __builtin_convertvector((f32x2{f0, f1}), bf16x2);
+      part[s][p] = __builtin_bit_cast(unsigned, h);
+      f0 = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, take0), f0, false);
+      f1 = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, take1), f1, false);
     }
+    part[2][p] = __builtin_amdgcn_perm(__float_as_uint(f1), __float_as_uint(f0), 0x07060302);  // fits: the upper halves of both
   }
 }
 
 // acc[i][j] += w[j] x[i]^T over a whole fp32 k-step, as six bf16 products of the operands' parts: all but
-// mid * lo, lo * mid and lo * lo, which are below 2^-24 of a product.  Why: v_mfma_f32_16x16x4_f32
-// moves 4 k in 32 cycles, the six bf16 instructions 32 k in 96; the splitting costs 11 vector
-// instructions per pair of values, about as long again (placing them between the matrix instructions
-// of the row block before changed nothing).  Error against float64 at K = 11008: 1.5e-6, with fp32
-// instructions 1.9e-6: fewer additions.  An infinity has no parts (inf - inf): a k-step that holds
-// one is multiplied in fp32.
+// mid * lo, lo * mid and lo * lo, together at most 2^-24 of a product and of either sign, so that sums of them
+// have no bias (parts cut off instead of rounded have the sign of their value: up to 7.8 x 2^-24 of a
+// product, all towards zero; all products but lo * lo in that form cost more than rounding).  The bf16
+// instruction rounds to nearest like the fp32 one, except that an accumulator smaller than the product
+// loses what lies below the result's last bit, towards minus infinity: the first additions of a sum may be
+// off by a whole last bit.
+// Why: v_mfma_f32_16x16x4_f32 moves 4 k in 32 cycles, the six bf16 instructions 32 k in 96; the splitting is
+// about as long again.  321 rows of the 7B shape, QKV / gate-up / down / O: 371 / 578 / 312 / 144 us, with parts
+// cut off 333 / 529 / 282 / 130.
+// A k-step is multiplied in fp32 where a lane of the wavefront holds an infinity, a value that rounds to one or
+// one whose products could overflow by their parts (2^63 and more).  So the last bits of a row may depend
+// on the rows beside it.
 template <int TM, int TN>
 __device__ __forceinline__ void mma_split(f32x4 (&acc)[TM][TN], const u32x4 (&w0)[TN], const u32x4 (&x0)[TM],
                                           const u32x4 (&w1)[TN], const u32x4 (&x1)[TM]) {
@@ -128,7 +142,7 @@ __device__ __forceinline__ void mma_split(f32x4 (&acc)[TM][TN], const u32x4 (&w0
   for (int i = 0; i < TM; ++i) { seen(x0[i]); seen(x1[i]); }
 #pragma unroll
   for (int j = 0; j < TN; ++j) { seen(w0[j]); seen(w1[j]); }
-  if (__builtin_amdgcn_ballot_w64(big == INFINITY) != 0) {
+  if (__builtin_amdgcn_ballot_w64(big >= 0x1p63f) != 0) {
     mma<TM, TN>(acc, w0, x0, float{});
     mma<TM, TN>(acc, w1, x1, float{});
     return;
