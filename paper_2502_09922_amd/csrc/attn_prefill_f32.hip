@@ -15,6 +15,10 @@
 // Bound by latency at the lengths fp32 is used for (two sequences of 131..190 tokens, 32 heads: 192
 // workgroups).  One wavefront per (row, head) that visited the keys one after the other took 300 us
 // there.
+//
+// A masked key's probability is zero, but zero times an infinite or NaN value is NaN: where a tile that
+// some row of the workgroup sees in part holds such a value, its value product is done on vector FMAs
+// over the visible keys only, so that no row is touched by keys behind it.
 #include "kernels.hpp"
 #include "device_util.hpp"
 
@@ -32,6 +36,7 @@ k_attn_prefill_f32(const float* __restrict__ qkv, int qkv_stride, const float* _
   constexpr int PIECES = BKV * HD / 4 / 256;  // 16-byte pieces of a tile per thread and operand
   constexpr int C = HD / 16;
   __shared__ __attribute__((aligned(16))) float ks[BKV * ROW], vs[BKV * ROW];
+  __shared__ int odd[4];  // wavefront w loaded an infinite or NaN value of the tile
   const int qi = blockIdx.x % nq, h = (blockIdx.x / nq) % hq, b = blockIdx.x / (nq * hq), kh = h / (hq / hkv);
   const int row0 = cu[b], len = cu[b + 1] - row0;
   const int qt = (len + BQ - 1) / BQ - 1 - qi;  // longest tiles first
@@ -71,7 +76,18 @@ k_attn_prefill_f32(const float* __restrict__ qkv, int qkv_stride, const float* _
       *reinterpret_cast<f32x4*>(ks + at) = kr[i];
       *reinterpret_cast<f32x4*>(vs + at) = vr[i];
     }
+    const bool part_seen = t0 + BKV - 1 > qt * BQ;  // workgroup-uniform
+    if (part_seen) {
+      float nul = 0.f;  // NaN from an infinity or NaN on
+#pragma unroll
+      for (int i = 0; i < PIECES; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) nul = fmaf(vr[i][e], 0.f, nul);
+      const bool any = __builtin_amdgcn_ballot_w64(!(nul == 0.f)) != 0;
+      if (lane == 0) odd[wave] = any;
+    }
     __syncthreads();
+    const bool by_key = part_seen && (odd[0] | odd[1] | odd[2] | odd[3]);
     if (t + 1 < ntk) load(t0 + BKV);
     if (t0 > q0 + 15) continue;  // above all rows of this wavefront
     f32x4 s[2];
@@ -109,6 +125,23 @@ k_attn_prefill_f32(const float* __restrict__ qkv, int qkv_stride, const float* _
         s[kt][e] = __builtin_amdgcn_exp2f((s[kt][e] - m_new) * cexp);
         l_run += s[kt][e];
       }
+    if (by_key) {
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          for (int g = 0; g < 4; ++g) {
+            const int key = kt * 16 + 4 * g + e;
+            const float p = __shfl(s[kt][e], 16 * g + l16);
+            if (t0 + key <= qpos) {
+#pragma unroll
+              for (int c = 0; c < C; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[c][r] = fmaf(p, vs[key * ROW + c * 16 + 4 * lq + r], o[c][r]);
+            }
+          }
+      continue;
+    }
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
