@@ -119,15 +119,20 @@ k_attn_decode(const T* __restrict__ qkv, int qkv_stride, const float2* __restric
     _Pragma("unroll") for (int off = LPK / 2; off; off >>= 1) s_ += __shfl_xor(s_, off);     \
     s_ = (valid) ? s_ : -INFINITY;                                                           \
     const float mn_ = fmaxf(m[g], s_);                                                       \
-    /* mn_ == -inf only while this slot has seen no valid key: keep everything at zero */    \
+    /* mn_ == -inf only while this slot has seen no valid key: keep everything at zero (a     \
+       NaN score, which no maximum shows, must not count as none) */                         \
     const float corr_ = (mn_ == -INFINITY) ? 1.f : __expf(m[g] - mn_);                       \
-    const float p_ = (mn_ == -INFINITY) ? 0.f : __expf(s_ - mn_);                            \
+    const float p_ = (s_ == -INFINITY) ? 0.f : __expf(s_ - mn_);                             \
     l[g] = l[g] * corr_ + p_;                                                                \
     _Pragma("unroll") for (int e = 0; e < 8; ++e) acc[g][e] = acc[g][e] * corr_ + p_ * vx[e]; \
     m[g] = mn_;                                                                              \
   }
 
-  // the new row first (wave 0): rotate k, round both to bf16, append to the cache, attend to
+  // fp32: a slot without a key takes zeros for its values, as zero times an infinite one is NaN.  (bf16,
+  // whose registers are full, multiplies what it loaded: NaN instead of an infinity there.)
+#define LS_SEEN(v) (sizeof(T) == 4 && !valid ? 0.f : (v))
+
+  // the new row first (wave 0): rotate k, round both to storage type, append to the cache, attend to
   // it.  Done before the cache stream so that the rotation table is dead inside the loop.
   if (wave == 0 && blockIdx.z == 0) {
     const T8 kn = *reinterpret_cast<const T8*>(row + (size_t)(hq + kh) * HD + dl * 8);
@@ -143,10 +148,10 @@ k_attn_decode(const T* __restrict__ qkv, int qkv_stride, const float2* __restric
       *reinterpret_cast<T8*>(kb + (size_t)pos * HD + dl * 8) = kr;
       *reinterpret_cast<T8*>(vb + (size_t)pos * HD + dl * 8) = vn;
     }
+    const bool valid = slot == 0;
     float kx[8], vx[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) { kx[e] = to_f(kr[e]); vx[e] = to_f(vn[e]); }
-    const bool valid = slot == 0;
+    for (int e = 0; e < 8; ++e) { kx[e] = to_f(kr[e]); vx[e] = LS_SEEN(to_f(vn[e])); }
     LS_KEY_UPDATE(kx, vx, valid)
   }
   // the cache is read once per step: non-temporal loads.  The cache stream is software pipelined: the loads of the next group of U*KPI keys are
@@ -166,8 +171,8 @@ k_attn_decode(const T* __restrict__ qkv, int qkv_stride, const float2* __restric
       const bool valid = ((j0_) + u * KPI + slot) < k_end;                                    \
       float kx[8], vx[8];                                                                     \
       _Pragma("unroll") for (int e = 0; e < 8; ++e) {                                         \
-        kx[e] = to_f(kf[buf][u][e]);                                                        \
-        vx[e] = to_f(vf[buf][u][e]);                                                        \
+        kx[e] = to_f(kf[buf][u][e]);                                                          \
+        vx[e] = LS_SEEN(to_f(vf[buf][u][e]));                                                 \
       }                                                                                       \
       LS_KEY_UPDATE(kx, vx, valid)                                                            \
     }                                                                                         \
@@ -186,6 +191,7 @@ k_attn_decode(const T* __restrict__ qkv, int qkv_stride, const float2* __restric
 #undef LS_LOAD_GROUP
 #undef LS_FOLD_GROUP
 
+#undef LS_SEEN
 #undef LS_KEY_UPDATE
 
   // merge the key slots of the wave (lanes that hold the same dimensions)
