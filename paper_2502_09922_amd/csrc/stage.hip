@@ -885,10 +885,15 @@ ls::GemmScratch workspace_scratch(const ls_stage* s) {
   return g;
 }
 
-// Largest split-K scratch any GEMM of one decode step over `rows` rows asks for.
+// The steps of ls_stage_decode_static that put partial tiles into the static array.
+bool uses_static_scratch(const ls_stage* s, int rows) { return s->cfg.dtype == LS_DTYPE_BF16 && rows > 16 && rows <= 64; }
+
+// What ls_stage_decode_static measures a step by: the largest split-K scratch that the weight-streaming GEMMs
+// would ask for over `rows` rows.  The limit is the entry point's contract (ls_stage.h) and stands also where
+// the tiled GEMM, whose plan always fits the array, takes the projections.
 size_t decode_scratch_need(const ls_stage* s, int rows) {
   const ls_cfg& c = s->cfg;
-  if (c.dtype != LS_DTYPE_BF16 || rows <= 16) return 0;
+  if (!uses_static_scratch(s, rows)) return 0;
   const int d = c.hidden, F = c.ffn, qd = c.n_q_heads * c.head_dim;
   const int qkv_cols = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
   size_t need = 0;
@@ -953,12 +958,24 @@ ls_status ls_stage_decode_static(ls_stage* s, const void* in, int batch, int max
   if (need > (size_t)LS_STATIC_SCRATCH_BYTES)
     return fail(LS_ERR_OOM, "ls_stage_decode_static: this step needs %zu bytes of scratch, the static array holds %zu",
                 need, (size_t)LS_STATIC_SCRATCH_BYTES);
-  // the K-split partials of this step go to the device's static array: every workgroup writes
-  // its whole partial tile before the finishing kernel reads it, so nothing has to start at zero
-  ls::GemmScratch g;
-  g.splitk = (float*)s->static_scratch;
-  g.bytes = LS_STATIC_SCRATCH_BYTES;
+  // The K-split partials of a bf16 step of 17..64 rows go to the device's static array: every workgroup
+  // writes its whole partial tile before the finishing kernel reads it, so nothing has to start at zero.
+  // Steps of other sizes and fp32 ones keep theirs in the stage's own workspace: the array is shared by all
+  // stages of the device, and only the steps that ls_stage.h names may have to be ordered for it.
+  ls::GemmScratch g = workspace_scratch(s);
+  if (uses_static_scratch(s, batch)) {
+    g.splitk = (float*)s->static_scratch;
+    g.bytes = LS_STATIC_SCRATCH_BYTES;
+  }
   return forward(s, false, in, nullptr, batch, batch, max_ctx + 1, kv, out, logits_out, (hipStream_t)hip_stream, g);
+}
+
+// For the tests; not declared in ls_stage.h: this device's static array, which a step must not touch that
+// ls_stage.h does not name.
+void* ls_test_static_scratch(void) {
+  int dev = -1;
+  void* p = nullptr;
+  return static_scratch_of_current_device(&dev, &p) == hipSuccess ? p : nullptr;
 }
 
 ls_status ls_stage_layer_times(ls_stage* s, float* copy_ms, float* compute_ms, float* copy_end_ms,
