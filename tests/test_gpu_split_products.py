@@ -91,3 +91,29 @@ def test_the_ends_of_the_range_and_infinities(tile):
     assert (np.abs(got - want)[np.ix_(rows, cols)] <= bound[np.ix_(rows, cols)]).all()
     assert (got[rows, 7] == np.where(a[rows, 33] > 0, np.inf, -np.inf)).all()
     assert (got[m - 1, cols] == np.where(w[cols, 64] > 0, -np.inf, np.inf)).all()
+
+
+@pytest.mark.parametrize("rows", [161, 257, 500])
+def test_prompts_on_the_large_tiles_against_the_oracle(rows):
+    """A layer as wide as the 7B shape's, K of the down projection with half a k-step at its end (688) and cut: the plan
+    takes 96 x 128, 160 x 128 and 256 x 128 tiles."""
+    import synth
+    from helpers import check_close, check_delta, make_gpu, make_oracle, to_dev, to_host
+    from oracle.stage_oracle import decode_values
+    from paper_2502_09922_amd import binding
+
+    fn = binding.lib.ls_test_tiled_plan
+    fn.argtypes = [C.c_uint32] + [C.c_int] * 5 + [C.c_size_t, C.POINTER(C.c_int * 3)]
+    for k in (4096, 688):  # O and down projection
+        plan = (C.c_int * 3)()
+        assert fn(F32, 0, rows, 4096, k, 1, 8 * rows * 4096 * 4, C.byref(plan))
+        assert plan[0] * plan[1] >= 96 * 128 and plan[2] > 1, list(plan)
+    shape = synth.StageShape("f32", 1, 4096, 32, 4, 128, 688, 0)
+    lengths = [rows - rows // 3, rows // 3]
+    gpu = make_gpu(shape, 3, 0, 1, 2, max(lengths), rows)
+    ora = make_oracle(shape, 3, 0, 1, 2, max(lengths))
+    x = synth.hidden_states(shape, 4, rows)
+    got, want = to_host(gpu.prefill(to_dev(shape, x), lengths)), ora.prefill(x, lengths)
+    check_close(got, want, "f32", "prompt")
+    check_delta(got, want, decode_values(x), "f32", "prompt")
+    gpu.close()

@@ -98,19 +98,27 @@ def test_fp32_infinities_pass_through_the_split_products():
     import torch
 
     shape = S("f32", 1, 512, 4, 4, 64, 512, 0)
-    gpu = make_gpu(shape, 11, 0, 1, 1, 512, 500)
-    view = gpu.block_view(0)
+    lengths = [460] * 5
+    rows = sum(lengths)
     from paper_2502_09922_amd import binding as b
     import ctypes as C
+
+    plan = (C.c_int * 3)()
+    fn = b.lib.ls_test_tiled_plan
+    fn.argtypes = [C.c_uint32] + [C.c_int] * 5 + [C.c_size_t, C.POINTER(C.c_int * 3)]
+    assert fn(0, 0, rows, 512, 512, 1, 8 * rows * 512 * 4, C.byref(plan))  # the down projection of this call
+    assert plan[0] * plan[1] >= 96 * 128, list(plan)  # goes by the parts
+    gpu = make_gpu(shape, 11, 0, 1, 5, 512, rows)
+    view = gpu.block_view(0)
 
     off, nb = C.c_size_t(), C.c_size_t()
     b.check(b.lib.ls_block_tensor(C.byref(gpu.cfg), 0, 5, C.byref(off), C.byref(nb)))  # w_down [hidden, ffn]
     wd = view[off.value : off.value + nb.value].view(torch.float32).view(512, 512)
-    x = to_dev(shape, synth.hidden_states(shape, 12, 500))
-    clean = gpu.prefill(x, [500]).clone()
-    h = gpu.workspace_region(b.LS_WS_FFN, 500).clone()
+    x = to_dev(shape, synth.hidden_states(shape, 12, rows))
+    clean = gpu.prefill(x, lengths).clone()
+    h = gpu.workspace_region(b.LS_WS_FFN, rows).clone()
     wd[7, 100] = float("inf")
-    got = gpu.prefill(x, [500])
+    got = gpu.prefill(x, lengths)
     others = torch.arange(512, device="cuda") != 7
     scale = clean.abs().max()
     assert ((got - clean)[:, others].abs() <= 1e-5 * scale).all()

@@ -54,3 +54,17 @@ def test_no_plan_for_what_the_kernel_does_not_take():
         assert plan(dt, STORE, m, n, k, False, 0).splits == 0
     assert plan(BF16, PART, 3000, 8192, 8192, True, big).splits == 0  # 98 MB of partial tiles
     assert plan(BF16, PART, 2000, 8192, 8192, True, big).splits == 1
+
+
+def test_launches_with_a_chosen_tile_that_are_refused():
+    """Nothing is launched for what the kernels do not take: other tiles, K not of half k-steps, a cut matrix that is not
+    partial tiles, more parts than K has, SwiGLU where gate and up do not lie in one wavefront."""
+    fn = binding.lib.ls_test_tiled_gemm
+    fn.argtypes = [C.c_uint32] + [C.c_int] * 4 + [C.c_void_p] * 2 + [C.c_int] * 3 + [C.c_void_p] * 2
+    p = 256  # never read
+    for dt, epi, bm, bn, splits, m, n, k in ((F32, STORE, 160, 256, 1, 40, 64, 64), (BF16, STORE, 48, 128, 1, 40, 64, 64),
+                                             (F32, STORE, 0, 0, 1, 4, 64, 64), (BF16, STORE, 32, 64, 1, 40, 64, 80),
+                                             (F32, STORE, 32, 64, 2, 40, 64, 512), (F32, PART, 32, 64, 5, 40, 64, 256),
+                                             (BF16, SWIGLU, 64, 64, 1, 40, 64, 64), (BF16, STORE, 32, 64, 1, 40, 24, 64),
+                                             (F32, ROPE, 32, 64, 1, 40, 64, 64)):
+        assert not fn(dt, epi, bm, bn, splits, p, p, m, n, k, p, None)
