@@ -4,16 +4,15 @@
 // What it is for.  The 256 x 256 tiles of k_gemm_mfma leave most of the chip idle when the output
 // has few of them (311 rows x 4096 columns: 32 tiles on 256 CUs), and the weight-streaming
 // kernels hold all rows of the call in one fragment set.  Here a 512-thread workgroup (8
-// wavefronts, one workgroup per CU) owns a tile of 32..256 rows x 64 or 128 weight rows, chosen
+// wavefronts, one workgroup per CU) owns a tile of 32..256 rows x 64, 128 or 256 weight rows, chosen
 // per launch (gemm_tiled_plan) so that the tiles, times the number of ways K is cut, fill the chip.
 //
 // Data path: both operands are K-contiguous; a k-step is 128 bytes of every row (64 bf16 or 32
 // fp32).  Rows go from global memory straight into LDS (global_load_lds_dwordx4) into a ring of
 // NS stages, 16-byte chunks XOR-swizzled by (row/2)&7 as in k_gemm_mfma, so that the 16 rows a
-// quarter-wave reads fall into different banks.  One barrier per stage (one or two
-// k-steps): behind it the stage of
-// this k-step has landed for every wavefront (each waited for its own fills, counted) and the stage of the
-// previous one has been read by all, so its slot takes the fills NS - 1 stages ahead.
+// quarter-wave reads fall into different banks.  One barrier per stage (one or two k-steps): behind it the
+// stage of this k-step has landed for every wavefront (each waited for its own fills, counted) and the stage
+// of the previous one has been read by all, so its slot takes the fills NS - 1 stages ahead.
 //
 // What bounds it: the fills.  With the LDS reads and the MFMAs taken out the kernel takes as long
 // as with them (1024 rows x 22016 x 4096, tiles of 128 x 128: 235 of 237 us), with the fills
@@ -26,7 +25,8 @@
 // Measured with cold weights, 7B layer (QKV / O / gate-up / down): 100 rows 33 / 13 / 45 / 22 us,
 // 311 rows 48 / 19 / 75 / 39, 1024 rows 118 / 37 / 177 / 86 (0.9-1.05 PFLOP/s); k_gemm_mfma takes
 // 104 / 106 / 102 / 242 for anything up to 256 rows and k_gemm_skinny 41 / 17 / 52 / 38 for 45, where this
-// kernel takes 24 / 10 / 36 / 19.  fp32: 321 rows 0.08-0.11 PFLOP/s of the 0.154 a large matrix
+// kernel takes 24 / 10 / 36 / 19.  Counters, 311 rows: matrix units busy 0.28-0.48 of the time, LDS 0.20-0.25,
+// no bank conflicts; 64 rows of the 70B layer 0.17-0.19 and 0.17-0.26.  fp32: 321 rows 0.08-0.11 PFLOP/s of the 0.154 a large matrix
 // product reaches (the 64 x 64 tile on vector FMAs that did this before: 0.024).
 //
 // fp32 uses v_mfma_f32_16x16x4_f32 (large tiles: mma_split): a lane's 16-byte chunk holds four consecutive k, and element
@@ -118,11 +118,13 @@ __device__ __forceinline__ void split3(u32x4 a, u32x4 b, u32x4 (&part)[3]) {
 
 // acc[i][j] += w[j] x[i]^T over a whole fp32 k-step, as six bf16 products of the operands' parts: all but
 // mid * lo, lo * mid and lo * lo, together at most 2^-24 of a product and of either sign, so that sums of them
-// have no bias (parts cut off instead of rounded have the sign of their value: up to 7.8 x 2^-24 of a
-// product, all towards zero; all products but lo * lo in that form cost more than rounding).  The bf16
-// instruction rounds to nearest like the fp32 one, except that an accumulator smaller than the product
-// loses what lies below the result's last bit, towards minus infinity: the first additions of a sum may be
-// off by a whole last bit.
+// do not drift.  (Parts cut off instead of rounded have the sign of their value: up to 7.8 x 2^-24 of a
+// product left out, all towards zero, and small products of one sign that a large sum swallows one by one.
+// All products but lo * lo in that form cost more than rounding.)  Relative error against float64 at K =
+// 11008, as here / cut off / fp32 instructions: 1.7e-6 / 1.8e-6 / 1.9e-6 for Gaussian operands, 0.9e-6 /
+// 17e-6 / 1.5e-6 for positive ones, 2.4e-6 / 18e-6 / 1.5e-6 for constant rows times positive ones.  The bf16 instruction rounds to nearest like the fp32 one, except that an
+// accumulator smaller than the product loses what lies below the result's last bit, towards minus
+// infinity: results lie 0.7e-6 of their mean magnitude low.
 // Why: v_mfma_f32_16x16x4_f32 moves 4 k in 32 cycles, the six bf16 instructions 32 k in 96; the splitting is
 // about as long again.  321 rows of the 7B shape, QKV / gate-up / down / O: 371 / 578 / 312 / 144 us, with parts
 // cut off 333 / 529 / 282 / 130.

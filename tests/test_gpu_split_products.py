@@ -93,6 +93,21 @@ def test_the_ends_of_the_range_and_infinities(tile):
     assert (got[m - 1, cols] == np.where(w[cols, 64] > 0, -np.inf, np.inf)).all()
 
 
+@pytest.mark.parametrize("tile", TILES)
+def test_sums_of_one_sign_do_not_drift(tile):
+    # n = 6 K / 32 additions; each rounds the sum so far, on average half the result, to 24 bits: errors of
+    # 2^-24 / sqrt(3) of it, as likely up as down, add up to sqrt(n / 3) * 2^-24 / sqrt(3) of the result
+    rng = np.random.default_rng(4)
+    k = 8192
+    a = np.abs(rng.standard_normal((tile[0], k))).astype(np.float32)
+    w = np.abs(rng.standard_normal((tile[1], k))).astype(np.float32)
+    want = a.astype(np.float64) @ w.astype(np.float64).T
+    err = np.linalg.norm(matmul(tile, a, w) - want) / np.linalg.norm(want)
+    expect = np.sqrt(6 * k / 32) / 3 * U
+    print("%.2e, %.1f of what independent roundings give" % (err, err / expect))
+    assert err <= 4 * expect
+
+
 @pytest.mark.parametrize("rows", [161, 257, 500])
 def test_prompts_on_the_large_tiles_against_the_oracle(rows):
     """A layer as wide as the 7B shape's, K of the down projection with half a k-step at its end (688) and cut: the plan
