@@ -298,10 +298,13 @@ ls_status ls_stage_probe(ls_stage* stage, int op, int layer, int phase);
 
 /* After the caller has synchronised: durations in ms of the probed launches since the
  * probe was set, oldest first, at most `cap`; *n receives the count.  Where the operator is
- * one kernel that the library launches with the runtime's per-kernel start/stop events (the
- * bf16 GEMMs of up to 16 rows and of more than 64 rows), a duration is that kernel's own
- * start-to-stop time, as a profiler's kernel trace reports it; otherwise it is the span
- * between two events recorded around the operator's launches, which includes launch gaps. */
+ * one kernel that the library launches with the runtime's per-kernel start/stop events (all
+ * GEMMs but the shape-generic one and those that leave partial tiles, as O and down
+ * projection do in every fp32 call and in bf16 ones whose whole tiles would not fill the
+ * chip), a duration is that kernel's own start-to-stop time, as a profiler's kernel trace
+ * reports it; otherwise it is the span between two events recorded around the operator's
+ * launches, which includes launch gaps and, for partial tiles, the kernel that adds them to
+ * the residual rows with the norm or the store it does along. */
 ls_status ls_stage_probe_times(ls_stage* stage, float* ms, int cap, int* n);
 
 /* ---- execution pipeline over several stages (2D pipelining) ---------------------------

@@ -1,5 +1,6 @@
-// Shape-based choice between the kernels of one operator.  fp32 always takes the generic
-// kernels; bf16 takes an MFMA kernel wherever its shape constraints hold.
+// Shape-based choice between the kernels of one operator.  GEMMs: what the stage's plans (gemm_tiled_plan) leave;
+// fp32 takes the generic kernel here, bf16 an MFMA kernel wherever its shape constraints hold.  Attention: the
+// kernel for the type and head shape, else the generic one.
 #include "kernels.hpp"
 
 namespace ls {

@@ -28,7 +28,9 @@ constexpr int ROWS_F32_MAX = 8;
 // layers, 1..2048 rows, cold weights): a k-step of a workgroup costs 0.05 us + 2.4 ns per tile
 // row it brings into LDS, whatever the arithmetic (64 x 64 0.41, 64 x 128 0.53, 128 x 128 0.67,
 // 160 x 128 0.76, 256 x 128 0.95 us measured), in fp32 at least its matrix work (64 x 64 at 0.4,
-// 64 x 128 at 0.46, 96 x 128 at 0.58, 128 x 128 at 0.64, 256 x 128 at 0.8 TFLOP/s per CU); one
+// 64 x 128 at 0.46, 96 x 128 at 0.58, 128 x 128 at 0.64, 256 x 128 at 0.8 TFLOP/s per CU; with parts rounded
+// instead of cut off the latter three reach 0.53, 0.57 and 0.74, and the tile chosen at 100..700 rows of the
+// four 7B projections is still the best or within 6 % of it); one
 // workgroup fits a CU, so the launch takes as many rounds as its fullest XCD has
 // workgroups for its 32 CUs; every K split writes and reads an fp32 tile.
 TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us) {

@@ -1,5 +1,5 @@
-// Shape-generic HIP kernels of the decoder stage: the fp32 path runs entirely on these,
-// and the bf16 path uses them for every shape its MFMA kernels do not cover.
+// Shape-generic HIP kernels of the decoder stage: both types use them for every shape that the kernels of
+// the other files do not take (fp32: GEMMs whose N or K is no multiple of 16, head_dim other than 64 and 128).
 // Operator definitions: Llama-2 pre-norm decoder block (the layer arithmetic that the
 // paper's Section 6 adopts from Meta's Llama inference code).
 #include "kernels.hpp"

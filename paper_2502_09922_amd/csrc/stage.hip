@@ -163,12 +163,13 @@ Carve carve(const ls_cfg* c, int lo, int hi) {
   w.ss_a = take(B * ((d + 15) / 16) * sizeof(float));
   w.ss_b = take(B * ((d + 15) / 16) * sizeof(float));
   {
-    // split-K scratch: the decode GEMMs for 17..64 rows (bf16 only)
+    // split-K scratch: the weight-streaming GEMMs for 17..64 rows (bf16: hidden sizes above 8192, logits at an
+    // odd address)
     size_t cols = qkv_cols > 2 * (size_t)c->ffn ? qkv_cols : 2 * (size_t)c->ffn;
     if (d > cols) cols = d;
     if (last && c->vocab > cols) cols = c->vocab;
     w.splitk_bytes = (c->dtype == LS_DTYPE_BF16 && B > 16) ? ls::gemm_scratch_bytes((int)B, cols) : 0;
-    // partial tiles of the tiled GEMMs that write residual rows: at most eight splits of every row
+    // ... and partial tiles of the tiled GEMMs that write residual rows: at most eight splits of every row
     size_t part = 8 * T * d * sizeof(float);
     if (part > TILED_SCRATCH_MAX) part = TILED_SCRATCH_MAX;
     // fp32 has no other fast GEMM: one partial tile of every row always fits

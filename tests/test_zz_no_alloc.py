@@ -13,7 +13,7 @@ from helpers import make_gpu, make_oracle, rel_l2, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
-# 17..64 rows take the weight-streaming GEMMs that split K across workgroups
+# of 17..64 rows: partial tiles of O and down projection go to the array
 SHAPE = synth.StageShape("bf16", 2, 512, 8, 2, 64, 1408, 1000)
 
 
