@@ -93,6 +93,31 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
+constexpr int waitcnt_vm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }  // vector memory only
+
+// Wait until at most n of this wavefront's vector memory instructions are on their way, n known at run time (the
+// instruction holds a constant).  More than 48: all are waited for.
+__device__ __forceinline__ void wait_vm(int n) {
+  switch (n) {
+#define LS_WAIT(i) case i: __builtin_amdgcn_s_waitcnt(waitcnt_vm(i)); break;
+#define LS_WAIT8(i) LS_WAIT(i) LS_WAIT(i + 1) LS_WAIT(i + 2) LS_WAIT(i + 3) LS_WAIT(i + 4) LS_WAIT(i + 5) LS_WAIT(i + 6) LS_WAIT(i + 7)
+    LS_WAIT8(1) LS_WAIT8(9) LS_WAIT8(17) LS_WAIT8(25) LS_WAIT8(33) LS_WAIT8(41)
+#undef LS_WAIT8
+#undef LS_WAIT
+    default: __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  }
+}
+
+// The workgroup's barrier for wavefronts that hand LDS slots over: no read or write of memory moves across it, and with
+// `done` every LDS read of this wavefront has its value before it.
+template <bool done>
+__device__ __forceinline__ void slot_barrier() {
+  if constexpr (done) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  else asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // silu(z) = z / (1 + exp(-z)), the quotient as a product with the hardware reciprocal (1 ulp):
 // a correctly rounded fp32 division is ten instructions, and every result is rounded to bf16
 __device__ __forceinline__ float silu_f(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }

@@ -10,6 +10,9 @@ bool launch_gemm_tiled_bf16(int epi, const TiledPlan& p, const void* A, const vo
 bool launch_gemm_tiled_f32(int epi, const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out,
                            const RopeAppend& rope, hipStream_t st);
 
+bool launch_gemm_split_f32(int epi, const TiledPlan& p, const void* A, void* parts, const void* W, int M, int N, int K, void* out,
+                           const RopeAppend& rope, hipStream_t st);
+
 int gemm_rows_f32_splits(int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes);
 bool launch_gemm_rows_f32(int epi, const void* A, const void* W, int M, int N, int K, int splits, void* out, hipStream_t st);
 
@@ -24,14 +27,20 @@ bool gemm_tiled_supported(uint32_t dt, int epi, int M, int N, int K) {
 // 299 / 352, 8 rows 219 / 250; the FMAs of each further row cost 6 us, the tiles nothing up to 32.
 constexpr int ROWS_F32_MAX = 8;
 
+// fp32 of more rows than this goes by split operands, unless the weights are so few (the tiny model's matrices) that
+// the launch of the kernel that splits the rows would be what the GEMM takes.  100 rows of the 7B shape, QKV / gate-up /
+// down: 134 / 160 / 89 us against 172 / 258 / 102 for 64 x 128 on fp32 instructions; 48 rows 127 / 155 / 64
+// against 103 / 156 / 63.
+constexpr int ROWS_F32_SPLIT = 96;
+constexpr size_t WEIGHTS_F32_SPLIT = 1u << 18;
+
 // Time of a launch, in microseconds, from what the kernel's sweep over tiles showed (7B and 13B
 // layers, 1..2048 rows, cold weights): a k-step of a workgroup costs 0.05 us + 2.4 ns per tile
 // row it brings into LDS, whatever the arithmetic (64 x 64 0.41, 64 x 128 0.53, 128 x 128 0.67,
 // 160 x 128 0.76, 256 x 128 0.95 us measured), in fp32 at least its matrix work (64 x 64 at 0.4,
-// 64 x 128 at 0.46, 96 x 128 at 0.58, 128 x 128 at 0.64, 256 x 128 at 0.8 TFLOP/s per CU; with parts rounded
-// instead of cut off the latter three reach 0.53, 0.57 and 0.74, and the tile chosen at 100..700 rows of the
-// four 7B projections is still the best or within 6 % of it); one
-// workgroup fits a CU, so the launch takes as many rounds as its fullest XCD has
+// 64 x 128 at 0.46 TFLOP/s per CU); by split operands 0.39 us + 0.055 per pair of 16-row fragments and wavefront
+// (96 x 128 1.05..1.1, 128 x 128 1.2..1.4, 176 x 128 1.6..1.7, 128 x 192 1.9..2.1 us measured) and the kernel in
+// front; one workgroup fits a CU, so the launch takes as many rounds as its fullest XCD has
 // workgroups for its 32 CUs; every K split writes and reads an fp32 tile.
 TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us) {
   TiledPlan best;
@@ -44,33 +53,42 @@ TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scr
     }
   }
   if (gemm_tiled_supported(dt, epi, M, N, K)) {
-    struct Shape { int bm, bn; bool f32, glu; };
-#define LS_TILE(bm_, bn_, wm_, tm_, tn_, f32_, glu_) {bm_, bn_, f32_, glu_},
-    static const Shape tiles[] = {LS_TILED_TILES(LS_TILE)};
-#undef LS_TILE
     const int kb = dt == F32 ? 32 : 64, nk = (K + kb - 1) / kb;
-    for (const auto& t : tiles) {
-      const int bm = t.bm, bn = t.bn;
-      if ((dt == F32 && !t.f32) || (epi == TILED_SWIGLU && !t.glu)) continue;
+    auto consider = [&](int bm, int bn, float step, float extra) {
       const int ncols = epi == TILED_SWIGLU ? bn / 2 : bn;
       const int tiles_m = (M + bm - 1) / bm, panels = ((N + ncols - 1) / ncols + 7) / 8;
-      float step = 0.05f + 0.0024f * (float)(bm + bn);
-      if (dt == F32) {
-        const float area = (float)(bm * bn);
-        const float mma = 64.f * area / (bm * bn >= 96 * 128 ? 0.45e6f + 10.7f * area : 0.36e6f + 12.f * area) + 0.05f;
-        if (mma > step) step = mma;
-      }
       for (int s = 1; s <= 8; ++s) {
         // partial tiles, also those of a single split, have to fit the scratch
         if ((to_scratch && (size_t)s * M * N * sizeof(float) > scratch_bytes) || (s > 1 && (!to_scratch || nk < 2 * s))) break;
         const long per_xcd = (long)panels * tiles_m * s;
         const float rounds = (float)((per_xcd + 31) / 32);
-        const float t_us = rounds * ((float)((nk + s - 1) / s) * step + 2.5f) + (float)s * (float)M * (float)N * 8.f / 4e6f;
+        const float t_us = rounds * ((float)((nk + s - 1) / s) * step + 2.5f) + (float)s * (float)M * (float)N * 8.f / 4e6f + extra;
         if (t_us < best_us) {
           best_us = t_us;
           best.bm = bm; best.bn = bn; best.splits = s;
         }
       }
+    };
+    struct Shape { int bm, bn; bool f32, glu; };
+#define LS_TILE(bm_, bn_, wm_, tm_, tn_, f32_, glu_) {bm_, bn_, f32_, glu_},
+    static const Shape tiles[] = {LS_TILED_TILES(LS_TILE)};
+#undef LS_TILE
+    const size_t weights = (size_t)N * (epi == TILED_SWIGLU ? 2 : 1) * K;
+    if (dt == BF16 || M <= ROWS_F32_SPLIT || weights < WEIGHTS_F32_SPLIT)
+      for (const auto& t : tiles) {
+        if ((dt == F32 && !t.f32) || (epi == TILED_SWIGLU && !t.glu)) continue;
+        float step = 0.05f + 0.0024f * (float)(t.bm + t.bn);
+        if (dt == F32) {
+          const float area = (float)(t.bm * t.bn);
+          const float mma = 64.f * area / (0.36e6f + 12.f * area) + 0.05f;
+          if (mma > step) step = mma;
+        }
+        consider(t.bm, t.bn, step, 0.f);
+      }
+    if (dt == F32) {
+#define LS_TILE(bm_, bn_) consider(bm_, bn_, 0.39f + 0.055f * (bm_ / 16) * (bn_ / 64) + (bn_ > 128 ? 0.2f : 0.f), 4.f);
+      LS_SPLIT_TILES(LS_TILE)
+#undef LS_TILE
     }
   }
   if (us) *us = best_us;
@@ -78,11 +96,12 @@ TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scr
 }
 
 bool launch_gemm_tiled(uint32_t dt, int epi, const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out,
-                       const RopeAppend& rope, hipStream_t st) {
+                       const RopeAppend& rope, hipStream_t st, void* parts) {
   if (!p.splits) return false;
   if (!p.bm) return launch_gemm_rows_f32(epi, A, W, M, N, K, p.splits, out, st);
-  return dt == F32 ? launch_gemm_tiled_f32(epi, p, A, W, M, N, K, out, rope, st)
-                   : launch_gemm_tiled_bf16(epi, p, A, W, M, N, K, out, rope, st);
+  if (dt != F32) return launch_gemm_tiled_bf16(epi, p, A, W, M, N, K, out, rope, st);
+  return launch_gemm_tiled_f32(epi, p, A, W, M, N, K, out, rope, st) ||
+         (parts && launch_gemm_split_f32(epi, p, A, parts, W, M, N, K, out, rope, st));
 }
 
 namespace {
@@ -276,5 +295,12 @@ extern "C" int ls_test_tiled_gemm(uint32_t dt, int epi, int bm, int bn, int spli
   if (splits > 1 && (epi != TILED_PART || nk < 2 * splits)) return 0;
   TiledPlan p;
   p.bm = bm; p.bn = bn; p.splits = splits;
-  return bm > 0 && launch_gemm_tiled(dt, epi, p, A, W, M, N, K, out, RopeAppend{}, (hipStream_t)hip_stream);
+  hipStream_t st = (hipStream_t)hip_stream;
+  if (bm <= 0 || dt != F32 || bm * bn < 96 * 128) return bm > 0 && launch_gemm_tiled(dt, epi, p, A, W, M, N, K, out, RopeAppend{}, st);
+  // the split tiles: what a caller of this entry has no scratch for; 160 and 256 rows of 128 name the tallest of them
+  if (bn == 128 && (bm == 160 || bm == 256)) p.bm = 176;
+  void* parts = nullptr;
+  if (hipMallocAsync(&parts, gemm_split_parts_bytes(M, K), st) != hipSuccess) return 0;
+  const int ok = launch_gemm_tiled(dt, epi, p, A, W, M, N, K, out, RopeAppend{}, st, parts);
+  return hipFreeAsync(parts, st) == hipSuccess && ok;
 }

@@ -26,10 +26,9 @@
 // 311 rows 48 / 19 / 75 / 39, 1024 rows 118 / 37 / 177 / 86 (0.9-1.05 PFLOP/s); k_gemm_mfma takes
 // 104 / 106 / 102 / 242 for anything up to 256 rows and k_gemm_skinny 41 / 17 / 52 / 38 for 45, where this
 // kernel takes 24 / 10 / 36 / 19.  Counters, 311 rows: matrix units busy 0.28-0.48 of the time, LDS 0.20-0.25,
-// no bank conflicts; 64 rows of the 70B layer 0.17-0.19 and 0.17-0.26.  fp32: 321 rows 0.08-0.11 PFLOP/s of the 0.154 a large matrix
-// product reaches (the 64 x 64 tile on vector FMAs that did this before: 0.024).
+// no bank conflicts; 64 rows of the 70B layer 0.17-0.19 and 0.17-0.26.
 //
-// fp32 uses v_mfma_f32_16x16x4_f32 (large tiles: mma_split): a lane's 16-byte chunk holds four consecutive k, and element
+// fp32 (up to 96 rows; more go by gemm_split_f32.hip) uses v_mfma_f32_16x16x4_f32: a lane's 16-byte chunk holds four consecutive k, and element
 // e of all four lane groups together is one instruction's k = 4: both operands agree on which k
 // a lane's element e is, and a sum does not care in what order k is visited.  So the fp32
 // fragments are read from LDS exactly like the bf16 ones, four instructions per fragment pair.
@@ -46,11 +45,6 @@ namespace tiled {
 
 constexpr int ROWB = 128;  // bytes of a row in one k-step
 constexpr int WAVES = 8;
-// fp32 tiles of this many elements or more are multiplied as bf16 parts (mma_split); in smaller ones the
-// splitting, which every wavefront repeats for its operands, costs more than it saves (64 x 64: 320 rows
-// of the 7B QKV 425 us in fp32, 516 split; 96 x 128 411 and 382, 256 x 128 495 and 370).
-constexpr int SPLIT_FROM = 96 * 128;
-
 // Tile of 16 WM TM rows x 16 WN TN columns, wavefronts WM x WN, ring as deep as LDS allows (at most
 // eight stages: no shape gained from more).
 template <int WM_, int TM_, int TN_>
@@ -88,81 +82,6 @@ __device__ __forceinline__ void mma(f32x4 (&acc)[TM][TN], const u32x4 (&w)[TN], 
       for (int j = 0; j < TN; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f32x4, w[j])[e], __builtin_bit_cast(f32x4, x[i])[e],
                                                          acc[i][j], 0, 0, 0);
-}
-
-// An fp32 value as the sum of three bf16 values, each the rest rounded to the nearest: of a value in [1, 2) the
-// second is at most 2^-8, the third at most 2^-17 (a multiple of 2^-23), both of either sign.  (Henry, Tang,
-// Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations",
-// ARITH 2019.)  The sum is exact from 2^-102 on; of smaller values what lies below 2^-126 may be lost, as
-// bf16 parts end there.  part[0..2][p]: the three parts of the pieces a and b of a row, two values per register.
-// The rest is taken by v_dot2 (-1 * part + 0 * its neighbour + value, exact), one instruction where widening
-// and subtracting are two; seven instructions per pair of values.
-__device__ __forceinline__ void split3(u32x4 a, u32x4 b, u32x4 (&part)[3]) {
-  typedef float f32x2 __attribute__((ext_vector_type(2)));
-  // (-1, 0) and (0, -1).  In registers: a constant in the instruction is not read as a pair of bf16 values.
-  unsigned take0 = 0x0000BF80u, take1 = 0xBF800000u;
-  asm("" : "+s"(take0), "+s"(take1));
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    float f0 = __uint_as_float(p < 2 ? a[2 * p] : b[2 * p - 4]), f1 = __uint_as_float(p < 2 ? a[2 * p + 1] : b[2 * p - 3]);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const bf16x2 h = __builtin_convertvector((f32x2{f0, f1}), bf16x2);
-      part[s][p] = __builtin_bit_cast(unsigned, h);
-      f0 = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, take0), f0, false);
-      f1 = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, take1), f1, false);
-    }
-    part[2][p] = __builtin_amdgcn_perm(__float_as_uint(f1), __float_as_uint(f0), 0x07060302);  // fits: the upper halves of both
-  }
-}
-
-// acc[i][j] += w[j] x[i]^T over a whole fp32 k-step, as six bf16 products of the operands' parts: all but
-// mid * lo, lo * mid and lo * lo, together at most 2^-24 of a product and of either sign, so that sums of them
-// do not drift.  (Parts cut off instead of rounded have the sign of their value: up to 7.8 x 2^-24 of a
-// product left out, all towards zero, and small products of one sign that a large sum swallows one by one.
-// All products but lo * lo in that form cost more than rounding.)  Relative error against float64 at K =
-// 11008, as here / cut off / fp32 instructions: 1.7e-6 / 1.8e-6 / 1.9e-6 for Gaussian operands, 0.9e-6 /
-// 17e-6 / 1.5e-6 for positive ones, 2.4e-6 / 18e-6 / 1.5e-6 for constant rows times positive ones.  The bf16 instruction rounds to nearest like the fp32 one, except that an
-// accumulator smaller than the product loses what lies below the result's last bit, towards minus
-// infinity: results lie 0.7e-6 of their mean magnitude low.
-// Why: v_mfma_f32_16x16x4_f32 moves 4 k in 32 cycles, the six bf16 instructions 32 k in 96; the splitting is
-// about as long again.  321 rows of the 7B shape, QKV / gate-up / down / O: 371 / 578 / 312 / 144 us, with parts
-// cut off 333 / 529 / 282 / 130.
-// A k-step is multiplied in fp32 where a lane of the wavefront holds an infinity, a value that rounds to one or
-// one whose products could overflow by their parts (2^63 and more).  So the last bits of a row may depend
-// on the rows beside it.
-template <int TM, int TN>
-__device__ __forceinline__ void mma_split(f32x4 (&acc)[TM][TN], const u32x4 (&w0)[TN], const u32x4 (&x0)[TM],
-                                          const u32x4 (&w1)[TN], const u32x4 (&x1)[TM]) {
-  float big = 0.f;
-  auto seen = [&](u32x4 v) {
-    const f32x4 f = __builtin_bit_cast(f32x4, v);
-    big = fmaxf(fmaxf(fabsf(f[0]), fabsf(f[1])), big);
-    big = fmaxf(fmaxf(fabsf(f[2]), fabsf(f[3])), big);
-  };
-#pragma unroll
-  for (int i = 0; i < TM; ++i) { seen(x0[i]); seen(x1[i]); }
-#pragma unroll
-  for (int j = 0; j < TN; ++j) { seen(w0[j]); seen(w1[j]); }
-  if (__builtin_amdgcn_ballot_w64(big >= 0x1p63f) != 0) {
-    mma<TM, TN>(acc, w0, x0, float{});
-    mma<TM, TN>(acc, w1, x1, float{});
-    return;
-  }
-  u32x4 xs[TM][3], ws[TN][3];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) split3(x0[i], x1[i], xs[i]);
-#pragma unroll
-  for (int j = 0; j < TN; ++j) split3(w0[j], w1[j], ws[j]);
-  constexpr int PW[6] = {2, 0, 1, 1, 0, 0}, PX[6] = {0, 2, 1, 0, 1, 0};  // smallest products first
-#pragma unroll
-  for (int p = 0; p < 6; ++p)
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ws[j][PW[p]]),
-                                                            __builtin_bit_cast(bf16x8, xs[i][PX[p]]), acc[i][j], 0, 0, 0);
 }
 
 // The operand fragments of a k-step: of each half, TM activation row blocks and TN weight row blocks, 16 rows
@@ -248,8 +167,6 @@ __device__ __forceinline__ void read_frags(unsigned xa0, unsigned wa0, unsigned 
 #undef LS_W
 #undef LS_O
 
-constexpr int waitcnt_vm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }  // vector memory only
-
 template <class T, int N> struct VecOf { typedef T type __attribute__((ext_vector_type(N))); };
 
 // Tile order: groups of up to eight tile rows; inside a group, the tiles of one column of tiles
@@ -261,7 +178,6 @@ k_gemm_tiled(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int
              int tiles_n, RopeAppend rp) {
   constexpr int NS = TL::NS, F = TL::F, KS = TL::KS, TM = TL::TM, TN = TL::TN, WN = TL::WN, BM = TL::BM, BN = TL::BN;
   constexpr bool GLU = EPI == TILED_SWIGLU;
-  constexpr bool SPLIT = sizeof(T) == 4 && TL::BM * TL::BN >= SPLIT_FROM;
   constexpr int NCOLS = GLU ? BN / 2 : BN;
   constexpr int KB = ROWB / (int)sizeof(T);  // elements of a row in one k-step
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -372,20 +288,9 @@ k_gemm_tiled(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int
       const unsigned so = (slot * KS + s) * TL::SUB;
       u32x4 x0[TM], w0[TN], x1[TM], w1[TN];
       read_frags<TM, TN>(xb + so + c0, wb + so + c0, xb + so + c1, wb + so + c1, x0, w0, x1, w1);
-      if constexpr (SPLIT) {
-        if (s == 0 && g + NS - 1 < ng) fill_group(fslot, g + NS - 1);
-        if (ragged && t0 + t == nk - 1) {  // chunks 4..7 of a ragged last k-step hold nothing
-#pragma unroll
-          for (int i = 0; i < TM; ++i) x1[i] = u32x4{0, 0, 0, 0};
-#pragma unroll
-          for (int j = 0; j < TN; ++j) w1[j] = u32x4{0, 0, 0, 0};
-        }
-        mma_split<TM, TN>(acc, w0, x0, w1, x1);
-      } else {
-        mma<TM, TN>(acc, w0, x0, T{});
-        if (s == 0 && g + NS - 1 < ng) fill_group(fslot, g + NS - 1);  // issued while the matrix pipe works on the first half
-        if (!ragged || t0 + t != nk - 1) mma<TM, TN>(acc, w1, x1, T{});  // see above
-      }
+      mma<TM, TN>(acc, w0, x0, T{});
+      if (s == 0 && g + NS - 1 < ng) fill_group(fslot, g + NS - 1);  // issued while the matrix pipe works on the first half
+      if (!ragged || t0 + t != nk - 1) mma<TM, TN>(acc, w1, x1, T{});  // see above
     }
     slot = slot + 1 == NS ? 0 : slot + 1;
     fslot = fslot + 1 == NS ? 0 : fslot + 1;

@@ -110,20 +110,24 @@ enum TiledEpi : int { TILED_PART = 0, TILED_STORE = 1, TILED_SWIGLU = 2, TILED_R
   X(32, 128, 2, 1, 2, true, true)  \
   X(64, 64, 2, 2, 1, true, false)  \
   X(64, 128, 2, 2, 2, true, true)  \
-  X(96, 128, 2, 3, 2, true, true)  \
+  X(96, 128, 2, 3, 2, false, true)  \
   X(128, 64, 2, 4, 1, true, false) \
-  X(128, 128, 2, 4, 2, true, true) \
-  X(160, 128, 2, 5, 2, true, true) \
+  X(128, 128, 2, 4, 2, false, true) \
+  X(160, 128, 2, 5, 2, false, true) \
   X(160, 256, 2, 5, 4, false, true) \
-  X(256, 128, 4, 4, 4, true, true)
+  X(256, 128, 4, 4, 4, false, true)
+// fp32 by bf16 products of split operands (gemm_split_f32.hip): rows at most, weight rows.
+#define LS_SPLIT_TILES(X) X(96, 128) X(128, 128) X(176, 128) X(128, 192)
 struct TiledPlan {
   int bm = 0, bn = 0, splits = 0;  // splits == 0: not supported
 };
 // The plan with the shortest estimated time, which `us` receives.  to_scratch: the output is partial tiles,
 // splits * M * N floats, which have to fit scratch_bytes; otherwise it is the caller's matrix and K is not cut.
 TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us);
+// parts: gemm_split_parts_bytes(M, K) of scratch for the parts of A, which the fp32 tiles of LS_SPLIT_TILES need.
 bool launch_gemm_tiled(uint32_t dt, int epi, const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out,
-                       const RopeAppend& rope, hipStream_t st);
+                       const RopeAppend& rope, hipStream_t st, void* parts = nullptr);
+size_t gemm_split_parts_bytes(int M, int K);
 // Estimated time of launch_gemm_mfma (ncols: output columns of a tile, 256 or with SwiGLU 128).
 float gemm_mfma_us(int M, int N, int K, int ncols);
 

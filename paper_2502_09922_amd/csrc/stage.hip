@@ -133,7 +133,7 @@ bool span_ok(const ls_cfg* c, int lo, int hi) {
 // ---- workspace carving ------------------------------------------------------------------
 struct Carve {
   size_t cs, x, y, qkv, attn, h, logits, row_seq, row_pos, last_rows, next_tok, xb, xb2, ss_a, ss_b, splitk, splitk_bytes,
-      attn_part, attn_part_bytes, total;
+      attn_part, attn_part_bytes, parts, total;
 };
 
 // more than 64 MiB of partial tiles are never wanted: a call that long fills the chip without splits
@@ -184,6 +184,14 @@ Carve carve(const ls_cfg* c, int lo, int hi) {
   const size_t chunks = ls::attn_decode_scratch_bytes((int)c->n_q_heads, (int)c->n_kv_heads, (int)c->head_dim, (int)c->max_seq);
   if (chunks > w.attn_part_bytes) w.attn_part_bytes = chunks;
   w.attn_part = take(w.attn_part_bytes);
+  // fp32: the bf16 parts of the rows a projection reads (gemm_split_f32.hip)
+  size_t parts = 0;
+  if (c->dtype == LS_DTYPE_F32)
+    for (size_t k : {d, (size_t)c->n_q_heads * c->head_dim, (size_t)c->ffn}) {
+      const size_t b = ls::gemm_split_parts_bytes((int)T, (int)k);
+      if (b > parts) parts = b;
+    }
+  w.parts = take(parts);
   (void)lo;
   w.total = off;
   return w;
@@ -562,6 +570,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   void* attn = ws + s->w.attn;
   void* hbuf = ws + s->w.h;
   const float* cs = (const float*)(ws + s->w.cs);
+  void* parts = ws + s->w.parts;  // fp32 only
   int32_t* row_seq = (int32_t*)(ws + s->w.row_seq);
   int32_t* row_pos = (int32_t*)(ws + s->w.row_pos);
   int32_t* last_rows = (int32_t*)(ws + s->w.last_rows);
@@ -745,7 +754,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     RowsArgs ra;
     ra.rows = rows; ra.d = d; ra.x = x; ra.gamma = gamma; ra.y = y; ra.eps = c.rms_eps; ra.out = to_out ? out : nullptr;
     if (p.splits) {
-      launch_gemm_tiled(dt, TILED_PART, p, A, W, rows, d, K, gsc.splitk, RopeAppend{}, st);
+      launch_gemm_tiled(dt, TILED_PART, p, A, W, rows, d, K, gsc.splitk, RopeAppend{}, st, parts);
       ra.part = gsc.splitk; ra.splits = p.splits;
       launch_rows(dt, ROWS_RESID, ra, st);
     } else if (to_out && dt == BF16 && rows > 64 && gemm_mfma_resid_out_supported(rows, d, K, out)) {
@@ -775,7 +784,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     bool roped = p_qkv.splits && !attn_rotates;
     if (p_qkv.splits) {
       PROBE(LS_OP_GEMM_QKV, launch_gemm_tiled(dt, roped ? TILED_ROPE : TILED_STORE, p_qkv, y, tensor(b, 1), rows, qkv_cols, d,
-                                              qkv, ra, st));
+                                              qkv, ra, st, parts));
     } else if (prefill && dt == BF16 && rows > 64 && attn_prefill_supported(hq, hkv, hd) &&
                gemm_mfma_rope_supported(rows, qkv_cols, d, hq, hkv, hd)) {
       roped = true;
@@ -791,7 +800,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     PROBE(LS_OP_GEMM_O, residual(p_o, attn, tensor(b, 2), hq * hd, tensor(b, 3), false));
     LS_HIP(gate(b, st, 2));
     if (p_gu.splits)
-      PROBE(LS_OP_GEMM_GATEUP, launch_gemm_tiled(dt, TILED_SWIGLU, p_gu, y, tensor(b, 4), rows, F, d, hbuf, RopeAppend{}, st));
+      PROBE(LS_OP_GEMM_GATEUP, launch_gemm_tiled(dt, TILED_SWIGLU, p_gu, y, tensor(b, 4), rows, F, d, hbuf, RopeAppend{}, st, parts));
     else
       PROBE(LS_OP_GEMM_GATEUP, launch_gemm(dt, EPI_SWIGLU, y, tensor(b, 4), rows, F, d, hbuf, nullptr, st, &gsc));
     // the next layer's norm goes along only if its block is known to be there: nothing of this
@@ -817,7 +826,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     const TiledPlan p_head = (dt == F32 || batch > (d > 4096 ? 8 : 16)) && ((uintptr_t)logits & 15) == 0
                                  ? gemm_tiled_plan(dt, TILED_PART, batch, (int)c.vocab, d, false, 0, nullptr)
                                  : TiledPlan{};
-    if (p_head.splits) launch_gemm_tiled(dt, TILED_PART, p_head, y, base + sp[1].off, batch, c.vocab, d, logits, RopeAppend{}, st);
+    if (p_head.splits) launch_gemm_tiled(dt, TILED_PART, p_head, y, base + sp[1].off, batch, c.vocab, d, logits, RopeAppend{}, st, parts);
     else launch_gemm(dt, EPI_F32, y, base + sp[1].off, batch, c.vocab, d, logits, nullptr, st, &gsc);
     launch_argmax(logits, batch, c.vocab, (int32_t*)out, st);
   }
