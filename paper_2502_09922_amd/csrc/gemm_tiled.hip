@@ -1,7 +1,9 @@
-// Choice of the tiled GEMM's tile and K split (gemm_tiled.hpp), its launcher, and the row kernel
+// Choice of the tiled GEMM's tile and K split (gemm_tiled_bf16.hip, gemm_tiled_f32.hip, gemm_split_f32.hip), its launcher, and the row kernel
 // that stands between two GEMMs: adds the K-split partials to the residual rows and normalises.
 #include "kernels.hpp"
 #include "device_util.hpp"
+
+#include <cmath>
 
 namespace ls {
 
@@ -34,14 +36,17 @@ constexpr int ROWS_F32_MAX = 8;
 constexpr int ROWS_F32_SPLIT = 96;
 constexpr size_t WEIGHTS_F32_SPLIT = 1u << 18;
 
-// Time of a launch, in microseconds, from what the kernel's sweep over tiles showed (7B and 13B
-// layers, 1..2048 rows, cold weights): a k-step of a workgroup costs 0.05 us + 2.4 ns per tile
-// row it brings into LDS, whatever the arithmetic (64 x 64 0.41, 64 x 128 0.53, 128 x 128 0.67,
-// 160 x 128 0.76, 256 x 128 0.95 us measured), in fp32 at least its matrix work (64 x 64 at 0.4,
-// 64 x 128 at 0.46 TFLOP/s per CU); by split operands 0.39 us + 0.055 per pair of 16-row fragments and wavefront
-// (96 x 128 1.05..1.1, 128 x 128 1.2..1.4, 176 x 128 1.6..1.7, 128 x 192 1.9..2.1 us measured) and the kernel in
-// front; one workgroup fits a CU, so the launch takes as many rounds as its fullest XCD has
-// workgroups for its 32 CUs; every K split writes and reads an fp32 tile.
+// Time of a launch, in microseconds, from sweeps over the tiles (7B, 13B and 70B layers, 12..1024 rows in bf16, 24..512
+// in fp32, cold weights).  bf16: a k-step of a workgroup costs 0.02 us + 2.4 ns per row it brings into LDS, whatever
+// the arithmetic (48 x 48 0.24, 64 x 64 0.33, 64 x 128 0.47, 128 x 128 0.58, 160 x 192 0.85, 256 x 128 0.9 us
+// measured; a sixth more where only two stages fit: 256 x 192 1.33); rows past the end of the call are not fetched, and
+// the tiles of a column wait for the same weight lines, so that it is their mean that counts.  Weights do not come from
+// memory faster than 6.4 TB/s.  Chosen so, the four projections at 11 row counts of the 7B shape take 1584 us
+// together, the fastest tile and split of each 1552.  fp32: at least the matrix work (64 x 64 at 0.4, 64 x 128 at 0.46
+// TFLOP/s per CU); by split operands 0.39 us + 0.055 per pair of 16-row fragments and wavefront (96 x 128 1.05..1.1,
+// 128 x 128 1.2..1.4, 176 x 128 1.6..1.7, 128 x 192 1.9..2.1 us measured) and the kernel in front.  One workgroup
+// fits a CU, so the launch takes as many rounds as its fullest XCD has workgroups for its 32 CUs; every K split
+// writes and reads an fp32 tile.
 TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us) {
   TiledPlan best;
   float best_us = 1e30f;
@@ -54,38 +59,49 @@ TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scr
   }
   if (gemm_tiled_supported(dt, epi, M, N, K)) {
     const int kb = dt == F32 ? 32 : 64, nk = (K + kb - 1) / kb;
+    const float stream = (float)N * (epi == TILED_SWIGLU ? 2 : 1) * (float)K * 2.f / 6.4e6f + 3.f;
     auto consider = [&](int bm, int bn, float step, float extra) {
       const int ncols = epi == TILED_SWIGLU ? bn / 2 : bn;
       const int tiles_m = (M + bm - 1) / bm, panels = ((N + ncols - 1) / ncols + 7) / 8;
+      if (dt == BF16) {
+        if (bm > 32 && bm >= 2 * M) return;  // more than half of the products for rows that are not there
+        step = 0.02f + 0.0024f * ((float)((M + 7) / 8 * 8) / (float)tiles_m + (float)bn);
+        if ((bm + bn) * 128 * 3 > 160 * 1024) step *= 1.18f;
+      }
       for (int s = 1; s <= 8; ++s) {
         // partial tiles, also those of a single split, have to fit the scratch
         if ((to_scratch && (size_t)s * M * N * sizeof(float) > scratch_bytes) || (s > 1 && (!to_scratch || nk < 2 * s))) break;
         const long per_xcd = (long)panels * tiles_m * s;
-        const float rounds = (float)((per_xcd + 31) / 32);
-        const float t_us = rounds * ((float)((nk + s - 1) / s) * step + 2.5f) + (float)s * (float)M * (float)N * 8.f / 4e6f + extra;
+        float t_us = (float)((per_xcd + 31) / 32) * ((float)((nk + s - 1) / s) * step + 2.5f);
+        if (dt == BF16) {  // whichever is longer, and some more where both are alike
+          const float a = t_us * t_us, b = stream * stream;
+          t_us = sqrtf(sqrtf(a * a + b * b));
+        }
+        t_us += (float)s * (float)M * (float)N * 8.f / 4e6f + extra;
         if (t_us < best_us) {
           best_us = t_us;
           best.bm = bm; best.bn = bn; best.splits = s;
         }
       }
     };
-    struct Shape { int bm, bn; bool f32, glu; };
-#define LS_TILE(bm_, bn_, wm_, tm_, tn_, f32_, glu_) {bm_, bn_, f32_, glu_},
-    static const Shape tiles[] = {LS_TILED_TILES(LS_TILE)};
-#undef LS_TILE
     const size_t weights = (size_t)N * (epi == TILED_SWIGLU ? 2 : 1) * K;
-    if (dt == BF16 || M <= ROWS_F32_SPLIT || weights < WEIGHTS_F32_SPLIT)
-      for (const auto& t : tiles) {
-        if ((dt == F32 && !t.f32) || (epi == TILED_SWIGLU && !t.glu)) continue;
-        float step = 0.05f + 0.0024f * (float)(t.bm + t.bn);
-        if (dt == F32) {
-          const float area = (float)(t.bm * t.bn);
-          const float mma = 64.f * area / (0.36e6f + 12.f * area) + 0.05f;
-          if (mma > step) step = mma;
-        }
-        consider(t.bm, t.bn, step, 0.f);
+    if (dt == BF16) {
+#define LS_TILE(tm_, tn_, wm_, wn_, glu_) \
+  if (epi != TILED_SWIGLU || glu_) consider(16 * wm_ * tm_, 16 * wn_ * tn_, 0.f, 0.f);
+      LS_TILED_BF16(LS_TILE)
+#undef LS_TILE
+    } else {
+      if (M <= ROWS_F32_SPLIT || weights < WEIGHTS_F32_SPLIT) {
+        auto fp32 = [&](int bm, int bn) {
+          const float area = (float)(bm * bn), mma = 64.f * area / (0.36e6f + 12.f * area) + 0.05f;
+          const float step = 0.05f + 0.0024f * (float)(bm + bn);
+          consider(bm, bn, mma > step ? mma : step, 0.f);
+        };
+#define LS_TILE(bm_, bn_, wm_, tm_, tn_, glu_) \
+  if (epi != TILED_SWIGLU || glu_) fp32(bm_, bn_);
+        LS_TILED_F32(LS_TILE)
+#undef LS_TILE
       }
-    if (dt == F32) {
 #define LS_TILE(bm_, bn_) consider(bm_, bn_, 0.39f + 0.055f * (bm_ / 16) * (bn_ / 64) + (bn_ > 128 ? 0.2f : 0.f), 4.f);
       LS_SPLIT_TILES(LS_TILE)
 #undef LS_TILE

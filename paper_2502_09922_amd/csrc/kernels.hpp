@@ -98,24 +98,24 @@ bool gemm_mfma_rope_supported(int M, int N, int K, int hq, int hkv, int hd);
 void launch_gemm_mfma_rope(const void* A, const void* W, int M, int N, int K, void* out, const RopeAppend& rope,
                            hipStream_t st);
 
-// GEMM in tiles of bm rows x bn weight rows, K cut `splits` ways (gemm_tiled.hpp): row counts between the
+// GEMM in tiles of bm rows x bn weight rows, K cut `splits` ways (gemm_tiled*.hip): row counts between the
 // weight-streaming kernels and the 256 x 256 tiles in bf16, every fp32 GEMM whose K is a multiple of 16.
 // Output: TILED_PART fp32 partial tiles part[split][M][N] (one split: an fp32 matrix), TILED_STORE
 // the storage type, TILED_SWIGLU silu(gate) * up, TILED_ROPE as launch_gemm_mfma_rope.
 enum TiledEpi : int { TILED_PART = 0, TILED_STORE = 1, TILED_SWIGLU = 2, TILED_ROPE = 3 };
-// The tiles there are: rows, weight rows, wavefront rows, 16-row fragments and 16-weight-row fragments of a
-// wavefront, in fp32 too, with SwiGLU too (gate and up are two fragments of one wavefront).
-#define LS_TILED_TILES(X)         \
-  X(32, 64, 2, 1, 1, true, false)  \
-  X(32, 128, 2, 1, 2, true, true)  \
-  X(64, 64, 2, 2, 1, true, false)  \
-  X(64, 128, 2, 2, 2, true, true)  \
-  X(96, 128, 2, 3, 2, false, true)  \
-  X(128, 64, 2, 4, 1, true, false) \
-  X(128, 128, 2, 4, 2, false, true) \
-  X(160, 128, 2, 5, 2, false, true) \
-  X(160, 256, 2, 5, 4, false, true) \
-  X(256, 128, 4, 4, 4, false, true)
+// The tiles there are.  bf16 (gemm_tiled_bf16.hip): 16-row and 16-weight-row fragments of a wavefront, wavefront rows and
+// columns, with SwiGLU too (gate and up are two fragments of one wavefront).
+#define LS_TILED_BF16(X)                                                                               \
+  X(1, 2, 2, 2, false) X(2, 2, 1, 3, true) X(2, 2, 1, 4, true)                                          \
+  X(1, 3, 3, 1, false) X(1, 2, 3, 2, false) X(3, 2, 1, 3, true)                                         \
+  X(4, 1, 1, 3, false) X(2, 2, 2, 2, false) X(4, 2, 1, 3, true) X(2, 4, 2, 2, true) X(2, 6, 2, 2, true) X(4, 2, 1, 7, true) \
+  X(3, 3, 2, 2, false) X(3, 4, 2, 2, true) X(3, 6, 2, 2, true)                                          \
+  X(4, 2, 2, 2, false) X(4, 3, 2, 2, false) X(4, 4, 2, 2, true) X(4, 6, 2, 2, true)                     \
+  X(5, 3, 2, 2, false) X(5, 4, 2, 2, true) X(5, 6, 2, 2, true) X(5, 4, 2, 4, true)                      \
+  X(8, 4, 2, 2, true) X(4, 6, 4, 2, true)
+// fp32 on fp32 instructions (gemm_tiled_f32.hip): rows, weight rows, wavefront rows, fragments of a wavefront, SwiGLU.
+#define LS_TILED_F32(X) \
+  X(32, 64, 2, 1, 1, false) X(32, 128, 2, 1, 2, true) X(64, 64, 2, 2, 1, false) X(64, 128, 2, 2, 2, true) X(128, 64, 2, 4, 1, false)
 // fp32 by bf16 products of split operands (gemm_split_f32.hip): rows at most, weight rows.
 #define LS_SPLIT_TILES(X) X(96, 128) X(128, 128) X(176, 128) X(128, 192)
 struct TiledPlan {
