@@ -8,6 +8,8 @@
 // the rows of W alone leave CUs idle; the row kernel adds the parts.
 // The tiled GEMM pads one row to 32 and pays a barrier per k-step: a layer of the 7B shape, one row, took 244 us
 // through it and takes 176 here (0.81 GB of weights); the tiny model's generation 776 and 647 us.
+// A step of the tiny model is nothing but launches, 3 us each: with the norms and the residual adds in here its
+// generation (32 tokens, then 8 steps) takes 555 us instead of 676.
 #include "kernels.hpp"
 #include "device_util.hpp"
 
@@ -15,9 +17,14 @@ namespace ls {
 
 namespace {
 
-template <int EPI, int M, int R, int U>
+// Widest rows whose norm the GEMM takes along: a wavefront keeps them in its registers.
+constexpr int NORM_MAX = 1024;
+
+// NORM: A holds residual rows and every wavefront normalises the ones it multiplies, all of K at once (K <= 256 U).  The
+// sums are those of k_rows in the order of k_rows, so a norm that is launched on its own gives the same bits.
+template <int EPI, int M, int R, int U, bool NORM>
 __global__ void __launch_bounds__(256)
-k_gemm_rows_f32(const float* __restrict__ A, const float* __restrict__ W, int N, int K, float* __restrict__ out) {
+k_gemm_rows_f32(const float* __restrict__ A, const float* __restrict__ W, int N, int K, float* out, RowsF32Fusion f) {
   constexpr bool GLU = EPI == TILED_SWIGLU;
   constexpr int C = GLU ? R / 2 : R;  // output columns of a wavefront
   const int lane = threadIdx.x & 63;
@@ -32,6 +39,16 @@ k_gemm_rows_f32(const float* __restrict__ A, const float* __restrict__ W, int N,
     const int n = min(n0 + r % C, N - 1) + (GLU && r >= C ? N : 0);
     w[r] = reinterpret_cast<const f32x4*>(W + (size_t)n * K);
   }
+  const float* a[M];
+#pragma unroll
+  for (int m = 0; m < M; ++m) a[m] = A + (size_t)(NORM && f.row_map ? f.row_map[m] : m) * K;
+  float base[EPI == TILED_PART ? C : 1][M];  // what the sums are added to
+  if constexpr (EPI == TILED_PART)
+    if (f.add)
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int m = 0; m < M; ++m) base[c][m] = f.add[(size_t)m * N + min(n0 + c, N - 1)];
   float acc[R][M];
 #pragma unroll
   for (int r = 0; r < R; ++r)
@@ -47,7 +64,31 @@ k_gemm_rows_f32(const float* __restrict__ A, const float* __restrict__ W, int N,
       for (int r = 0; r < R; ++r) wv[u][r] = live ? __builtin_nontemporal_load(w[r] + i) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int m = 0; m < M; ++m)
-        xv[u][m] = live ? reinterpret_cast<const f32x4*>(A + (size_t)m * K)[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+        xv[u][m] = live ? reinterpret_cast<const f32x4*>(a[m])[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    if constexpr (NORM) {
+      f32x4 gv[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = (b + u) * 64 + lane;
+        gv[u] = i < nv ? reinterpret_cast<const f32x4*>(f.gamma)[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        float tot = 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const f32x4 v = xv[u][m];
+          float ss = 0.f;
+          ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+          tot += wave_sum(ss);
+        }
+        const float inv = 1.0f / sqrtf(tot / (float)K + f.eps);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) xv[u][m][e] = xv[u][m][e] * inv * gv[u][e];
+      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -72,30 +113,33 @@ k_gemm_rows_f32(const float* __restrict__ A, const float* __restrict__ W, int N,
     if (n0 + c < N)
 #pragma unroll
       for (int m = 0; m < M; ++m) {
-        const float v = GLU ? silu_f(acc[c][m]) * acc[C + c][m] : acc[c][m];
+        float v = GLU ? silu_f(acc[c][m]) * acc[C + c][m] : acc[c][m];
+        if constexpr (EPI == TILED_PART)
+          if (f.add) v += base[c][m];
         out[((size_t)blockIdx.y * M + m) * N + n0 + c] = v;
       }
 }
 
 template <int EPI, int M>
-void launch_m(const float* A, const float* W, int N, int K, int splits, float* out, hipStream_t st) {
+void launch_m(const float* A, const float* W, int N, int K, int splits, float* out, const RowsF32Fusion& f, hipStream_t st) {
   constexpr int R = 4, U = M <= 2 ? 4 : 2, C = EPI == TILED_SWIGLU ? R / 2 : R;
   const dim3 grid((unsigned)((N + 4 * C - 1) / (4 * C)), (unsigned)splits);
-  if (EPI == TILED_PART) hipLaunchKernelGGL((k_gemm_rows_f32<EPI, M, R, U>), grid, dim3(256), 0, st, A, W, N, K, out);
-  else launch_kernel(k_gemm_rows_f32<EPI, M, R, U>, grid, dim3(256), 0, st, A, W, N, K, out);
+  if (f.gamma) launch_kernel(k_gemm_rows_f32<EPI, M, R, NORM_MAX / 256, true>, grid, dim3(256), 0, st, A, W, N, K, out, f);
+  else if (EPI == TILED_PART && !f.add) hipLaunchKernelGGL((k_gemm_rows_f32<EPI, M, R, U, false>), grid, dim3(256), 0, st, A, W, N, K, out, f);
+  else launch_kernel(k_gemm_rows_f32<EPI, M, R, U, false>, grid, dim3(256), 0, st, A, W, N, K, out, f);
 }
 
 template <int EPI>
-bool launch_e(const float* A, const float* W, int M, int N, int K, int splits, float* out, hipStream_t st) {
+bool launch_e(const float* A, const float* W, int M, int N, int K, int splits, float* out, const RowsF32Fusion& f, hipStream_t st) {
   switch (M) {
-    case 1: launch_m<EPI, 1>(A, W, N, K, splits, out, st); return true;
-    case 2: launch_m<EPI, 2>(A, W, N, K, splits, out, st); return true;
-    case 3: launch_m<EPI, 3>(A, W, N, K, splits, out, st); return true;
-    case 4: launch_m<EPI, 4>(A, W, N, K, splits, out, st); return true;
-    case 5: launch_m<EPI, 5>(A, W, N, K, splits, out, st); return true;
-    case 6: launch_m<EPI, 6>(A, W, N, K, splits, out, st); return true;
-    case 7: launch_m<EPI, 7>(A, W, N, K, splits, out, st); return true;
-    case 8: launch_m<EPI, 8>(A, W, N, K, splits, out, st); return true;
+    case 1: launch_m<EPI, 1>(A, W, N, K, splits, out, f, st); return true;
+    case 2: launch_m<EPI, 2>(A, W, N, K, splits, out, f, st); return true;
+    case 3: launch_m<EPI, 3>(A, W, N, K, splits, out, f, st); return true;
+    case 4: launch_m<EPI, 4>(A, W, N, K, splits, out, f, st); return true;
+    case 5: launch_m<EPI, 5>(A, W, N, K, splits, out, f, st); return true;
+    case 6: launch_m<EPI, 6>(A, W, N, K, splits, out, f, st); return true;
+    case 7: launch_m<EPI, 7>(A, W, N, K, splits, out, f, st); return true;
+    case 8: launch_m<EPI, 8>(A, W, N, K, splits, out, f, st); return true;
   }
   return false;
 }
@@ -112,12 +156,16 @@ int gemm_rows_f32_splits(int epi, int M, int N, int K, bool to_scratch, size_t s
   return s;
 }
 
-bool launch_gemm_rows_f32(int epi, const void* A, const void* W, int M, int N, int K, int splits, void* out, hipStream_t st) {
+bool gemm_rows_f32_norm_supported(int M, int K) { return M >= 1 && M <= 8 && K >= 4 && K % 4 == 0 && K <= NORM_MAX; }
+
+bool launch_gemm_rows_f32(int epi, const void* A, const void* W, int M, int N, int K, int splits, void* out, hipStream_t st,
+                          const RowsF32Fusion& f) {
   const float *a = (const float*)A, *w = (const float*)W;
+  if ((f.gamma && (splits != 1 || !gemm_rows_f32_norm_supported(M, K))) || (f.add && (splits != 1 || epi != TILED_PART))) return false;
   switch (epi) {
-    case TILED_PART: return launch_e<TILED_PART>(a, w, M, N, K, splits, (float*)out, st);
-    case TILED_STORE: return launch_e<TILED_STORE>(a, w, M, N, K, splits, (float*)out, st);
-    case TILED_SWIGLU: return launch_e<TILED_SWIGLU>(a, w, M, N, K, splits, (float*)out, st);
+    case TILED_PART: return launch_e<TILED_PART>(a, w, M, N, K, splits, (float*)out, f, st);
+    case TILED_STORE: return launch_e<TILED_STORE>(a, w, M, N, K, splits, (float*)out, f, st);
+    case TILED_SWIGLU: return launch_e<TILED_SWIGLU>(a, w, M, N, K, splits, (float*)out, f, st);
   }
   return false;
 }

@@ -15,9 +15,6 @@ bool launch_gemm_tiled_f32(int epi, const TiledPlan& p, const void* A, const voi
 bool launch_gemm_split_f32(int epi, const TiledPlan& p, const void* A, void* parts, const void* W, int M, int N, int K, void* out,
                            const RopeAppend& rope, hipStream_t st);
 
-int gemm_rows_f32_splits(int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes);
-bool launch_gemm_rows_f32(int epi, const void* A, const void* W, int M, int N, int K, int splits, void* out, hipStream_t st);
-
 bool gemm_tiled_supported(uint32_t dt, int epi, int M, int N, int K) {
   const size_t e = dt == F32 ? 4 : 2, wrows = (size_t)N * (epi == TILED_SWIGLU ? 2 : 1);
   // half k-steps; whole 16-column fragments; 32-bit byte offsets into both operands

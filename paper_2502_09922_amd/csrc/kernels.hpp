@@ -131,6 +131,20 @@ size_t gemm_split_parts_bytes(int M, int K);
 // Estimated time of launch_gemm_mfma (ncols: output columns of a tile, 256 or with SwiGLU 128).
 float gemm_mfma_us(int M, int N, int K, int ncols);
 
+// fp32 GEMM of one to eight rows (gemm_rows_f32.hip), a plan with bm == 0.  gamma: A holds residual rows, their RMSNorm is
+// what is multiplied (row_map: row m of the call is row row_map[m] of A).  add: the output is added to it (TILED_PART).
+// Both need a plan that does not cut K, the norm rows that gemm_rows_f32_norm_supported takes.
+struct RowsF32Fusion {
+  const float* gamma = nullptr;
+  float eps = 0.f;
+  const int32_t* row_map = nullptr;
+  const float* add = nullptr;
+};
+int gemm_rows_f32_splits(int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes);
+bool gemm_rows_f32_norm_supported(int M, int K);
+bool launch_gemm_rows_f32(int epi, const void* A, const void* W, int M, int N, int K, int splits, void* out, hipStream_t st,
+                          const RowsF32Fusion& f = {});
+
 // One pass over rows of width d (a multiple of 4, at most 8192).  Source: the residual rows plus `splits`
 // partial tiles, the call's hidden rows, or embedding rows; the latter two also write the call's
 // bookkeeping (row -> sequence and position, last rows, seq_lens).  Result: the stage's output rows

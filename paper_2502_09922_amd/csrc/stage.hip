@@ -692,30 +692,6 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   auto norm_alone = [&](Block& b) { return probing && s->probe_op == LS_OP_NORM && s->probe_layer == b.layer; };
   bool y_ready = false;  // y holds the normalised rows the next GEMM reads
 
-  const void* table = nullptr;
-  if (s->first) {
-    Block* eb = s->find(LS_BLOCK_EMBED);
-    LS_HIP(gate(*eb, st));  // gate: embedding block has landed
-    table = s->slab + eb->off;
-  }
-  if (rows_one_pass) {
-    RowsArgs ra;
-    ra.rows = rows; ra.d = d; ra.x = x; ra.in = in; ra.table = table; ra.vocab = c.vocab;
-    ra.cu = prefill ? cu_dev : nullptr; ra.batch = batch; ra.max_seq = c.max_seq;
-    ra.row_seq = row_seq; ra.row_pos = row_pos; ra.last_rows = last_rows; ra.seq_lens = kv->seq_lens;
-    Block& b0 = s->blocks[s->layer0];
-    if (landed(b0) && !norm_alone(b0)) {
-      ra.gamma = tensor(b0, 0); ra.y = y; ra.eps = c.rms_eps;
-      y_ready = true;
-    }
-    launch_rows(dt, s->first ? ROWS_EMBED : ROWS_HIDDEN, ra, st);
-  } else {
-    if (prefill) launch_row_index_prefill(cu_dev, batch, rows, row_seq, row_pos, last_rows, st);
-    else launch_row_index_decode(kv->seq_lens, batch, c.max_seq, row_seq, row_pos, last_rows, st);
-    if (s->first) launch_embed(dt, table, (const int32_t*)in, x, rows, d, c.vocab, st);
-    else launch_load_hidden(dt, in, x, (size_t)rows * d, st);
-  }
-
   // The tiled GEMM takes every fp32 projection it supports, and the bf16 ones of all but few rows
   // where it is estimated faster than the 256 x 256 tiles.
   // Partial tiles of a generation step fit the static scratch too, so that both entry points take
@@ -738,6 +714,35 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   const TiledPlan p_o = rows_one_pass && gsc.splitk ? plan(TILED_PART, d, hq * hd) : TiledPlan{};
   const TiledPlan p_gu = plan(TILED_SWIGLU, F, d);
   const TiledPlan p_dn = rows_one_pass && gsc.splitk ? plan(TILED_PART, d, F) : TiledPlan{};
+  // Few fp32 rows of small matrices are a chain of launches of 2 us each.  A projection whose K is not cut takes the norm
+  // of its rows along, and adds its sums to the residual rows itself: 13 launches for a step of the two-layer tiny model
+  // instead of 18.  A norm that is folded into the row kernel instead, behind a projection whose K is cut, costs nothing.
+  auto rows_f32 = [&](const TiledPlan& p) { return dt == F32 && p.splits == 1 && !p.bm; };
+  auto folds_norm = [&](const TiledPlan& p) { return rows_one_pass && rows_f32(p) && gemm_rows_f32_norm_supported(rows, d); };
+
+  const void* table = nullptr;
+  if (s->first) {
+    Block* eb = s->find(LS_BLOCK_EMBED);
+    LS_HIP(gate(*eb, st));  // gate: embedding block has landed
+    table = s->slab + eb->off;
+  }
+  if (rows_one_pass) {
+    RowsArgs ra;
+    ra.rows = rows; ra.d = d; ra.x = x; ra.in = in; ra.table = table; ra.vocab = c.vocab;
+    ra.cu = prefill ? cu_dev : nullptr; ra.batch = batch; ra.max_seq = c.max_seq;
+    ra.row_seq = row_seq; ra.row_pos = row_pos; ra.last_rows = last_rows; ra.seq_lens = kv->seq_lens;
+    Block& b0 = s->blocks[s->layer0];
+    if (landed(b0) && !norm_alone(b0) && !folds_norm(p_qkv)) {
+      ra.gamma = tensor(b0, 0); ra.y = y; ra.eps = c.rms_eps;
+      y_ready = true;
+    }
+    launch_rows(dt, s->first ? ROWS_EMBED : ROWS_HIDDEN, ra, st);
+  } else {
+    if (prefill) launch_row_index_prefill(cu_dev, batch, rows, row_seq, row_pos, last_rows, st);
+    else launch_row_index_decode(kv->seq_lens, batch, c.max_seq, row_seq, row_pos, last_rows, st);
+    if (s->first) launch_embed(dt, table, (const int32_t*)in, x, rows, d, c.vocab, st);
+    else launch_load_hidden(dt, in, x, (size_t)rows * d, st);
+  }
 
   auto norm = [&](const void* gamma) {
     if (rows_one_pass) {
@@ -753,7 +758,11 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   auto residual = [&](const TiledPlan& p, const void* A, const void* W, int K, const void* gamma, bool to_out) {
     RowsArgs ra;
     ra.rows = rows; ra.d = d; ra.x = x; ra.gamma = gamma; ra.y = y; ra.eps = c.rms_eps; ra.out = to_out ? out : nullptr;
-    if (p.splits) {
+    if (rows_f32(p) && !gamma) {
+      RowsF32Fusion f;
+      f.add = x;
+      launch_gemm_rows_f32(TILED_PART, A, W, rows, d, K, 1, to_out ? out : x, st, f);
+    } else if (p.splits) {
       launch_gemm_tiled(dt, TILED_PART, p, A, W, rows, d, K, gsc.splitk, RopeAppend{}, st, parts);
       ra.part = gsc.splitk; ra.splits = p.splits;
       launch_rows(dt, ROWS_RESID, ra, st);
@@ -775,14 +784,20 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     char* kc = (char*)kv->k + li * kv_layer;
     char* vc = (char*)kv->v + li * kv_layer;
 
-    if (!y_ready) PROBE(LS_OP_NORM, norm(tensor(b, 0)));
+    const bool fold_qkv = folds_norm(p_qkv) && !norm_alone(b), fold_gu = folds_norm(p_gu);
+    RowsF32Fusion normed;
+    normed.eps = c.rms_eps;
+    if (!y_ready && !fold_qkv) PROBE(LS_OP_NORM, norm(tensor(b, 0)));
     RopeAppend ra;
     ra.cs = cs; ra.row_seq = row_seq; ra.row_pos = row_pos;
     ra.hq = hq; ra.hkv = hkv; ra.hd = hd; ra.max_seq = c.max_seq;
     ra.kc = (__bf16*)kc; ra.vc = (__bf16*)vc;
     // RoPE and the cache append ride in the QKV projection's epilogue
     bool roped = p_qkv.splits && !attn_rotates;
-    if (p_qkv.splits) {
+    if (fold_qkv) {
+      normed.gamma = (const float*)tensor(b, 0);
+      PROBE(LS_OP_GEMM_QKV, launch_gemm_rows_f32(TILED_STORE, x, tensor(b, 1), rows, qkv_cols, d, 1, qkv, st, normed));
+    } else if (p_qkv.splits) {
       PROBE(LS_OP_GEMM_QKV, launch_gemm_tiled(dt, roped ? TILED_ROPE : TILED_STORE, p_qkv, y, tensor(b, 1), rows, qkv_cols, d,
                                               qkv, ra, st, parts));
     } else if (prefill && dt == BF16 && rows > 64 && attn_prefill_supported(hq, hkv, hd) &&
@@ -797,9 +812,12 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
                                                   s->w.attn_part_bytes ? (float*)(ws + s->w.attn_part) : nullptr,
                                                   s->w.attn_part_bytes, roped));
     LS_HIP(gate(b, st, 1));
-    PROBE(LS_OP_GEMM_O, residual(p_o, attn, tensor(b, 2), hq * hd, tensor(b, 3), false));
+    PROBE(LS_OP_GEMM_O, residual(p_o, attn, tensor(b, 2), hq * hd, fold_gu ? nullptr : tensor(b, 3), false));
     LS_HIP(gate(b, st, 2));
-    if (p_gu.splits)
+    normed.gamma = (const float*)tensor(b, 3);
+    if (fold_gu)
+      PROBE(LS_OP_GEMM_GATEUP, launch_gemm_rows_f32(TILED_SWIGLU, x, tensor(b, 4), rows, F, d, 1, hbuf, st, normed));
+    else if (p_gu.splits)
       PROBE(LS_OP_GEMM_GATEUP, launch_gemm_tiled(dt, TILED_SWIGLU, p_gu, y, tensor(b, 4), rows, F, d, hbuf, RopeAppend{}, st, parts));
     else
       PROBE(LS_OP_GEMM_GATEUP, launch_gemm(dt, EPI_SWIGLU, y, tensor(b, 4), rows, F, d, hbuf, nullptr, st, &gsc));
@@ -807,7 +825,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     // layer waits for it
     const bool more = li + 1 < n_layers;
     Block* next = more ? &s->blocks[s->layer0 + li + 1] : nullptr;
-    y_ready = more && p_dn.splits && landed(*next) && !norm_alone(*next);
+    y_ready = more && p_dn.splits && landed(*next) && !norm_alone(*next) && !folds_norm(p_qkv);
     LS_HIP(gate(b, st, 3));
     PROBE(LS_OP_GEMM_DOWN, residual(p_dn, hbuf, tensor(b, 5), F, y_ready ? tensor(*next, 0) : nullptr, !more && !s->last));
     if (timed) LS_HIP(hipEventRecord(s->comp_end[li], st));
@@ -822,12 +840,18 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     const char* base = s->slab + hb->off;
     LS_HIP(gate(*hb, st));  // gate: head block has landed
     float* logits = logits_out ? logits_out : (float*)(ws + s->w.logits);
-    launch_rmsnorm(dt, x, base + sp[0].off, y, batch, d, c.rms_eps, last_rows, st);
     const TiledPlan p_head = (dt == F32 || batch > (d > 4096 ? 8 : 16)) && ((uintptr_t)logits & 15) == 0
                                  ? gemm_tiled_plan(dt, TILED_PART, batch, (int)c.vocab, d, false, 0, nullptr)
                                  : TiledPlan{};
-    if (p_head.splits) launch_gemm_tiled(dt, TILED_PART, p_head, y, base + sp[1].off, batch, c.vocab, d, logits, RopeAppend{}, st, parts);
-    else launch_gemm(dt, EPI_F32, y, base + sp[1].off, batch, c.vocab, d, logits, nullptr, st, &gsc);
+    if (rows_f32(p_head) && gemm_rows_f32_norm_supported(batch, d)) {
+      RowsF32Fusion f;
+      f.gamma = (const float*)(base + sp[0].off); f.eps = c.rms_eps; f.row_map = last_rows;
+      launch_gemm_rows_f32(TILED_PART, x, base + sp[1].off, batch, c.vocab, d, 1, logits, st, f);
+    } else {
+      launch_rmsnorm(dt, x, base + sp[0].off, y, batch, d, c.rms_eps, last_rows, st);
+      if (p_head.splits) launch_gemm_tiled(dt, TILED_PART, p_head, y, base + sp[1].off, batch, c.vocab, d, logits, RopeAppend{}, st, parts);
+      else launch_gemm(dt, EPI_F32, y, base + sp[1].off, batch, c.vocab, d, logits, nullptr, st, &gsc);
+    }
     launch_argmax(logits, batch, c.vocab, (int32_t*)out, st);
   }
 
