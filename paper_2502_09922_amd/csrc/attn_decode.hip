@@ -65,7 +65,7 @@ k_attn_decode(const T* __restrict__ qkv, int qkv_stride, const float2* __restric
   constexpr int U = (G >= 4 && sizeof(T) == 2) ? 2 : LS_ATTN_U;  // load instructions in flight per operand
   __shared__ float sm_m[NW][G], sm_l[NW][G];
   __shared__ float sm_acc[NW][G][HD];
-  const int r = blockIdx.x, kh = blockIdx.y;
+  const int r = blockIdx.y, kh = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int pos = row_pos[r];
   if (pos < 0) return;  // a sequence with no room left: whole workgroup leaves together
@@ -292,7 +292,7 @@ struct Args {
 
 template <class T, int HD, int G>
 void launch_g(const Args& a, hipStream_t st) {
-  k_attn_decode<T, HD, G><<<dim3(a.rows, a.hkv, a.nchunk), waves_for<T>(G) * 64, 0, st>>>(
+  k_attn_decode<T, HD, G><<<dim3(a.hkv, a.rows, a.nchunk), waves_for<T>(G) * 64, 0, st>>>(
       (const T*)a.qkv, a.qkv_stride, (const float2*)a.cs, (T*)a.kc, (T*)a.vc, a.row_seq, a.row_pos, a.hkv * G, a.hkv, a.max_seq,
       (T*)a.out, a.part, a.nchunk, a.chunk_keys);
   if (a.nchunk > 1)

@@ -65,7 +65,7 @@ k_attn_decode_gqa(const bf16* __restrict__ qkv, int qkv_stride, const float2* __
                   const int32_t* __restrict__ row_pos, int hq, int hkv, int G, int max_seq, bf16* __restrict__ out,
                   float* __restrict__ part, int nchunk, int tpc) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int r = blockIdx.x, kh = blockIdx.y;
+  const int r = blockIdx.y, kh = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int pos = row_pos[r];
   if (pos < 0) return;  // a sequence with no room left: whole workgroup leaves together
@@ -296,7 +296,7 @@ void launch_nw(const void* qkv, int qkv_stride, const float* cs, void* kc, void*
   constexpr int SMEM = NW * 2 * TILE_BYTES;  // >= the merge area: NW * (32 + 16*128) floats
   static std::atomic<uint64_t> lds_allowed{0};
   allow_dynamic_lds((const void*)k_attn_decode_gqa<NW>, SMEM, lds_allowed);
-  dim3 grid(rows, hkv, nchunk);
+  dim3 grid(hkv, rows, nchunk);
   k_attn_decode_gqa<NW><<<grid, NW * 64, SMEM, st>>>((const bf16*)qkv, qkv_stride, (const float2*)cs, (bf16*)kc,
                                                      (bf16*)vc, row_seq, row_pos, hq, hkv, hq / hkv, max_seq, (bf16*)out,
                                                      part, nchunk, tpc);
