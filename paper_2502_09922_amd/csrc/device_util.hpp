@@ -93,6 +93,30 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
+// Sequences of a decode attention launch by length: which row has rank `rank`, the longest first (of equals the lower
+// index), among `rows` <= MOST rows.  All threads of a workgroup of at least MOST threads call it.
+template <int MOST>
+__device__ __forceinline__ int row_by_length(const int32_t* __restrict__ row_pos, int rows, int rank) {
+  __shared__ __attribute__((aligned(16))) int len[MOST];
+  __shared__ int found;
+  const int t = threadIdx.x;
+  int p = -2;  // shorter than any row
+  if (t < rows) p = row_pos[t];
+  if (t < MOST) len[t] = p;
+  __syncthreads();
+  if (t < rows) {
+    int before = 0;
+    for (int j = 0; j < rows; j += 4) {
+      const int4 v = *reinterpret_cast<const int4*>(len + j);
+      before += (v.x > p || (v.x == p && j < t)) + (v.y > p || (v.y == p && j + 1 < t)) + (v.z > p || (v.z == p && j + 2 < t)) +
+                (v.w > p || (v.w == p && j + 3 < t));
+    }
+    if (before == rank) found = t;
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(found);
+}
+
 constexpr int waitcnt_vm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }  // vector memory only
 
 // Wait until at most n of this wavefront's vector memory instructions are on their way, n known at run time (the
