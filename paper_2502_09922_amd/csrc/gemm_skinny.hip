@@ -253,7 +253,7 @@ void launch_kn(const void* X, const void* W, int M, int N, int K, void* out, flo
 template <int MT, int EPI, int KS>
 void launch_k(const void* X, const void* W, int M, int N, int K, void* out, float* resid, const SkinnyFusion& fu,
               hipStream_t st) {
-  if constexpr (EPI == EPI_STORE || EPI == EPI_SWIGLU) {
+  if constexpr (EPI == EPI_STORE || EPI == EPI_SWIGLU || (EPI == EPI_F32 && MT == 1)) {
     if (fu.ss_in) { launch_kn<MT, EPI, KS, true>(X, W, M, N, K, out, resid, fu, st); return; }
   }
   launch_kn<MT, EPI, KS, false>(X, W, M, N, K, out, resid, fu, st);

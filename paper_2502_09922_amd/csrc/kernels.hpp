@@ -178,7 +178,7 @@ void launch_rows(uint32_t dt, int src, const RowsArgs& a, hipStream_t st);
 //   xb_out != nullptr (EPI_RESID): also write xb_out[M,N] = bf16(x_new * gamma_out[n])
 //     (gamma_out == nullptr: no gain) and each row's sum of squares of x_new per 16-column
 //     tile to ss_out[M][N/16].
-//   ss_in != nullptr (EPI_STORE / EPI_SWIGLU): X is such a copy; the accumulator is scaled
+//   ss_in != nullptr (EPI_STORE / EPI_SWIGLU, EPI_F32 of up to 16 rows): X is such a copy; the accumulator is scaled
 //     by 1/sqrt(sum(ss_in[row][0..n_part)) / K + eps) of its row in the epilogue.
 struct SkinnyFusion {
   const float* ss_in = nullptr;
