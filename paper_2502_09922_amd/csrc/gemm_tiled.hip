@@ -167,6 +167,18 @@ __global__ void __launch_bounds__(NT) k_rows(RowsArgs a) {
     return v;
   };
   float* xr = a.x + (size_t)r * a.d;
+  // few rows: the gain is asked for before the rows, so that it is there when they are; many rows have the registers
+  // for it only behind them
+  constexpr bool EARLY = P <= 2;
+  T4 gain[P];
+  auto load_gain = [&]() {
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const int idx = threadIdx.x + NT * i;
+      gain[i] = reinterpret_cast<const T4*>(a.gamma)[idx < nv ? idx : 0];
+    }
+  };
+  if (EARLY && a.gamma) load_gain();
   f32x4 v[P];
   if constexpr (SRC == ROWS_RESID) {
 #pragma unroll
@@ -234,12 +246,7 @@ __global__ void __launch_bounds__(NT) k_rows(RowsArgs a) {
       if (idx < nv) reinterpret_cast<f32x4*>(xr)[idx] = v[i];
     }
   if (!a.gamma) return;
-  f32x4 g[P];
-#pragma unroll
-  for (int i = 0; i < P; ++i) {
-    const int idx = threadIdx.x + NT * i;
-    g[i] = idx < nv ? widen((const T*)a.gamma + idx * 4, true) : f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  if (!EARLY) load_gain();
   float ss = 0.f;
 #pragma unroll
   for (int i = 0; i < P; ++i) ss += v[i][0] * v[i][0] + v[i][1] * v[i][1] + v[i][2] * v[i][2] + v[i][3] * v[i][3];
@@ -257,7 +264,7 @@ __global__ void __launch_bounds__(NT) k_rows(RowsArgs a) {
     if (idx < nv) {
       T4 t;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) t[e] = from_f<T>(v[i][e] * inv * g[i][e]);
+      for (int e = 0; e < 4; ++e) t[e] = from_f<T>(v[i][e] * inv * to_f(gain[i][e]));
       *reinterpret_cast<T4*>(yr + idx * 4) = t;
     }
   }
