@@ -53,6 +53,12 @@ struct Tile {
   static constexpr int BM = 16 * WM * TM, BN = 16 * WN * TN, SIZE = (BM + BN) * 128;
   static constexpr int FIT = 160 * 1024 / SIZE, NS = FIT > 6 ? 6 : FIT, SMEM = NS * SIZE;
   static constexpr int F = ((BM + BN) / 8 + FILLERS - 1) / FILLERS;  // fills of a wavefront in a k-step, eight rows each
+  // Two k-steps are filled at a time, the two lines of a row that lie side by side one after the other, where six stages
+  // are all that fits and what is on its way is enough with two stages less: 171..213 lines.  Two layers of a step: 13B,
+  // 100 rows, whose QKV takes 128 x 64, 664 -> 658 us; 70B, 64 rows, whose O and down take 64 x 128, 725 -> 718.  With
+  // fewer lines a k-step the two stages are missed, also with eight or ten of them (48 x 48 and 48 x 64, 45 rows: +2.5 %
+  // of the pass); with more lines there is no sixth stage.
+  static constexpr bool PAIRS = NS == 6 && FIT < 8;
   static_assert(NS >= 2 && (NS - 2) * F < 64, "");
 };
 
@@ -115,7 +121,7 @@ k_gemm_tiled(const bf16* __restrict__ A, const bf16* __restrict__ W, int M, int 
     auto run = [&](auto once_, auto count_) {
       constexpr bool ONCE = decltype(once_)::value;
       constexpr int C = decltype(count_)::value;  // f, or -1: not known
-      int kc = ONCE && !ragged ? tn % n : 0, slot = 0;
+      int kc = ONCE && !ragged ? (TL::PAIRS ? tn % n & ~1 : tn % n) : 0, slot = 0;
       auto fill = [&]() {
         const size_t ko = (size_t)(t0 + kc) * 128;
         const char *a = (const char*)A + ko, *w = (const char*)W + ko;
@@ -134,20 +140,67 @@ k_gemm_tiled(const bf16* __restrict__ A, const bf16* __restrict__ W, int M, int 
         }
         slot = slot + 1 == NS ? 0 : slot + 1;
       };
-      for (int s = 0; s < NS; ++s)
-        if (s < n) fill();
-      wait_vm((min(n, NS) - 1) * f);
-      __builtin_amdgcn_s_barrier();  // 0
-      int t = 1;
-      for (; t + NS - 1 < n; ++t) {
-        if constexpr (C >= 0) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NS - 2) * C));
-        else wait_vm((NS - 2) * f);
-        __builtin_amdgcn_s_barrier();  // t
-        fill();                        // of k-step t + NS - 1, into the slot of t - 1
-      }
-      for (; t < n; ++t) {
-        wait_vm((n - t - 1) * f);
-        __builtin_amdgcn_s_barrier();  // t
+      auto fill2 = [&](bool two) {  // the next k-step and the one behind it
+        if (!two) {
+          fill();
+          return;
+        }
+        const int ka = t0 + kc;
+        if (++kc == n) kc = 0;
+        const int kb = t0 + kc;
+        if (++kc == n) kc = 0;
+        unsigned char* to = smem + slot * TL::SIZE;
+        const bool ha = ragged && ka == nk - 1, hb = ragged && kb == nk - 1;
+        auto line = [&](int i, int k, bool half, unsigned char* at) {
+          unsigned o = off[i];
+          if (half) o -= (((lane >> 2) & 1) ^ ((dst[i] >> 10) & 1)) != 0 ? 64u : 0u;
+          const size_t ko = (size_t)k * 128;
+          if (p + FILLERS * i < la) __builtin_amdgcn_global_load_lds((const void*)((const char*)A + ko + o), (lds_void*)(at + dst[i]), 16, 0, 0);
+          else __builtin_amdgcn_global_load_lds((const void*)((const char*)W + ko + o), (lds_void*)(at + dst[i]), 16, 0, ONCE ? 2 : 0);
+        };
+#pragma unroll
+        for (int i = 0; i < F; ++i) {
+          if (C >= 0 ? i >= C : i >= f) continue;
+          line(i, ka, ha, to);
+          line(i, kb, hb, to + TL::SIZE);
+        }
+        slot = slot + 2 == NS ? 0 : slot + 2;
+      };
+      if constexpr (TL::PAIRS) {
+        for (int s = 0; s < NS; s += 2)
+          if (s < n) fill2(s + 1 < n);
+        wait_vm((min(n, NS) - min(n, 2)) * f);
+        __builtin_amdgcn_s_barrier();  // 0
+        int t = 1;
+        for (; t + NS < n; t += 2) {
+          __builtin_amdgcn_s_barrier();  // t: came with t - 1
+          if constexpr (C >= 0) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NS - 4) * C));
+          else wait_vm((NS - 4) * f);
+          __builtin_amdgcn_s_barrier();  // t + 1
+          fill2(true);                   // of k-steps t + NS - 1 and t + NS, into the slots of t - 1 and t
+        }
+        for (; t < n; ++t) {
+          const bool even = !(t & 1);
+          if (even) wait_vm((min(n, t - 2 + NS) - min(n, t + 2)) * f);
+          __builtin_amdgcn_s_barrier();  // t
+          if (even && t + NS - 2 < n) fill2(t + NS - 1 < n);
+        }
+      } else {
+        for (int s = 0; s < NS; ++s)
+          if (s < n) fill();
+        wait_vm((min(n, NS) - 1) * f);
+        __builtin_amdgcn_s_barrier();  // 0
+        int t = 1;
+        for (; t + NS - 1 < n; ++t) {
+          if constexpr (C >= 0) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NS - 2) * C));
+          else wait_vm((NS - 2) * f);
+          __builtin_amdgcn_s_barrier();  // t
+          fill();                        // of k-step t + NS - 1, into the slot of t - 1
+        }
+        for (; t < n; ++t) {
+          wait_vm((n - t - 1) * f);
+          __builtin_amdgcn_s_barrier();  // t
+        }
       }
       __builtin_amdgcn_s_barrier();  // n
     };
