@@ -207,6 +207,13 @@ ls_status ls_stage_prefill(ls_stage* stage, const void* in, const int32_t* cu_se
                            const ls_kv* kv, void* out, float* logits_out, void* hip_stream);
 
 /*
+ * dev[0..n) = host[0..n), in the order of `hip_stream`: the values ride in the arguments of kernels (64 to a
+ * launch), so the call neither waits for the stream, as a copy from pageable memory does, nor needs pinned memory,
+ * and `host` may change as soon as it returns.  For the cu_seqlens of a prompt pass.
+ */
+ls_status ls_write_ints(int32_t* dev, const int32_t* host, int n, void* hip_stream);
+
+/*
  * One generation step: one new row per sequence at position seq_lens[b], appended to the
  * cache; attends to positions 0..seq_lens[b].
  *   in        device: int32 [batch] token ids (first stage) or hidden [batch, hidden].

@@ -78,6 +78,7 @@ _SIGS = {
     "ls_stage_adopt_block": (C.c_int, [_P, C.c_int, _P]),
     "ls_stage_reset_blocks": (C.c_int, [_P]),
     "ls_stage_prefill": (C.c_int, [_P, _P, _P, C.POINTER(C.c_int32), C.c_int, C.c_int, C.POINTER(ls_kv), _P, _P, _P]),
+    "ls_write_ints": (C.c_int, [_P, C.POINTER(C.c_int32), C.c_int, _P]),
     "ls_stage_decode": (C.c_int, [_P, _P, C.c_int, C.c_int, C.POINTER(ls_kv), _P, _P, _P]),
     "ls_stage_decode_static": (C.c_int, [_P, _P, C.c_int, C.c_int, C.POINTER(ls_kv), _P, _P, _P]),
     "ls_stage_check_prefill": (C.c_int, [_P, C.POINTER(C.c_int32), C.c_int, C.c_int]),
@@ -249,7 +250,13 @@ class Stage:
         cu = np.zeros(len(lengths) + 1, np.int32)
         cu[1:] = np.cumsum(np.asarray(lengths, dtype=np.int64))
         total, batch = int(cu[-1]), len(lengths)
-        cu_dev = torch.from_numpy(cu).to(self.device)
+        if torch.cuda.current_stream(self.device).cuda_stream == self._stream_ptr(stream):
+            # in stream order: a copy from pageable memory would wait here for everything enqueued before
+            cu_dev = torch.empty(batch + 1, dtype=torch.int32, device=self.device)
+            check(lib.ls_write_ints(cu_dev.data_ptr(), cu.ctypes.data_as(C.POINTER(C.c_int32)), batch + 1, self._stream_ptr(stream)))
+            inp.record_stream(torch.cuda.current_stream(self.device))  # may be another stream's, and the pass outlives this call
+        else:
+            cu_dev = torch.from_numpy(cu).to(self.device)
         out = (torch.empty(batch, dtype=torch.int32, device=self.device) if self.last
                else torch.empty(total, self.shape.hidden, dtype=self.tdtype, device=self.device))
         logits = (torch.empty(batch, self.shape.vocab, dtype=torch.float32, device=self.device)

@@ -54,7 +54,7 @@ struct Tile {
   static constexpr int FIT = 160 * 1024 / SIZE, NS = FIT > 6 ? 6 : FIT, SMEM = NS * SIZE;
   static constexpr int F = ((BM + BN) / 8 + FILLERS - 1) / FILLERS;  // fills of a wavefront in a k-step, eight rows each
   // Two k-steps are filled at a time, the two lines of a row that lie side by side one after the other, where six stages
-  // are all that fits and what is on its way is enough with two stages less: 171..213 lines.  Two layers of a step: 13B,
+  // are all that fits and what is on its way is enough with two stages less: 161..213 lines.  Two layers of a step: 13B,
   // 100 rows, whose QKV takes 128 x 64, 664 -> 658 us; 70B, 64 rows, whose O and down take 64 x 128, 725 -> 718.  With
   // fewer lines a k-step the two stages are missed, also with eight or ten of them (48 x 48 and 48 x 64, 45 rows: +2.5 %
   // of the pass); with more lines there is no sixth stage.

@@ -21,6 +21,9 @@ struct LaunchTiming {
 };
 LaunchTiming& launch_timing();
 
+// dst[0..n) = src[0..n) (host), by value in the kernels' arguments.
+void launch_write_int32(int32_t* dst, const int32_t* src, int n, hipStream_t st);
+
 // What a GEMM does with its fp32 accumulators.
 enum Epilogue : int {
   EPI_STORE = 0,   // out[M,N] in dtype

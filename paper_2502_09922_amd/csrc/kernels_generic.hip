@@ -499,6 +499,23 @@ void launch_attention_generic(uint32_t dt, const void* qkv, int qkv_stride, cons
                                                    (bf16*)out);
 }
 
+// ------------------------------------------------------------------ small host arrays
+struct Int32s {
+  int32_t v[64];
+};
+__global__ void __launch_bounds__(64) k_write_int32(int32_t* dst, Int32s src, int n) {
+  if ((int)threadIdx.x < n) dst[threadIdx.x] = src.v[threadIdx.x];
+}
+
+void launch_write_int32(int32_t* dst, const int32_t* src, int n, hipStream_t st) {
+  for (int i = 0; i < n; i += 64) {
+    const int m = n - i < 64 ? n - i : 64;
+    Int32s a{};
+    for (int j = 0; j < m; ++j) a.v[j] = src[i + j];
+    k_write_int32<<<1, 64, 0, st>>>(dst + i, a, m);
+  }
+}
+
 // ------------------------------------------------------------------ greedy argmax
 // One 1024-thread workgroup per row.  A thread walks its indices in ascending order, eight
 // independent loads at a time (one memory round trip per eight elements instead of per element).

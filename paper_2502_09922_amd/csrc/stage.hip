@@ -981,6 +981,13 @@ ls_status ls_stage_prefill(ls_stage* s, const void* in, const int32_t* cu_dev, c
                  workspace_scratch(s));
 }
 
+ls_status ls_write_ints(int32_t* dev, const int32_t* host, int n, void* hip_stream) {
+  if (!dev || !host || n < 0) return fail(LS_ERR_INVALID_ARG, "ls_write_ints: NULL pointer or negative count");
+  ls::launch_write_int32(dev, host, n, (hipStream_t)hip_stream);
+  LS_HIP(hipGetLastError());
+  return LS_OK;
+}
+
 ls_status ls_stage_decode(ls_stage* s, const void* in, int batch, int max_ctx, const ls_kv* kv, void* out,
                           float* logits_out, void* hip_stream) {
   ls_status rc = check_pointers("ls_stage_decode", s, in, kv, out, logits_out);
