@@ -12,10 +12,13 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libls_stage.so")
 
-# packed fp32 instructions are switched off for every device compile
+# packed fp32 instructions are switched off for every device compile; a kernel's first arguments (up to a structure, at
+# most 12 to 14 words) arrive in scalar registers instead of by a load that its first addresses wait for: steps of
+# few rows 172.7 -> 169.7 us (7B, one row) and 142.7 -> 140.9 (8 rows and head), other passes 0.2 to 0.7 %
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
 ]
 
 

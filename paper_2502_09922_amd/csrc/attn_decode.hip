@@ -54,10 +54,9 @@ template <class T, int HD, int G>
 // with one query head per kv head the kernel fits 64 registers: eight wavefronts per SIMD, two
 // 16-wavefront workgroups per CU
 __global__ void __launch_bounds__(waves_for<T>(G) * 64, (G == 1 && sizeof(T) == 2 ? 8 : 1))
-k_attn_decode(const T* __restrict__ qkv, int qkv_stride, const float2* __restrict__ cs,
-              T* __restrict__ kc, T* __restrict__ vc, const int32_t* __restrict__ row_seq,
-              const int32_t* __restrict__ row_pos, int hq, int hkv, int max_seq, T* __restrict__ out,
-              float* __restrict__ part, int nchunk, int chunk_keys) {
+k_attn_decode(const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_seq, const T* __restrict__ qkv,
+              const float2* __restrict__ cs, T* __restrict__ kc, T* __restrict__ vc, int qkv_stride, int hq, int hkv, int max_seq,
+              T* __restrict__ out, float* __restrict__ part, int nchunk, int chunk_keys) {
   typedef typename Vec8<T>::type T8;
   constexpr int NW = waves_for<T>(G);
   constexpr int LPK = HD / 8;     // lanes per key
@@ -293,7 +292,7 @@ struct Args {
 template <class T, int HD, int G>
 void launch_g(const Args& a, hipStream_t st) {
   k_attn_decode<T, HD, G><<<dim3(a.hkv, a.rows, a.nchunk), waves_for<T>(G) * 64, 0, st>>>(
-      (const T*)a.qkv, a.qkv_stride, (const float2*)a.cs, (T*)a.kc, (T*)a.vc, a.row_seq, a.row_pos, a.hkv * G, a.hkv, a.max_seq,
+      a.row_pos, a.row_seq, (const T*)a.qkv, (const float2*)a.cs, (T*)a.kc, (T*)a.vc, a.qkv_stride, a.hkv * G, a.hkv, a.max_seq,
       (T*)a.out, a.part, a.nchunk, a.chunk_keys);
   if (a.nchunk > 1)
     k_attn_decode_merge<T, HD><<<dim3(a.rows, a.hkv * G), HD, 0, st>>>(a.part, a.row_pos, a.hkv * G, a.nchunk, a.chunk_keys, (T*)a.out);

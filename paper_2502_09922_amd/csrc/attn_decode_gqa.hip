@@ -65,10 +65,9 @@ constexpr int PART_HDR = 32;             // floats in front of a partial result:
 
 template <int NW>
 __global__ void __launch_bounds__(NW * 64)
-k_attn_decode_gqa(const bf16* __restrict__ qkv, int qkv_stride, const float2* __restrict__ cs,
-                  bf16* __restrict__ kc, bf16* __restrict__ vc, const int32_t* __restrict__ row_seq,
-                  const int32_t* __restrict__ row_pos, int hq, int hkv, int G, int max_seq, bf16* __restrict__ out,
-                  float* __restrict__ part, int nchunk, int tpc, bool by_length) {
+k_attn_decode_gqa(const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_seq, const bf16* __restrict__ qkv,
+                  const float2* __restrict__ cs, bf16* __restrict__ kc, bf16* __restrict__ vc, int qkv_stride, int hq, int hkv,
+                  int G, int max_seq, bf16* __restrict__ out, float* __restrict__ part, int nchunk, int tpc, bool by_length) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int kh = blockIdx.x;
   int r = blockIdx.y;
@@ -307,8 +306,8 @@ void launch_nw(const void* qkv, int qkv_stride, const float* cs, void* kc, void*
   static std::atomic<uint64_t> lds_allowed{0};
   allow_dynamic_lds((const void*)k_attn_decode_gqa<NW>, SMEM, lds_allowed);
   dim3 grid(hkv, rows, nchunk);
-  k_attn_decode_gqa<NW><<<grid, NW * 64, SMEM, st>>>((const bf16*)qkv, qkv_stride, (const float2*)cs, (bf16*)kc,
-                                                     (bf16*)vc, row_seq, row_pos, hq, hkv, hq / hkv, max_seq, (bf16*)out,
+  k_attn_decode_gqa<NW><<<grid, NW * 64, SMEM, st>>>(row_pos, row_seq, (const bf16*)qkv, (const float2*)cs, (bf16*)kc,
+                                                     (bf16*)vc, qkv_stride, hq, hkv, hq / hkv, max_seq, (bf16*)out,
                                                      part, nchunk, tpc, nchunk == 1 && rows > 1 && rows <= NW * 64 /* a thread each */);
   if (nchunk > 1)
     k_attn_gqa_merge<<<dim3(rows, hkv), 256, 0, st>>>(part, row_pos, hq, hkv, hq / hkv, nchunk, tpc, (bf16*)out);

@@ -38,9 +38,8 @@ constexpr int BQ = 128, BKV = 64;
 
 template <int HD>
 __global__ void __launch_bounds__(256, 2)
-k_attn_prefill(const bf16* __restrict__ qkv, int qkv_stride, const bf16* __restrict__ kc,
-               const bf16* __restrict__ vc, const int32_t* __restrict__ cu, int hq, int hkv, int max_seq,
-               bf16* __restrict__ out, int nq, int batch) {
+k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batch, const bf16* __restrict__ qkv, int qkv_stride,
+               int max_seq, const bf16* __restrict__ kc, const bf16* __restrict__ vc, bf16* __restrict__ out) {
   constexpr int ROWB = HD * 2;            // bytes per K / V row
   constexpr int CPR = HD / 8;             // 16-byte chunks per row: 16 or 8
   constexpr int TILE = BKV * ROWB;        // one K or V tile
@@ -258,11 +257,11 @@ void launch_attn_prefill(const void* qkv, int qkv_stride, const void* kc, const 
   const int nq = (max_len + BQ - 1) / BQ;
   dim3 grid((unsigned)nq * hq * batch);
   if (hd == 128)
-    k_attn_prefill<128><<<grid, 256, 0, st>>>((const bf16*)qkv, qkv_stride, (const bf16*)kc, (const bf16*)vc,
-                                              cu_seqlens, hq, hkv, max_seq, (bf16*)out, nq, batch);
+    k_attn_prefill<128><<<grid, 256, 0, st>>>(cu_seqlens, hq, hkv, nq, batch, (const bf16*)qkv, qkv_stride, max_seq,
+                                              (const bf16*)kc, (const bf16*)vc, (bf16*)out);
   else
-    k_attn_prefill<64><<<grid, 256, 0, st>>>((const bf16*)qkv, qkv_stride, (const bf16*)kc, (const bf16*)vc,
-                                             cu_seqlens, hq, hkv, max_seq, (bf16*)out, nq, batch);
+    k_attn_prefill<64><<<grid, 256, 0, st>>>(cu_seqlens, hq, hkv, nq, batch, (const bf16*)qkv, qkv_stride, max_seq,
+                                              (const bf16*)kc, (const bf16*)vc, (bf16*)out);
 }
 
 }  // namespace ls

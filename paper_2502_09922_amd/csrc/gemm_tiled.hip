@@ -125,7 +125,11 @@ namespace {
 // latency of a chain of loads: 1024 threads, and the partial tiles four at a time in flight
 // (45..311 rows of 4096 columns, 4 to 8 splits: 8.5 us with 256 threads and one split after the other).
 template <class T, int SRC, int NT, int P>
-__global__ void __launch_bounds__(NT) k_rows(RowsArgs a) {
+__global__ void __launch_bounds__(NT) k_rows(const void* in, float* x, const void* gamma, void* y, int rows, int d, int splits, RowsArgs a) {
+  // what the first loads need comes in registers, ahead of the structure
+  if (SRC == ROWS_RESID) a.part = (const float*)in;
+  else a.in = in;
+  a.x = x; a.gamma = gamma; a.y = y; a.rows = rows; a.d = d; a.splits = splits;
   typedef T T4 __attribute__((ext_vector_type(4)));
   __shared__ float wsum[NT / 64];
   const int r = blockIdx.x, nv = a.d >> 2;
@@ -272,9 +276,10 @@ __global__ void __launch_bounds__(NT) k_rows(RowsArgs a) {
 
 template <class T, int NT, int P>
 void launch_rows_n(int src, const RowsArgs& a, hipStream_t st) {
-  if (src == ROWS_RESID) k_rows<T, ROWS_RESID, NT, P><<<a.rows, NT, 0, st>>>(a);
-  else if (src == ROWS_HIDDEN) k_rows<T, ROWS_HIDDEN, NT, P><<<a.rows, NT, 0, st>>>(a);
-  else k_rows<T, ROWS_EMBED, NT, P><<<a.rows, NT, 0, st>>>(a);
+  const void* in = src == ROWS_RESID ? a.part : a.in;
+  if (src == ROWS_RESID) k_rows<T, ROWS_RESID, NT, P><<<a.rows, NT, 0, st>>>(in, a.x, a.gamma, a.y, a.rows, a.d, a.splits, a);
+  else if (src == ROWS_HIDDEN) k_rows<T, ROWS_HIDDEN, NT, P><<<a.rows, NT, 0, st>>>(in, a.x, a.gamma, a.y, a.rows, a.d, a.splits, a);
+  else k_rows<T, ROWS_EMBED, NT, P><<<a.rows, NT, 0, st>>>(in, a.x, a.gamma, a.y, a.rows, a.d, a.splits, a);
 }
 
 // up to 512 rows every one of them fits the chip at once with 1024 threads.  The choice depends on
