@@ -31,6 +31,7 @@ def test_passes_without_a_wait_between_them():
     shape = synth.StageShape("bf16", 1, 256, 2, 2, 128, 256, 0)
     gpu = make_gpu(shape, 3, 0, 1, 300, 8, 1200)
     side = torch.cuda.Stream()
+    gpu.prefill(to_dev(shape, synth.hidden_states(shape, 9, 3)), [3])  # the first behind a load copies its bounds
     lens = [[1 + (i * k) % 4 for i in range(300)] for k in (1, 2, 3)] + [[4, 2, 1], [8]]
     xs = [to_dev(shape, synth.hidden_states(shape, 4 + i, sum(n))) for i, n in enumerate(lens)]
     torch.cuda.synchronize()
