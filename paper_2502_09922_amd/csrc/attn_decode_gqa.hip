@@ -58,9 +58,14 @@ constexpr int TPC_MAX = 256;             // 8192 keys
 constexpr int TPC_MIN = 16;              // 512 keys
 // Sequences that are one chunk go to the workgroups by length, so that a ragged batch does not wait for CUs that got two
 // of the longest: the longest first, and where all workgroups fit the chip at once, two to a CU, the second half the
-// other way round, the shortest beside the longest.  Two layers of the 70B shape, 64 sequences of 128..2287 keys: 769 us
-// in the order of the rows, 750 so; 100 of 100..1800: 858 and 844; sequences of one length the same.
+// other way round, the shortest beside the longest.  Two layers of the 70B shape, 64 sequences of 128..2287 keys: 726 us
+// in the order of the rows, 709 so; a layer of 16 query and 4 kv heads, 160 of 500..4000 keys: 176 and 163.
+// Finding a rank takes every workgroup about half a microsecond, which short contexts do not give back (16 query
+// and 8 kv heads, 200 of at most 32 keys: 73 us in the order of the rows, 77 by length; at most 1000: 131 and 134,
+// 256 of them 150 and 149), and more rows than ORDERED are more than the registers of a wavefront hold.
 constexpr int RESIDENT = 512;
+constexpr int ORDERED = 256;             // rows at most
+constexpr int ORDERED_KEYS = 512;        // contexts are ordered only where some are longer
 constexpr int PART_HDR = 32;             // floats in front of a partial result: 16 maxima, 16 sums
 
 template <int NW>
@@ -70,13 +75,14 @@ k_attn_decode_gqa(const int32_t* __restrict__ row_pos, const int32_t* __restrict
                   int G, int max_seq, bf16* __restrict__ out, float* __restrict__ part, int nchunk, int tpc, bool by_length) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int kh = blockIdx.x;
-  int r = blockIdx.y;
+  int r = blockIdx.y, pos;
   if (by_length) {
     const int rows = gridDim.y, half = (int)gridDim.x * rows <= RESIDENT ? RESIDENT / 2 / (int)gridDim.x : rows;
-    r = row_by_length<NW * 64>(row_pos, rows, r < half ? r : rows - 1 - (r - half));
+    r = row_by_length<ORDERED / 64>(row_pos, rows, r < half ? r : rows - 1 - (r - half), max_seq, pos);
+  } else {
+    pos = row_pos[r];
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int pos = row_pos[r];
   if (pos < 0) return;  // a sequence with no room left: whole workgroup leaves together
   if ((int)blockIdx.z * tpc * TK > pos) return;  // this chunk lies beyond the sequence's context
   const int seq = row_seq[r];
@@ -301,14 +307,14 @@ k_attn_gqa_merge(const float* __restrict__ part, const int32_t* __restrict__ row
 template <int NW>
 void launch_nw(const void* qkv, int qkv_stride, const float* cs, void* kc, void* vc, const int32_t* row_seq,
                const int32_t* row_pos, int rows, int hq, int hkv, int max_seq, void* out, hipStream_t st, float* part,
-               int nchunk, int tpc) {
+               int nchunk, int tpc, bool by_length) {
   constexpr int SMEM = NW * 2 * TILE_BYTES;  // >= the merge area: NW * (32 + 16*128) floats
   static std::atomic<uint64_t> lds_allowed{0};
   allow_dynamic_lds((const void*)k_attn_decode_gqa<NW>, SMEM, lds_allowed);
   dim3 grid(hkv, rows, nchunk);
   k_attn_decode_gqa<NW><<<grid, NW * 64, SMEM, st>>>(row_pos, row_seq, (const bf16*)qkv, (const float2*)cs, (bf16*)kc,
                                                      (bf16*)vc, qkv_stride, hq, hkv, hq / hkv, max_seq, (bf16*)out,
-                                                     part, nchunk, tpc, nchunk == 1 && rows > 1 && rows <= NW * 64 /* a thread each */);
+                                                     part, nchunk, tpc, by_length);
   if (nchunk > 1)
     k_attn_gqa_merge<<<dim3(rows, hkv), 256, 0, st>>>(part, row_pos, hq, hkv, hq / hkv, nchunk, tpc, (bf16*)out);
 }
@@ -362,7 +368,7 @@ void launch_attn_decode_gqa(const void* qkv, int qkv_stride, const float* cs_tab
   if (nchunk > 1 && (!scratch || gqa_part_bytes(rows, hq, hkv, nchunk) > scratch_bytes)) nchunk = 1;
   if (nchunk == 1) tpc = (max_seq + TK - 1) / TK;
   launch_nw<LS_ATTN_GQA_NW>(qkv, qkv_stride, cs_table, kc, vc, row_seq, row_pos, rows, hq, hkv, max_seq, out, st, scratch,
-                            nchunk, tpc);
+                            nchunk, tpc, nchunk == 1 && rows > 1 && rows <= ORDERED && max_keys > ORDERED_KEYS);
 }
 
 }  // namespace ls

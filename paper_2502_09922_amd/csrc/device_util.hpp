@@ -94,27 +94,35 @@ __device__ __forceinline__ float row16_sum(float v) {
 }
 
 // Sequences of a decode attention launch by length: which row has rank `rank`, the longest first (of equals the lower
-// index), among `rows` <= MOST rows.  All threads of a workgroup of at least MOST threads call it.
-template <int MOST>
-__device__ __forceinline__ int row_by_length(const int32_t* __restrict__ row_pos, int rows, int rank) {
-  __shared__ __attribute__((aligned(16))) int len[MOST];
-  __shared__ int found;
-  const int t = threadIdx.x;
-  int p = -2;  // shorter than any row
-  if (t < rows) p = row_pos[t];
-  if (t < MOST) len[t] = p;
-  __syncthreads();
-  if (t < rows) {
-    int before = 0;
-    for (int j = 0; j < rows; j += 4) {
-      const int4 v = *reinterpret_cast<const int4*>(len + j);
-      before += (v.x > p || (v.x == p && j < t)) + (v.y > p || (v.y == p && j + 1 < t)) + (v.z > p || (v.z == p && j + 2 < t)) +
-                (v.w > p || (v.w == p && j + 3 < t));
-    }
-    if (before == rank) found = t;
+// index), among `rows` <= 64 C rows with positions below `limit`, and its position.  Every wavefront finds it on its
+// own, a bit of the position at a time by counting the rows that reach it: no LDS, no barrier.  (Comparing every row
+// with every other through LDS took 5 us of every workgroup at 256 rows.)
+template <int C>
+__device__ __forceinline__ int row_by_length(const int32_t* __restrict__ row_pos, int rows, int rank, int limit, int& pos) {
+  const int lane = threadIdx.x & 63;
+  int len[C];  // position + 1: a sequence without room has 0, a row that is not there -1
+#pragma unroll
+  for (int c = 0; c < C; ++c) len[c] = c * 64 + lane < rows ? row_pos[c * 64 + lane] + 1 : -1;
+  auto reach = [&](int v) {
+    int n = 0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(len[c] >= v));
+    return n;
+  };
+  int v = 0;  // the largest length that more than `rank` rows reach
+  for (int bit = 1 << (31 - __builtin_clz(limit | 1)); bit; bit >>= 1)
+    if (reach(v | bit) > rank) v |= bit;
+  int nth = rank - reach(v + 1), row = 0;  // among the rows of that length
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const uint64_t like = __builtin_amdgcn_ballot_w64(len[c] == v);
+    const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(like >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)like, 0));
+    const uint64_t is = __builtin_amdgcn_ballot_w64(len[c] == v && before == nth);
+    if (is) row = c * 64 + __builtin_ctzll(is);
+    nth -= __builtin_popcountll(like);
   }
-  __syncthreads();
-  return __builtin_amdgcn_readfirstlane(found);
+  pos = v - 1;
+  return row;
 }
 
 constexpr int waitcnt_vm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }  // vector memory only
