@@ -54,8 +54,8 @@ template <class T, int HD, int G>
 // with one query head per kv head the kernel fits 64 registers: eight wavefronts per SIMD, two
 // 16-wavefront workgroups per CU
 __global__ void __launch_bounds__(waves_for<T>(G) * 64, (G == 1 && sizeof(T) == 2 ? 8 : 1))
-k_attn_decode(const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_seq, const T* __restrict__ qkv,
-              const float2* __restrict__ cs, T* __restrict__ kc, T* __restrict__ vc, int qkv_stride, int hq, int hkv, int max_seq,
+k_attn_decode(const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_seq, int heads_first, int qkv_stride,
+              const T* __restrict__ qkv, const float2* __restrict__ cs, T* __restrict__ kc, T* __restrict__ vc, int hq, int hkv, int max_seq,
               T* __restrict__ out, float* __restrict__ part, int nchunk, int chunk_keys) {
   typedef typename Vec8<T>::type T8;
   constexpr int NW = waves_for<T>(G);
@@ -64,7 +64,7 @@ k_attn_decode(const int32_t* __restrict__ row_pos, const int32_t* __restrict__ r
   constexpr int U = (G >= 4 && sizeof(T) == 2) ? 2 : LS_ATTN_U;  // load instructions in flight per operand
   __shared__ float sm_m[NW][G], sm_l[NW][G];
   __shared__ float sm_acc[NW][G][HD];
-  const int r = blockIdx.y, kh = blockIdx.x;
+  const int r = heads_first ? blockIdx.y : blockIdx.x, kh = heads_first ? blockIdx.x : blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int pos = row_pos[r];
   if (pos < 0) return;  // a sequence with no room left: whole workgroup leaves together
@@ -291,8 +291,9 @@ struct Args {
 
 template <class T, int HD, int G>
 void launch_g(const Args& a, hipStream_t st) {
-  k_attn_decode<T, HD, G><<<dim3(a.hkv, a.rows, a.nchunk), waves_for<T>(G) * 64, 0, st>>>(
-      a.row_pos, a.row_seq, (const T*)a.qkv, (const float2*)a.cs, (T*)a.kc, (T*)a.vc, a.qkv_stride, a.hkv * G, a.hkv, a.max_seq,
+  const AttnGrid g = attn_decode_grid(a.rows, a.hkv, a.nchunk);
+  k_attn_decode<T, HD, G><<<dim3(g.x, g.y, g.z), waves_for<T>(G) * 64, 0, st>>>(
+      a.row_pos, a.row_seq, g.heads_first, a.qkv_stride, (const T*)a.qkv, (const float2*)a.cs, (T*)a.kc, (T*)a.vc, a.hkv * G, a.hkv, a.max_seq,
       (T*)a.out, a.part, a.nchunk, a.chunk_keys);
   if (a.nchunk > 1)
     k_attn_decode_merge<T, HD><<<dim3(a.rows, a.hkv * G), HD, 0, st>>>(a.part, a.row_pos, a.hkv * G, a.nchunk, a.chunk_keys, (T*)a.out);

@@ -70,12 +70,12 @@ constexpr int PART_HDR = 32;             // floats in front of a partial result:
 
 template <int NW>
 __global__ void __launch_bounds__(NW * 64)
-k_attn_decode_gqa(const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_seq, const bf16* __restrict__ qkv,
-                  const float2* __restrict__ cs, bf16* __restrict__ kc, bf16* __restrict__ vc, int qkv_stride, int hq, int hkv,
+k_attn_decode_gqa(const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_seq, int heads_first, int qkv_stride,
+                  const bf16* __restrict__ qkv, const float2* __restrict__ cs, bf16* __restrict__ kc, bf16* __restrict__ vc, int hq, int hkv,
                   int G, int max_seq, bf16* __restrict__ out, float* __restrict__ part, int nchunk, int tpc, bool by_length) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int kh = blockIdx.x;
-  int r = blockIdx.y, pos;
+  const int kh = heads_first ? blockIdx.x : blockIdx.y;
+  int r = heads_first ? blockIdx.y : blockIdx.x, pos;
   if (by_length) {
     const int rows = gridDim.y, half = (int)gridDim.x * rows <= RESIDENT ? RESIDENT / 2 / (int)gridDim.x : rows;
     r = row_by_length<ORDERED / 64>(row_pos, rows, r < half ? r : rows - 1 - (r - half), max_seq, pos);
@@ -311,10 +311,10 @@ void launch_nw(const void* qkv, int qkv_stride, const float* cs, void* kc, void*
   constexpr int SMEM = NW * 2 * TILE_BYTES;  // >= the merge area: NW * (32 + 16*128) floats
   static std::atomic<uint64_t> lds_allowed{0};
   allow_dynamic_lds((const void*)k_attn_decode_gqa<NW>, SMEM, lds_allowed);
-  dim3 grid(hkv, rows, nchunk);
-  k_attn_decode_gqa<NW><<<grid, NW * 64, SMEM, st>>>(row_pos, row_seq, (const bf16*)qkv, (const float2*)cs, (bf16*)kc,
-                                                     (bf16*)vc, qkv_stride, hq, hkv, hq / hkv, max_seq, (bf16*)out,
-                                                     part, nchunk, tpc, by_length);
+  const AttnGrid g = attn_decode_grid(rows, hkv, nchunk);
+  k_attn_decode_gqa<NW><<<dim3(g.x, g.y, g.z), NW * 64, SMEM, st>>>(
+      row_pos, row_seq, g.heads_first, qkv_stride, (const bf16*)qkv, (const float2*)cs, (bf16*)kc, (bf16*)vc, hq, hkv, hq / hkv, max_seq,
+      (bf16*)out, part, nchunk, tpc, by_length);
   if (nchunk > 1)
     k_attn_gqa_merge<<<dim3(rows, hkv), 256, 0, st>>>(part, row_pos, hq, hkv, hq / hkv, nchunk, tpc, (bf16*)out);
 }

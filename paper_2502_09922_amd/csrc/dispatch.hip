@@ -33,6 +33,12 @@ void launch_gemm(uint32_t dt, Epilogue epi, const void* A, const void* W, int M,
   launch_gemm_generic(dt, epi, A, W, M, N, K, out, resid, st);
 }
 
+// Rows in y only as far as y goes (65535); x takes any number.
+AttnGrid attn_decode_grid(int rows, int hkv, int nchunk) {
+  const bool heads_first = rows <= 65535;
+  return heads_first ? AttnGrid{(unsigned)hkv, (unsigned)rows, (unsigned)nchunk, 1} : AttnGrid{(unsigned)rows, (unsigned)hkv, (unsigned)nchunk, 0};
+}
+
 void launch_attention_block(uint32_t dt, const int32_t* cu_seqlens, int batch, int max_len, void* qkv,
                             const float* cs_table, void* kcache, void* vcache, const int32_t* row_seq,
                             const int32_t* row_pos, int rows, int hq, int hkv, int hd, int max_seq, void* out,
@@ -62,3 +68,9 @@ void launch_attention_block(uint32_t dt, const int32_t* cu_seqlens, int batch, i
 }
 
 }  // namespace ls
+
+// For the tests; not declared in ls_stage.h: grid and order of a decode attention launch.
+extern "C" void ls_test_attn_decode_grid(int rows, int hkv, int nchunk, int out[4]) {
+  const ls::AttnGrid g = ls::attn_decode_grid(rows, hkv, nchunk);
+  out[0] = (int)g.x; out[1] = (int)g.y; out[2] = (int)g.z; out[3] = g.heads_first;
+}

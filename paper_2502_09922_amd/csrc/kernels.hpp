@@ -233,6 +233,15 @@ void launch_attn_decode(uint32_t dt, const void* qkv, int qkv_stride, const floa
                         const int32_t* row_seq, const int32_t* row_pos, int rows, int hq, int hkv, int hd,
                         int max_seq, void* out, hipStream_t st, int max_keys, float* scratch, size_t scratch_bytes);
 
+// Workgroups of a decode attention launch: a (sequence, kv head, chunk of the context) each, chunks in grid z.
+// Workgroup ids go round the eight XCDs; with the heads in x (heads_first) those of one sequence are spread over them, and
+// no XCD gets all of a ragged batch's longest contexts.
+struct AttnGrid {
+  unsigned x, y, z;
+  int heads_first;
+};
+AttnGrid attn_decode_grid(int rows, int hkv, int nchunk);
+
 // bf16 decode attention on the matrix cores for grouped-query models (head_dim 128,
 // 2 <= Hq/Hkv <= 16), fused with RoPE and the cache append like launch_attn_decode.
 bool attn_decode_gqa_supported(int hq, int hkv, int hd);
