@@ -33,9 +33,11 @@ void launch_gemm(uint32_t dt, Epilogue epi, const void* A, const void* W, int M,
   launch_gemm_generic(dt, epi, A, W, M, N, K, out, resid, st);
 }
 
-// Rows in y only as far as y goes (65535); x takes any number.
+// Heads first only where a workgroup takes a whole context (few sequences cut into chunks, a layer of 16 query and 4 kv heads, 4 of
+// 4000 keys, rows first / heads first: 41.8 / 45.5 us; 16 heads, 4 of 1000: 39.0 / 40.9), and as far as y goes (65535); x takes any
+// number.
 AttnGrid attn_decode_grid(int rows, int hkv, int nchunk) {
-  const bool heads_first = rows <= 65535;
+  const bool heads_first = nchunk == 1 && rows <= 65535;
   return heads_first ? AttnGrid{(unsigned)hkv, (unsigned)rows, (unsigned)nchunk, 1} : AttnGrid{(unsigned)rows, (unsigned)hkv, (unsigned)nchunk, 0};
 }
 

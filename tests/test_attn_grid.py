@@ -20,3 +20,9 @@ def test_sizes(rows, hkv):
         x, y, z, heads_first = grid(rows, hkv, nchunk)
         assert (x, y, z) == ((hkv, rows, nchunk) if heads_first else (rows, hkv, nchunk))
         assert y <= 65535 and z <= 65535
+
+
+@pytest.mark.parametrize("rows", [1, 4, 64, 100])
+def test_heads_go_round_the_xcds_only_where_contexts_are_whole(rows):
+    assert grid(rows, 8, 1)[3] == 1
+    assert grid(rows, 8, 2)[3] == grid(rows, 8, 16)[3] == 0
