@@ -9,7 +9,7 @@
 // The tiled GEMM pads one row to 32 and pays a barrier per k-step: a layer of the 7B shape, one row, took 244 us
 // through it and takes 176 here (0.81 GB of weights); the tiny model's generation 776 and 647 us.
 // A step of the tiny model is nothing but launches, 3 us each: with the norms and the residual adds in here its
-// generation (32 tokens, then 8 steps) takes 555 us instead of 676.
+// generation (32 tokens, then 8 steps) takes 500 us instead of 620.
 #include "kernels.hpp"
 #include "device_util.hpp"
 
@@ -17,8 +17,13 @@ namespace ls {
 
 namespace {
 
-// Widest rows whose norm the GEMM takes along: a wavefront keeps them in its registers.
-constexpr int NORM_MAX = 1024;
+// Rows whose norm the GEMM takes along: a wavefront keeps them in its registers, 256 columns to a piece, up to NORM_MAX
+// columns.  Every wavefront (N / 4 of them) normalises every piece again, which has to take less than the launch it saves:
+// three layers of a step, norms launched / taken along, 512 columns (two pieces) 1 row 81 / 73 us, 8 rows 106 / 106; 768
+// columns 5 rows 102 / 101, 6 rows 107 / 108, 8 rows 117 / 132; layer and head of 32000 entries, 384 columns 2 rows 45.3 / 44.6,
+// 3 rows 47.0 / 48.0; 768 columns 1 row 49.8 / 48.5, 2 rows 54.4 / 54.8, 8 rows 76 / 152.
+constexpr int NORM_MAX = 1024, NORM_PIECES = 16;
+constexpr long NORM_WORK = 160000;  // pieces times N
 
 // NORM: A holds residual rows and every wavefront normalises the ones it multiplies, all of K at once (K <= 256 U).  The
 // sums are those of k_rows in the order of k_rows, so a norm that is launched on its own gives the same bits.
@@ -124,8 +129,11 @@ template <int EPI, int M>
 void launch_m(const float* A, const float* W, int N, int K, int splits, float* out, const RowsF32Fusion& f, hipStream_t st) {
   constexpr int R = 4, U = M <= 2 ? 4 : 2, C = EPI == TILED_SWIGLU ? R / 2 : R;
   const dim3 grid((unsigned)((N + 4 * C - 1) / (4 * C)), (unsigned)splits);
-  if (f.gamma) launch_kernel(k_gemm_rows_f32<EPI, M, R, NORM_MAX / 256, true>, grid, dim3(256), 0, st, A, W, N, K, out, f);
-  else if (EPI == TILED_PART && !f.add) hipLaunchKernelGGL((k_gemm_rows_f32<EPI, M, R, U, false>), grid, dim3(256), 0, st, A, W, N, K, out, f);
+  if (f.gamma) {  // as many pieces as a row has: the registers of more cost wavefronts
+    if (K <= 256) launch_kernel(k_gemm_rows_f32<EPI, M, R, 1, true>, grid, dim3(256), 0, st, A, W, N, K, out, f);
+    else if (K <= 512) launch_kernel(k_gemm_rows_f32<EPI, M, R, 2, true>, grid, dim3(256), 0, st, A, W, N, K, out, f);
+    else if constexpr (M * 3 <= NORM_PIECES) launch_kernel(k_gemm_rows_f32<EPI, M, R, 4, true>, grid, dim3(256), 0, st, A, W, N, K, out, f);
+  } else if (EPI == TILED_PART && !f.add) hipLaunchKernelGGL((k_gemm_rows_f32<EPI, M, R, U, false>), grid, dim3(256), 0, st, A, W, N, K, out, f);
   else launch_kernel(k_gemm_rows_f32<EPI, M, R, U, false>, grid, dim3(256), 0, st, A, W, N, K, out, f);
 }
 
@@ -156,12 +164,15 @@ int gemm_rows_f32_splits(int epi, int M, int N, int K, bool to_scratch, size_t s
   return s;
 }
 
-bool gemm_rows_f32_norm_supported(int M, int K) { return M >= 1 && M <= 8 && K >= 4 && K % 4 == 0 && K <= NORM_MAX; }
+bool gemm_rows_f32_norm_supported(int M, int N, int K) {
+  const int pieces = M * ((K + 255) / 256);
+  return M >= 1 && M <= 8 && K >= 4 && K % 4 == 0 && K <= NORM_MAX && pieces <= NORM_PIECES && (long)pieces * N <= NORM_WORK;
+}
 
 bool launch_gemm_rows_f32(int epi, const void* A, const void* W, int M, int N, int K, int splits, void* out, hipStream_t st,
                           const RowsF32Fusion& f) {
   const float *a = (const float*)A, *w = (const float*)W;
-  if ((f.gamma && (splits != 1 || !gemm_rows_f32_norm_supported(M, K))) || (f.add && (splits != 1 || epi != TILED_PART))) return false;
+  if ((f.gamma && (splits != 1 || !gemm_rows_f32_norm_supported(M, N, K))) || (f.add && (splits != 1 || epi != TILED_PART))) return false;
   switch (epi) {
     case TILED_PART: return launch_e<TILED_PART>(a, w, M, N, K, splits, (float*)out, f, st);
     case TILED_STORE: return launch_e<TILED_STORE>(a, w, M, N, K, splits, (float*)out, f, st);

@@ -144,7 +144,7 @@ struct RowsF32Fusion {
   const float* add = nullptr;
 };
 int gemm_rows_f32_splits(int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes);
-bool gemm_rows_f32_norm_supported(int M, int K);
+bool gemm_rows_f32_norm_supported(int M, int N, int K);
 bool launch_gemm_rows_f32(int epi, const void* A, const void* W, int M, int N, int K, int splits, void* out, hipStream_t st,
                           const RowsF32Fusion& f = {});
 

@@ -731,7 +731,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   // of its rows along, and adds its sums to the residual rows itself: 13 launches for a step of the two-layer tiny model
   // instead of 18.  A norm that is folded into the row kernel instead, behind a projection whose K is cut, costs nothing.
   auto rows_f32 = [&](const TiledPlan& p) { return dt == F32 && p.splits == 1 && !p.bm; };
-  auto folds_norm = [&](const TiledPlan& p) { return rows_one_pass && rows_f32(p) && gemm_rows_f32_norm_supported(rows, d); };
+  auto folds_norm = [&](const TiledPlan& p, int N) { return rows_one_pass && rows_f32(p) && gemm_rows_f32_norm_supported(rows, N, d); };
 
   const void* table = nullptr;
   if (s->first) {
@@ -745,7 +745,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     ra.cu = prefill ? cu_dev : nullptr; ra.batch = batch; ra.max_seq = c.max_seq;
     ra.row_seq = row_seq; ra.row_pos = row_pos; ra.last_rows = last_rows; ra.seq_lens = kv->seq_lens;
     Block& b0 = s->blocks[s->layer0];
-    if (landed(b0) && !norm_alone(b0) && !folds_norm(p_qkv)) {
+    if (landed(b0) && !norm_alone(b0)) {
       ra.gamma = tensor(b0, 0); ra.y = y; ra.eps = c.rms_eps;
       y_ready = true;
     }
@@ -797,7 +797,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     char* kc = (char*)kv->k + li * kv_layer;
     char* vc = (char*)kv->v + li * kv_layer;
 
-    const bool fold_qkv = folds_norm(p_qkv) && !norm_alone(b), fold_gu = folds_norm(p_gu);
+    const bool fold_qkv = !y_ready && folds_norm(p_qkv, qkv_cols) && !norm_alone(b), fold_gu = rows_f32(p_o) && folds_norm(p_gu, F);
     RowsF32Fusion normed;
     normed.eps = c.rms_eps;
     if (!y_ready && !fold_qkv) PROBE(LS_OP_NORM, norm(tensor(b, 0)));
@@ -838,7 +838,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     // layer waits for it
     const bool more = li + 1 < n_layers;
     Block* next = more ? &s->blocks[s->layer0 + li + 1] : nullptr;
-    y_ready = more && p_dn.splits && landed(*next) && !norm_alone(*next) && !folds_norm(p_qkv);
+    y_ready = more && p_dn.splits && landed(*next) && !norm_alone(*next) && !(rows_f32(p_dn) && folds_norm(p_qkv, qkv_cols));
     LS_HIP(gate(b, st, 3));
     PROBE(LS_OP_GEMM_DOWN, residual(p_dn, hbuf, tensor(b, 5), F, y_ready ? tensor(*next, 0) : nullptr, !more && !s->last));
     if (timed) LS_HIP(hipEventRecord(s->comp_end[li], st));
@@ -856,7 +856,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     const TiledPlan p_head = (dt == F32 || batch > (d > 4096 ? 8 : 16)) && ((uintptr_t)logits & 15) == 0
                                  ? gemm_tiled_plan(dt, TILED_PART, batch, (int)c.vocab, d, false, 0, nullptr)
                                  : TiledPlan{};
-    if (rows_f32(p_head) && gemm_rows_f32_norm_supported(batch, d)) {
+    if (rows_f32(p_head) && gemm_rows_f32_norm_supported(batch, (int)c.vocab, d)) {
       RowsF32Fusion f;
       f.gamma = (const float*)(base + sp[0].off); f.eps = c.rms_eps; f.row_map = last_rows;
       launch_gemm_rows_f32(TILED_PART, x, base + sp[1].off, batch, c.vocab, d, 1, logits, st, f);
