@@ -26,13 +26,6 @@ bool gemm_tiled_supported(uint32_t dt, int epi, int M, int N, int K) {
 // 299 / 352, 8 rows 219 / 250; the FMAs of each further row cost 6 us, the tiles nothing up to 32.
 constexpr int ROWS_F32_MAX = 8;
 
-// fp32 of more rows than this goes by split operands, unless the weights are so few (the tiny model's matrices) that
-// the launch of the kernel that splits the rows would be what the GEMM takes.  100 rows of the 7B shape, QKV / gate-up /
-// down: 134 / 160 / 89 us against 172 / 258 / 102 for 64 x 128 on fp32 instructions; 48 rows 127 / 155 / 64
-// against 103 / 156 / 63.
-constexpr int ROWS_F32_SPLIT = 96;
-constexpr size_t WEIGHTS_F32_SPLIT = 1u << 18;
-
 // Time of a launch, in microseconds, from sweeps over the tiles (7B, 13B and 70B layers, 12..1024 rows in bf16, 24..512
 // in fp32, cold weights).  bf16: a k-step of a workgroup costs 0.02 us + 2.4 ns per row it brings into LDS, whatever
 // the arithmetic (48 x 48 0.24, 64 x 64 0.33, 64 x 128 0.47, 128 x 128 0.58, 160 x 192 0.85, 256 x 128 0.9 us
@@ -41,8 +34,9 @@ constexpr size_t WEIGHTS_F32_SPLIT = 1u << 18;
 // memory faster than 6.4 TB/s.  Chosen so, the four projections at 11 row counts of the 7B shape take 1584 us
 // together, the fastest tile and split of each 1552.  fp32: at least the matrix work (64 x 64 at 0.4, 64 x 128 at 0.46
 // TFLOP/s per CU); by split operands 0.39 us + 0.055 per pair of 16-row fragments and wavefront (96 x 128 1.05..1.1,
-// 128 x 128 1.2..1.4, 176 x 128 1.6..1.7, 128 x 192 1.9..2.1 us measured) and the kernel in front.  One workgroup
-// fits a CU, so the launch takes as many rounds as its fullest XCD has workgroups for its 32 CUs; every K split
+// 128 x 128 1.2..1.4, 176 x 128 1.6..1.7, 128 x 192 1.9..2.1 us measured) and the kernel in front, whose launch and tall
+// tiles do not pay for small matrices (two layers of 512 columns, 97..512 rows on fp32 instructions 103..196 us, by split
+// operands 175..263; 1024 columns, 97 rows 152 and 244, 311 rows 251 and 292).  One workgroup fits a CU, so the launch takes as many rounds as its fullest XCD has workgroups for its 32 CUs; every K split
 // writes and reads an fp32 tile.
 TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us) {
   TiledPlan best;
@@ -81,25 +75,22 @@ TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scr
         }
       }
     };
-    const size_t weights = (size_t)N * (epi == TILED_SWIGLU ? 2 : 1) * K;
     if (dt == BF16) {
 #define LS_TILE(tm_, tn_, wm_, wn_, glu_) \
   if (epi != TILED_SWIGLU || glu_) consider(16 * wm_ * tm_, 16 * wn_ * tn_, 0.f, 0.f);
       LS_TILED_BF16(LS_TILE)
 #undef LS_TILE
     } else {
-      if (M <= ROWS_F32_SPLIT || weights < WEIGHTS_F32_SPLIT) {
-        auto fp32 = [&](int bm, int bn) {
-          const float area = (float)(bm * bn), mma = 64.f * area / (0.36e6f + 12.f * area) + 0.05f;
-          const float step = 0.05f + 0.0024f * (float)(bm + bn);
-          consider(bm, bn, mma > step ? mma : step, 0.f);
-        };
+      auto fp32 = [&](int bm, int bn) {
+        const float area = (float)(bm * bn), mma = 64.f * area / (0.36e6f + 12.f * area) + 0.05f;
+        const float step = 0.05f + 0.0024f * (float)(bm + bn);
+        consider(bm, bn, mma > step ? mma : step, 0.f);
+      };
 #define LS_TILE(bm_, bn_, wm_, tm_, tn_, glu_) \
   if (epi != TILED_SWIGLU || glu_) fp32(bm_, bn_);
-        LS_TILED_F32(LS_TILE)
+      LS_TILED_F32(LS_TILE)
 #undef LS_TILE
-      }
-#define LS_TILE(bm_, bn_) consider(bm_, bn_, 0.39f + 0.055f * (bm_ / 16) * (bn_ / 64) + (bn_ > 128 ? 0.2f : 0.f), 4.f);
+#define LS_TILE(bm_, bn_) consider(bm_, bn_, 0.39f + 0.055f * (bm_ / 16) * (bn_ / 64) + (bn_ > 128 ? 0.2f : 0.f), 3.5f);
       LS_SPLIT_TILES(LS_TILE)
 #undef LS_TILE
     }

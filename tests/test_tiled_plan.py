@@ -68,3 +68,18 @@ def test_launches_with_a_chosen_tile_that_are_refused():
                                              (BF16, SWIGLU, 64, 64, 1, 40, 64, 64), (BF16, STORE, 32, 64, 1, 40, 24, 64),
                                              (F32, ROPE, 32, 64, 1, 40, 64, 64)):
         assert not fn(dt, epi, bm, bn, splits, p, p, m, n, k, p, None)
+
+
+def test_fp32_by_split_operands_only_where_it_pays():
+    """The kernel that splits the rows in front and the tall tiles cost small matrices more than they save (512 columns, 97..512
+    rows: 175..263 us for two layers against 103..196); at the 7B shape they are the faster ones from some 70 rows on."""
+    for d, f in ((256, 688), (384, 1024), (512, 1376)):
+        for m in (97, 128, 200, 311, 512):
+            for epi, n, k in ((ROPE, 3 * d, d), (PART, d, d), (SWIGLU, f, d), (PART, d, f)):
+                p = plan(F32, epi, m, n, k, epi == PART, 8 * m * n * 4)
+                assert p.bm * p.bn < 96 * 128, (d, m, epi, p.bm, p.bn)
+    assert [(p.bm, p.bn) for p in (plan(F32, SWIGLU, m, 688, 256, False, 0) for m in (97, 200, 512))] == [(32, 128)] * 3
+    for m in (97, 200, 325, 1000):
+        for epi, n, k in ((ROPE, 12288, 4096), (PART, 4096, 4096), (SWIGLU, 11008, 4096), (PART, 4096, 11008)):
+            p = plan(F32, epi, m, n, k, epi == PART, 64 << 20)
+            assert p.bm * p.bn >= 96 * 128, (m, epi, p.bm, p.bn)
