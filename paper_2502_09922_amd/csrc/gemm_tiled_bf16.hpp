@@ -224,8 +224,9 @@ k_gemm_tiled(const bf16* __restrict__ A, const bf16* __restrict__ W, int M, int 
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // RoPE: sequence and position of this lane's rows, before the products where the registers last
-  constexpr bool ROPE = EPI == TILED_ROPE, EARLY = 4 * TM * TN + 8 * (TM + TN) + 2 * TM <= 200;
+  // RoPE: sequence and position of this lane's rows, before the products where the registers last: 256 for a wavefront, with
+  // more than eight wavefronts 168 (256 x 192, 8 + 4 of them: 40 registers spilled if loaded before)
+  constexpr bool ROPE = EPI == TILED_ROPE, EARLY = 4 * TM * TN + 8 * (TM + TN) + 2 * TM <= (TL::WAVES > 8 ? 168 : 200);
   int pos[ROPE ? TM : 1], seq[ROPE ? TM : 1];
   auto positions = [&]() {
 #pragma unroll
@@ -286,9 +287,10 @@ k_gemm_tiled(const bf16* __restrict__ A, const bf16* __restrict__ W, int M, int 
     *reinterpret_cast<bf16x4*>(p) = y;
   };
   // RoPE: a row block's (cos, sin) are on their way while the block before is stored; one after the other each block waits
-  // for memory (7B, 311 rows, four row blocks and more: 2.4 us of 48)
+  // for memory (7B, 311 rows, four row blocks and more: 2.4 us of 48).  256 x 192 has no registers for two blocks' (24 spilled).
+  constexpr bool AHEAD = 4 * TM * TN + 10 * TN + 2 * TM <= (TL::WAVES > 8 ? 150 : 220);
   int head[ROPE ? TN : 1], dim[ROPE ? TN : 1];
-  f32x4 cs[2][ROPE ? TN : 1];
+  f32x4 cs[AHEAD ? 2 : 1][ROPE ? TN : 1];
   auto turns = [&](int i, f32x4 (&to)[ROPE ? TN : 1]) {
 #pragma unroll
     for (int j = 0; j < TN; ++j)
@@ -318,7 +320,8 @@ k_gemm_tiled(const bf16* __restrict__ A, const bf16* __restrict__ W, int M, int 
         if (col < N) put((bf16*)outv + (size_t)m * N + col, v);
       }
     } else if constexpr (EPI == TILED_ROPE) {
-      if (i + 1 < TM) turns(i + 1, cs[(i + 1) & 1]);
+      if (!AHEAD && i) turns(i, cs[0]);
+      if (AHEAD && i + 1 < TM) turns(i + 1, cs[(i + 1) & 1]);
       if (m >= M) continue;
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
@@ -328,7 +331,7 @@ k_gemm_tiled(const bf16* __restrict__ A, const bf16* __restrict__ W, int M, int 
         f32x4 v = acc[i][j];
         if (!is_v && pos[i] >= 0) {
           // the projection's output in storage type is what turns (pairs 2p, 2p + 1)
-          const f32x4 c = cs[i & 1][j];
+          const f32x4 c = cs[AHEAD ? i & 1 : 0][j];
           const float u0 = to_f(from_f<bf16>(v[0])), u1 = to_f(from_f<bf16>(v[1])), u2 = to_f(from_f<bf16>(v[2])), u3 = to_f(from_f<bf16>(v[3]));
           v = f32x4{u0 * c[0] - u1 * c[1], u0 * c[1] + u1 * c[0], u2 * c[2] - u3 * c[3], u2 * c[3] + u3 * c[2]};
         }
