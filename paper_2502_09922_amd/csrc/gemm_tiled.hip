@@ -30,7 +30,9 @@ constexpr int ROWS_F32_MAX = 8;
 // in fp32, cold weights).  bf16: a k-step of a workgroup costs 0.02 us + 2.4 ns per row it brings into LDS, whatever
 // the arithmetic (48 x 48 0.24, 64 x 64 0.33, 64 x 128 0.47, 128 x 128 0.58, 160 x 192 0.85, 256 x 128 0.9 us
 // measured; a sixth more where only two stages fit: 256 x 192 1.33); rows past the end of the call are not fetched, and
-// the tiles of a column wait for the same weight lines, so that it is their mean that counts.  Weights do not come from
+// the tiles of a column wait for the same weight lines, so that it is their mean that counts; one tile row is a little
+// faster than two of the same lines (7B gate-up, 128 rows, 128 x 128 44.0, 96 x 192 46.9, 64 x 192 48.4 us; 13B, 256 rows,
+// 256 x 128 76.3, 160 x 256 82.7; 70B 244 and 262).  Weights do not come from
 // memory faster than 6.4 TB/s.  Chosen so, the four projections at 11 row counts of the 7B shape take 1584 us
 // together, the fastest tile and split of each 1552.  fp32: at least the matrix work (64 x 64 at 0.4, 64 x 128 at 0.46
 // TFLOP/s per CU); by split operands 0.39 us + 0.055 per pair of 16-row fragments and wavefront (96 x 128 1.05..1.1,
@@ -57,6 +59,7 @@ TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scr
       if (dt == BF16) {
         if (bm > 32 && bm >= 2 * M) return;  // more than half of the products for rows that are not there
         step = 0.02f + 0.0024f * ((float)((M + 7) / 8 * 8) / (float)tiles_m + (float)bn);
+        if (tiles_m > 1 && !to_scratch) step *= 1.02f;
         if ((bm + bn) * 128 * 3 > 160 * 1024) step *= 1.18f;
       }
       for (int s = 1; s <= 8; ++s) {

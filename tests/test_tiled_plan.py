@@ -83,3 +83,12 @@ def test_fp32_by_split_operands_only_where_it_pays():
         for epi, n, k in ((ROPE, 12288, 4096), (PART, 4096, 4096), (SWIGLU, 11008, 4096), (PART, 4096, 11008)):
             p = plan(F32, epi, m, n, k, epi == PART, 64 << 20)
             assert p.bm * p.bn >= 96 * 128, (m, epi, p.bm, p.bn)
+
+
+def test_one_tile_row_before_two_of_the_same_lines():
+    """Gate-up of 7B, 121..136 rows, and of 13B and 70B, 249..256 rows: measured 7 to 10 % faster in one tile row."""
+    for m in (121, 124, 128):
+        assert (plan(BF16, SWIGLU, m, 11008, 4096, False, 0).bm, plan(BF16, SWIGLU, m, 11008, 4096, False, 0).bn) == (128, 128)
+    for m in (249, 256):
+        for n, k in ((13824, 5120), (28672, 8192)):
+            assert (plan(BF16, SWIGLU, m, n, k, False, 0).bm, plan(BF16, SWIGLU, m, n, k, False, 0).bn) == (256, 128)
