@@ -149,7 +149,7 @@ size_t ls_stage_block_bytes(const ls_stage* stage, int layer);
  * Enqueue the copy of one packed block from host memory into its place in the slab on
  * hip_stream (the "copy stream"), then record the block's event there.  A large layer block goes as
  * four copies in the order the layer reads its weights, each with an event of its own, so that the
- * layer starts before all of it is there.  host_ptr must hold
+ * layer starts before all of it is there; a large head block as two, final norm and LM head.  host_ptr must hold
  * ls_stage_block_bytes(stage, layer) bytes, be pinned for the copy to be asynchronous, and
  * stay valid until the event has completed.  Blocks may arrive in any order (the paper's
  * Algorithm 1 hands sub-groups circularly shifted orders).  `layer` is a decoder layer in

@@ -203,7 +203,8 @@ constexpr int PROBE_CAP = 512;
 // A layer block is copied as four pieces in the order the layer reads them: attention norm and QKV weights, O weights
 // and FFN norm, gate-up weights, down weights.  The layer starts with the first piece's arrival, and
 // when the last block of a stage has landed only its down projection is left to do (7B layers, 8 x 512
-// tokens: 0.35 ms behind the copy instead of 1.4).
+// tokens: 0.35 ms behind the copy instead of 1.4).  The head block is copied as two, final norm and LM head, as a step's last
+// down projection may apply the norm's gain.
 constexpr int PIECES = 4;
 constexpr size_t PIECES_FROM = 8u << 20;  // smaller blocks go in one copy: a piece costs a few microseconds of its own
 
@@ -213,7 +214,7 @@ struct Block {
   int state;
   bool timed;  // copy_start / loaded bracket a copy made with profiling on
   hipEvent_t copy_start, loaded;
-  // A layer block copied in pieces (pieces_of): piece[g] is recorded behind piece g, `loaded` behind the last.
+  // A block copied in pieces (ls_stage_load_block): piece[g] is recorded behind piece g, `loaded` behind the last.
   bool in_pieces;
   hipEvent_t piece[PIECES - 1];
   // the host has seen `loaded` complete since the block was enqueued: the bytes are in HBM for
@@ -381,7 +382,7 @@ ls_status ls_stage_create(const ls_cfg* cfg, int lo, int hi, void* weight_slab, 
   };
   for (auto& b : s->blocks) {
     bool ok = hipEventCreate(&b.copy_start) == hipSuccess && hipEventCreate(&b.loaded) == hipSuccess;
-    if (b.layer >= lo && b.layer < hi)
+    if (b.layer != LS_BLOCK_EMBED)
       for (auto& e : b.piece) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
     if (!ok) {
       cleanup();
@@ -474,12 +475,14 @@ ls_status ls_stage_load_block(ls_stage* s, const void* host_ptr, int layer, void
   }
   b->in_pieces = b->piece[0] && b->bytes >= PIECES_FROM;
   if (b->in_pieces) {
-    TensorSpan sp[6];
+    TensorSpan sp[6] = {};
     block_tensors(&s->cfg, layer, sp, nullptr);
-    const size_t cut[PIECES + 1] = {0, sp[2].off, sp[4].off, sp[5].off, b->bytes};
-    for (int g = 0; g < PIECES; ++g) {
+    const bool head = layer == s->hi;
+    const int pieces = head ? 2 : PIECES;
+    const size_t cut[PIECES + 1] = {0, head ? sp[1].off : sp[2].off, head ? b->bytes : sp[4].off, sp[5].off, b->bytes};
+    for (int g = 0; g < pieces; ++g) {
       LS_HIP(hipMemcpyAsync(s->slab + b->off + cut[g], (const char*)host_ptr + cut[g], cut[g + 1] - cut[g], hipMemcpyHostToDevice, st));
-      LS_HIP(hipEventRecord(g + 1 < PIECES ? b->piece[g] : b->loaded, st));
+      LS_HIP(hipEventRecord(g + 1 < pieces ? b->piece[g] : b->loaded, st));
     }
   } else {
     LS_HIP(hipMemcpyAsync(s->slab + b->off, host_ptr, b->bytes, hipMemcpyHostToDevice, st));
@@ -670,7 +673,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
       PROBE(LS_OP_GEMM_O, launch_gemm(dt, EPI_RESID, attn, base + sp[2].off, rows, d, hq * hd, nullptr, x, st, &gsc, &f_o));
       PROBE(LS_OP_GEMM_GATEUP, launch_gemm(dt, EPI_SWIGLU, xb2, base + sp[4].off, rows, F, d, hbuf, nullptr, st, &gsc, &f_gu));
       if (more) LS_HIP(gate(s->blocks[s->layer0 + li + 1], st));  // its gain is read next
-      else if (head_folds) LS_HIP(gate(*hb, st));
+      else if (head_folds) LS_HIP(gate(*hb, st, 0));  // only the gain: the LM head may still be on its way
       PROBE(LS_OP_GEMM_DOWN, launch_gemm(dt, EPI_RESID, hbuf, base + sp[5].off, rows, d, F, nullptr, x, st, &gsc, &f_dn));
     }
     if (s->last) {

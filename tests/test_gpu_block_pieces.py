@@ -1,6 +1,8 @@
 """Layer blocks of 8 MiB and more arrive in four pieces, and a layer starts behind the first: prompt passes and
 steps that run behind such copies give the bits of a stage whose weights were resident, with blocks in any
-order, with profiling on, and after the blocks were forgotten and loaded again."""
+order, with profiling on, and after the blocks were forgotten and loaded again.  A head block arrives in two."""
+import time
+
 import pytest
 
 import synth
@@ -33,4 +35,43 @@ def test_a_pass_behind_pieces_equals_a_pass_on_resident_weights(order, rows):
         got = st.prefill(x, [rows])
         assert torch.equal(got, want)
         assert torch.equal(st.decode(x[:1], 1, rows), step)
+    st.close()
+
+
+def test_a_step_waits_for_the_lm_head_only_in_front_of_it():
+    """A step of few rows applies the final norm's gain in its last down projection; the LM head behind the gain, 512 MB, is
+    still on its way when that is done.  Same bits as with resident weights."""
+    import torch
+    from paper_2502_09922_amd import binding
+
+    shape = synth.StageShape("bf16", 2, 1024, 8, 8, 128, 2816, 262144)
+    st = binding.Stage(shape, 1, 2, 2, 16, 16)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    host = {}
+    for layer in st.block_ids():
+        view = st.block_view(layer)
+        view.view(torch.bfloat16).normal_(0, 0.02, generator=gen)
+        host[layer] = torch.empty(view.numel(), dtype=torch.uint8, pin_memory=True)
+        host[layer].copy_(view)
+        st.adopt_block(layer)
+    x = torch.randn(2, 1024, generator=gen, device="cuda").to(torch.bfloat16)
+    _, want = st.decode(x, 2, 0, want_logits=True)
+    copies = torch.cuda.Stream()
+    for order in ((1, 2), (2, 1)):
+        torch.cuda.synchronize()
+        st.reset_blocks()
+        st.slab.zero_()
+        st.seq_lens.zero_()
+        st.probe(binding.LS_OP_GEMM_DOWN, 1, 1)
+        copies.wait_stream(torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        for layer in order:
+            st.load_block(layer, host[layer], copies)
+        _, got = st.decode(x, 2, 0, want_logits=True)
+        if order == (1, 2):
+            time.sleep(0.004)  # the layer arrives in 0.4 ms, the head takes 9
+            st.probe_times()   # an error if the projection is not done
+            assert not copies.query()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
     st.close()
