@@ -116,7 +116,9 @@ ls_status ls_block_tensor(const ls_cfg* cfg, int layer, int index, size_t* offse
  * the embedding block if lo == 0 and the head block if hi == n_layers_total (vocab > 0). */
 size_t ls_stage_slab_bytes(const ls_cfg* cfg, int layer_lo, int layer_hi);
 
-/* Device bytes for the intermediate results of one call at the cfg's limits. */
+/* Device bytes for the intermediate results of one call at the cfg's limits.  fp32 stages of layers wide enough for it hold
+ * a second, split copy of the rows of one projection: 6 bytes for each of max_tokens (as far as 4 GB of rows) times the
+ * largest of hidden size, query width and ffn, 2.2 GB of 7.4 at 32768 tokens of a 7B-shaped layer. */
 size_t ls_stage_workspace_bytes(const ls_cfg* cfg, int layer_lo, int layer_hi);
 
 /* Device bytes of EACH of ls_kv.k and ls_kv.v. */

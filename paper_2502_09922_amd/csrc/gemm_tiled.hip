@@ -40,7 +40,8 @@ constexpr int ROWS_F32_MAX = 8;
 // tiles do not pay for small matrices (two layers of 512 columns, 97..512 rows on fp32 instructions 103..196 us, by split
 // operands 175..263; 1024 columns, 97 rows 152 and 244, 311 rows 251 and 292).  One workgroup fits a CU, so the launch takes as many rounds as its fullest XCD has workgroups for its 32 CUs; every K split
 // writes and reads an fp32 tile.
-TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us) {
+TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us,
+                          size_t parts_bytes) {
   TiledPlan best;
   float best_us = 1e30f;
   if (dt == F32 && M <= ROWS_F32_MAX) {  // bm == 0: the kernel for few fp32 rows
@@ -94,7 +95,7 @@ TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scr
       LS_TILED_F32(LS_TILE)
 #undef LS_TILE
 #define LS_TILE(bm_, bn_) consider(bm_, bn_, 0.39f + 0.055f * (bm_ / 16) * (bn_ / 64) + (bn_ > 128 ? 0.2f : 0.f), 3.5f);
-      LS_SPLIT_TILES(LS_TILE)
+      if (gemm_split_parts_bytes(M, K) <= parts_bytes) { LS_SPLIT_TILES(LS_TILE) }
 #undef LS_TILE
     }
   }

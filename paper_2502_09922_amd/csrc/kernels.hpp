@@ -125,8 +125,11 @@ struct TiledPlan {
   int bm = 0, bn = 0, splits = 0;  // splits == 0: not supported
 };
 // The plan with the shortest estimated time, which `us` receives.  to_scratch: the output is partial tiles,
-// splits * M * N floats, which have to fit scratch_bytes; otherwise it is the caller's matrix and K is not cut.
-TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us);
+// splits * M * N floats, which have to fit scratch_bytes; otherwise it is the caller's matrix and K is not cut.  parts_bytes: room
+// for the parts of A, without which the tiles of LS_SPLIT_TILES are not planned.
+TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us,
+                          size_t parts_bytes = SIZE_MAX);
+inline bool gemm_by_parts(uint32_t dt, const TiledPlan& p) { return dt == F32 && p.bm * p.bn >= 96 * 128; }
 // parts: gemm_split_parts_bytes(M, K) of scratch for the parts of A, which the fp32 tiles of LS_SPLIT_TILES need.
 bool launch_gemm_tiled(uint32_t dt, int epi, const TiledPlan& p, const void* A, const void* W, int M, int N, int K, void* out,
                        const RopeAppend& rope, hipStream_t st, void* parts = nullptr);

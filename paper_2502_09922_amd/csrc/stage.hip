@@ -4,6 +4,7 @@
 #include "../../include/ls_stage.h"
 #include "kernels.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -133,7 +134,7 @@ bool span_ok(const ls_cfg* c, int lo, int hi) {
 // ---- workspace carving ------------------------------------------------------------------
 struct Carve {
   size_t cs, x, y, qkv, attn, h, logits, row_seq, row_pos, last_rows, next_tok, xb, xb2, ss_a, ss_b, splitk, splitk_bytes,
-      attn_part, attn_part_bytes, parts, total;
+      attn_part, attn_part_bytes, parts, parts_bytes, total;
 };
 
 // more than 64 MiB of partial tiles are never wanted: a call that long fills the chip without splits
@@ -184,14 +185,25 @@ Carve carve(const ls_cfg* c, int lo, int hi) {
   const size_t chunks = ls::attn_decode_scratch_bytes((int)c->n_q_heads, (int)c->n_kv_heads, (int)c->head_dim, (int)c->max_seq);
   if (chunks > w.attn_part_bytes) w.attn_part_bytes = chunks;
   w.attn_part = take(w.attn_part_bytes);
-  // fp32: the bf16 parts of the rows a projection reads (gemm_split_f32.hip)
-  size_t parts = 0;
-  if (c->dtype == LS_DTYPE_F32)
-    for (size_t k : {d, (size_t)c->n_q_heads * c->head_dim, (size_t)c->ffn}) {
-      const size_t b = ls::gemm_split_parts_bytes((int)T, (int)k);
-      if (b > parts) parts = b;
-    }
-  w.parts = take(parts);
+  // fp32: the bf16 parts of the rows a projection reads (gemm_split_f32.hip), for the most rows of it that are planned so (up to
+  // 4 GB of them); a call whose row count is between those looked at is planned without if its parts do not fit
+  if (c->dtype == LS_DTYPE_F32) {
+    auto parts_of = [&](int epi, size_t rows, size_t n, size_t k) {
+      if (n > INT32_MAX || k > INT32_MAX) return;
+      for (size_t m = std::min(rows, (size_t)UINT32_MAX / (4 * k)); m >= 64; m = m * 7 / 8)
+        if (ls::gemm_by_parts(c->dtype, ls::gemm_tiled_plan(c->dtype, epi, (int)m, (int)n, (int)k, epi == ls::TILED_PART, w.splitk_bytes, nullptr))) {
+          w.parts_bytes = std::max(w.parts_bytes, ls::gemm_split_parts_bytes((int)m, (int)k));
+          return;
+        }
+    };
+    const size_t qd = (size_t)c->n_q_heads * c->head_dim;
+    parts_of(ls::TILED_STORE, T, qkv_cols, d);
+    parts_of(ls::TILED_PART, T, d, qd);
+    parts_of(ls::TILED_SWIGLU, T, c->ffn, d);
+    parts_of(ls::TILED_PART, T, d, c->ffn);
+    if (last) parts_of(ls::TILED_STORE, B, c->vocab, d);
+  }
+  w.parts = take(w.parts_bytes);
   (void)lo;
   w.total = off;
   return w;
@@ -716,7 +728,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   auto plan = [&](int epi, int N, int K) {
     if (few_rows) return TiledPlan{};
     float us = 0.f;
-    const TiledPlan p = gemm_tiled_plan(dt, epi, rows, N, K, epi == TILED_PART, part_bytes, &us);
+    const TiledPlan p = gemm_tiled_plan(dt, epi, rows, N, K, epi == TILED_PART, part_bytes, &us, s->w.parts_bytes);
     if (dt == BF16 && rows > 64 && gemm_mfma_supported(rows, N, K) &&
         gemm_mfma_us(rows, N, K, epi == TILED_SWIGLU ? 128 : 256) <= us)
       return TiledPlan{};
@@ -857,7 +869,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     LS_HIP(gate(*hb, st));  // gate: head block has landed
     float* logits = logits_out ? logits_out : (float*)(ws + s->w.logits);
     const TiledPlan p_head = (dt == F32 || batch > (d > 4096 ? 8 : 16)) && ((uintptr_t)logits & 15) == 0
-                                 ? gemm_tiled_plan(dt, TILED_PART, batch, (int)c.vocab, d, false, 0, nullptr)
+                                 ? gemm_tiled_plan(dt, TILED_PART, batch, (int)c.vocab, d, false, 0, nullptr, s->w.parts_bytes)
                                  : TiledPlan{};
     if (rows_f32(p_head) && gemm_rows_f32_norm_supported(batch, (int)c.vocab, d)) {
       RowsF32Fusion f;

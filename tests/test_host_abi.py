@@ -119,3 +119,22 @@ def test_measurement_probes_reject_bad_arguments_without_a_gpu():
     assert b.ls_probe_mfma_tflops(0, 1, None, None) < 0
     assert b.ls_probe_mfma_tflops(10, 0, None, None) < 0
     assert b"ls_probe" in b.lib.ls_last_error()
+
+
+def test_workspace_of_fp32_stages():
+    """The split copy of a projection's rows is there only where some projection is planned with it, and for no more rows
+    than its kernels address (4 GB of them)."""
+    def workspace(shape, tokens):
+        cfg = b.make_cfg(shape, 1, 256, tokens)
+        return b.lib.ls_stage_workspace_bytes(C.byref(cfg), 0, 1)
+
+    def per_token(s):  # x, y, qkv, attn, h, the two row maps, one partial tile
+        return 4 * (3 * s.hidden + s.qkv_rows + s.n_q_heads * s.head_dim + s.ffn) + 8
+
+    tiny, big = synth.CONFIGS["tiny_f32"], synth.CONFIGS["llama7b"].with_(dtype="f32")
+    fixed = workspace(tiny, 1) + 7 * 8 * 4 * tiny.hidden * 512  # eight partial tiles of a row instead of one
+    assert workspace(tiny, 512) <= fixed + 512 * per_token(tiny)
+    parts = [workspace(big, t) - t * per_token(big) for t in (1024, 1 << 15, 1 << 18, 1 << 20)]
+    assert 6 * 11008 * 1024 <= parts[0] <= 6.5 * 11008 * 1024 + (64 << 20)
+    assert 6 * 11008 * (1 << 15) <= parts[1] <= 6.5 * 11008 * (1 << 15) + (64 << 20)
+    assert parts[2] <= 6.5 * 2**30 + (64 << 20) and parts[3] <= 6.5 * 2**30 + (64 << 20)
