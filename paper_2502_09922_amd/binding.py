@@ -253,8 +253,9 @@ class Stage:
         cu = np.zeros(len(lengths) + 1, np.int32)
         cu[1:] = np.cumsum(np.asarray(lengths, dtype=np.int64))
         total, batch = int(cu[-1]), len(lengths)
-        if not self._arriving and torch.cuda.current_stream(self.device).cuda_stream == self._stream_ptr(stream):
-            # in stream order: a copy from pageable memory would wait here for everything enqueued before
+        if inp.is_cuda and not self._arriving and torch.cuda.current_stream(self.device).cuda_stream == self._stream_ptr(stream):
+            # in stream order: a copy from pageable memory would wait here for everything enqueued before (rows in pinned host
+            # memory, which knows no streams, need that wait: the pass before reads the ones that are let go here)
             cu_dev = torch.empty(batch + 1, dtype=torch.int32, device=self.device)
             check(lib.ls_write_ints(cu_dev.data_ptr(), cu.ctypes.data_as(C.POINTER(C.c_int32)), batch + 1, self._stream_ptr(stream)))
             inp.record_stream(torch.cuda.current_stream(self.device))  # may be another stream's, and the pass outlives this call

@@ -1,5 +1,6 @@
 """The sequence bounds of a prompt pass: written in stream order on the current stream (more of them than one kernel
-carries), copied where the pass runs on another stream; passes one behind the other with nothing waited for between them."""
+carries), copied where the pass runs on another stream or reads rows in pinned host memory; passes one behind the other with nothing
+waited for between them."""
 import ctypes as C
 
 import numpy as np
@@ -46,4 +47,20 @@ def test_passes_without_a_wait_between_them():
         torch.cuda.synchronize()
         assert torch.equal(out, same)
         assert gpu.seq_lens[: len(n)].cpu().tolist() == n
+    gpu.close()
+
+
+def test_rows_in_pinned_host_memory():
+    import torch
+
+    shape = synth.StageShape("bf16", 1, 256, 2, 2, 128, 256, 0)
+    gpu = make_gpu(shape, 3, 0, 1, 4, 64, 256)
+    x = to_dev(shape, synth.hidden_states(shape, 5, 64))
+    for lens in ([64], [3, 40, 21]):
+        want = gpu.prefill(x, lens).clone()
+        host = torch.empty(x.shape, dtype=x.dtype, pin_memory=True)
+        host.copy_(x)
+        assert torch.equal(gpu.prefill(host, lens), want)
+        assert torch.equal(gpu.prefill(host, lens), want)
+        assert torch.equal(gpu.prefill(x, lens), want)
     gpu.close()
