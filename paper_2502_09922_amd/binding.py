@@ -161,7 +161,6 @@ class Stage:
         self.shape, self.lo, self.hi = shape, layer_lo, layer_hi
         self.cfg = make_cfg(shape, max_batch, max_seq, max_tokens)
         self.device = torch.device(device)
-        self._arriving = False  # blocks were enqueued for copy since the last prompt pass
         self.first = shape.vocab > 0 and layer_lo == 0
         self.last = shape.vocab > 0 and layer_hi == shape.n_layers_total
         self.tdtype = torch.float32 if shape.dtype == "f32" else torch.bfloat16
@@ -217,12 +216,10 @@ class Stage:
     def load_block(self, layer: int, host, stream=None):
         """host: pinned torch uint8 tensor or numpy uint8 array holding the packed block."""
         ptr = host.data_ptr() if hasattr(host, "data_ptr") else host.ctypes.data
-        self._arriving = True
         check(lib.ls_stage_load_block(self.handle, ptr, layer, self._stream_ptr(stream)))
 
     def load_layers(self, first: int, last: int, host, stream=None):
         """host: pinned uint8 tensor holding the packed blocks of layers first..last back to back."""
-        self._arriving = True
         check(lib.ls_stage_load_layers(self.handle, host.data_ptr(), first, last, self._stream_ptr(stream)))
 
     def adopt_block(self, layer: int, stream=None):
@@ -253,17 +250,14 @@ class Stage:
         cu = np.zeros(len(lengths) + 1, np.int32)
         cu[1:] = np.cumsum(np.asarray(lengths, dtype=np.int64))
         total, batch = int(cu[-1]), len(lengths)
-        if inp.is_cuda and not self._arriving and torch.cuda.current_stream(self.device).cuda_stream == self._stream_ptr(stream):
+        if inp.is_cuda and torch.cuda.current_stream(self.device).cuda_stream == self._stream_ptr(stream):
             # in stream order: a copy from pageable memory would wait here for everything enqueued before (rows in pinned host
             # memory, which knows no streams, need that wait: the pass before reads the ones that are let go here)
             cu_dev = torch.empty(batch + 1, dtype=torch.int32, device=self.device)
             check(lib.ls_write_ints(cu_dev.data_ptr(), cu.ctypes.data_as(C.POINTER(C.c_int32)), batch + 1, self._stream_ptr(stream)))
             inp.record_stream(torch.cuda.current_stream(self.device))  # may be another stream's, and the pass outlives this call
         else:
-            # behind blocks that are still arriving nothing is gained: the next pass's copies then wait for this one on
-            # the device, which takes longer (two 7B blocks, passes one behind the other: 14.75 ms against 14.68)
             cu_dev = torch.from_numpy(cu).to(self.device)
-            self._arriving = False
         out = (torch.empty(batch, dtype=torch.int32, device=self.device) if self.last
                else torch.empty(total, self.shape.hidden, dtype=self.tdtype, device=self.device))
         logits = (torch.empty(batch, self.shape.vocab, dtype=torch.float32, device=self.device)

@@ -2,6 +2,7 @@
 carries), copied where the pass runs on another stream or reads rows in pinned host memory; passes one behind the other with nothing
 waited for between them."""
 import ctypes as C
+import time
 
 import numpy as np
 import pytest
@@ -32,7 +33,7 @@ def test_passes_without_a_wait_between_them():
     shape = synth.StageShape("bf16", 1, 256, 2, 2, 128, 256, 0)
     gpu = make_gpu(shape, 3, 0, 1, 300, 8, 1200)
     side = torch.cuda.Stream()
-    gpu.prefill(to_dev(shape, synth.hidden_states(shape, 9, 3)), [3])  # the first behind a load copies its bounds
+    gpu.prefill(to_dev(shape, synth.hidden_states(shape, 9, 3)), [3])  # behind the load
     lens = [[1 + (i * k) % 4 for i in range(300)] for k in (1, 2, 3)] + [[4, 2, 1], [8]]
     xs = [to_dev(shape, synth.hidden_states(shape, 4 + i, sum(n))) for i, n in enumerate(lens)]
     torch.cuda.synchronize()
@@ -64,3 +65,39 @@ def test_rows_in_pinned_host_memory():
         assert torch.equal(gpu.prefill(host, lens), want)
         assert torch.equal(gpu.prefill(x, lens), want)
     gpu.close()
+
+
+def test_the_host_does_not_wait_for_arriving_blocks():
+    """Load and run, twice: all of it is enqueued while the first blocks are still on their way (a copy of the bounds from
+    pageable memory waited for the pass before, 9 ms)."""
+    import torch
+
+    shape = synth.StageShape("bf16", 2, 4096, 32, 32, 128, 11008, 0)
+    st = binding.Stage(shape, 0, 2, 1, 64, 64)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    host = []
+    for layer in st.block_ids():
+        view = st.block_view(layer)
+        view.view(torch.bfloat16).normal_(0, 0.02, generator=gen)
+        host.append(torch.empty(view.numel(), dtype=torch.uint8, pin_memory=True))
+        host[-1].copy_(view)
+        st.adopt_block(layer)
+    x = torch.randn(64, 4096, generator=gen, device="cuda").to(torch.bfloat16)
+    want = st.prefill(x[:40], [40]).clone()
+    copies = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    outs = []
+    for _ in range(2):
+        st.reset_blocks()
+        copies.wait_stream(torch.cuda.current_stream())
+        for layer, t in zip(st.block_ids(), host):
+            st.load_block(layer, t, copies)
+        outs.append(st.prefill(x[:40], [40]))
+    waited = time.perf_counter() - t0
+    arriving = not copies.query()
+    torch.cuda.synchronize()
+    took = time.perf_counter() - t0
+    assert arriving and waited < took / 3, (waited, took)
+    assert all(torch.equal(o, want) for o in outs)
+    st.close()
