@@ -297,7 +297,29 @@ void launch_rows(uint32_t dt, int src, const RowsArgs& a, hipStream_t st) {
 
 }  // namespace ls
 
-// For the tests, which choose a tile themselves to reach its edges; not declared in ls_stage.h.  Both return 0
+namespace {
+
+// A launch with a chosen tile.  The split tiles bring their own room for the parts, which the callers have not.
+bool launch_chosen(uint32_t dt, int epi, int bm, int bn, int splits, const void* A, const void* W, int M, int N, int K, void* out,
+                   const ls::RopeAppend& rope, hipStream_t st) {
+  using namespace ls;
+  TiledPlan p;
+  p.bm = bm; p.bn = bn; p.splits = splits;
+  if (bm <= 0) return false;
+  bool by_parts = false;
+#define LS_TILE(bm_, bn_) by_parts |= dt == F32 && bm == bm_ && bn == bn_;
+  LS_SPLIT_TILES(LS_TILE)
+#undef LS_TILE
+  if (!by_parts) return launch_gemm_tiled(dt, epi, p, A, W, M, N, K, out, rope, st);
+  void* parts = nullptr;
+  if (hipMallocAsync(&parts, gemm_split_parts_bytes(M, K), st) != hipSuccess) return false;
+  const bool ok = launch_gemm_tiled(dt, epi, p, A, W, M, N, K, out, rope, st, parts);
+  return hipFreeAsync(parts, st) == hipSuccess && ok;
+}
+
+}  // namespace
+
+// For the tests, which choose a tile themselves to reach its edges; not declared in ls_stage.h.  All return 0
 // where there is no plan, or where the launch would not be one that the kernels take.
 extern "C" int ls_test_tiled_plan(uint32_t dt, int epi, int M, int N, int K, int to_scratch, size_t scratch_bytes, int* plan) {
   const ls::TiledPlan p = ls::gemm_tiled_plan(dt, epi, M, N, K, to_scratch != 0, scratch_bytes, nullptr);
@@ -313,14 +335,5 @@ extern "C" int ls_test_tiled_gemm(uint32_t dt, int epi, int bm, int bn, int spli
   if ((dt != F32 && dt != BF16) || epi < TILED_PART || epi > TILED_SWIGLU || !A || !W || !out) return 0;
   if (!gemm_tiled_supported(dt, epi, M, N, K) || splits < 1 || splits > 8) return 0;
   if (splits > 1 && (epi != TILED_PART || nk < 2 * splits)) return 0;
-  TiledPlan p;
-  p.bm = bm; p.bn = bn; p.splits = splits;
-  hipStream_t st = (hipStream_t)hip_stream;
-  if (bm <= 0 || dt != F32 || bm * bn < 96 * 128) return bm > 0 && launch_gemm_tiled(dt, epi, p, A, W, M, N, K, out, RopeAppend{}, st);
-  // the split tiles: what a caller of this entry has no scratch for; 160 and 256 rows of 128 name the tallest of them
-  if (bn == 128 && (bm == 160 || bm == 256)) p.bm = 176;
-  void* parts = nullptr;
-  if (hipMallocAsync(&parts, gemm_split_parts_bytes(M, K), st) != hipSuccess) return 0;
-  const int ok = launch_gemm_tiled(dt, epi, p, A, W, M, N, K, out, RopeAppend{}, st, parts);
-  return hipFreeAsync(parts, st) == hipSuccess && ok;
+  return launch_chosen(dt, epi, bm, bn, splits, A, W, M, N, K, out, RopeAppend{}, (hipStream_t)hip_stream);
 }

@@ -1,23 +1,12 @@
-"""The fp32 tiles by split operands (gemm_split_f32.hip) that the tests of the tiled GEMM do not name: the tallest and the
-widest.  Rows that are cut evenly over tiles, matrices that end inside a tile, half a k-step at the end, K of
-fewer k-steps than the ring has stages; single products; values the parts cannot hold in the first and in a later k-step."""
+"""The fp32 tiles by split operands (gemm_split_f32.hip): a value that the parts cannot hold, in the first, a middle and the
+last k-step, in a row and in a weight; rows that are cut evenly over tiles, half a k-step at the end.  (Edges and single
+products of these tiles: test_gpu_tiled_tiles.py, test_gpu_split_products.py.)"""
 import numpy as np
 import pytest
 
-from test_gpu_split_products import matmul, test_every_product_keeps_its_bits_and_has_no_bias as products
-from test_gpu_split_products import test_the_ends_of_the_range_and_infinities as ends
-from test_gpu_tiled_tiles import F32, test_tile_edges as edges
+from test_gpu_split_products import TILES, matmul
 
 pytestmark = pytest.mark.gpu
-
-TILES = [(176, 128), (128, 192)]
-
-
-@pytest.mark.parametrize("tile", TILES)
-def test_edges_and_products(tile):
-    edges(F32, tile)
-    products(tile)
-    ends(tile)
 
 
 @pytest.mark.parametrize("tile", TILES)

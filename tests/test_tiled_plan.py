@@ -63,6 +63,7 @@ def test_launches_with_a_chosen_tile_that_are_refused():
     fn.argtypes = [C.c_uint32] + [C.c_int] * 4 + [C.c_void_p] * 2 + [C.c_int] * 3 + [C.c_void_p] * 2
     p = 256  # never read
     for dt, epi, bm, bn, splits, m, n, k in ((F32, STORE, 160, 256, 1, 40, 64, 64), (BF16, STORE, 48, 128, 1, 40, 64, 64),
+                                             (F32, STORE, 160, 128, 1, 40, 64, 64), (F32, STORE, 256, 128, 1, 40, 64, 64),
                                              (F32, STORE, 0, 0, 1, 4, 64, 64), (BF16, STORE, 32, 64, 1, 40, 64, 80),
                                              (F32, STORE, 32, 64, 2, 40, 64, 512), (F32, PART, 32, 64, 5, 40, 64, 256),
                                              (BF16, SWIGLU, 64, 64, 1, 40, 64, 64), (BF16, STORE, 32, 64, 1, 40, 24, 64),
