@@ -337,3 +337,19 @@ extern "C" int ls_test_tiled_gemm(uint32_t dt, int epi, int bm, int bn, int spli
   if (splits > 1 && (epi != TILED_PART || nk < 2 * splits)) return 0;
   return launch_chosen(dt, epi, bm, bn, splits, A, W, M, N, K, out, RopeAppend{}, (hipStream_t)hip_stream);
 }
+
+// The same with RoPE and the cache append: N = (hq + 2 hkv) hd, out [M,N], cs [max_seq][hd/2][2], caches [seq][hkv][max_seq][hd].
+extern "C" int ls_test_tiled_rope(uint32_t dt, int bm, int bn, const void* A, const void* W, int M, int K, void* out, const float* cs,
+                                  const int32_t* row_seq, const int32_t* row_pos, int hq, int hkv, int hd, int max_seq, void* kc,
+                                  void* vc, void* hip_stream) {
+  using namespace ls;
+  if ((dt != F32 && dt != BF16) || !A || !W || !out || !cs || !row_seq || !row_pos || !kc || !vc) return 0;
+  if (hq < 1 || hkv < 1 || hd < 16 || hd % 16 || max_seq < 1) return 0;
+  const int N = (hq + 2 * hkv) * hd;
+  if (!gemm_tiled_supported(dt, TILED_ROPE, M, N, K)) return 0;
+  RopeAppend r;
+  r.cs = cs; r.row_seq = row_seq; r.row_pos = row_pos;
+  r.hq = hq; r.hkv = hkv; r.hd = hd; r.max_seq = max_seq;
+  r.kc = (__bf16*)kc; r.vc = (__bf16*)vc;
+  return launch_chosen(dt, TILED_ROPE, bm, bn, 1, A, W, M, N, K, out, r, (hipStream_t)hip_stream);
+}
