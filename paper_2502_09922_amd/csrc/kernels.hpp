@@ -107,11 +107,18 @@ void launch_gemm_mfma_rope(const void* A, const void* W, int M, int N, int K, vo
 // the storage type, TILED_SWIGLU silu(gate) * up, TILED_ROPE as launch_gemm_mfma_rope.
 enum TiledEpi : int { TILED_PART = 0, TILED_STORE = 1, TILED_SWIGLU = 2, TILED_ROPE = 3 };
 // The tiles there are.  bf16 (gemm_tiled_bf16.hip): 16-row and 16-weight-row fragments of a wavefront, wavefront rows and
-// columns, with SwiGLU too (gate and up are two fragments of one wavefront).
+// columns, with SwiGLU too (gate and up are two fragments of one wavefront).  What a tile gains over the next best, where it
+// gains most (7B, 13B and 70B projections, 24..400 rows, cold weights): 32 x 64 32 % (70B QKV, 24 rows), 32 x 96 9 % and
+// 32 x 128 41 % (7B and 13B gate-up, 24), 48 x 48 7 % and 48 x 64 1 % (70B QKV and O, 45), 48 x 96 as fast as 64 x 96 (7B
+// gate-up, 45), 64 x 48 11 % (7B QKV, 64), 64 x 64 18 % (13B QKV, 64), 64 x 96 10 % (7B gate-up, 64), 64 x 128 28 % (13B gate-up,
+// 45), 64 x 224 6 % (70B gate-up, 64: 139.5 us, 64 x 128 148.1), 96 x 96 6 % (70B QKV, 120), 96 x 128 12 % (70B gate-up, 80),
+// 96 x 192 4 % (7B QKV, 350), 128 x 64 16 % (7B down, 128), 128 x 96 5 % (70B QKV, 160), 128 x 128 13 % (70B QKV, 311),
+// 128 x 192 12 % (7B QKV, 400), 160 x 96 4 % (7B QKV, 290), 160 x 128 20 % (70B QKV, 400), 160 x 192 12 % (7B gate-up, 311),
+// 160 x 256 32 % (70B gate-up, 160), 256 x 128 18 % (70B gate-up, 192), 256 x 192 11 % (7B gate-up, 400).
 #define LS_TILED_BF16(X)                                                                               \
   X(1, 2, 2, 2, false) X(2, 2, 1, 3, true) X(2, 2, 1, 4, true)                                          \
   X(1, 3, 3, 1, false) X(1, 2, 3, 2, false) X(3, 2, 1, 3, true)                                         \
-  X(4, 1, 1, 3, false) X(2, 2, 2, 2, false) X(4, 2, 1, 3, true) X(2, 4, 2, 2, true) X(2, 6, 2, 2, true) X(4, 2, 1, 7, true) \
+  X(4, 1, 1, 3, false) X(2, 2, 2, 2, false) X(4, 2, 1, 3, true) X(2, 4, 2, 2, true) X(4, 2, 1, 7, true) \
   X(3, 3, 2, 2, false) X(3, 4, 2, 2, true) X(3, 6, 2, 2, true)                                          \
   X(4, 2, 2, 2, false) X(4, 3, 2, 2, false) X(4, 4, 2, 2, true) X(4, 6, 2, 2, true)                     \
   X(5, 3, 2, 2, false) X(5, 4, 2, 2, true) X(5, 6, 2, 2, true) X(5, 4, 2, 4, true)                      \

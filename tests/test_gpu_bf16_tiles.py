@@ -10,7 +10,7 @@ from test_gpu_tiled_tiles import BF16, PART, STORE, test_tile_edges as edges
 
 pytestmark = pytest.mark.gpu
 
-GLU = [(32, 96), (48, 96), (64, 96), (64, 192), (64, 224), (96, 192), (128, 192), (160, 192), (256, 192)]
+GLU = [(32, 96), (48, 96), (64, 96), (64, 224), (96, 192), (128, 192), (160, 192), (256, 192)]
 PLAIN = [(48, 48), (48, 64), (64, 48), (96, 96), (128, 96), (160, 96)]
 
 

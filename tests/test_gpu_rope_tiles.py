@@ -12,7 +12,7 @@ from test_gpu_tiled_gemm import run
 pytestmark = pytest.mark.gpu
 
 F32, BF16 = 0, 1
-BF16_TILES = [(32, 64), (32, 96), (32, 128), (48, 48), (48, 64), (48, 96), (64, 48), (64, 64), (64, 96), (64, 128), (64, 192), (64, 224),
+BF16_TILES = [(32, 64), (32, 96), (32, 128), (48, 48), (48, 64), (48, 96), (64, 48), (64, 64), (64, 96), (64, 128), (64, 224),
               (96, 96), (96, 128), (96, 192), (128, 64), (128, 96), (128, 128), (128, 192), (160, 96), (160, 128), (160, 192),
               (160, 256), (256, 128), (256, 192)]
 F32_TILES = [(32, 64), (32, 128), (64, 64), (64, 128), (128, 64), (96, 128), (128, 128), (176, 128), (128, 192)]
