@@ -43,7 +43,7 @@ constexpr int ROWS_F32_MAX = 8;
 TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us,
                           size_t parts_bytes) {
   TiledPlan best;
-  float best_us = 1e30f;
+  float best_us = 1e30f, best_rank = 1e30f;
   if (dt == F32 && M <= ROWS_F32_MAX) {  // bm == 0: the kernel for few fp32 rows
     best.splits = gemm_rows_f32_splits(epi, M, N, K, to_scratch, scratch_bytes);
     if (best.splits) {
@@ -60,21 +60,25 @@ TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scr
       if (dt == BF16) {
         if (bm > 32 && bm >= 2 * M) return;  // more than half of the products for rows that are not there
         step = 0.02f + 0.0024f * ((float)((M + 7) / 8 * 8) / (float)tiles_m + (float)bn);
-        if (tiles_m > 1 && !to_scratch) step *= 1.02f;
         if ((bm + bn) * 128 * 3 > 160 * 1024) step *= 1.18f;
       }
       for (int s = 1; s <= 8; ++s) {
         // partial tiles, also those of a single split, have to fit the scratch
         if ((to_scratch && (size_t)s * M * N * sizeof(float) > scratch_bytes) || (s > 1 && (!to_scratch || nk < 2 * s))) break;
         const long per_xcd = (long)panels * tiles_m * s;
-        float t_us = (float)((per_xcd + 31) / 32) * ((float)((nk + s - 1) / s) * step + 2.5f);
-        if (dt == BF16) {  // whichever is longer, and some more where both are alike
-          const float a = t_us * t_us, b = stream * stream;
-          t_us = sqrtf(sqrtf(a * a + b * b));
-        }
-        t_us += (float)s * (float)M * (float)N * 8.f / 4e6f + extra;
-        if (t_us < best_us) {
-          best_us = t_us;
+        auto estimate = [&](float a_step) {
+          float t = (float)((per_xcd + 31) / 32) * ((float)((nk + s - 1) / s) * a_step + 2.5f);
+          if (dt == BF16) {  // whichever is longer, and some more where both are alike
+            const float a = t * t, b = stream * stream;
+            t = sqrtf(sqrtf(a * a + b * b));
+          }
+          return t + (float)s * (float)M * (float)N * 8.f / 4e6f + extra;
+        };
+        // one tile row goes before two that bring the same lines; the time that others compare with stays the estimate's
+        const float rank = estimate(dt == BF16 && tiles_m > 1 && !to_scratch ? 1.02f * step : step);
+        if (rank < best_rank) {
+          best_rank = rank;
+          best_us = estimate(step);
           best.bm = bm; best.bn = bn; best.splits = s;
         }
       }
