@@ -742,9 +742,10 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   const TiledPlan p_o = rows_one_pass && gsc.splitk ? plan(TILED_PART, d, hq * hd) : TiledPlan{};
   const TiledPlan p_gu = plan(TILED_SWIGLU, F, d);
   const TiledPlan p_dn = rows_one_pass && gsc.splitk ? plan(TILED_PART, d, F) : TiledPlan{};
-  // Few fp32 rows of small matrices are a chain of launches of 2 us each.  A projection whose K is not cut takes the norm
-  // of its rows along, and adds its sums to the residual rows itself: 13 launches for a step of the two-layer tiny model
-  // instead of 18.  A norm that is folded into the row kernel instead, behind a projection whose K is cut, costs nothing.
+  // Few fp32 rows of small matrices are a chain of launches of 3 us each.  A projection whose K is not cut adds its sums to
+  // the residual rows itself and takes the norm of its rows along: 13 launches for a step of the two-layer tiny model
+  // instead of 18.  A norm that a row kernel makes on its way costs nothing: in front of the first layer and behind a
+  // projection whose K is cut it stays there.
   auto rows_f32 = [&](const TiledPlan& p) { return dt == F32 && p.splits == 1 && !p.bm; };
   auto folds_norm = [&](const TiledPlan& p, int N) { return rows_one_pass && rows_f32(p) && gemm_rows_f32_norm_supported(rows, N, d); };
 
