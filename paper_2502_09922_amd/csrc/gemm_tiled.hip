@@ -26,20 +26,20 @@ bool gemm_tiled_supported(uint32_t dt, int epi, int M, int N, int K) {
 // 299 / 352, 8 rows 219 / 250; the FMAs of each further row cost 6 us, the tiles nothing up to 32.
 constexpr int ROWS_F32_MAX = 8;
 
-// Time of a launch, in microseconds, from sweeps over the tiles (7B, 13B and 70B layers, 12..1024 rows in bf16, 24..512
-// in fp32, cold weights).  bf16: a k-step of a workgroup costs 0.02 us + 2.4 ns per row it brings into LDS, whatever
-// the arithmetic (48 x 48 0.24, 64 x 64 0.33, 64 x 128 0.47, 128 x 128 0.58, 160 x 192 0.85, 256 x 128 0.9 us
-// measured; a sixth more where only two stages fit: 256 x 192 1.33); rows past the end of the call are not fetched, and
-// the tiles of a column wait for the same weight lines, so that it is their mean that counts; one tile row is a little
-// faster than two of the same lines (7B gate-up, 128 rows, 128 x 128 44.0, 96 x 192 46.9, 64 x 192 48.4 us; 13B, 256 rows,
-// 256 x 128 76.3, 160 x 256 82.7; 70B 244 and 262).  Weights do not come from
-// memory faster than 6.4 TB/s.  Chosen so, the four projections at 11 row counts of the 7B shape take 1584 us
-// together, the fastest tile and split of each 1552.  fp32: at least the matrix work (64 x 64 at 0.4, 64 x 128 at 0.46
-// TFLOP/s per CU); by split operands 0.39 us + 0.055 per pair of 16-row fragments and wavefront (96 x 128 1.05..1.1,
-// 128 x 128 1.2..1.4, 176 x 128 1.6..1.7, 128 x 192 1.9..2.1 us measured) and the kernel in front, whose launch and tall
-// tiles do not pay for small matrices (two layers of 512 columns, 97..512 rows on fp32 instructions 103..196 us, by split
-// operands 175..263; 1024 columns, 97 rows 152 and 244, 311 rows 251 and 292).  One workgroup fits a CU, so the launch takes as many rounds as its fullest XCD has workgroups for its 32 CUs; every K split
-// writes and reads an fp32 tile.
+// Time of a launch, in microseconds, from sweeps over the tiles (7B, 13B and 70B layers, 12..1024 rows in bf16,
+// 24..512 in fp32, cold weights).  bf16: a k-step of a workgroup costs 0.02 us + 2.4 ns per row it brings into LDS,
+// whatever the arithmetic (48 x 48 0.24, 64 x 64 0.33, 64 x 128 0.47, 128 x 128 0.58, 160 x 192 0.85, 256 x 128 0.9 us
+// measured; a sixth more where only two stages fit: 256 x 192 1.33); rows past the end of the call are not fetched,
+// and the tiles of a column wait for the same weight lines, so that it is their mean that counts; one tile row is a
+// little faster than two of the same lines (7B gate-up, 128 rows, 128 x 128 44.0, 96 x 192 46.9, 64 x 192 48.4 us;
+// 13B, 256 rows, 256 x 128 76.3, 160 x 256 82.7; 70B 244 and 262).  Weights do not come from memory faster than 6.4
+// TB/s.  Chosen so, the four projections at 11 row counts of the 7B shape take 1584 us together, the fastest tile and
+// split of each 1552.  fp32: at least the matrix work (64 x 64 at 0.4, 64 x 128 at 0.46 TFLOP/s per CU); by split
+// operands 0.39 us + 0.055 per pair of 16-row fragments and wavefront (96 x 128 1.05..1.1, 128 x 128 1.2..1.4, 176 x
+// 128 1.6..1.7, 128 x 192 1.9..2.1 us measured) and the kernel in front, whose launch and tall tiles do not pay for
+// small matrices (two layers of 512 columns, 97..512 rows on fp32 instructions 103..196 us, by split operands
+// 175..263; 1024 columns, 97 rows 152 and 244, 311 rows 251 and 292).  One workgroup fits a CU, so the launch takes as
+// many rounds as its fullest XCD has workgroups for its 32 CUs; every K split writes and reads an fp32 tile.
 TiledPlan gemm_tiled_plan(uint32_t dt, int epi, int M, int N, int K, bool to_scratch, size_t scratch_bytes, float* us,
                           size_t parts_bytes) {
   TiledPlan best;
