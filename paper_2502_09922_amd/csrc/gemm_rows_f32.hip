@@ -27,7 +27,9 @@ constexpr long NORM_WORK = 160000;  // pieces times N
 
 // NORM: A holds residual rows and every wavefront normalises the ones it multiplies, all of K at once (K <= 256 U).  The
 // sums are those of k_rows in the order of k_rows, so a norm that is launched on its own gives the same bits.
-template <int EPI, int M, int R, int U, bool NORM>
+// ADD (TILED_PART): the sums are added to f.add.  An instance of its own, as f is not in registers when a kernel starts: without
+// one the weights' first loads waited for it (8 rows, 1024 columns, K cut: 5.1 -> 6.3 us).
+template <int EPI, int M, int R, int U, bool NORM, bool ADD>
 __global__ void __launch_bounds__(256)
 k_gemm_rows_f32(const float* __restrict__ A, const float* __restrict__ W, int N, int K, float* out, RowsF32Fusion f) {
   constexpr bool GLU = EPI == TILED_SWIGLU;
@@ -47,13 +49,12 @@ k_gemm_rows_f32(const float* __restrict__ A, const float* __restrict__ W, int N,
   const float* a[M];
 #pragma unroll
   for (int m = 0; m < M; ++m) a[m] = A + (size_t)(NORM && f.row_map ? f.row_map[m] : m) * K;
-  float base[EPI == TILED_PART ? C : 1][M];  // what the sums are added to
-  if constexpr (EPI == TILED_PART)
-    if (f.add)
+  float base[ADD ? C : 1][M];  // what the sums are added to
+  if constexpr (ADD)
 #pragma unroll
-      for (int c = 0; c < C; ++c)
+    for (int c = 0; c < C; ++c)
 #pragma unroll
-        for (int m = 0; m < M; ++m) base[c][m] = f.add[(size_t)m * N + min(n0 + c, N - 1)];
+      for (int m = 0; m < M; ++m) base[c][m] = f.add[(size_t)m * N + min(n0 + c, N - 1)];
   float acc[R][M];
 #pragma unroll
   for (int r = 0; r < R; ++r)
@@ -119,8 +120,7 @@ k_gemm_rows_f32(const float* __restrict__ A, const float* __restrict__ W, int N,
 #pragma unroll
       for (int m = 0; m < M; ++m) {
         float v = GLU ? silu_f(acc[c][m]) * acc[C + c][m] : acc[c][m];
-        if constexpr (EPI == TILED_PART)
-          if (f.add) v += base[c][m];
+        if constexpr (ADD) v += base[c][m];
         out[((size_t)blockIdx.y * M + m) * N + n0 + c] = v;
       }
 }
@@ -130,11 +130,15 @@ void launch_m(const float* A, const float* W, int N, int K, int splits, float* o
   constexpr int R = 4, U = M <= 2 ? 4 : 2, C = EPI == TILED_SWIGLU ? R / 2 : R;
   const dim3 grid((unsigned)((N + 4 * C - 1) / (4 * C)), (unsigned)splits);
   if (f.gamma) {  // as many pieces as a row has: the registers of more cost wavefronts
-    if (K <= 256) launch_kernel(k_gemm_rows_f32<EPI, M, R, 1, true>, grid, dim3(256), 0, st, A, W, N, K, out, f);
-    else if (K <= 512) launch_kernel(k_gemm_rows_f32<EPI, M, R, 2, true>, grid, dim3(256), 0, st, A, W, N, K, out, f);
-    else if constexpr (M * 3 <= NORM_PIECES) launch_kernel(k_gemm_rows_f32<EPI, M, R, 4, true>, grid, dim3(256), 0, st, A, W, N, K, out, f);
-  } else if (EPI == TILED_PART && !f.add) hipLaunchKernelGGL((k_gemm_rows_f32<EPI, M, R, U, false>), grid, dim3(256), 0, st, A, W, N, K, out, f);
-  else launch_kernel(k_gemm_rows_f32<EPI, M, R, U, false>, grid, dim3(256), 0, st, A, W, N, K, out, f);
+    if (K <= 256) launch_kernel(k_gemm_rows_f32<EPI, M, R, 1, true, false>, grid, dim3(256), 0, st, A, W, N, K, out, f);
+    else if (K <= 512) launch_kernel(k_gemm_rows_f32<EPI, M, R, 2, true, false>, grid, dim3(256), 0, st, A, W, N, K, out, f);
+    else if constexpr (M * 3 <= NORM_PIECES) launch_kernel(k_gemm_rows_f32<EPI, M, R, 4, true, false>, grid, dim3(256), 0, st, A, W, N, K, out, f);
+  } else if constexpr (EPI == TILED_PART) {
+    if (f.add) launch_kernel(k_gemm_rows_f32<EPI, M, R, U, false, true>, grid, dim3(256), 0, st, A, W, N, K, out, f);
+    else hipLaunchKernelGGL((k_gemm_rows_f32<EPI, M, R, U, false, false>), grid, dim3(256), 0, st, A, W, N, K, out, f);
+  } else {
+    launch_kernel(k_gemm_rows_f32<EPI, M, R, U, false, false>, grid, dim3(256), 0, st, A, W, N, K, out, f);
+  }
 }
 
 template <int EPI>
@@ -172,7 +176,7 @@ bool gemm_rows_f32_norm_supported(int M, int N, int K) {
 bool launch_gemm_rows_f32(int epi, const void* A, const void* W, int M, int N, int K, int splits, void* out, hipStream_t st,
                           const RowsF32Fusion& f) {
   const float *a = (const float*)A, *w = (const float*)W;
-  if ((f.gamma && (splits != 1 || !gemm_rows_f32_norm_supported(M, N, K))) || (f.add && (splits != 1 || epi != TILED_PART))) return false;
+  if ((f.gamma && (f.add || splits != 1 || !gemm_rows_f32_norm_supported(M, N, K))) || (f.add && (splits != 1 || epi != TILED_PART))) return false;
   switch (epi) {
     case TILED_PART: return launch_e<TILED_PART>(a, w, M, N, K, splits, (float*)out, f, st);
     case TILED_STORE: return launch_e<TILED_STORE>(a, w, M, N, K, splits, (float*)out, f, st);

@@ -145,7 +145,7 @@ size_t gemm_split_parts_bytes(int M, int K);
 float gemm_mfma_us(int M, int N, int K, int ncols);
 
 // fp32 GEMM of one to eight rows (gemm_rows_f32.hip), a plan with bm == 0.  gamma: A holds residual rows, their RMSNorm is
-// what is multiplied (row_map: row m of the call is row row_map[m] of A).  add: the output is added to it (TILED_PART).
+// what is multiplied (row_map: row m of the call is row row_map[m] of A).  add: the output is added to it (TILED_PART, no gamma).
 // Both need a plan that does not cut K, the norm rows that gemm_rows_f32_norm_supported takes.
 struct RowsF32Fusion {
   const float* gamma = nullptr;
