@@ -36,9 +36,11 @@ void launch_gemm(uint32_t dt, Epilogue epi, const void* A, const void* W, int M,
 // Heads first but where few sequences are cut into chunks, and as far as y goes (65535); x takes any number.  A layer of 16 query
 // and 4 kv heads, contexts of 500..4000 keys, rows first / heads first: 4 sequences 41.3 / 44.0 us, 16 54.0 / 57.2, 32 80.3 / 82.0,
 // 48 95.1 / 88.1; 8 kv heads, 16 sequences 69.6 / 70.4, 40 121.2 / 109.6.  16 heads, 4 sequences of 1000 keys: 39.0 / 40.9.
+// fp32, 2 kv heads, 48 sequences of 200..1500 keys: 58.3 / 54.9 us the kernel.
+constexpr int ROWS_FIRST_ROWS = 32;
 constexpr long ROWS_FIRST_PAIRS = 128;
 AttnGrid attn_decode_grid(int rows, int hkv, int nchunk) {
-  const bool heads_first = (nchunk == 1 || (long)rows * hkv > ROWS_FIRST_PAIRS) && rows <= 65535;
+  const bool heads_first = (nchunk == 1 || rows > ROWS_FIRST_ROWS || (long)rows * hkv > ROWS_FIRST_PAIRS) && rows <= 65535;
   return heads_first ? AttnGrid{(unsigned)hkv, (unsigned)rows, (unsigned)nchunk, 1} : AttnGrid{(unsigned)rows, (unsigned)hkv, (unsigned)nchunk, 0};
 }
 

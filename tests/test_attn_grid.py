@@ -22,7 +22,8 @@ def test_sizes(rows, hkv):
         assert y <= 65535 and z <= 65535
 
 
-@pytest.mark.parametrize("rows", [1, 4, 16, 17, 64, 100])
+@pytest.mark.parametrize("rows", [1, 4, 16, 17, 32, 33, 64, 100])
 def test_heads_go_round_the_xcds_but_for_few_sequences_in_chunks(rows):
     assert grid(rows, 8, 1)[3] == 1
     assert grid(rows, 8, 2)[3] == grid(rows, 8, 16)[3] == (0 if rows <= 16 else 1)
+    assert grid(rows, 2, 4)[3] == (0 if rows <= 32 else 1)
