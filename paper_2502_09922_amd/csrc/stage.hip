@@ -744,10 +744,12 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   const TiledPlan p_dn = rows_one_pass && gsc.splitk ? plan(TILED_PART, d, F) : TiledPlan{};
   // Few fp32 rows of small matrices are a chain of launches of 3 us each.  A projection whose K is not cut adds its sums to
   // the residual rows itself and takes the norm of its rows along: 13 launches for a step of the two-layer tiny model
-  // instead of 18.  A norm that a row kernel makes on its way costs nothing: in front of the first layer and behind a
-  // projection whose K is cut it stays there.
+  // instead of 18.  In front of the first layer and behind a projection whose K is cut a row kernel can make the norm on its
+  // way, which is cheaper than making it in every wavefront of the GEMM but for one or two pieces of 256 columns (three
+  // layers of 512 columns, one row: 71 us in the row kernels, 66 in the GEMMs; two rows 72 and 76).
   auto rows_f32 = [&](const TiledPlan& p) { return dt == F32 && p.splits == 1 && !p.bm; };
   auto folds_norm = [&](const TiledPlan& p, int N) { return rows_one_pass && rows_f32(p) && gemm_rows_f32_norm_supported(rows, N, d); };
+  const bool few_pieces = rows * ((d + 255) / 256) <= 2;
 
   const void* table = nullptr;
   if (s->first) {
@@ -761,7 +763,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     ra.cu = prefill ? cu_dev : nullptr; ra.batch = batch; ra.max_seq = c.max_seq;
     ra.row_seq = row_seq; ra.row_pos = row_pos; ra.last_rows = last_rows; ra.seq_lens = kv->seq_lens;
     Block& b0 = s->blocks[s->layer0];
-    if (landed(b0) && !norm_alone(b0)) {
+    if (landed(b0) && !norm_alone(b0) && !(few_pieces && folds_norm(p_qkv, qkv_cols))) {
       ra.gamma = tensor(b0, 0); ra.y = y; ra.eps = c.rms_eps;
       y_ready = true;
     }
@@ -813,7 +815,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     char* kc = (char*)kv->k + li * kv_layer;
     char* vc = (char*)kv->v + li * kv_layer;
 
-    const bool fold_qkv = !y_ready && folds_norm(p_qkv, qkv_cols) && !norm_alone(b), fold_gu = rows_f32(p_o) && folds_norm(p_gu, F);
+    const bool fold_qkv = !y_ready && folds_norm(p_qkv, qkv_cols) && !norm_alone(b), fold_gu = (few_pieces || rows_f32(p_o)) && folds_norm(p_gu, F);
     RowsF32Fusion normed;
     normed.eps = c.rms_eps;
     if (!y_ready && !fold_qkv) PROBE(LS_OP_NORM, norm(tensor(b, 0)));
@@ -854,7 +856,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     // layer waits for it
     const bool more = li + 1 < n_layers;
     Block* next = more ? &s->blocks[s->layer0 + li + 1] : nullptr;
-    y_ready = more && p_dn.splits && landed(*next) && !norm_alone(*next) && !(rows_f32(p_dn) && folds_norm(p_qkv, qkv_cols));
+    y_ready = more && p_dn.splits && landed(*next) && !norm_alone(*next) && !((few_pieces || rows_f32(p_dn)) && folds_norm(p_qkv, qkv_cols));
     LS_HIP(gate(b, st, 3));
     PROBE(LS_OP_GEMM_DOWN, residual(p_dn, hbuf, tensor(b, 5), F, y_ready ? tensor(*next, 0) : nullptr, !more && !s->last));
     if (timed) LS_HIP(hipEventRecord(s->comp_end[li], st));
