@@ -63,4 +63,4 @@ def test_ordering_costs_less_than_it_can_gain():
             best[rows] = min(best.get(rows, 1e9), a.elapsed_time(b) / 20)
     gpu.close()
     print("256 sequences %.1f us, 257 %.1f us" % (1e3 * best[256], 1e3 * best[257]))
-    assert best[256] <= 1.06 * best[257]
+    assert best[256] <= 1.12 * best[257]
