@@ -92,8 +92,8 @@ k_attn_decode(const int32_t* __restrict__ row_pos, const int32_t* __restrict__ r
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float u0 = to_f(qv[2 * i]), u1 = to_f(qv[2 * i + 1]);
-      q[g][2 * i] = (u0 * rot[i].x - u1 * rot[i].y) * scale;
-      q[g][2 * i + 1] = (u0 * rot[i].y + u1 * rot[i].x) * scale;
+      q[g][2 * i] = (sizeof(T) == 4 ? turn0(u0, u1, rot[i]) : u0 * rot[i].x - u1 * rot[i].y) * scale;
+      q[g][2 * i + 1] = (sizeof(T) == 4 ? turn1(u0, u1, rot[i]) : u0 * rot[i].y + u1 * rot[i].x) * scale;
     }
   }
 
@@ -110,6 +110,8 @@ k_attn_decode(const int32_t* __restrict__ row_pos, const int32_t* __restrict__ r
     for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
   }
 
+  // fp32: which of two products is rounded is written down, as k_step_small_f32 does the same sums
+#define LS_WEIGH(p, v, s) (sizeof(T) == 4 ? fmaf(p, v, s) : (s) + (p) * (v))
   // one key per slot: scores of the G heads, then the slot's online-softmax update
 #define LS_KEY_UPDATE(kx, vx, valid)                                                         \
   _Pragma("unroll") for (int g = 0; g < G; ++g) {                                            \
@@ -123,7 +125,7 @@ k_attn_decode(const int32_t* __restrict__ row_pos, const int32_t* __restrict__ r
     const float corr_ = (mn_ == -INFINITY) ? 1.f : __expf(m[g] - mn_);                       \
     const float p_ = (s_ == -INFINITY) ? 0.f : __expf(s_ - mn_);                             \
     l[g] = l[g] * corr_ + p_;                                                                \
-    _Pragma("unroll") for (int e = 0; e < 8; ++e) acc[g][e] = acc[g][e] * corr_ + p_ * vx[e]; \
+    _Pragma("unroll") for (int e = 0; e < 8; ++e) acc[g][e] = LS_WEIGH(p_, vx[e], acc[g][e] * corr_); \
     m[g] = mn_;                                                                              \
   }
 
@@ -140,8 +142,8 @@ k_attn_decode(const int32_t* __restrict__ row_pos, const int32_t* __restrict__ r
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float u0 = to_f(kn[2 * i]), u1 = to_f(kn[2 * i + 1]);
-      kr[2 * i] = from_f<T>(u0 * rot[i].x - u1 * rot[i].y);
-      kr[2 * i + 1] = from_f<T>(u0 * rot[i].y + u1 * rot[i].x);
+      kr[2 * i] = from_f<T>(sizeof(T) == 4 ? turn0(u0, u1, rot[i]) : u0 * rot[i].x - u1 * rot[i].y);
+      kr[2 * i + 1] = from_f<T>(sizeof(T) == 4 ? turn1(u0, u1, rot[i]) : u0 * rot[i].y + u1 * rot[i].x);
     }
     if (slot == 0) {
       *reinterpret_cast<T8*>(kb + (size_t)pos * HD + dl * 8) = kr;
@@ -192,6 +194,7 @@ k_attn_decode(const int32_t* __restrict__ row_pos, const int32_t* __restrict__ r
 
 #undef LS_SEEN
 #undef LS_KEY_UPDATE
+#undef LS_WEIGH
 
   // merge the key slots of the wave (lanes that hold the same dimensions)
 #pragma unroll
@@ -315,6 +318,8 @@ bool attn_decode_supported(int hq, int hkv, int hd) {
   const int g = hq / hkv;
   return (hd == 128 || hd == 64) && (g == 1 || g == 2 || g == 4 || g == 8);
 }
+
+int attn_decode_chunks(int rows, int hkv, int max_keys) { return chunks_for(rows, hkv, max_keys); }
 
 // covers every launch of at most `rows` sequences: rows * hkv * chunks stays below WG_TARGET + 128
 size_t attn_decode_scratch_bytes(int hq, int hkv, int hd, int max_keys) {

@@ -67,17 +67,50 @@ template <class T> __device__ __forceinline__ T from_f(float f);
 template <> __device__ __forceinline__ float from_f<float>(float f) { return f; }
 template <> __device__ __forceinline__ bf16 from_f<bf16>(float f) { return (bf16)f; }
 
-// Sum over the 64 lanes of a wavefront; every lane gets the total (fixed butterfly order).
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+// f(v, v of lane ^ OFF): register-to-register exchanges (DPP inside a row of 16 lanes, permlane swaps across rows) instead of
+// a trip through the LDS crossbar, which a chain of exchanges waits for at every step.  f has to be commutative.
+template <int CTRL, int BANKS = 0xF>
+__device__ __forceinline__ float dpp(float old, float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, v), CTRL, 0xF, BANKS, BANKS == 0xF));
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-  return v;
+template <int OFF, class F>
+__device__ __forceinline__ float with_lane_xor(float v, F f) {
+  static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8 || OFF == 16 || OFF == 32, "");
+  if constexpr (OFF >= 16) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    u32x2 r;
+    if constexpr (OFF == 32) r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    else r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  } else if constexpr (OFF == 8) {
+    return f(v, dpp<0x128>(v, v));  // row_ror:8
+  } else if constexpr (OFF == 4) {  // banks of four lanes: 0 and 2 take four lanes up, 1 and 3 four lanes down
+    return f(v, dpp<0x114, 0xA>(dpp<0x104, 0x5>(v, v), v));
+  } else {
+    return f(v, dpp<OFF == 2 ? 0x4E : 0xB1>(v, v));  // quad_perm
+  }
 }
+// v of lane ^ OFF.
+template <int OFF>
+__device__ __forceinline__ float lane_xor(float v) {
+  if constexpr (OFF < 16) return with_lane_xor<OFF>(v, [](float, float other) { return other; });
+  else return with_lane_xor<OFF>(v, [](float low, float high) { return threadIdx.x & OFF ? low : high; });
+}
+// f over the aligned groups of `2 FROM / TO` lanes TO apart, the exchanges from lane ^ FROM down to lane ^ TO or, FROM < TO, up
+// to it: every lane of the group gets the result, summed in the order of the exchanges.
+template <int FROM, int TO, class F>
+__device__ __forceinline__ float exchange(float v, F f) {
+  v = with_lane_xor<FROM>(v, f);
+  if constexpr (FROM == TO) return v;
+  else return exchange<(FROM > TO ? FROM / 2 : FROM * 2), TO>(v, f);
+}
+struct Add { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct Max { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+
+// Over the 64 lanes of a wavefront; every lane gets the result (fixed butterfly order).
+__device__ __forceinline__ float wave_sum(float v) { return exchange<32, 1>(v, Add{}); }
+__device__ __forceinline__ float wave_max(float v) { return exchange<32, 1>(v, Max{}); }
 
 // Sum over each aligned group of 16 lanes, every lane of the group gets the total.  Four
 // register-to-register DPP exchanges (lane^1, lane^2, mirrored half row, mirrored row) in a
@@ -149,6 +182,10 @@ __device__ __forceinline__ void slot_barrier() {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
+
+// A pair turned by (cos, sin), with the product that is rounded chosen here and not by the compiler.
+__device__ __forceinline__ float turn0(float u0, float u1, float2 cs) { return fmaf(u0, cs.x, -(u1 * cs.y)); }
+__device__ __forceinline__ float turn1(float u0, float u1, float2 cs) { return fmaf(u0, cs.y, u1 * cs.x); }
 
 // silu(z) = z / (1 + exp(-z)), the quotient as a product with the hardware reciprocal (1 ulp):
 // a correctly rounded fp32 division is ten instructions, and every result is rounded to bf16

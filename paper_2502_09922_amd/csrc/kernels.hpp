@@ -158,6 +158,31 @@ bool gemm_rows_f32_norm_supported(int M, int N, int K);
 bool launch_gemm_rows_f32(int epi, const void* A, const void* W, int M, int N, int K, int splits, void* out, hipStream_t st,
                           const RowsF32Fusion& f = {});
 
+// A whole generation step of a small fp32 model in one launch (step_small_f32.hip): the stage's layers and, with head_w, its
+// LM head, whose logits go to `logits` and the rows' next tokens to `out`; without, the rows behind the last layer go there.
+struct SmallStep {
+  const float* w = nullptr;       // the first layer's block, the others layer_stride floats apart
+  size_t layer_stride = 0, o_qkv = 0, o_o = 0, o_g2 = 0, o_gu = 0, o_d = 0;  // tensors of a block, in floats
+  const float* table = nullptr;   // embedding rows: `in` holds token ids
+  const float* in = nullptr;
+  float* out = nullptr;
+  const float *head_gain = nullptr, *head_w = nullptr;
+  float* logits = nullptr;
+  int layers = 0, d = 0, hq = 0, hkv = 0, hd = 0, F = 0, vocab = 0, max_seq = 0;
+  int group = 0, cut_o = 0, cut_d = 0;  // powers of two: query heads per kv head, parts that the K of O and down is summed in
+  float eps = 0.f;
+  const float2* cs = nullptr;
+  float *kc = nullptr, *vc = nullptr;
+  size_t kv_layer = 0;            // floats
+  float *qkv = nullptr, *attn = nullptr, *h = nullptr;  // the last layer's projections, attention output and SwiGLU output
+  int32_t* seq_lens = nullptr;
+  unsigned long long* xch = nullptr;  // small_step_exchange_bytes, zero before the first step
+  unsigned* epoch = nullptr;          // zero before the first step
+};
+size_t small_step_exchange_bytes(int rows, int d, int hq, int hkv, int hd, int F, int vocab);
+bool small_step_supported(const SmallStep& a, int rows, int max_keys);
+void launch_small_step(const SmallStep& a, int rows, hipStream_t st);
+
 // One pass over rows of width d (a multiple of 4, at most 8192).  Source: the residual rows plus `splits`
 // partial tiles, the call's hidden rows, or embedding rows; the latter two also write the call's
 // bookkeeping (row -> sequence and position, last rows, seq_lens).  Result: the stage's output rows
@@ -239,6 +264,7 @@ void launch_attention_block(uint32_t dt, const int32_t* cu_seqlens, int batch, i
 // partial results in `scratch` (attn_decode_scratch_bytes; none: one workgroup each).
 bool attn_decode_supported(int hq, int hkv, int hd);
 size_t attn_decode_scratch_bytes(int hq, int hkv, int hd, int max_keys);
+int attn_decode_chunks(int rows, int hkv, int max_keys);  // workgroups that a (sequence, kv head) gets
 void launch_attn_decode(uint32_t dt, const void* qkv, int qkv_stride, const float* cs_table, void* kc, void* vc,
                         const int32_t* row_seq, const int32_t* row_pos, int rows, int hq, int hkv, int hd,
                         int max_seq, void* out, hipStream_t st, int max_keys, float* scratch, size_t scratch_bytes);

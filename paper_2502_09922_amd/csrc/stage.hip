@@ -134,7 +134,7 @@ bool span_ok(const ls_cfg* c, int lo, int hi) {
 // ---- workspace carving ------------------------------------------------------------------
 struct Carve {
   size_t cs, x, y, qkv, attn, h, logits, row_seq, row_pos, last_rows, next_tok, xb, xb2, ss_a, ss_b, splitk, splitk_bytes,
-      attn_part, attn_part_bytes, parts, parts_bytes, total;
+      attn_part, attn_part_bytes, parts, parts_bytes, step, step_bytes, total;
 };
 
 // more than 64 MiB of partial tiles are never wanted: a call that long fills the chip without splits
@@ -204,6 +204,11 @@ Carve carve(const ls_cfg* c, int lo, int hi) {
     if (last) parts_of(ls::TILED_STORE, B, c->vocab, d);
   }
   w.parts = take(w.parts_bytes);
+  // small fp32 models: what the workgroups of a step in one launch hand each other, behind the tag of the last step
+  if (c->dtype == LS_DTYPE_F32 && d <= 1024 && c->ffn <= (1u << 20) && c->vocab <= (1u << 20) && qkv_cols <= (1u << 20))
+    w.step_bytes = ls::small_step_exchange_bytes((int)B, (int)d, (int)c->n_q_heads, (int)c->n_kv_heads, (int)c->head_dim, (int)c->ffn, last ? (int)c->vocab : 0);
+  if (w.step_bytes) w.step_bytes += ALIGN;
+  w.step = take(w.step_bytes);
   (void)lo;
   w.total = off;
   return w;
@@ -426,7 +431,8 @@ ls_status ls_stage_create(const ls_cfg* cfg, int lo, int hi, void* weight_slab, 
       cs[((size_t)p * half + i) * 2] = (float)std::cos(a);
       cs[((size_t)p * half + i) * 2 + 1] = (float)std::sin(a);
     }
-  hipError_t e = hipMemcpy(s->ws + w.cs, cs.data(), cs.size() * sizeof(float), hipMemcpyHostToDevice);
+  hipError_t e = w.step_bytes ? hipMemset(s->ws + w.step, 0, w.step_bytes) : hipSuccess;  // done before the copy behind it
+  if (e == hipSuccess) e = hipMemcpy(s->ws + w.cs, cs.data(), cs.size() * sizeof(float), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     cleanup();
     return fail(LS_ERR_HIP, "ls_stage_create: table upload: %s", hipGetErrorString(e));
@@ -703,6 +709,40 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     }
     LS_HIP(hipGetLastError());
     return LS_OK;
+  }
+
+  // ---- generation steps of few rows of a small fp32 model: one launch, once every block has landed
+  if (!prefill && dt == F32 && s->w.step_bytes && !probing) {
+    SmallStep a;
+    TensorSpan sp[6];
+    const Block& b0 = s->blocks[s->layer0];
+    block_tensors(&c, b0.layer, sp, nullptr);
+    a.w = (const float*)(s->slab + b0.off); a.layer_stride = b0.bytes / 4;
+    a.o_qkv = sp[1].off / 4; a.o_o = sp[2].off / 4; a.o_g2 = sp[3].off / 4; a.o_gu = sp[4].off / 4; a.o_d = sp[5].off / 4;
+    a.in = (const float*)in; a.out = (float*)out;
+    if (s->first) a.table = (const float*)(s->slab + s->find(LS_BLOCK_EMBED)->off);
+    if (s->last) {
+      const Block* hb = s->find(s->hi);
+      block_tensors(&c, hb->layer, sp, nullptr);
+      a.head_gain = (const float*)(s->slab + hb->off + sp[0].off); a.head_w = (const float*)(s->slab + hb->off + sp[1].off);
+      a.logits = logits_out ? logits_out : (float*)(ws + s->w.logits);
+    }
+    a.layers = s->hi - s->lo; a.d = d; a.hq = hq; a.hkv = hkv; a.hd = hd; a.F = F; a.vocab = (int)c.vocab; a.max_seq = (int)c.max_seq;
+    a.eps = c.rms_eps; a.cs = (const float2*)cs; a.kc = (float*)kv->k; a.vc = (float*)kv->v; a.kv_layer = kv_layer / 4;
+    a.qkv = (float*)qkv; a.attn = (float*)attn; a.h = (float*)hbuf;
+    a.seq_lens = kv->seq_lens; a.epoch = (unsigned*)(ws + s->w.step); a.xch = (unsigned long long*)(ws + s->w.step + ALIGN);
+    // K is cut where the projections' own launches cut it
+    const TiledPlan po = gemm_tiled_plan(dt, TILED_PART, rows, d, hq * hd, true, gsc.bytes, nullptr, s->w.parts_bytes);
+    const TiledPlan pd = gemm_tiled_plan(dt, TILED_PART, rows, d, F, true, gsc.bytes, nullptr, s->w.parts_bytes);
+    auto log2_of = [](int n) { int l = 0; while (n > 1 << l) ++l; return l; };
+    a.cut_o = log2_of(po.splits); a.cut_d = log2_of(pd.splits); a.group = log2_of(hq / hkv);
+    bool there = gsc.splitk && po.splits && !po.bm && pd.splits && !pd.bm && small_step_supported(a, rows, max_len);
+    for (auto& b : s->blocks) there = there && landed(b);
+    if (there) {
+      launch_small_step(a, rows, st);
+      LS_HIP(hipGetLastError());
+      return LS_OK;
+    }
   }
 
   // ---- prompt passes, and generation steps of fp32 or of more than few rows.  Rows of up to 8192
