@@ -3,7 +3,7 @@
 // One 256-thread workgroup handles 128 consecutive query rows of one (sequence, query head);
 // each of its 4 wavefronts owns 32 rows and keeps them, the running maximum, the running sum
 // and the output accumulator in registers while the workgroup walks the keys 0..last row in
-// tiles of 64, double-buffered in LDS.  Both products are computed transposed so that all
+// tiles of 64 or 32, double-buffered in LDS.  Both products are computed transposed so that all
 // per-row softmax state is per-lane:
 //   S^T[key][q] = K[key][:] . Q[q][:]      MFMA A = K tile rows,  B = Q rows (registers)
 //   O^T[d][q]  += V^T[d][key] . P^T[key][q] MFMA A = V^T,          B = P^T
@@ -24,9 +24,15 @@
 // K operand read (one 16-byte chunk per row) and the 4 rows x 32 bytes of a transposing read.
 //
 // A wavefront whose 32 rows all lie above a key tile skips that tile's arithmetic (it still
-// takes part in the fills and barriers); the output rescale is skipped when no row's running
-// maximum moved.  Keys beyond a row's position get a score of -inf before the exponential;
+// takes part in the fills and barriers); the output rescale is skipped while no row's running
+// maximum has moved far.  Keys beyond a row's position get a score of -inf before the exponential;
 // cache rows at or beyond the sequence length are never read (indices are clamped).
+//
+// Measured, 32 x 40 heads x 1024^2 / six prompts of up to 2048 rows on 64 heads: 680 / 278 us with fills by the compiler's
+// builtin, which had the next tile's arrive before this one's values were read, and a rescale whenever a maximum moved;
+// 630 / 256 with tiles of 64 keys now, 572 / 242 with 32.  A tile of 64 takes a CU 3000 cycles: matrix instructions 0.33 of
+// them, other vector instructions 0.38 (a quarter fewer of those, by fills without address arithmetic and two tiles a
+// loop, gained nothing by themselves), one after the other in a wavefront that then waits for LDS and for the ones beside it.
 #include "kernels.hpp"
 #include "device_util.hpp"
 
@@ -34,10 +40,16 @@ namespace ls {
 
 namespace {
 
-constexpr int BQ = 128, BKV = 64;
+constexpr int BQ = 128;
+// More workgroups than two a CU take tiles of 32 keys, of which a CU holds three: half the sums and exchanges to a barrier, but
+// three wavefronts on a SIMD that fill each other's waits.  head_dim 128, tiles of 64 / 32 keys: 32 x 40 heads x 1024^2 637 / 572 us,
+// 640 workgroups (5 prompts of 512, 32 heads) 36.3 / 31.5, 1024 (2 of 2048) 114.6 / 106.8, 512 (4 of 512, 1 of 2048) 26.1 / 25.7 and
+// 66.9 / 69.2, 256 (1 of 1024) 28.5 / 31.4.  head_dim 64 fits more workgroups either way: 2 of 2048 70.9 / 75.1.
+constexpr unsigned RESIDENT = 512;
 
-template <int HD>
-__global__ void __launch_bounds__(256, 2)
+// BKV: keys of a tile.  64, or 32 for three workgroups on a CU instead of two.
+template <int HD, int BKV>
+__global__ void __launch_bounds__(256, BKV == 32 ? 3 : 2)
 k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batch, const bf16* __restrict__ qkv, int qkv_stride,
                int max_seq, const bf16* __restrict__ kc, const bf16* __restrict__ vc, bf16* __restrict__ out) {
   constexpr int ROWB = HD * 2;            // bytes per K / V row
@@ -48,7 +60,12 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
   constexpr int DT = HD / 32;             // 32-row tiles of O^T
   constexpr int KS = HD / 16;             // k-steps of the score product
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2][2 * TILE];
-  typedef __attribute__((address_space(3))) void lds_void;
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  // Fills are written in assembly: of the builtin the compiler knows that it writes LDS but not where, and has the next
+  // tile's arrive before it reads this one's values.  The waits for them are LS_TILE_BARRIER's.
+  auto fill = [](const bf16* base, unsigned off, unsigned to) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory");
+  };
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
@@ -109,15 +126,28 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
   // ---- fills: wavefront w brings rows (w*FI + i)*RPI .. +RPI-1 of both tiles; the lane that
   // fills physical chunk p of row r fetches logical chunk p ^ swz(r)
   const int frow = lane / CPR, fchunk = lane % CPR;
-#define LS_FILL(buf, t0)                                                                          \
-  _Pragma("unroll") for (int i_ = 0; i_ < FI; ++i_) {                                             \
-    const int r_ = (wave * FI + i_) * RPI + frow;                                                 \
-    const size_t g_ = (size_t)min((t0) + r_, len - 1) * HD + ((fchunk ^ swz(r_)) << 3);            \
-    __builtin_amdgcn_global_load_lds((const void*)(kb + g_),                                      \
-        (lds_void*)(smem[buf] + (wave * FI + i_) * 1024), 16, 0, 0);                              \
-    __builtin_amdgcn_global_load_lds((const void*)(vb + g_),                                      \
-        (lds_void*)(smem[buf] + TILE + (wave * FI + i_) * 1024), 16, 0, 0);                       \
+  // byte offsets of a whole tile's rows from its first one; the last tile of the sequence may end before
+  unsigned foff[FI];
+#pragma unroll
+  for (int i = 0; i < FI; ++i) {
+    const int r = (wave * FI + i) * RPI + frow;
+    foff[i] = (unsigned)(r * HD + ((fchunk ^ swz(r)) << 3)) * 2;
   }
+  auto fill_tile = [&](int buf, int t0) {
+    const bf16 *kt = kb + (size_t)t0 * HD, *vt = vb + (size_t)t0 * HD;
+    const unsigned to = lds0 + buf * (2 * TILE) + wave * (FI * 1024);
+    const int have = len - t0;
+#pragma unroll
+    for (int i = 0; i < FI; ++i) {
+      unsigned off = foff[i];
+      if (have < BKV) {
+        const int r = (wave * FI + i) * RPI + frow;
+        off -= (unsigned)(r - min(r, have - 1)) * ROWB;
+      }
+      fill(kt, off, to + i * 1024);
+      fill(vt, off, to + TILE + i * 1024);
+    }
+  };
   // all fills this wavefront issued have landed, then the workgroup meets
 #define LS_TILE_BARRIER()                    \
   asm volatile("" ::: "memory");             \
@@ -138,29 +168,39 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
   const int v_col = 16 * (tg & 1) + 4 * (tj & 3);  // + 32 dt: first dim this lane addresses
   const int v_sub = (v_col & 7) * 2;              // byte offset inside its 16-byte chunk
 
-  LS_FILL(0, 0)
+  fill_tile(0, 0);
+  // the query's operands are in registers from here on: a wait for them inside the loop would be one for fills
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    u32x4 q = __builtin_bit_cast(u32x4, qf[ks]);
+    asm volatile("" : "+v"(q));
+    qf[ks] = __builtin_bit_cast(bf16x8, q);
+  }
   LS_TILE_BARRIER()
-  for (int t = 0; t < ntk; ++t) {
-    const int buf = t & 1;
+  auto tile = [&](int t, auto buf_) {
+    constexpr int buf = decltype(buf_)::value;
     const int t0 = t * BKV;
     // buffer buf^1 was last read in iteration t-1, which every wavefront has left
-    if (t + 1 < ntk) LS_FILL(buf ^ 1, t0 + BKV)
+    if (t + 1 < ntk) fill_tile(buf ^ 1, t0 + BKV);
     const unsigned char* ks_ = smem[buf];
     const unsigned char* vs_ = smem[buf] + TILE;
 
     if (t0 <= wave_last) {  // wave-uniform: some row of this wavefront sees some key of the tile
-      // ---- S^T = K Q^T for the 64 keys of the tile (two 32-key row tiles)
-      f32x16 s[2];
+      __builtin_amdgcn_s_setprio(1);
+      // ---- S^T = K Q^T for the keys of the tile (32-key row tiles)
+      f32x16 s[BKV / 32];
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
+      for (int kt = 0; kt < BKV / 32; ++kt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[kt][i] = 0.f;
 #pragma unroll
-        for (int ksn = 0; ksn < KS; ++ksn) {
+      for (int ksn = 0; ksn < KS; ++ksn)
+#pragma unroll
+        for (int kt = 0; kt < BKV / 32; ++kt) {
           const bf16x8 kf = *reinterpret_cast<const bf16x8*>(ks_ + kt * 32 * ROWB + k_row + (((ksn * 2 + lh) ^ ksw) << 4));
           s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ksn], s[kt], 0, 0, 0);
         }
-      }
+      __builtin_amdgcn_s_setprio(0);
       // ---- causal mask, online softmax (all for this lane's query row).  Scores stay unscaled:
       // the running maximum is kept in score units and the scale (with the change to base 2)
       // is folded into the exponential's argument, p = 2^(c s - c m).
@@ -169,7 +209,7 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
       float mx = -INFINITY;
       if (diag) {
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
+        for (int kt = 0; kt < BKV / 32; ++kt)
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             const int key = t0 + kt * 32 + 8 * (i >> 2) + 4 * lh + (i & 3);
@@ -179,37 +219,40 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
           }
       } else {
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
+        for (int kt = 0; kt < BKV / 32; ++kt)
 #pragma unroll
           for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kt][i]);
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      mx = with_lane_xor<32>(mx, Max{});
+      // A row's sums and outputs are rescaled only where its largest probability would exceed 2^8: floating point does
+      // not mind the factor, and in a short context some row's maximum moves in almost every tile.
       const float m_new = fmaxf(m_run, mx);  // finite from the first tile on: key 0 is visible
-      const float mc = m_new * c;
-      float psum = 0.f;
-      bf16x8 pf[4];
+      const float m_up = (m_new - m_run) * c > 8.f ? m_new : m_run;
+      if (__builtin_amdgcn_ballot_w64(m_up > m_run) != 0) {
+        const float corr = __builtin_amdgcn_exp2f((m_run - m_up) * c);
+        l_run *= corr;
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[dt][i] *= corr;
+        m_run = m_up;
+      }
+      const float mc = m_run * c;
+      float psum = 0.f;
+      bf16x8 pf[BKV / 16];
+#pragma unroll
+      for (int kt = 0; kt < BKV / 32; ++kt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const float p = __builtin_amdgcn_exp2f(fmaf(s[kt][i], c, -mc));
           psum += p;
           pf[kt * 2 + (i >> 3)][i & 7] = (bf16)p;
         }
-      // the running maximum moved for some row of the wavefront: rescale sums and outputs
-      if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-        const float corr = __builtin_amdgcn_exp2f((m_run - m_new) * c);
-        l_run *= corr;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) o[dt][i] *= corr;
-        m_run = m_new;
-      }
       l_run += psum;
+      __builtin_amdgcn_s_setprio(1);
       // ---- O^T += V^T P^T; the V^T operand comes out of two transposing reads
 #pragma unroll
-      for (int kp = 0; kp < 4; ++kp) {  // 16-key steps
+      for (int kp = 0; kp < BKV / 16; ++kp) {  // 16-key steps
         const int key0 = 16 * kp + v_key, key1 = key0 + 8;
         const int sw0 = swz(key0), sw1 = swz(key1);
 #pragma unroll
@@ -224,10 +267,16 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
           o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf[kp], o[dt], 0, 0, 0);
         }
       }
+      __builtin_amdgcn_s_setprio(0);
     }
     LS_TILE_BARRIER()
+  };
+  const std::integral_constant<int, 0> even{};
+  const std::integral_constant<int, 1> odd{};
+  for (int t = 0; t < ntk; t += 2) {
+    tile(t, even);
+    if (t + 1 < ntk) tile(t + 1, odd);
   }
-#undef LS_FILL
 #undef LS_TILE_BARRIER
 
   // ---- normalise and store this lane's query row
@@ -255,13 +304,14 @@ void launch_attn_prefill(const void* qkv, int qkv_stride, const void* kc, const 
                          int batch, int max_len, int hq, int hkv, int hd, int max_seq, void* out, hipStream_t st) {
   if (batch <= 0 || max_len <= 0) return;
   const int nq = (max_len + BQ - 1) / BQ;
-  dim3 grid((unsigned)nq * hq * batch);
-  if (hd == 128)
-    k_attn_prefill<128><<<grid, 256, 0, st>>>(cu_seqlens, hq, hkv, nq, batch, (const bf16*)qkv, qkv_stride, max_seq,
-                                              (const bf16*)kc, (const bf16*)vc, (bf16*)out);
-  else
-    k_attn_prefill<64><<<grid, 256, 0, st>>>(cu_seqlens, hq, hkv, nq, batch, (const bf16*)qkv, qkv_stride, max_seq,
-                                              (const bf16*)kc, (const bf16*)vc, (bf16*)out);
+  const dim3 grid((unsigned)nq * hq * batch);
+#define LS_ATTN(hd_, bkv_)                                                                                             \
+  k_attn_prefill<hd_, bkv_><<<grid, 256, 0, st>>>(cu_seqlens, hq, hkv, nq, batch, (const bf16*)qkv, qkv_stride, max_seq, \
+                                                  (const bf16*)kc, (const bf16*)vc, (bf16*)out)
+  if (hd == 64) LS_ATTN(64, 64);
+  else if (grid.x > RESIDENT) LS_ATTN(128, 32);
+  else LS_ATTN(128, 64);
+#undef LS_ATTN
 }
 
 }  // namespace ls
