@@ -97,6 +97,9 @@ struct RopeAppend {
 // out[M,N] = bf16(resid + A W^T), the stage's output rows; `resid` is not changed.
 bool gemm_mfma_resid_out_supported(int M, int N, int K, const void* out);
 void launch_gemm_mfma_resid_out(const void* A, const void* W, int M, int N, int K, const float* resid, void* out, hipStream_t st);
+// resid = in + A W^T with `in` in bf16: the first residual add of a stage that is given hidden rows
+bool gemm_mfma_resid_in_supported(int M, int N, int K, const void* in);
+void launch_gemm_mfma_resid_in(const void* A, const void* W, int M, int N, int K, const void* in, float* resid, hipStream_t st);
 bool gemm_mfma_rope_supported(int M, int N, int K, int hq, int hkv, int hd);
 void launch_gemm_mfma_rope(const void* A, const void* W, int M, int N, int K, void* out, const RopeAppend& rope,
                            hipStream_t st);
