@@ -11,7 +11,7 @@
 //
 // Sixteen: with 32 workgroups a step takes 23.5 us, with 16 of them 27.3, but all of a launch have to be on the chip together.
 // A CU holds two (512 threads, at most 128 registers, at most 64 KB of LDS), the chip 512, which is 32 such launches at once,
-// more than the device runs hardware queues; what else runs there ends by itself.  A poll is bounded all the same (POLLS, many
+// more than the device has hardware queues (24); what else runs there ends by itself.  A poll is bounded all the same (POLLS, many
 // seconds): a value that has not come by then reads as NaN.
 //
 // Who writes a place again.  Every phase has places of its own, written again a layer later.  Every workgroup has columns of
