@@ -224,13 +224,15 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
           for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kt][i]);
       }
       mx = with_lane_xor<32>(mx, Max{});
-      const float m_new = fmaxf(m_run, mx);  // finite from the first tile on: key 0 is visible
+      // key 0 is visible, but its score and others may have overflowed to -inf: such keys count nothing, as if the row's
+      // maximum were in the same tile
+      const float m_new = fmaxf(m_run, mx), m_ref = m_new == -INFINITY ? 0.f : m_new;
       // The running maximum moved for some row of the wavefront: rescale sums and outputs.  At once, and not only when it has
       // moved far: a row's largest probability is 1 and loses nothing in bf16.  With maxima up to 2^8 behind (a factor that
       // published kernels allow) 32 x 40 heads x 1024^2 took 572 us instead of 595, but the error against float64 grew from
       // 1.82e-3 to 2.08e-3, from 1.43e-3 to 1.63e-3 where the softmax is sharp.
       if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-        const float corr = __builtin_amdgcn_exp2f((m_run - m_new) * c);
+        const float corr = __builtin_amdgcn_exp2f((m_run - m_ref) * c);
         l_run *= corr;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
@@ -238,7 +240,7 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
           for (int i = 0; i < 16; ++i) o[dt][i] *= corr;
         m_run = m_new;
       }
-      const float mc = m_run * c;
+      const float mc = m_ref * c;
       float psum = 0.f;
       bf16x8 pf[BKV / 16];
 #pragma unroll

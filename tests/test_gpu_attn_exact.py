@@ -66,3 +66,41 @@ def test_the_largest_probability_is_exact(hq, hkv, hd, lengths):
     assert seen > 100  # rows that are nothing but their largest probability
     torch.cuda.synchronize()
     st.close()
+
+
+@pytest.mark.parametrize("hq,hkv,lengths", [(32, 32, [100] * 20), (32, 8, [97, 40] * 24), (4, 4, [100, 200])])
+@pytest.mark.parametrize("first", [31, 32, 33, 64])
+def test_first_keys_whose_scores_overflow_count_nothing(hq, hkv, lengths, first):
+    """The first keys of a prompt score -inf in all later rows: a whole key tile of them, more and less."""
+    import torch
+
+    hd = 128
+
+    def fill(w):
+        # the slowest pair of each head, which positions hardly turn, multiplies column 0 (keys) and column 1 (queries); the
+        # rest knows neither
+        w.normal_(0, 0.05, generator=torch.Generator(device="cuda").manual_seed(7))
+        w[:, :2] = 0.0
+        qk = w[: (hq + hkv) * hd].view(-1, hd, 256)
+        qk[:, hd - 2 :] = 0.0
+        qk[:hq, hd - 2, 1] = 1e20
+        qk[hq:, hd - 2, 0] = -1e20
+
+    lengths = [max(n, first + 5) for n in lengths]
+    st = stage_of(hq, hkv, hd, lengths, fill)
+    x = torch.randn(sum(lengths), 256, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3)).bfloat16()
+    x[:, 0], x[:, 1] = 0.0, 1.0
+    row = 0
+    for n in lengths:
+        x[row : row + first, 0], x[row : row + first, 1] = 1.0, 0.0
+        row += n
+    for (got, s, v), n in zip(attention(st, hq, hkv, hd, x, lengths), lengths):
+        assert bool((s[:, first:, :first].masked_fill(s[:, first:, :first].isnan(), 0) < -1e38).all())
+        s[:, first:, :first] = float("-inf")
+        p = torch.softmax(s, -1)
+        want, size = torch.bmm(p, v), torch.bmm(p, v.abs())
+        # probabilities and results are rounded to 8 bits; scores, none beyond 100 here, carry the errors of sums of hd products
+        bound = 2.0**-7 * (want.abs() + size) + 2.0**-20 * hd * 100 * size
+        assert bool(((got - want).abs() <= bound).all())
+    torch.cuda.synchronize()
+    st.close()
