@@ -28,11 +28,12 @@
 // maximum moved.  Keys beyond a row's position get a score of -inf before the exponential;
 // cache rows at or beyond the sequence length are never read (indices are clamped).
 //
-// Measured, 32 x 40 heads x 1024^2 / six prompts of up to 2048 rows on 64 heads: 680 / 278 us with fills by the compiler's
-// builtin, which had the next tile's arrive before this one's values were read, and a rescale whenever a maximum moved;
-// 630 / 256 with tiles of 64 keys now, 572 / 242 with 32.  A tile of 64 takes a CU 3000 cycles: matrix instructions 0.33 of
-// them, other vector instructions 0.38 (a quarter fewer of those, by fills without address arithmetic and two tiles a
-// loop, gained nothing by themselves), one after the other in a wavefront that then waits for LDS and for the ones beside it.
+// Measured, 32 x 40 heads x 1024^2 / six prompts of up to 2048 rows on 64 heads: 610 / 240 us with fills by the compiler's
+// builtin, which had the next tile's arrive before this one's values were read; now 584 / 232 with tiles of 64 keys, 560 / 226
+// with 32 (0.61 PFLOP/s).  A tile of 64 takes a CU 3000 cycles: matrix instructions 0.33 of them, other vector instructions
+// 0.38, one after the other in a wavefront that then waits for LDS and for the ones beside it.  Matrix instructions before all
+// else (s_setprio) only with tiles of 32, where three wavefronts share a SIMD: on another card of the kind 592 us with, 690
+// without; tiles of 64 lose 3 to 8 % by it (512 rows on 32 heads 16.9 us with, 15.9 without).
 #include "kernels.hpp"
 #include "device_util.hpp"
 
@@ -41,11 +42,18 @@ namespace ls {
 namespace {
 
 constexpr int BQ = 128;
-// More workgroups than two a CU take tiles of 32 keys, of which a CU holds three: half the sums and exchanges to a barrier, but
-// three wavefronts on a SIMD that fill each other's waits.  head_dim 128, tiles of 64 / 32 keys: 32 x 40 heads x 1024^2 637 / 572 us,
-// 640 workgroups (5 prompts of 512, 32 heads) 36.3 / 31.5, 1024 (2 of 2048) 114.6 / 106.8, 512 (4 of 512, 1 of 2048) 26.1 / 25.7 and
-// 66.9 / 69.2, 256 (1 of 1024) 28.5 / 31.4.  head_dim 64 fits more workgroups either way: 2 of 2048 70.9 / 75.1.
-constexpr unsigned RESIDENT = 512;
+// Tiles of 32 keys, of which a CU holds three workgroups instead of two: half the sums and exchanges to a barrier, but three
+// wavefronts on a SIMD that fill each other's waits.  For head_dim 128, more workgroups than two a CU (rows and half a tile a
+// sequence; workgroups of the grid beyond a sequence's end leave at once), and a head of a sequence for each CU: fewer but longer
+// ones are all on the chip at once with 32 keys, and the CU that got three long ones ends last.  64 / 32 keys: 32 x 40 heads x
+// 1024^2 584 / 560 us, six prompts of up to 2048 rows on 64 heads 232 / 226, 16 of 384 rows on 16 heads 30.2 / 26.2; 40 heads, one
+// prompt of 2048 rows (640 workgroups) 72 / 97, 2 of 1024 46 / 54; 1 of 2048 on 32 heads 66 / 71; 2048 rows and 7 x 300 on 40
+// heads 94 / 103.  Over 156 batches on 8 to 64 heads the faster one of each would gain 0.8 % on this rule, 1.2 % on the grid's size.
+// head_dim 64 fits more workgroups either way: 2 of 2048 rows 70.9 / 75.1.
+bool short_key_tiles(int hq, int hd, int batch, int rows) {
+  constexpr int CUS = 256;
+  return hd == 128 && (long)hq * batch >= CUS && (long)hq * (rows + (long)batch * (BQ / 2)) > 2 * CUS * BQ;
+}
 
 // BKV: keys of a tile.  64, or 32 for three workgroups on a CU instead of two.
 template <int HD, int BKV>
@@ -186,7 +194,7 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
     const unsigned char* vs_ = smem[buf] + TILE;
 
     if (t0 <= wave_last) {  // wave-uniform: some row of this wavefront sees some key of the tile
-      __builtin_amdgcn_s_setprio(1);
+      if constexpr (BKV == 32) __builtin_amdgcn_s_setprio(1);
       // ---- S^T = K Q^T for the keys of the tile (32-key row tiles)
       f32x16 s[BKV / 32];
 #pragma unroll
@@ -200,7 +208,7 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
           const bf16x8 kf = *reinterpret_cast<const bf16x8*>(ks_ + kt * 32 * ROWB + k_row + (((ksn * 2 + lh) ^ ksw) << 4));
           s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ksn], s[kt], 0, 0, 0);
         }
-      __builtin_amdgcn_s_setprio(0);
+      if constexpr (BKV == 32) __builtin_amdgcn_s_setprio(0);
       // ---- causal mask, online softmax (all for this lane's query row).  Scores stay unscaled:
       // the running maximum is kept in score units and the scale (with the change to base 2)
       // is folded into the exponential's argument, p = 2^(c s - c m).
@@ -252,7 +260,7 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
           pf[kt * 2 + (i >> 3)][i & 7] = (bf16)p;
         }
       l_run += psum;
-      __builtin_amdgcn_s_setprio(1);
+      if constexpr (BKV == 32) __builtin_amdgcn_s_setprio(1);
       // ---- O^T += V^T P^T; the V^T operand comes out of two transposing reads
 #pragma unroll
       for (int kp = 0; kp < BKV / 16; ++kp) {  // 16-key steps
@@ -270,7 +278,7 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
           o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf[kp], o[dt], 0, 0, 0);
         }
       }
-      __builtin_amdgcn_s_setprio(0);
+      if constexpr (BKV == 32) __builtin_amdgcn_s_setprio(0);
     }
     LS_TILE_BARRIER()
   };
@@ -304,7 +312,7 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
 bool attn_prefill_supported(int hq, int hkv, int hd) { return (hd == 128 || hd == 64) && hq % hkv == 0; }
 
 void launch_attn_prefill(const void* qkv, int qkv_stride, const void* kc, const void* vc, const int32_t* cu_seqlens,
-                         int batch, int max_len, int hq, int hkv, int hd, int max_seq, void* out, hipStream_t st) {
+                         int batch, int rows, int max_len, int hq, int hkv, int hd, int max_seq, void* out, hipStream_t st) {
   if (batch <= 0 || max_len <= 0) return;
   const int nq = (max_len + BQ - 1) / BQ;
   const dim3 grid((unsigned)nq * hq * batch);
@@ -312,9 +320,12 @@ void launch_attn_prefill(const void* qkv, int qkv_stride, const void* kc, const 
   k_attn_prefill<hd_, bkv_><<<grid, 256, 0, st>>>(cu_seqlens, hq, hkv, nq, batch, (const bf16*)qkv, qkv_stride, max_seq, \
                                                   (const bf16*)kc, (const bf16*)vc, (bf16*)out)
   if (hd == 64) LS_ATTN(64, 64);
-  else if (grid.x > RESIDENT) LS_ATTN(128, 32);
+  else if (short_key_tiles(hq, hd, batch, rows)) LS_ATTN(128, 32);
   else LS_ATTN(128, 64);
 #undef LS_ATTN
 }
 
 }  // namespace ls
+
+// For the tests; not declared in ls_stage.h: keys of the tiles that a prompt pass walks.
+extern "C" int ls_test_attn_prefill_keys(int hq, int hd, int batch, int rows) { return ls::short_key_tiles(hq, hd, batch, rows) ? 32 : 64; }

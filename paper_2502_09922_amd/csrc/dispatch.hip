@@ -62,7 +62,7 @@ void launch_attention_block(uint32_t dt, const int32_t* cu_seqlens, int batch, i
   }
   if (!rope_done) launch_rope_append(dt, qkv, cs_table, row_seq, row_pos, rows, hq, hkv, hd, max_seq, kcache, vcache, st);
   if (dt == BF16 && !decode && attn_prefill_supported(hq, hkv, hd)) {
-    launch_attn_prefill(qkv, qkv_stride, kcache, vcache, cu_seqlens, batch, max_len, hq, hkv, hd, max_seq, out, st);
+    launch_attn_prefill(qkv, qkv_stride, kcache, vcache, cu_seqlens, batch, rows, max_len, hq, hkv, hd, max_seq, out, st);
     return;
   }
   if (dt == F32 && !decode && attn_prefill_f32_supported(hq, hkv, hd)) {

@@ -296,7 +296,7 @@ void launch_attn_decode_gqa(const void* qkv, int qkv_stride, const float* cs_tab
 // bf16 flash-style causal attention for the prompt pass; head_dim 64 or 128.
 bool attn_prefill_supported(int hq, int hkv, int hd);
 void launch_attn_prefill(const void* qkv, int qkv_stride, const void* kc, const void* vc, const int32_t* cu_seqlens,
-                         int batch, int max_len, int hq, int hkv, int hd, int max_seq, void* out, hipStream_t st);
+                         int batch, int rows, int max_len, int hq, int hkv, int hd, int max_seq, void* out, hipStream_t st);
 
 // The same in fp32; head_dim 64 or 128.
 bool attn_prefill_f32_supported(int hq, int hkv, int hd);
