@@ -71,9 +71,13 @@ k_attn_prefill(const int32_t* __restrict__ cu, int hq, int hkv, int nq, int batc
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
   // Fills are written in assembly: of the builtin the compiler knows that it writes LDS but not where, and has the next
   // tile's arrive before it reads this one's values.  The waits for them are LS_TILE_BARRIER's.
+  // m0 is reserved, which the compiler warns of; named all the same, so that it keeps no value of its own there.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
   auto fill = [](const bf16* base, unsigned off, unsigned to) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory", "m0");
   };
+#pragma clang diagnostic pop
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
