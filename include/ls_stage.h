@@ -116,9 +116,11 @@ ls_status ls_block_tensor(const ls_cfg* cfg, int layer, int index, size_t* offse
  * the embedding block if lo == 0 and the head block if hi == n_layers_total (vocab > 0). */
 size_t ls_stage_slab_bytes(const ls_cfg* cfg, int layer_lo, int layer_hi);
 
-/* Device bytes for the intermediate results of one call at the cfg's limits.  fp32 stages of layers wide enough for it hold
- * a second, split copy of the rows of one projection: 6 bytes for each of max_tokens (as far as 4 GB of rows) times the
- * largest of hidden size, query width and ffn, 2.2 GB of 7.4 at 32768 tokens of a 7B-shaped layer. */
+/* Device bytes for the intermediate results of one call at the cfg's limits, behind a table that ls_stage_create
+ * writes in front: cos and sin of every position, the same for all stages of one max_seq, head_dim and rope_base.  Nothing
+ * else in it outlasts a call, so such stages may take turns on one workspace, in stream order.  fp32 stages of layers
+ * wide enough for it hold a second, split copy of the rows of one projection: 6 bytes for each of max_tokens (as far as
+ * 4 GB of rows) times the largest of hidden size, query width and ffn, 2.2 GB of 7.4 at 32768 tokens of a 7B-shaped layer. */
 size_t ls_stage_workspace_bytes(const ls_cfg* cfg, int layer_lo, int layer_hi);
 
 /* Device bytes of EACH of ls_kv.k and ls_kv.v. */
@@ -132,6 +134,10 @@ size_t ls_stage_kv_bytes(const ls_cfg* cfg, int layer_lo, int layer_hi);
  * queries above return (else LS_ERR_OOM), 256-byte aligned, owned by the caller, and must
  * outlive the stage.  The stage owns only host metadata and HIP events.  All blocks start
  * NOT LOADED.  *out is written only on success.
+ * Generation steps of small fp32 models (up to 256 columns) run as one launch, whose workgroups exchange activations through
+ * memory.  Each stage of such a model holds a part of a static array of its GPU for that (64 parts, 16 MiB in all, held
+ * until the process ends), from here to ls_stage_destroy; while 64 others hold them, its steps are separate launches with the
+ * same results.  Steps of one stage are ordered by the caller, as all of its calls are: they share workspace and cache.
  */
 ls_status ls_stage_create(const ls_cfg* cfg, int layer_lo, int layer_hi, void* weight_slab,
                           size_t slab_bytes, void* workspace, size_t ws_bytes, ls_stage** out);

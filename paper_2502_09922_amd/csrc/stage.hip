@@ -134,7 +134,7 @@ bool span_ok(const ls_cfg* c, int lo, int hi) {
 // ---- workspace carving ------------------------------------------------------------------
 struct Carve {
   size_t cs, x, y, qkv, attn, h, logits, row_seq, row_pos, last_rows, next_tok, xb, xb2, ss_a, ss_b, splitk, splitk_bytes,
-      attn_part, attn_part_bytes, parts, parts_bytes, step, step_bytes, total;
+      attn_part, attn_part_bytes, parts, parts_bytes, total;
 };
 
 // more than 64 MiB of partial tiles are never wanted: a call that long fills the chip without splits
@@ -204,11 +204,6 @@ Carve carve(const ls_cfg* c, int lo, int hi) {
     if (last) parts_of(ls::TILED_STORE, B, c->vocab, d);
   }
   w.parts = take(w.parts_bytes);
-  // small fp32 models: what the workgroups of a step in one launch hand each other, behind the tag of the last step
-  if (c->dtype == LS_DTYPE_F32 && d <= 1024 && c->ffn <= (1u << 20) && c->vocab <= (1u << 20) && qkv_cols <= (1u << 20))
-    w.step_bytes = ls::small_step_exchange_bytes((int)B, (int)d, (int)c->n_q_heads, (int)c->n_kv_heads, (int)c->head_dim, (int)c->ffn, last ? (int)c->vocab : 0);
-  if (w.step_bytes) w.step_bytes += ALIGN;
-  w.step = take(w.step_bytes);
   (void)lo;
   w.total = off;
   return w;
@@ -268,6 +263,7 @@ struct ls_stage {
   int layer0;                 // index in blocks of layer lo
   int device;             // HIP device the stage was created on
   void* static_scratch;   // this device's copy of the library's static scratch array
+  unsigned long long* step_places;  // of a small fp32 model's steps in one launch, or null
   bool profiling;
   bool compute_timed;
   int origin_block;  // first block copied with profiling on since the last reset, or -1
@@ -431,18 +427,21 @@ ls_status ls_stage_create(const ls_cfg* cfg, int lo, int hi, void* weight_slab, 
       cs[((size_t)p * half + i) * 2] = (float)std::cos(a);
       cs[((size_t)p * half + i) * 2 + 1] = (float)std::sin(a);
     }
-  hipError_t e = w.step_bytes ? hipMemset(s->ws + w.step, 0, w.step_bytes) : hipSuccess;  // done before the copy behind it
-  if (e == hipSuccess) e = hipMemcpy(s->ws + w.cs, cs.data(), cs.size() * sizeof(float), hipMemcpyHostToDevice);
+  hipError_t e = hipMemcpy(s->ws + w.cs, cs.data(), cs.size() * sizeof(float), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     cleanup();
     return fail(LS_ERR_HIP, "ls_stage_create: table upload: %s", hipGetErrorString(e));
   }
+  if (cfg->dtype == LS_DTYPE_F32 && cfg->hidden <= 1024 && cfg->ffn <= (1u << 20) && cfg->vocab <= (1u << 20) && cfg->n_q_heads <= 1024)
+    s->step_places = ls::take_small_step_places(device, (int)std::min(cfg->max_batch, 1024u), (int)cfg->hidden, (int)cfg->n_q_heads,
+                                                (int)cfg->n_kv_heads, (int)cfg->head_dim, (int)cfg->ffn, s->last ? (int)cfg->vocab : 0);
   *out = s;
   return LS_OK;
 }
 
 void ls_stage_destroy(ls_stage* s) {
   if (!s) return;
+  ls::give_small_step_places(s->device, s->step_places);
   for (auto& b : s->blocks) {
     (void)hipEventDestroy(b.copy_start);
     (void)hipEventDestroy(b.loaded);
@@ -712,7 +711,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   }
 
   // ---- generation steps of few rows of a small fp32 model: one launch, once every block has landed
-  if (!prefill && dt == F32 && s->w.step_bytes && !probing) {
+  if (!prefill && dt == F32 && s->step_places && !probing) {
     SmallStep a;
     TensorSpan sp[6];
     const Block& b0 = s->blocks[s->layer0];
@@ -730,7 +729,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     a.layers = s->hi - s->lo; a.d = d; a.hq = hq; a.hkv = hkv; a.hd = hd; a.F = F; a.vocab = (int)c.vocab; a.max_seq = (int)c.max_seq;
     a.eps = c.rms_eps; a.cs = (const float2*)cs; a.kc = (float*)kv->k; a.vc = (float*)kv->v; a.kv_layer = kv_layer / 4;
     a.qkv = (float*)qkv; a.attn = (float*)attn; a.h = (float*)hbuf;
-    a.seq_lens = kv->seq_lens; a.epoch = (unsigned*)(ws + s->w.step); a.xch = (unsigned long long*)(ws + s->w.step + ALIGN);
+    a.seq_lens = kv->seq_lens; a.places = s->step_places;
     // K is cut where the projections' own launches cut it
     const TiledPlan po = gemm_tiled_plan(dt, TILED_PART, rows, d, hq * hd, true, gsc.bytes, nullptr, s->w.parts_bytes);
     const TiledPlan pd = gemm_tiled_plan(dt, TILED_PART, rows, d, F, true, gsc.bytes, nullptr, s->w.parts_bytes);

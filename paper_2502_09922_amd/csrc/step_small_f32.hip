@@ -14,6 +14,9 @@
 // more than the device has hardware queues (24); what else runs there ends by itself.  A poll is bounded all the same (POLLS, many
 // seconds): a value that has not come by then reads as NaN.
 //
+// Where the places are.  They and the last step's tag have to outlast the step, which a workspace need not: each stage has a
+// part of a static array of its device for as long as it lives (take_small_step_places), and no other stage's calls write there.
+//
 // Who writes a place again.  Every phase has places of its own, written again a layer later.  Every workgroup has columns of
 // the projections (small_step_shape), so whoever has gathered a phase's values knows that every workgroup is past the phases
 // before it; a launch ends before the next begins, which goes on with tags behind the last one's.
@@ -23,6 +26,8 @@
 #include "device_util.hpp"
 
 #include <algorithm>
+#include <atomic>
+#include <mutex>
 
 namespace ls {
 
@@ -32,6 +37,7 @@ typedef unsigned long long u64;
 
 constexpr int NT = 512, NW = NT / 64, WGS = 16, GW = WGS * NW;
 constexpr int POLLS = 1 << 25;
+constexpr int HEAD = 32;     // words of a stage's places in front, which hold the last step's tag
 constexpr int ATTN_NW = NW;  // ranges a context is cut into, as in k_attn_decode<float>
 constexpr int AMAX_NW = 16;  // ... wavefronts of k_argmax
 
@@ -185,8 +191,9 @@ __global__ void __launch_bounds__(NT, 4) k_step_small_f32(SmallStep a) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int d = a.d, F = a.F, qd = a.hq * HD, nq = qd + 2 * a.hkv * HD;
   float *xs = sm, *x2s = xs + R * d, *as = x2s + R * d, *hs = as + R * qd;  // rows, rows behind O, attention (q, k, v first), SwiGLU
-  u64 *lx = a.xch, *lq = lx + R * d, *la = lq + R * nq, *lx2 = la + R * qd, *lh = lx2 + R * d, *ll = lh + R * F;
-  const unsigned tag0 = __hip_atomic_load(a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+  unsigned* const epoch = (unsigned*)a.places;
+  u64 *lx = a.places + HEAD, *lq = lx + R * d, *la = lq + R * nq, *lx2 = la + R * qd, *lh = lx2 + R * d, *ll = lh + R * F;
+  const unsigned tag0 = __hip_atomic_load(epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
   if ((int)threadIdx.x < R) {
     const int p = a.seq_lens[threadIdx.x];
     spos[threadIdx.x] = p >= 0 && p < a.max_seq ? p : -1;
@@ -407,12 +414,25 @@ __global__ void __launch_bounds__(NT, 4) k_step_small_f32(SmallStep a) {
   }
   // Workgroup 0 has seen values of all others that they sent behind their reads of the tag and of the lengths.
   if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) *a.epoch = tag0 + a.layers;
+    if (threadIdx.x == 0) *epoch = tag0 + a.layers;
     if ((int)threadIdx.x < R && spos[threadIdx.x] >= 0) a.seq_lens[threadIdx.x] = spos[threadIdx.x] + 1;
   }
 }
 
 constexpr int ROWS = 4;
+std::atomic<long> launches{0};
+
+// Parts of the static array, one to a stage.  A stage that finds all of them taken, or needs more, takes the separate launches.
+constexpr int PARTS = 64, PART_WORDS = 32 * 1024, MAX_DEVICES = 64;
+__device__ __align__(256) u64 places[PARTS][PART_WORDS];
+
+struct Pool {
+  u64* base = nullptr;  // this device's copy of the array
+  u64 taken = 0;        // bit i: part i
+};
+std::mutex pool_mutex;
+Pool pools[MAX_DEVICES];
+
 constexpr size_t LDS_MOST = 60 * 1024;  // two workgroups and what they hold besides to a CU's 160 KB
 
 size_t lds_bytes(const SmallStep& a, int rows) {
@@ -444,18 +464,43 @@ bool small_step_shape(int d, int hq, int hkv, int hd, int F, int vocab) {
   return (size_t)d * (2 * (hq + hkv) * hd + 3 * F) <= (1u << 20);  // weights of a layer
 }
 
-size_t small_step_exchange_bytes(int rows, int d, int hq, int hkv, int hd, int F, int vocab) {
-  if (!small_step_shape(d, hq, hkv, hd, F, vocab)) return 0;
-  return (size_t)std::min(rows, ROWS) * ((size_t)2 * d + (2 * (size_t)hq + 2 * (size_t)hkv) * hd + F + vocab) * sizeof(u64);
+unsigned long long* take_small_step_places(int device, int rows, int d, int hq, int hkv, int hd, int F, int vocab) {
+  static_assert(PARTS == 64, "");
+  const size_t r = std::min(rows, ROWS);
+  if (device < 0 || device >= MAX_DEVICES || !small_step_shape(d, hq, hkv, hd, F, vocab) ||
+      HEAD + r * ((size_t)2 * d + (2 * (size_t)hq + 2 * (size_t)hkv) * hd + F + vocab) > PART_WORDS)
+    return nullptr;
+  std::lock_guard<std::mutex> lock(pool_mutex);
+  Pool& p = pools[device];
+  if (!p.base) {
+    void* base = nullptr;
+    if (hipGetSymbolAddress(&base, HIP_SYMBOL(places)) != hipSuccess || hipMemset(base, 0, sizeof places) != hipSuccess ||
+        hipStreamSynchronize(nullptr) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    p.base = (u64*)base;
+  }
+  if (!~p.taken) return nullptr;
+  const int i = __builtin_ctzll(~p.taken);
+  p.taken |= (u64)1 << i;
+  return p.base + (size_t)i * PART_WORDS;  // a stage before this one may have left tags: the next steps go on behind them
+}
+
+void give_small_step_places(int device, unsigned long long* part) {
+  if (!part) return;
+  std::lock_guard<std::mutex> lock(pool_mutex);
+  pools[device].taken &= ~((u64)1 << (part - pools[device].base) / PART_WORDS);
 }
 
 bool small_step_supported(const SmallStep& a, int rows, int max_keys) {
-  return rows >= 1 && rows <= ROWS && a.xch && small_step_shape(a.d, a.hq, a.hkv, a.hd, a.F, a.head_w ? a.vocab : 0) &&
+  return rows >= 1 && rows <= ROWS && a.places && small_step_shape(a.d, a.hq, a.hkv, a.hd, a.F, a.head_w ? a.vocab : 0) &&
          attn_decode_chunks(rows, a.hkv, max_keys) == 1 && lds_bytes(a, rows) <= LDS_MOST &&
          (!a.head_w || gemm_rows_f32_norm_supported(rows, a.vocab, a.d));
 }
 
 void launch_small_step(const SmallStep& a, int rows, hipStream_t st) {
+  ++launches;
   switch (rows) {
     case 1: launch_r<1>(a, st); break;
     case 2: launch_r<2>(a, st); break;
@@ -465,3 +510,6 @@ void launch_small_step(const SmallStep& a, int rows, hipStream_t st) {
 }
 
 }  // namespace ls
+
+// For the tests; not declared in ls_stage.h: steps that took the one launch so far.
+extern "C" long ls_test_small_steps(void) { return ls::launches; }
