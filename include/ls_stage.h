@@ -135,7 +135,7 @@ size_t ls_stage_kv_bytes(const ls_cfg* cfg, int layer_lo, int layer_hi);
  * outlive the stage.  The stage owns only host metadata and HIP events.  All blocks start
  * NOT LOADED.  *out is written only on success.
  * Generation steps of small fp32 models (up to 256 columns) run as one launch, whose workgroups exchange activations through
- * memory.  Each stage of such a model holds a part of a static array of its GPU for that (64 parts, 16 MiB in all, held
+ * memory.  Each stage of such a model holds a part of a static array of its GPU for that (64 parts, 9 MiB in all, held
  * until the process ends), from here to ls_stage_destroy; while 64 others hold them, its steps are separate launches with the
  * same results.  Steps of one stage are ordered by the caller, as all of its calls are: they share workspace and cache.
  */

@@ -181,9 +181,9 @@ struct SmallStep {
   int32_t* seq_lens = nullptr;
   unsigned long long* places = nullptr;  // take_small_step_places
 };
-// Where the workgroups of such a step of up to `rows` rows hand each other activations, on the current device: a stage's own from
-// its creation to its end, and null where it has no such steps or other stages hold all there is.
-unsigned long long* take_small_step_places(int device, int rows, int d, int hq, int hkv, int hd, int F, int vocab);
+// Where the workgroups of such a step hand each other activations, on the current device: a stage's own from its creation to
+// its end, and null where it has no such steps or other stages hold all there is.
+unsigned long long* take_small_step_places(int device, int d, int hq, int hkv, int hd, int F, int vocab);
 void give_small_step_places(int device, unsigned long long* places);
 bool small_step_supported(const SmallStep& a, int rows, int max_keys);
 void launch_small_step(const SmallStep& a, int rows, hipStream_t st);

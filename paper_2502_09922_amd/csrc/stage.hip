@@ -433,8 +433,8 @@ ls_status ls_stage_create(const ls_cfg* cfg, int lo, int hi, void* weight_slab, 
     return fail(LS_ERR_HIP, "ls_stage_create: table upload: %s", hipGetErrorString(e));
   }
   if (cfg->dtype == LS_DTYPE_F32 && cfg->hidden <= 1024 && cfg->ffn <= (1u << 20) && cfg->vocab <= (1u << 20) && cfg->n_q_heads <= 1024)
-    s->step_places = ls::take_small_step_places(device, (int)std::min(cfg->max_batch, 1024u), (int)cfg->hidden, (int)cfg->n_q_heads,
-                                                (int)cfg->n_kv_heads, (int)cfg->head_dim, (int)cfg->ffn, s->last ? (int)cfg->vocab : 0);
+    s->step_places = ls::take_small_step_places(device, (int)cfg->hidden, (int)cfg->n_q_heads, (int)cfg->n_kv_heads, (int)cfg->head_dim, (int)cfg->ffn,
+                                                s->last ? (int)cfg->vocab : 0);
   *out = s;
   return LS_OK;
 }

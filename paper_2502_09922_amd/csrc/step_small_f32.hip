@@ -422,8 +422,8 @@ __global__ void __launch_bounds__(NT, 4) k_step_small_f32(SmallStep a) {
 constexpr int ROWS = 4;
 std::atomic<long> launches{0};
 
-// Parts of the static array, one to a stage.  A stage that finds all of them taken, or needs more, takes the separate launches.
-constexpr int PARTS = 64, PART_WORDS = 32 * 1024, MAX_DEVICES = 64;
+// Parts of the static array, one to a stage.  A stage that finds all of them taken takes the separate launches.
+constexpr int PARTS = 64, PART_WORDS = 18 * 1024, MAX_DEVICES = 64;
 __device__ __align__(256) u64 places[PARTS][PART_WORDS];
 
 struct Pool {
@@ -433,7 +433,10 @@ struct Pool {
 std::mutex pool_mutex;
 Pool pools[MAX_DEVICES];
 
-constexpr size_t LDS_MOST = 60 * 1024;  // two workgroups and what they hold besides to a CU's 160 KB
+// The shapes that are taken (small_step_shape, small_step_rows).
+constexpr int COLUMNS = 256, VOCAB = 1024, UNITS = WGS, FFN_ROWS = 3072, HD_MOST = 128;
+static_assert(HEAD + 2 * ROWS * COLUMNS + 4 * UNITS * HD_MOST + FFN_ROWS + ROWS * VOCAB <= PART_WORDS, "places of the largest step");
+static_assert((2 * ROWS * COLUMNS + UNITS * HD_MOST + FFN_ROWS) * sizeof(float) <= 60 * 1024, "two workgroups and what they hold besides to a CU's 160 KB");
 
 size_t lds_bytes(const SmallStep& a, int rows) {
   const size_t r = rows, acts = 2 * r * a.d + std::max(r * (a.hq * a.hd + a.F), (size_t)3 * a.hd);
@@ -460,16 +463,20 @@ void launch_r(const SmallStep& a, hipStream_t st) {
 // 600 keys: 128 columns 37.7 / 24.5, 50.5 / 39.4, 43.2 / 28.2, 54.5 / 42.9 us; 256 columns 39.2 / 28.4, 51.1 / 46.2, 56.1 / 33.0,
 // 68.4 / 51.1; 384 columns 47.7 / 44.7, 58.3 / 83.6: sixteen CUs then take longer over the weights than the launches cost.
 bool small_step_shape(int d, int hq, int hkv, int hd, int F, int vocab) {
-  if (!attn_decode_supported(hq, hkv, hd) || d % 4 || F % 4 || d < WGS || F < WGS || d > 256 || (vocab && vocab < WGS) || vocab > 1024) return false;
-  return (size_t)d * (2 * (hq + hkv) * hd + 3 * F) <= (1u << 20);  // weights of a layer
+  if (!attn_decode_supported(hq, hkv, hd) || d % 4 || F % 4 || d < WGS || F < WGS || d > COLUMNS || (vocab && vocab < WGS) || vocab > VOCAB) return false;
+  return (size_t)d * (2 * (size_t)(hq + hkv) * hd + 3 * (size_t)F) <= (1u << 20);  // weights of a layer
 }
 
-unsigned long long* take_small_step_places(int device, int rows, int d, int hq, int hkv, int hd, int F, int vocab) {
+// A workgroup takes its heads of a row one after the other, each behind an exchange: no more of them than workgroups.  Every
+// workgroup gathers all of the SwiGLU's output, 1024 values to an exchange: three of them.  Separate launches / this one, two
+// layers: 44 columns, 32 heads, 4 rows, 200 keys (8 units to a workgroup) 58 / 143 us, 32 heads and one row (2) 44 / 55, 8 and
+// two rows (1) 42 / 36; ffn of 6540 and one row 45 / 80, 3324 47 / 53, 2792 53 / 49, 1608 and two rows 48 / 51, 804 and two 40 / 33.
+// Of 30 such shapes drawn at random none is slower.
+bool small_step_rows(int rows, int hq, int F) { return rows >= 1 && rows <= ROWS && (long)rows * hq <= UNITS && (long)rows * F <= FFN_ROWS; }
+
+unsigned long long* take_small_step_places(int device, int d, int hq, int hkv, int hd, int F, int vocab) {
   static_assert(PARTS == 64, "");
-  const size_t r = std::min(rows, ROWS);
-  if (device < 0 || device >= MAX_DEVICES || !small_step_shape(d, hq, hkv, hd, F, vocab) ||
-      HEAD + r * ((size_t)2 * d + (2 * (size_t)hq + 2 * (size_t)hkv) * hd + F + vocab) > PART_WORDS)
-    return nullptr;
+  if (device < 0 || device >= MAX_DEVICES || !small_step_shape(d, hq, hkv, hd, F, vocab) || !small_step_rows(1, hq, F)) return nullptr;
   std::lock_guard<std::mutex> lock(pool_mutex);
   Pool& p = pools[device];
   if (!p.base) {
@@ -494,9 +501,8 @@ void give_small_step_places(int device, unsigned long long* part) {
 }
 
 bool small_step_supported(const SmallStep& a, int rows, int max_keys) {
-  return rows >= 1 && rows <= ROWS && a.places && small_step_shape(a.d, a.hq, a.hkv, a.hd, a.F, a.head_w ? a.vocab : 0) &&
-         attn_decode_chunks(rows, a.hkv, max_keys) == 1 && lds_bytes(a, rows) <= LDS_MOST &&
-         (!a.head_w || gemm_rows_f32_norm_supported(rows, a.vocab, a.d));
+  return a.places && small_step_shape(a.d, a.hq, a.hkv, a.hd, a.F, a.head_w ? a.vocab : 0) && small_step_rows(rows, a.hq, a.F) &&
+         attn_decode_chunks(rows, a.hkv, max_keys) == 1 && (!a.head_w || gemm_rows_f32_norm_supported(rows, a.vocab, a.d));
 }
 
 void launch_small_step(const SmallStep& a, int rows, hipStream_t st) {
