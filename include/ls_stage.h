@@ -138,6 +138,9 @@ size_t ls_stage_kv_bytes(const ls_cfg* cfg, int layer_lo, int layer_hi);
  * memory.  Each stage of such a model holds a part of a static array of its GPU for that (64 parts, 9 MiB in all, held
  * until the process ends), from here to ls_stage_destroy; while 64 others hold them, its steps are separate launches with the
  * same results.  Steps of one stage are ordered by the caller, as all of its calls are: they share workspace and cache.
+ * The workgroups of such a launch wait for each other, so all of them have to be on the chip together.  On streams that a CU
+ * mask restricts to fewer than 24 CUs of an XCD the steps are separate launches; a graph of such steps is replayed only on
+ * streams that are not restricted so, and an environment that restricts the CUs of the whole process leaves as many.
  */
 ls_status ls_stage_create(const ls_cfg* cfg, int layer_lo, int layer_hi, void* weight_slab,
                           size_t slab_bytes, void* workspace, size_t ws_bytes, ls_stage** out);

@@ -186,6 +186,7 @@ struct SmallStep {
 unsigned long long* take_small_step_places(int device, int d, int hq, int hkv, int hd, int F, int vocab);
 void give_small_step_places(int device, unsigned long long* places);
 bool small_step_supported(const SmallStep& a, int rows, int max_keys);
+bool small_step_room(hipStream_t st);  // all workgroups of such steps on all queues can be on the stream's CUs together
 void launch_small_step(const SmallStep& a, int rows, hipStream_t st);
 
 // One pass over rows of width d (a multiple of 4, at most 8192).  Source: the residual rows plus `splits`

@@ -737,7 +737,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     a.cut_o = log2_of(po.splits); a.cut_d = log2_of(pd.splits); a.group = log2_of(hq / hkv);
     bool there = gsc.splitk && po.splits && !po.bm && pd.splits && !pd.bm && small_step_supported(a, rows, max_len);
     for (auto& b : s->blocks) there = there && landed(b);
-    if (there) {
+    if (there && small_step_room(st)) {
       launch_small_step(a, rows, st);
       LS_HIP(hipGetLastError());
       return LS_OK;

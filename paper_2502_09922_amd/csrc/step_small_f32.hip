@@ -11,8 +11,9 @@
 //
 // Sixteen: with 32 workgroups a step takes 23.5 us, with 16 of them 27.3, but all of a launch have to be on the chip together.
 // A CU holds two (512 threads, at most 128 registers, at most 64 KB of LDS), the chip 512, which is 32 such launches at once,
-// more than the device has hardware queues (24); what else runs there ends by itself.  A poll is bounded all the same (POLLS, many
-// seconds): a value that has not come by then reads as NaN.
+// more than the device has hardware queues (24); what else runs there ends by itself.  A stream that may use fewer CUs than
+// those of 24 launches gets the separate launches (small_step_room).  A poll is bounded all the same (POLLS, many seconds): a value
+// that has not come by then reads as NaN.
 //
 // Where the places are.  They and the last step's tag have to outlast the step, which a workspace need not: each stage has a
 // part of a static array of its device for as long as it lives (take_small_step_places), and no other stage's calls write there.
@@ -503,6 +504,25 @@ void give_small_step_places(int device, unsigned long long* part) {
 bool small_step_supported(const SmallStep& a, int rows, int max_keys) {
   return a.places && small_step_shape(a.d, a.hq, a.hkv, a.hd, a.F, a.head_w ? a.vocab : 0) && small_step_rows(rows, a.hq, a.F) &&
          attn_decode_chunks(rows, a.hkv, max_keys) == 1 && (!a.head_w || gemm_rows_f32_norm_supported(rows, a.vocab, a.d));
+}
+
+// Room for one launch on each of the device's hardware queues, on every XCD (two workgroups of each launch go to each, whatever is
+// free elsewhere), on the CUs that the stream's mask leaves it; the mask's bits may be dealt to the XCDs in turn or one after the
+// other.  Asked for anew each time: 0.2 us.
+bool small_step_room(hipStream_t st) {
+  constexpr int QUEUES = 24, XCDS = 8, CUS = QUEUES * (WGS / XCDS) / 2, MASK_WORDS = 32;
+  if (st == hipStreamLegacy || st == hipStreamPerThread) st = nullptr;  // the query knows no handle of these
+  uint32_t mask[MASK_WORDS] = {};
+  if (hipExtStreamGetCUMask(st, MASK_WORDS, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  for (int x = 0; x < XCDS; ++x) {
+    int in_turn = 0;
+    for (int i = 0; i < XCDS; ++i) in_turn += __builtin_popcount(mask[i] & 0x01010101u << x);
+    if (in_turn < CUS || __builtin_popcount(mask[x]) < CUS) return false;
+  }
+  return true;
 }
 
 void launch_small_step(const SmallStep& a, int rows, hipStream_t st) {

@@ -111,3 +111,34 @@ def test_steps_on_several_streams_at_once():
         same(out, want)
     assert small_steps() == before + 20 * 6
     close(stages)
+
+
+def test_streams_restricted_to_few_cus_take_separate_launches():
+    import ctypes
+
+    import torch
+
+    hip = ctypes.CDLL([l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l][0])  # the one torch uses
+    own = make_stages([(0, 2)], False)
+    want = run(own, 6)
+    few, enough, odd = (1 << 16) - 1, (1 << 24) - 1, 0xFFFF0FFF
+    for words, one_launch in (([few] * 8, False), ([enough] * 8, True), ([odd] * 8, True), ([0xFFFFFFFF] * 7 + [few], False), ([0xFFFFFFFF] * 8, True)):
+        handle = ctypes.c_void_p()
+        mask = (ctypes.c_uint32 * 8)(*words)
+        assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), 8, mask) == 0
+        stream, before = torch.cuda.ExternalStream(handle.value), small_steps()
+        with torch.cuda.stream(stream):
+            own[0].reset_blocks()
+            for layer in own[0].block_ids():
+                own[0].adopt_block(layer, stream)
+            stream.synchronize()
+            rows = torch.randint(0, SHAPE.vocab, (33,), dtype=torch.int32, device="cuda", generator=torch.Generator(device="cuda").manual_seed(2))
+            rows, got = own[0].prefill(rows, [30, 3], stream=stream), []
+            for t in range(6):
+                rows = own[0].decode(rows, 2, 30 + t, stream=stream)
+                got.append(rows.clone())
+        stream.synchronize()
+        same(got, want)
+        assert small_steps() - before == (6 if one_launch else 0)
+        assert hip.hipStreamDestroy(handle) == 0
+    close(own)
