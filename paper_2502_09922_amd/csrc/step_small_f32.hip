@@ -435,7 +435,7 @@ std::mutex pool_mutex;
 Pool pools[MAX_DEVICES];
 
 // The shapes that are taken (small_step_shape, small_step_rows).
-constexpr int COLUMNS = 256, VOCAB = 1024, UNITS = WGS, FFN_ROWS = 3072, HD_MOST = 128;
+constexpr int COLUMNS = 256, QUERY = 1024, FFN = 2048, VOCAB = 1024, UNITS = WGS, FFN_ROWS = 3072, HD_MOST = 128;
 static_assert(HEAD + 2 * ROWS * COLUMNS + 4 * UNITS * HD_MOST + FFN_ROWS + ROWS * VOCAB <= PART_WORDS, "places of the largest step");
 static_assert((2 * ROWS * COLUMNS + UNITS * HD_MOST + FFN_ROWS) * sizeof(float) <= 60 * 1024, "two workgroups and what they hold besides to a CU's 160 KB");
 
@@ -462,17 +462,19 @@ void launch_r(const SmallStep& a, hipStream_t st) {
 
 // Rows of one piece of 256 columns.  Two layers and a head of 512 entries, separate launches / this one, 1 row and 4, 40 and
 // 600 keys: 128 columns 37.7 / 24.5, 50.5 / 39.4, 43.2 / 28.2, 54.5 / 42.9 us; 256 columns 39.2 / 28.4, 51.1 / 46.2, 56.1 / 33.0,
-// 68.4 / 51.1; 384 columns 47.7 / 44.7, 58.3 / 83.6: sixteen CUs then take longer over the weights than the launches cost.
+// 68.4 / 51.1; 384 columns 47.7 / 44.7, 58.3 / 83.6: sixteen CUs then take longer over the weights than the launches cost.  The O
+// and down projections' rows likewise, one row: 16 heads of 128 37 / 46, 16 of 64 39 / 33; ffn of 2904 42 / 48, 2376 43 / 49, 1884
+// 54 / 51.  Of 76 shapes drawn at random that are taken the slowest takes 0.98 of the separate launches' time, all in the mean 0.75.
 bool small_step_shape(int d, int hq, int hkv, int hd, int F, int vocab) {
-  if (!attn_decode_supported(hq, hkv, hd) || d % 4 || F % 4 || d < WGS || F < WGS || d > COLUMNS || (vocab && vocab < WGS) || vocab > VOCAB) return false;
+  if (!attn_decode_supported(hq, hkv, hd) || d % 4 || F % 4 || d < WGS || F < WGS || (vocab && vocab < WGS)) return false;
+  if (d > COLUMNS || (long)hq * hd > QUERY || F > FFN || vocab > VOCAB) return false;
   return (size_t)d * (2 * (size_t)(hq + hkv) * hd + 3 * (size_t)F) <= (1u << 20);  // weights of a layer
 }
 
 // A workgroup takes its heads of a row one after the other, each behind an exchange: no more of them than workgroups.  Every
 // workgroup gathers all of the SwiGLU's output, 1024 values to an exchange: three of them.  Separate launches / this one, two
 // layers: 44 columns, 32 heads, 4 rows, 200 keys (8 units to a workgroup) 58 / 143 us, 32 heads and one row (2) 44 / 55, 8 and
-// two rows (1) 42 / 36; ffn of 6540 and one row 45 / 80, 3324 47 / 53, 2792 53 / 49, 1608 and two rows 48 / 51, 804 and two 40 / 33.
-// Of 30 such shapes drawn at random none is slower.
+// two rows (1) 42 / 36; ffn of 1608 and two rows 48 / 51, 804 and two 40 / 33.
 bool small_step_rows(int rows, int hq, int F) { return rows >= 1 && rows <= ROWS && (long)rows * hq <= UNITS && (long)rows * F <= FFN_ROWS; }
 
 unsigned long long* take_small_step_places(int device, int d, int hq, int hkv, int hd, int F, int vocab) {
