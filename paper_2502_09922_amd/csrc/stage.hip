@@ -574,6 +574,14 @@ ls_status ls_stage_set_profiling(ls_stage* s, int on) {
 // ---- the forward pass -------------------------------------------------------------------
 namespace {
 
+// The memory at `p` is this device's own: not pinned host memory and not a peer's, which each read brings over a link.
+bool own_memory(const ls_stage* s, const void* p) {
+  hipPointerAttribute_t a{};
+  if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type == hipMemoryTypeDevice && a.device == s->device;
+  (void)hipGetLastError();
+  return false;
+}
+
 // `gsc`: where GEMM kernels that split K across workgroups put their partial tiles.
 ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_dev, int batch, int rows, int max_len,
                   const ls_kv* kv, void* out, float* logits_out, hipStream_t st, const ls::GemmScratch& gsc) {
@@ -808,8 +816,9 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
       y_ready = true;
       // The O projection of 256 x 256 tiles adds to the call's own bf16 rows: nobody reads them in fp32 before it.  13B, 32768
       // rows: this kernel 139 us instead of 228, the projection 1305 instead of 1320; 70B, 7296 rows: 52 and 83, 764 and 776.
-      // Partial tiles are added up by a row kernel, which reads fp32 rows; an input on fewer than eight bytes is widened here.
-      from_in = !s->first && dt == BF16 && rows > 64 && !p_o.splits && gemm_mfma_resid_in_supported(rows, d, hq * hd, in);
+      // Partial tiles are added up by a row kernel, which reads fp32 rows; an input on fewer than eight bytes is widened here, and
+      // one that is not this device's own memory read once (13B, 32768 rows in pinned host memory: 22.8 ms, read twice 29.8).
+      from_in = !s->first && dt == BF16 && rows > 64 && !p_o.splits && gemm_mfma_resid_in_supported(rows, d, hq * hd, in) && own_memory(s, in);
       ra.norm_only = from_in;
     }
     launch_rows(dt, s->first ? ROWS_EMBED : ROWS_HIDDEN, ra, st);

@@ -41,3 +41,34 @@ def test_same_bits_wherever_the_rows_lie(hidden, hq, hkv, hd, lengths, layers):
     for other in got[1:]:
         assert torch.equal(got[0], other)
     st.close()
+
+
+def test_rows_in_host_memory_are_read_once():
+    """By the first row kernel: the O projection takes as long as with rows in device memory (over the host link their 32 MB alone
+    would take four times that)."""
+    import torch
+
+    from paper_2502_09922_amd import Stage, binding as b
+
+    shape = synth.StageShape("bf16", 4, 4096, 32, 8, 128, 512, 0)
+    lengths = [1500, 1, 2595]
+    st = Stage(shape, 1, 2, len(lengths), max(lengths) + 4, sum(lengths))
+    for i in st.block_ids():
+        st.block_view(i).view(torch.bfloat16).normal_(0, 0.05, generator=torch.Generator(device="cuda").manual_seed(1))
+        st.adopt_block(i)
+    rows = torch.randn(sum(lengths), 4096, device="cuda", generator=torch.Generator(device="cuda").manual_seed(2)).bfloat16()
+    pinned = torch.empty(rows.shape, dtype=rows.dtype, pin_memory=True)
+    pinned.copy_(rows)
+    out, time = [], []
+    for x in (rows, pinned):
+        st.prefill(x, lengths)
+        st.probe(b.LS_OP_GEMM_O, 1, 0)
+        for _ in range(5):
+            out.append(st.prefill(x, lengths).clone())
+        torch.cuda.synchronize()
+        time.append(min(st.probe_times()))
+        st.probe(b.LS_OP_NONE)
+    print("O projection %.3f ms, rows in host memory %.3f ms" % tuple(time))
+    assert all(torch.equal(o, out[0]) for o in out)
+    assert time[1] < 2 * time[0]
+    st.close()
