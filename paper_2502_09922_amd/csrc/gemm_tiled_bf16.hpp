@@ -118,16 +118,16 @@ k_gemm_tiled(const bf16* __restrict__ A, const bf16* __restrict__ W, int M, int 
     // ONCE (one tile row): no other workgroup reads these weights.  Their fills are non-temporal, and the k-steps are
     // visited in cyclic order from a start of the tile's own: with rows a power of two apart (hidden sizes 4096,
     // 8192) workgroups in lock step would all ask the same memory channels.  The tiles of an XCD, eight apart, start eight
-    // k-steps from each other, or four where the call's rows take more than 1 MB, or two where they exceed the XCD's 4 MB of
-    // L2: what one of them brought of the rows has to be there when the next one asks.  Eight k-steps, four and two: down
-    // projection of 70B, 224 rows, 256 x 128 tiles 186 / 120 / 105 us, 120 rows 108 / 92 / 92; of 13B, 160 rows 45 / 36 / 36,
-    // 250 rows 61 / 48 / 43; of 7B, 250 rows 40 / 39 / 32; 70B, 64 rows (1 MB), O 25.3 / 25.0 / 26.5, gate-up 138.6 / 140.6 / 139.0, O of
-    // 100 rows 28.3 / 28.2 / 30.9; QKV of 7B, 45 rows 19.0 / 19.4 / 18.9, of 13B, 32 rows 28.6 / 29.0 / 29.2.
+    // k-steps from each other, or two where the call's rows take more than five sixths of the XCD's 4 MB of L2: what one of
+    // them brought of the rows has to be there when the next one asks.  Eight k-steps apart / two, down projections: 13B, 104
+    // rows (2.7 MB) 31.2 / 30.6 us, 128 (3.4) 34.2 / 32.9, 160 (4.2) 43.9 / 35.1, 250 rows 61 / 42; 7B, 128 rows (2.7) 23.6 / 23.7,
+    // 250 rows (5.3) 40 / 32; 70B, 72 rows (3.9) 81.7 / 81.9, 120 (6.6) 107.7 / 90.9, 224 (12.3) 178 / 109.  Gate-up of 70B, 64 rows
+    // (1.0) 139.3 / 139.9, 96 (1.5) 142.0 / 141.6, 192 (3.0) 231 / 237, 208 (3.25) 230 / 235, 224 (3.5) 234 / 230.
     auto run = [&](auto once_, auto count_) {
       constexpr bool ONCE = decltype(once_)::value;
       constexpr int C = decltype(count_)::value;  // f, or -1: not known
       const unsigned bytes = 2u * M * K;  // below 4 GB
-      const int lag = bytes > 4u << 20 ? 2 : bytes > 1u << 20 ? 4 : 8, start = ((tn >> 3) * lag + (tn & 7)) % n;
+      const int lag = bytes > (4u << 20) / 6 * 5 ? 2 : 8, start = ((tn >> 3) * lag + (tn & 7)) % n;
       int kc = ONCE && !ragged ? (TL::PAIRS ? start & ~1 : start) : 0, slot = 0;
       auto fill = [&]() {
         const size_t ko = (size_t)(t0 + kc) * 128;
