@@ -179,12 +179,17 @@ struct SmallStep {
   size_t kv_layer = 0;            // floats
   float *qkv = nullptr, *attn = nullptr, *h = nullptr;  // the last layer's projections, attention output and SwiGLU output
   int32_t* seq_lens = nullptr;
-  unsigned long long* places = nullptr;  // take_small_step_places
+  unsigned long long* xch = nullptr;  // SmallStepPlaces
+  unsigned* epoch = nullptr;
 };
 // Where the workgroups of such a step hand each other activations, on the current device: a stage's own from its creation to
 // its end, and null where it has no such steps or other stages hold all there is.
-unsigned long long* take_small_step_places(int device, int d, int hq, int hkv, int hd, int F, int vocab);
-void give_small_step_places(int device, unsigned long long* places);
+struct SmallStepPlaces {
+  unsigned long long* xch = nullptr;
+  unsigned* epoch = nullptr;  // the last step's tag
+};
+SmallStepPlaces take_small_step_places(int device, int d, int hq, int hkv, int hd, int F, int vocab);
+void give_small_step_places(int device, SmallStepPlaces places);
 bool small_step_supported(const SmallStep& a, int rows, int max_keys);
 bool small_step_room(hipStream_t st);  // all workgroups of such steps on all queues can be on the stream's CUs together
 void launch_small_step(const SmallStep& a, int rows, hipStream_t st);

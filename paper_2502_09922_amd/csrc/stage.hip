@@ -263,7 +263,7 @@ struct ls_stage {
   int layer0;                 // index in blocks of layer lo
   int device;             // HIP device the stage was created on
   void* static_scratch;   // this device's copy of the library's static scratch array
-  unsigned long long* step_places;  // of a small fp32 model's steps in one launch, or null
+  ls::SmallStepPlaces step_places;  // of a small fp32 model's steps in one launch, or null
   bool profiling;
   bool compute_timed;
   int origin_block;  // first block copied with profiling on since the last reset, or -1
@@ -719,7 +719,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
   }
 
   // ---- generation steps of few rows of a small fp32 model: one launch, once every block has landed
-  if (!prefill && dt == F32 && s->step_places && !probing) {
+  if (!prefill && dt == F32 && s->step_places.xch && !probing) {
     SmallStep a;
     TensorSpan sp[6];
     const Block& b0 = s->blocks[s->layer0];
@@ -737,7 +737,7 @@ ls_status forward(ls_stage* s, bool prefill, const void* in, const int32_t* cu_d
     a.layers = s->hi - s->lo; a.d = d; a.hq = hq; a.hkv = hkv; a.hd = hd; a.F = F; a.vocab = (int)c.vocab; a.max_seq = (int)c.max_seq;
     a.eps = c.rms_eps; a.cs = (const float2*)cs; a.kc = (float*)kv->k; a.vc = (float*)kv->v; a.kv_layer = kv_layer / 4;
     a.qkv = (float*)qkv; a.attn = (float*)attn; a.h = (float*)hbuf;
-    a.seq_lens = kv->seq_lens; a.places = s->step_places;
+    a.seq_lens = kv->seq_lens; a.xch = s->step_places.xch; a.epoch = s->step_places.epoch;
     // K is cut where the projections' own launches cut it
     const TiledPlan po = gemm_tiled_plan(dt, TILED_PART, rows, d, hq * hd, true, gsc.bytes, nullptr, s->w.parts_bytes);
     const TiledPlan pd = gemm_tiled_plan(dt, TILED_PART, rows, d, F, true, gsc.bytes, nullptr, s->w.parts_bytes);

@@ -38,7 +38,6 @@ typedef unsigned long long u64;
 
 constexpr int NT = 512, NW = NT / 64, WGS = 16, GW = WGS * NW;
 constexpr int POLLS = 1 << 25;
-constexpr int HEAD = 32;     // words of a stage's places in front, which hold the last step's tag
 constexpr int ATTN_NW = NW;  // ranges a context is cut into, as in k_attn_decode<float>
 constexpr int AMAX_NW = 16;  // ... wavefronts of k_argmax
 
@@ -192,9 +191,8 @@ __global__ void __launch_bounds__(NT, 4) k_step_small_f32(SmallStep a) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int d = a.d, F = a.F, qd = a.hq * HD, nq = qd + 2 * a.hkv * HD;
   float *xs = sm, *x2s = xs + R * d, *as = x2s + R * d, *hs = as + R * qd;  // rows, rows behind O, attention (q, k, v first), SwiGLU
-  unsigned* const epoch = (unsigned*)a.places;
-  u64 *lx = a.places + HEAD, *lq = lx + R * d, *la = lq + R * nq, *lx2 = la + R * qd, *lh = lx2 + R * d, *ll = lh + R * F;
-  const unsigned tag0 = __hip_atomic_load(epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+  u64 *lx = a.xch, *lq = lx + R * d, *la = lq + R * nq, *lx2 = la + R * qd, *lh = lx2 + R * d, *ll = lh + R * F;
+  const unsigned tag0 = __hip_atomic_load(a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
   if ((int)threadIdx.x < R) {
     const int p = a.seq_lens[threadIdx.x];
     spos[threadIdx.x] = p >= 0 && p < a.max_seq ? p : -1;
@@ -415,7 +413,7 @@ __global__ void __launch_bounds__(NT, 4) k_step_small_f32(SmallStep a) {
   }
   // Workgroup 0 has seen values of all others that they sent behind their reads of the tag and of the lengths.
   if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) *epoch = tag0 + a.layers;
+    if (threadIdx.x == 0) *a.epoch = tag0 + a.layers;
     if ((int)threadIdx.x < R && spos[threadIdx.x] >= 0) a.seq_lens[threadIdx.x] = spos[threadIdx.x] + 1;
   }
 }
@@ -423,8 +421,8 @@ __global__ void __launch_bounds__(NT, 4) k_step_small_f32(SmallStep a) {
 constexpr int ROWS = 4;
 std::atomic<long> launches{0};
 
-// Parts of the static array, one to a stage.  A stage that finds all of them taken takes the separate launches.
-constexpr int PARTS = 64, PART_WORDS = 18 * 1024, MAX_DEVICES = 64;
+// Parts of the static array, one to a stage: HEAD words for the last step's tag, then the places.  A stage that finds all of them taken takes the separate launches.
+constexpr int PARTS = 64, HEAD = 32, PART_WORDS = 18 * 1024, MAX_DEVICES = 64;
 __device__ __align__(256) u64 places[PARTS][PART_WORDS];
 
 struct Pool {
@@ -477,9 +475,9 @@ bool small_step_shape(int d, int hq, int hkv, int hd, int F, int vocab) {
 // two rows (1) 42 / 36; ffn of 1608 and two rows 48 / 51, 804 and two 40 / 33.
 bool small_step_rows(int rows, int hq, int F) { return rows >= 1 && rows <= ROWS && (long)rows * hq <= UNITS && (long)rows * F <= FFN_ROWS; }
 
-unsigned long long* take_small_step_places(int device, int d, int hq, int hkv, int hd, int F, int vocab) {
+SmallStepPlaces take_small_step_places(int device, int d, int hq, int hkv, int hd, int F, int vocab) {
   static_assert(PARTS == 64, "");
-  if (device < 0 || device >= MAX_DEVICES || !small_step_shape(d, hq, hkv, hd, F, vocab) || !small_step_rows(1, hq, F)) return nullptr;
+  if (device < 0 || device >= MAX_DEVICES || !small_step_shape(d, hq, hkv, hd, F, vocab) || !small_step_rows(1, hq, F)) return {};
   std::lock_guard<std::mutex> lock(pool_mutex);
   Pool& p = pools[device];
   if (!p.base) {
@@ -487,24 +485,25 @@ unsigned long long* take_small_step_places(int device, int d, int hq, int hkv, i
     if (hipGetSymbolAddress(&base, HIP_SYMBOL(places)) != hipSuccess || hipMemset(base, 0, sizeof places) != hipSuccess ||
         hipStreamSynchronize(nullptr) != hipSuccess) {
       (void)hipGetLastError();
-      return nullptr;
+      return {};
     }
     p.base = (u64*)base;
   }
-  if (!~p.taken) return nullptr;
+  if (!~p.taken) return {};
   const int i = __builtin_ctzll(~p.taken);
   p.taken |= (u64)1 << i;
-  return p.base + (size_t)i * PART_WORDS;  // a stage before this one may have left tags: the next steps go on behind them
+  u64* part = p.base + (size_t)i * PART_WORDS;
+  return {part + HEAD, (unsigned*)part};  // a stage before this one may have left tags: the next steps go on behind them
 }
 
-void give_small_step_places(int device, unsigned long long* part) {
-  if (!part) return;
+void give_small_step_places(int device, SmallStepPlaces places) {
+  if (!places.xch) return;
   std::lock_guard<std::mutex> lock(pool_mutex);
-  pools[device].taken &= ~((u64)1 << (part - pools[device].base) / PART_WORDS);
+  pools[device].taken &= ~((u64)1 << (places.xch - pools[device].base) / PART_WORDS);
 }
 
 bool small_step_supported(const SmallStep& a, int rows, int max_keys) {
-  return a.places && small_step_shape(a.d, a.hq, a.hkv, a.hd, a.F, a.head_w ? a.vocab : 0) && small_step_rows(rows, a.hq, a.F) &&
+  return a.xch && small_step_shape(a.d, a.hq, a.hkv, a.hd, a.F, a.head_w ? a.vocab : 0) && small_step_rows(rows, a.hq, a.F) &&
          attn_decode_chunks(rows, a.hkv, max_keys) == 1 && (!a.head_w || gemm_rows_f32_norm_supported(rows, a.vocab, a.d));
 }
 
