@@ -311,6 +311,9 @@ ls_status ls_stage_pass_times(ls_stage* stage, float* before_layers_ms, float* a
  * LS_OP_NONE switches the probe off and keeps what was recorded; setting an operator starts a new
  * record.  The last 512 launches are kept.  Used to measure one
  * kernel's duration inside a timed run without a profiler attached.
+ * Generation steps that are one launch otherwise (ls_stage_create) are separate launches, with the
+ * same results, while an operator of decode calls is set: what is timed is an operator's own
+ * kernel, which such a step does not have.
  */
 ls_status ls_stage_probe(ls_stage* stage, int op, int layer, int phase);
 

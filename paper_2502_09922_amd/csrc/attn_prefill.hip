@@ -30,7 +30,8 @@
 //
 // Measured, 32 x 40 heads x 1024^2 / six prompts of up to 2048 rows on 64 heads: 610 / 240 us with fills by the compiler's
 // builtin, which had the next tile's arrive before this one's values were read; now 584 / 232 with tiles of 64 keys, 560 / 226
-// with 32 (0.61 PFLOP/s).  A tile of 64 takes a CU 3000 cycles: matrix instructions 0.33 of them, other vector instructions
+// with 32 (0.61 PFLOP/s); inside the 13B and 70B prompt passes, at the clock the GEMMs leave, 704 / 273 before and 644 / 259 now.
+// A tile of 64 takes a CU 3000 cycles: matrix instructions 0.33 of them, other vector instructions
 // 0.38, one after the other in a wavefront that then waits for LDS and for the ones beside it.  Matrix instructions before all
 // else (s_setprio) only with tiles of 32, where three wavefronts share a SIMD: on another card of the kind 592 us with, 690
 // without; tiles of 64 lose 3 to 8 % by it (512 rows on 32 heads 16.9 us with, 15.9 without).

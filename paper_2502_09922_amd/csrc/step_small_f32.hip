@@ -6,7 +6,7 @@
 // for the values it needs until they carry the tag.  No flag, no fence and no wait for a store stands between producer and
 // consumer: 1.2 us from one phase to the next (256 values; with flags 1.8, with a counter that all add to and fences 5 to 9).
 // What a phase multiplies with is asked for before its values are.  The tiny model (2 layers of 256 columns, one row, 40 keys):
-// a step 43 -> 27 us on the device, the generation of 8 tokens behind a 32-token prompt 470 -> 300 us.  What bounds it now: of
+// a step 43 -> 27 us on the device, the generation of 8 tokens behind a 32-token prompt 491 -> 317 us.  What bounds it now: of
 // the 27 us eleven exchanges take 13, the attention's softmax and merges 1.3 a layer, a projection's sums 0.7 to 1.8.
 //
 // Sixteen: with 32 workgroups a step takes 23.5 us, with 16 of them 27.3, but all of a launch have to be on the chip together.
