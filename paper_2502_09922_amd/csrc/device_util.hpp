@@ -108,9 +108,8 @@ __device__ __forceinline__ float exchange(float v, F f) {
 struct Add { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
 struct Max { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
 
-// Over the 64 lanes of a wavefront; every lane gets the result (fixed butterfly order).
+// Sum over the 64 lanes of a wavefront; every lane gets the total (fixed butterfly order).
 __device__ __forceinline__ float wave_sum(float v) { return exchange<32, 1>(v, Add{}); }
-__device__ __forceinline__ float wave_max(float v) { return exchange<32, 1>(v, Max{}); }
 
 // Sum over each aligned group of 16 lanes, every lane of the group gets the total.  Four
 // register-to-register DPP exchanges (lane^1, lane^2, mirrored half row, mirrored row) in a
